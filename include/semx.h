@@ -69,7 +69,10 @@ typedef struct semx_ctx semx_ctx;
 #define SEMX_C_MFMA_F32 3  /* FP32-operand MFMA contractions (v_mfma_f32_16x16x4f32) */
 
 /* assembly of element forces into the global vector (Sec. IV-C) */
-#define SEMX_ASM_COLORED 0 /* colour by colour, plain read-modify-write, deterministic */
+#define SEMX_ASM_COLORED 0 /* the sums of a pass colour by colour, deterministic: element-local forces
+                              summed per node in colour order (one launch over the mesh and one sum),
+                              or colour by colour with plain read-modify-write (element blocks, a
+                              colouring set by the caller, no memory for the element-local forces) */
 #define SEMX_ASM_ATOMIC 1  /* one launch, FP32 global atomic adds */
 
 /* storage and arithmetic of the state vectors and the time loop */
@@ -104,7 +107,8 @@ int semx_upload_mesh(semx_ctx *ctx, int64_t nspec, int64_t nglob, const int32_t 
 /* Replace the colouring: elem_order [nspec] lists the elements colour by
  * colour, colour c owning elem_order[color_ptr[c] .. color_ptr[c+1]-1].
  * Rejected (SEMX_EINVAL) unless it is a permutation and no two elements of a
- * colour share a global node. */
+ * colour share a global node.  With a colouring of the caller's the force runs
+ * colour by colour, one launch per colour.  The model must be uploaded again. */
 int semx_set_coloring(semx_ctx *ctx, int ncolors, const int32_t *color_ptr, const int32_t *elem_order);
 
 /* Read the current colouring.  color_ptr needs ncolors+1 entries and
@@ -375,15 +379,16 @@ int semx_upload_model_acoustic(semx_ctx *ctx, int nmodels, const double *kappa, 
 int semx_gll(int ngll, double *xi, double *w);
 
 /* Kernel timing.  With stride k > 0, every k-th force pass (one
- * semx_apply_force, or the force part of one time step: all its colour
- * launches back to back; the first, then k, 2k, ... counted from this call)
- * is bracketed by one pair of HIP events recorded on the context stream; 0
- * turns timing off, a negative stride is SEMX_EINVAL.  semx_force_timing()
- * synchronises the stream, returns the number of force-kernel launches
- * inside the timed passes and their summed event-measured duration in
- * milliseconds since the last read (so the average launch includes the
- * short gaps between launches, not the latency of an event per launch), and
- * clears the record. */
+ * semx_apply_force, or the force part of one time step; the first, then k,
+ * 2k, ... counted from this call) is bracketed by one pair of HIP events
+ * recorded on the context stream; 0 turns timing off, a negative stride is
+ * SEMX_EINVAL.  semx_force_timing() synchronises the stream, returns the
+ * number of colour ranges that the timed passes covered (SEMX_ASM_COLORED: the
+ * mesh's colours, also where one launch covers them all; SEMX_ASM_ATOMIC: its
+ * launches) and the passes' summed event-measured duration in milliseconds
+ * since the last read, and clears the record.  In the time loop the nodal sum
+ * of the element-local forces belongs to the Newmark pass that follows, not to
+ * the force pass. */
 int semx_set_timing(semx_ctx *ctx, int stride);
 int semx_force_timing(semx_ctx *ctx, int64_t *launches, double *total_ms);
 
@@ -398,13 +403,13 @@ int semx_stream_bandwidth(semx_ctx *ctx, int64_t nbytes, int reps, double *gbps)
 
 /* Access-pattern reference for the force pass (Sec. II-B operator, Sec. IV-D
  * fused traversal): runs, reps times after one warm-up pass, the memory
- * skeleton of the FP32 per-element force pass that semx_apply_force and
- * semx_step launch with coloured assembly (one lane per point up to NGLL
- * 10, one lane per column from 11): the same colour launches, grid,
- * block-to-element mapping and per-point loads and stores (node numbers,
- * geometry, material, the gather of u, the first-touch bits, the read of f
- * where the point is not first and the store of f) without the
- * contractions, the stress arithmetic and the slice barriers.  The clearing of f that a pass
+ * skeleton of the FP32 per-element force pass that semx_apply_force launches
+ * with SEMX_ASM_COLORED (one lane per point up to NGLL 10, one lane per column
+ * from 11): the same launches, grid, block-to-element mapping and per-point
+ * loads and stores (node numbers, geometry, material, the gather of u, the
+ * element-local forces and their nodal sum; colour by colour the first-touch
+ * bits and f instead) without the contractions, the stress arithmetic and the
+ * slice barriers.  The clearing of f that a pass
  * without first-touch coverage needs is not included.  Returns the average
  * milliseconds per pass (HIP events on the context stream); the force pass
  * cannot take less time than its skeleton.

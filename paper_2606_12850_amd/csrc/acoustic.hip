@@ -58,7 +58,7 @@ __global__ __launch_bounds__(Shape<NG>::BLK) void force_ac_kernel(ForceArgs a) {
   const int ngrp = (int)a.count;
   const int grp = xcd_group(ngrp);
   if (grp >= ngrp) return;  // uniform over the block
-  const int pos = (int)a.pos0 + grp;
+  const int pos = elem_pos(a, grp);
 
   const int p = threadIdx.x;
   const bool act = p < N3;
@@ -142,7 +142,8 @@ __global__ __launch_bounds__(Shape<NG>::BLK) void force_ac_kernel(ForceArgs a) {
       else unsafeAtomicAdd(f + g, -sum);
     } else {
       const float out = fo - sum;
-      if constexpr (AFF) store_affine<1>(sp, &out);
+      if (a.part) store_part<1>(a, model, pos, N3, p, &out);
+      else if constexpr (AFF) store_affine<1>(sp, &out);
       else f[g] = out;
     }
   }
@@ -174,7 +175,7 @@ __global__ __launch_bounds__(AcColShape<NG>::BLK) void force_ac_col_kernel(Force
   const int ngrp = (int)a.count;
   const int grp = xcd_group(ngrp);
   if (grp >= ngrp) return;  // uniform over the block
-  const int pos = (int)a.pos0 + grp;
+  const int pos = elem_pos(a, grp);
 
   const int l = threadIdx.x;
   const bool act = l < N2;
@@ -278,7 +279,9 @@ __global__ __launch_bounds__(AcColShape<NG>::BLK) void force_ac_col_kernel(Force
       if constexpr (ATOMIC) {
         unsafeAtomicAdd(fg, -acc[k]);
       } else {
-        if (first_bit(a, pos, q)) *fg = -acc[k];
+        const float out = -acc[k];
+        if (a.part) store_part<1>(a, model, pos, N3, q, &out);
+        else if (first_bit(a, pos, q)) *fg = -acc[k];
         else *fg = *fg - acc[k];
       }
     }

@@ -54,7 +54,7 @@ __global__ __launch_bounds__(Shape<NG>::BLK) void adjoint_force_kernel(AdjArgs A
   const ForceArgs& a = A.fa;
   const int grp = xcd_group((int)a.count);
   if (grp >= a.count) return;
-  const int pos = (int)a.pos0 + grp;
+  const int pos = elem_pos(a, grp);
   const int p = threadIdx.x;
   const bool act = p < N3;
   const int pp = act ? p : 0;
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(AdjCol<NG>::BLK) __attribute__((amdgpu_waves_per_eu
   const ForceArgs& a = A.fa;
   const int grp = xcd_group((int)a.count);
   if (grp >= a.count) return;
-  const int pos = (int)a.pos0 + grp;
+  const int pos = elem_pos(a, grp);
   const int l = threadIdx.x;
   const bool act = l < N2;
   const int ll = act ? l : 0;
@@ -622,6 +622,8 @@ int semx_adjoint(semx_ctx* c, const float* gseis_dev, int64_t nt, double* g_lamb
   if (!rc) rc = dev_alloc(c, acc, 3 * sizeof(double) * npt);
   if (rc) { cleanup(); return rc; }
   // keep the caller's forward state
+  rc = settle_force(c);
+  if (rc) { cleanup(); return rc; }
   const int64_t it_saved = c->it;
   const bool pend_saved = c->pending_correct;
   char* sv = saved.as<char>();
@@ -669,7 +671,12 @@ int semx_adjoint(semx_ctx* c, const float* gseis_dev, int64_t nt, double* g_lamb
   const float dt = (float)c->dt;
   A.coef = -dt * dt;
   const bool atomic = c->ncolors == 0;
-  const auto& launches = atomic ? c->atomic_launches : c->colored_launches;
+  if (!atomic) {
+    rc = build_colored(c);
+    if (rc) { cleanup(); return rc; }
+    A.fa.list = c->d_clist.as<int32_t>();
+  }
+  const auto& launches = atomic ? c->kind_launches : c->colored_launches;
   int i0 = 0, i1 = 1, i2 = 2;  // p[i0] = psi^{m+2}, p[i1] = psi^{m+1}, p[i2] = psi^m
 
   for (int64_t seg = nseg - 1; seg >= 0 && !rc; --seg) {
@@ -682,6 +689,7 @@ int semx_adjoint(semx_ctx* c, const float* gseis_dev, int64_t nt, double* g_lamb
     if (!rc) rc = fill_zero(c, c->d_f.as<float>(), len);
     c->it = n0;
     c->pending_correct = false;
+    c->f_in_part = false;
     if (!rc) rc = d2d(c, segu.as<char>(), c->d_u.p, vb);
     if (!rc) rc = d2d(c, sega.as<char>(), c->d_a.p, vb);
     // the forward run's own fused Newmark pass stores u^s and a^{s-1} into the
@@ -750,6 +758,7 @@ int semx_adjoint(semx_ctx* c, const float* gseis_dev, int64_t nt, double* g_lamb
   if (!rc2) rc2 = d2d(c, c->d_f.p, sv + 3 * vb, vb);
   c->it = it_saved;
   c->pending_correct = pend_saved;
+  c->f_in_part = false;
   if (!rc && !rc2) {
     hipError_t e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) rc = hip_fail(c, e, "adjoint sync");

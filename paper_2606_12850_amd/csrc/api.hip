@@ -13,6 +13,7 @@
 #include <string>
 #include <vector>
 
+#include "newmark.hpp"
 #include "semx_internal.hpp"
 
 namespace semx {
@@ -187,40 +188,6 @@ __global__ void material_kernel(int n3, int64_t nspec, int nmodels, const int32_
   }
 }
 
-// Lumped mass over the launch positions [pbeg, pbeg + count) of one colour
-// (no two elements of a colour share a node, so plain read-modify-write in
-// FP64 is race free and deterministic).  ibool and wdet are in launch order,
-// rho in user order.
-__global__ void mass_color_kernel(int n3, int64_t nspec, int64_t nglob, int nmodels, int64_t pbeg,
-                                  int64_t count, const int32_t* __restrict__ order,
-                                  const int32_t* __restrict__ ibool, const double* __restrict__ rho,
-                                  const double* __restrict__ wdet, double* __restrict__ mass) {
-  const int64_t total = (int64_t)nmodels * count * n3;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t mp = t / n3;
-    const int q = (int)(t - mp * n3);
-    const int model = (int)(mp / count);
-    const int64_t pos = pbeg + (mp - (int64_t)model * count);
-    const int64_t pt = pos * n3 + q;
-    mass[(int64_t)model * nglob + ibool[pt]] +=
-        rho[((int64_t)model * nspec + order[pos]) * n3 + q] * wdet[pt];
-  }
-}
-
-// Same sum by one thread in position order (meshes without a valid colouring).
-__global__ void mass_serial_kernel(int n3, int64_t nspec, int64_t nglob, int nmodels,
-                                   const int32_t* __restrict__ order, const int32_t* __restrict__ ibool,
-                                   const double* __restrict__ rho, const double* __restrict__ wdet,
-                                   double* __restrict__ mass) {
-  for (int model = 0; model < nmodels; ++model)
-    for (int64_t pt = 0; pt < nspec * n3; ++pt) {
-      const int64_t pos = pt / n3;
-      mass[(int64_t)model * nglob + ibool[pt]] +=
-          rho[((int64_t)model * nspec + order[pos]) * n3 + (pt - pos * n3)] * wdet[pt];
-    }
-}
-
 __global__ void minv_kernel(int64_t n, const double* __restrict__ mass, float* __restrict__ minv) {
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n;
        t += (int64_t)gridDim.x * blockDim.x)
@@ -237,38 +204,6 @@ __global__ void fill_f64(double* __restrict__ p, int64_t n, double v) {
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n;
        t += (int64_t)gridDim.x * blockDim.x)
     p[t] = v;
-}
-
-// ---------------------------------------------------------------------------
-// Explicit Newmark (beta = 0, gamma = 1/2) update, one thread per global node
-// and model.  mode bit 1 (kCorrect): acc = M^{-1} f, v += dt/2 acc, and acc
-// is stored to a if kStoreA; without it acc is read from a.  Bit 2
-// (kPredict): u += dt v + dt^2/2 acc, v += dt/2 acc, f = 0 unless kKeepF
-// (the coming force pass overwrites every node).  A step is "correct then
-// predict" in one pass, so a never has to be written.
-// ---------------------------------------------------------------------------
-// kSeg (the adjoint's forward recomputation): also store acc to seg_a and the
-// predicted u to seg_u, the segment buffers, in the same pass.
-constexpr int kCorrect = 1, kPredict = 2, kStoreA = 4, kKeepF = 8, kSeg = 16;
-
-// One entry (node, component) of the update: m = M^{-1} at the node, ff
-// and aa its f and a; uu and vv are updated in place, the acceleration used
-// is returned.  Both kernels below apply exactly this.
-template <int MODE>
-__device__ __forceinline__ float newmark_entry(float m, float ff, float aa, float dt, float hdt, float hdt2, float& uu,
-                                               float& vv) {
-  float acc;
-  if constexpr ((MODE & kCorrect) != 0) {
-    acc = m * ff;
-    vv = vv + hdt * acc;
-  } else {
-    acc = aa;
-  }
-  if constexpr ((MODE & kPredict) != 0) {
-    uu = uu + dt * vv + hdt2 * acc;
-    vv = vv + hdt * acc;
-  }
-  return acc;
 }
 
 // NC: field components per node (3 elastic, 1 acoustic).  One entry per lane.
@@ -700,17 +635,15 @@ int build_blocks(semx_ctx* c, const std::vector<int32_t>& pos_of, const std::vec
   return SEMX_OK;
 }
 
-// Launch-ordered layout: every per-element array on the device is stored by
-// launch position, positions sorted by (geometry kind, colour, element), so
-// that each launch (one colour of one kind, or one kind for atomic assembly)
-// streams one contiguous range with no element-list indirection.  Then the
-// FP64 geometry kernel fills Gamma and W det J in that order.
+// Layout: every per-element array on the device is stored by launch position,
+// positions sorted by (geometry kind, affine numbering first, element), so
+// that a launch over one kind streams one contiguous range and elements that
+// share nodes run close together.  A pass colour by colour takes its elements
+// from a list of positions.  Then the node tables, and the FP64 geometry
+// kernel fills Gamma and W det J in that order.
 int build_layout(semx_ctx* c) {
   const int n3 = c->n3;
   const int64_t nspec = c->nspec;
-  std::vector<int32_t> order;
-  order.reserve(nspec);
-  struct Range { int64_t beg, cnt; bool irr; int color; int64_t naff; };
   // affine numbering: ibool(e, i, j, k) = g0 + i sx + j sy + k sz at every point
   // (a lattice numbering); aff[e] = {g0, sx, sy, sz}, g0 = -1 if not affine
   const int n = c->n;
@@ -733,44 +666,41 @@ int build_layout(semx_ctx* c) {
     aff[e] = ok ? std::array<int32_t, 4>{(int32_t)g0, (int32_t)sx, (int32_t)sy, (int32_t)sz}
                 : std::array<int32_t, 4>{-1, 0, 0, 0};
   }
-  std::vector<Range> col;
-  const int nc = c->ncolors > 0 ? c->ncolors : 1;
-  std::vector<int64_t> kind_beg(3, 0);
+  std::vector<int32_t> order;
+  order.reserve(nspec);
+  c->kind_launches.clear();
   for (int irr = 0; irr < 2; ++irr) {
-    kind_beg[irr] = (int64_t)order.size();
-    for (int k = 0; k < nc; ++k) {
-      Range r{(int64_t)order.size(), 0, irr == 1, k, 0};
-      if (c->ncolors > 0) {
-        for (int32_t t = c->color_ptr[k]; t < c->color_ptr[k + 1]; ++t) {
-          const int32_t e = c->elem_order[t];
-          if ((c->h_regular[e] == 0) == (irr == 1)) order.push_back(e);
-        }
-      } else {
-        for (int64_t e = 0; e < nspec; ++e)
-          if ((c->h_regular[e] == 0) == (irr == 1)) order.push_back((int32_t)e);
-      }
-      r.cnt = (int64_t)order.size() - r.beg;
-      // elements with an affine numbering first (stable): the FP32 force
-      // kernel computes their node numbers instead of streaming them
-      auto mid = std::stable_partition(order.begin() + r.beg, order.end(),
-                                       [&](int32_t e) { return aff[e][0] >= 0; });
-      r.naff = mid - (order.begin() + r.beg);
-      if (r.cnt) col.push_back(r);
+    const int64_t beg = (int64_t)order.size();
+    int64_t naff = 0;
+    for (int affine = 1; affine >= 0; --affine) {
+      for (int64_t e = 0; e < nspec; ++e)
+        if ((c->h_regular[e] == 0) == (irr == 1) && (aff[e][0] >= 0) == (affine == 1)) order.push_back((int32_t)e);
+      if (affine) naff = (int64_t)order.size() - beg;
     }
+    if ((int64_t)order.size() > beg) c->kind_launches.push_back({beg, (int64_t)order.size() - beg, irr == 1, naff});
   }
-  kind_beg[2] = (int64_t)order.size();
   c->h_order = order;
+  std::vector<int32_t> pos_of(nspec);
+  for (int64_t pos = 0; pos < nspec; ++pos) pos_of[order[pos]] = (int32_t)pos;
+  // colour by colour: regular before irregular, affine-numbered first
+  c->h_clist.clear();
   c->colored_launches.clear();
-  c->atomic_launches.clear();
-  // coloured: colour-major execution order, regular before irregular in a colour
-  for (int k = 0; k < nc; ++k)
-    for (const auto& r : col)
-      if (r.color == k) c->colored_launches.push_back({r.beg, r.cnt, r.irr, r.naff});
-  // atomic: one launch per kind; its affine elements are not contiguous, so
-  // the whole range takes the node-number stream
-  for (int irr = 0; irr < 2; ++irr)
-    if (kind_beg[irr + 1] > kind_beg[irr])
-      c->atomic_launches.push_back({kind_beg[irr], kind_beg[irr + 1] - kind_beg[irr], irr == 1, 0});
+  dev_free(c->d_clist);
+  dev_free(c->d_first);
+  c->h_first.clear();
+  c->first_words = 0;
+  for (int k = 0; k < c->ncolors; ++k)
+    for (int irr = 0; irr < 2; ++irr) {
+      const int64_t beg = (int64_t)c->h_clist.size();
+      for (int32_t t = c->color_ptr[k]; t < c->color_ptr[k + 1]; ++t) {
+        const int32_t e = c->elem_order[t];
+        if ((c->h_regular[e] == 0) == (irr == 1)) c->h_clist.push_back(pos_of[e]);
+      }
+      auto mid = std::stable_partition(c->h_clist.begin() + beg, c->h_clist.end(),
+                                       [&](int32_t pos) { return aff[order[pos]][0] >= 0; });
+      const int64_t cnt = (int64_t)c->h_clist.size() - beg;
+      if (cnt) c->colored_launches.push_back({beg, cnt, irr == 1, mid - (c->h_clist.begin() + beg)});
+    }
 
   std::vector<int32_t> ib((size_t)nspec * n3), affpos((size_t)nspec * 4);
   std::vector<float> gel((size_t)nspec * 9);
@@ -793,27 +723,6 @@ int build_layout(semx_ctx* c) {
     for (int a = 0; a < 3; ++a)
       for (int m = 0; m < 8; ++m) tri[pos * 24 + 8 * a + m] = (float)cm[a][m];
   }
-  // first touch in coloured launch order (colour-major, regular then irregular)
-  const int fw = (n3 + 31) / 32;
-  std::vector<uint32_t> first;
-  c->elem_cover = false;
-  c->first_words = 0;
-  if (c->ncolors > 0) {
-    first.assign((size_t)nspec * fw, 0u);
-    std::vector<uint8_t> touched(c->nglob, 0);
-    for (const auto& L : c->colored_launches)
-      for (int64_t pos = L.pos0; pos < L.pos0 + L.count; ++pos)
-        for (int q = 0; q < n3; ++q) {
-          const int32_t g = ib[pos * n3 + q];
-          if (!touched[g]) {
-            touched[g] = 1;
-            first[pos * fw + q / 32] |= 1u << (q % 32);
-          }
-        }
-    c->elem_cover = true;
-    for (int64_t g = 0; g < c->nglob && c->elem_cover; ++g) c->elem_cover = touched[g] != 0;
-    c->first_words = fw;
-  }
   // element-interior points that are the only reference to their node
   {
     std::vector<uint8_t> refs(c->nglob, 0);
@@ -826,10 +735,10 @@ int build_layout(semx_ctx* c) {
         if (interior) excl = refs[ib[pos * n3 + q]] == 1;
       }
     c->interior_exclusive = excl;
+    c->elem_cover = c->ncolors > 0;
+    for (int64_t g = 0; g < c->nglob && c->elem_cover; ++g) c->elem_cover = refs[g] != 0;
   }
   int rc = dev_alloc(c, c->d_order, sizeof(int32_t) * nspec);
-  if (!rc && !first.empty()) rc = dev_alloc(c, c->d_first, sizeof(uint32_t) * first.size());
-  if (!rc && first.empty()) dev_free(c->d_first);
   if (!rc) rc = dev_alloc(c, c->d_ibool, sizeof(int32_t) * nspec * n3);
   if (!rc) rc = dev_alloc(c, c->d_aff, sizeof(int32_t) * 4 * nspec);
   if (!rc) rc = dev_alloc(c, c->d_gam_el, sizeof(float) * 9 * nspec);
@@ -841,18 +750,14 @@ int build_layout(semx_ctx* c) {
   SEMX_HIP(c, hipMemcpy(c->d_order.p, order.data(), sizeof(int32_t) * nspec, hipMemcpyHostToDevice));
   SEMX_HIP(c, hipMemcpy(c->d_ibool.p, ib.data(), sizeof(int32_t) * nspec * n3, hipMemcpyHostToDevice));
   SEMX_HIP(c, hipMemcpy(c->d_aff.p, affpos.data(), sizeof(int32_t) * 4 * nspec, hipMemcpyHostToDevice));
-  if (!first.empty())
-    SEMX_HIP(c, hipMemcpy(c->d_first.p, first.data(), sizeof(uint32_t) * first.size(), hipMemcpyHostToDevice));
-  c->h_first = std::move(first);
   c->first_tl_dirty = true;
+  c->srcbits_dirty = true;
   SEMX_HIP(c, hipMemcpy(c->d_gam_el.p, gel.data(), sizeof(float) * 9 * nspec, hipMemcpyHostToDevice));
   SEMX_HIP(c, hipMemcpy(c->d_tri.p, tri.data(), sizeof(float) * 24 * nspec, hipMemcpyHostToDevice));
-  {
-    std::vector<int32_t> pos_of(nspec);
-    for (int64_t pos = 0; pos < nspec; ++pos) pos_of[order[pos]] = (int32_t)pos;
-    rc = build_blocks(c, pos_of, aff, order);
-    if (rc) return rc;
-  }
+  rc = build_blocks(c, pos_of, aff, order);
+  find_lattice(c, aff);
+  if (!rc) rc = build_node_points(c);
+  if (rc) return rc;
   int* bad = scratch_i(c);
   SEMX_HIP(c, hipMemsetAsync(bad, 0, sizeof(int), c->stream));
   geom_kernel<<<grid_for(nspec * n3, 8192), kThreads, 0, c->stream>>>(
@@ -902,7 +807,7 @@ ForceArgs force_args(const semx_ctx* c, const float* u, float* f, bool first_tou
   a.nspec = c->nspec;
   a.nglob = c->nglob;
   a.nmodels = c->nmodels;
-  if (first_touch && c->assembly != SEMX_ASM_ATOMIC && c->d_first.p) {
+  if (first_touch && c->assembly != SEMX_ASM_ATOMIC && !parts_active(c) && c->d_first.p) {
     a.first = c->d_first.as<uint32_t>();
     a.first_words = c->first_words;
   }
@@ -918,19 +823,16 @@ ForceArgs force_args(const semx_ctx* c, const float* u, float* f, bool first_tou
 // launched nchunks times on the context's stream, the counter set from the
 // host index before each launch.  The captured steps are the ones
 // step_once would launch directly: bitwise the same results.
-bool prestores(const semx_ctx* c);
-int build_first_tl(semx_ctx* c);
-
 int run_graph_chunks(semx_ctx* c, int64_t nchunks, int64_t G) {
   int rc = SEMX_OK;
   // nothing may allocate or copy synchronously inside the capture
-  if (prestores(c) && c->first_tl_dirty) rc = build_first_tl(c);
+  if (prestores(c)) rc = build_first_tl(c);
   if (!rc && !c->d_step.p) rc = dev_alloc(c, c->d_step, sizeof(int64_t));
   if (rc) return rc;
   if (!c->cap_stream) SEMX_HIP(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
   int64_t* dstep = c->d_step.as<int64_t>();
   const int64_t it0 = c->it;
-  const bool pend0 = c->pending_correct;
+  const bool pend0 = c->pending_correct, part0 = c->f_in_part;
   hipStream_t home = c->stream;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -944,6 +846,7 @@ int run_graph_chunks(semx_ctx* c, int64_t nchunks, int64_t G) {
   c->stream = home;
   c->it = it0;  // the capture ran nothing
   c->pending_correct = pend0;
+  c->f_in_part = part0;
   if (rc || e_end != hipSuccess) {
     if (graph) (void)hipGraphDestroy(graph);
     return rc ? rc : hip_fail(c, e_end, "time-loop graph capture");
@@ -958,6 +861,7 @@ int run_graph_chunks(semx_ctx* c, int64_t nchunks, int64_t G) {
     c->it += G;
   }
   c->pending_correct = true;
+  c->f_in_part = parts_active(c);
   const hipError_t e_destroy = hipGraphExecDestroy(exec);
   if (e != hipSuccess) return hip_fail(c, e, "time-loop graph launch");
   if (e_destroy != hipSuccess) return hip_fail(c, e_destroy, "time-loop graph destroy");
@@ -980,13 +884,52 @@ bool blocks_active(const semx_ctx* c) {
   return c->blocks_mode == SEMX_BLOCKS_ON || (c->blocks_irregular && c->irregular_geo == kStored);
 }
 
+}  // namespace
+
+bool parts_active(const semx_ctx* c) {
+  return c->assembly == SEMX_ASM_COLORED && !c->user_colors && c->d_part.p != nullptr && !blocks_active(c);
+}
+
+// Device list of positions colour by colour, and the first touch of each
+// node in that order.
+int build_colored(semx_ctx* c) {
+  if (c->d_clist.p || c->ncolors == 0) return SEMX_OK;
+  const int n3 = c->n3, fw = (n3 + 31) / 32;
+  std::vector<uint32_t> first((size_t)c->nspec * fw, 0u);
+  std::vector<uint8_t> touched(c->nglob, 0);
+  for (int32_t pos : c->h_clist) {
+    const int32_t* ib = &c->h_ibool[(size_t)c->h_order[pos] * n3];
+    for (int q = 0; q < n3; ++q)
+      if (!touched[ib[q]]) {
+        touched[ib[q]] = 1;
+        first[(size_t)pos * fw + q / 32] |= 1u << (q % 32);
+      }
+  }
+  int rc = dev_alloc(c, c->d_first, sizeof(uint32_t) * first.size());
+  if (!rc) rc = dev_alloc(c, c->d_clist, sizeof(int32_t) * c->nspec);
+  if (rc) return rc;
+  SEMX_HIP(c, hipMemcpy(c->d_first.p, first.data(), sizeof(uint32_t) * first.size(), hipMemcpyHostToDevice));
+  SEMX_HIP(c, hipMemcpy(c->d_clist.p, c->h_clist.data(), sizeof(int32_t) * c->nspec, hipMemcpyHostToDevice));
+  c->h_first = std::move(first);
+  c->first_words = fw;
+  c->first_tl_dirty = true;
+  return SEMX_OK;
+}
+
+namespace {
+
 // `tl`: the time loop's pass after the source force was stored into f
 // (prestores()): the first-touch bits with the source nodes cleared.
 int force_accumulate(semx_ctx* c, const float* u, float* f, bool first_touch = false, bool f_zero = false,
-                     bool tl = false) {
+                     bool tl = false, bool defer = false) {
+  const bool atomic = c->assembly == SEMX_ASM_ATOMIC;
+  const bool parts = parts_active(c), colored = !atomic && !parts && !blocks_active(c);
+  if (colored) {
+    int rc = build_colored(c);
+    if (rc) return rc;
+  }
   ForceArgs a = force_args(c, u, f, first_touch);
   if (tl && a.first) a.first = c->d_first_tl.as<uint32_t>();
-  const bool atomic = c->assembly == SEMX_ASM_ATOMIC;
   a.excl_interior = atomic && f_zero && c->interior_exclusive ? 1 : 0;
   if (blocks_active(c)) {
     hipEvent_t e1 = nullptr;
@@ -1004,11 +947,14 @@ int force_accumulate(semx_ctx* c, const float* u, float* f, bool first_touch = f
     if (e1) SEMX_HIP(c, hipEventRecord(e1, c->stream));
     return SEMX_OK;
   }
-  const auto& launches = atomic ? c->atomic_launches : c->colored_launches;
+  if (colored) a.list = c->d_clist.as<int32_t>();
+  if (parts) a.part = c->d_part.as<float>();
+  const auto& launches = colored ? c->colored_launches : c->kind_launches;
   hipEvent_t e1 = nullptr;
   if (!launches.empty() && c->timing_stride > 0 && (c->timing_seq++ % c->timing_stride) == 0) {
     SEMX_HIP(c, time_pass_begin(c, &e1));
-    c->timed_launches += (int64_t)launches.size();
+    // a pass of the deterministic assembly covers every colour
+    c->timed_launches += (int64_t)(atomic ? launches : c->colored_launches).size();
   }
   for (const auto& L : launches) {
     a.pos0 = L.pos0;
@@ -1029,6 +975,13 @@ int force_accumulate(semx_ctx* c, const float* u, float* f, bool first_touch = f
     else
       e = launch_force_mfma(c->n, c->contraction, geo, atomic, a, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "force kernel launch");
+  }
+  if (parts && defer) {
+    c->f_in_part = true;
+    c->part_src = tl;
+  } else if (parts) {
+    const hipError_t e = launch_gather(c, f, tl ? c->d_srcbits.as<uint32_t>() : nullptr, c->stream);
+    if (e != hipSuccess) return hip_fail(c, e, "nodal sum launch");
   }
   if (e1) SEMX_HIP(c, hipEventRecord(e1, c->stream));
   return SEMX_OK;
@@ -1064,43 +1017,62 @@ int alloc_seismograms(semx_ctx* c) {
 // passes with first-touch stores over a mesh whose nodes all belong to some
 // element), so f needs no clearing before it.
 bool force_overwrites(const semx_ctx* c) {
-  return c->assembly == SEMX_ASM_COLORED && c->elem_cover && c->d_first.p != nullptr;
+  return c->assembly == SEMX_ASM_COLORED && (parts_active(c) || c->elem_cover);
 }
 
 // f = -K u.  `f_zeroed`: f already holds zeros.  `tl`: see force_accumulate.
-int force_into(semx_ctx* c, const float* u, float* f, bool f_zeroed, bool tl = false) {
+// `defer`: element-local forces may stay unsummed (the time loop's own f).
+int force_into(semx_ctx* c, const float* u, float* f, bool f_zeroed, bool tl = false, bool defer = false) {
+  int rs = settle_force(c);
+  if (rs) return rs;
   if (!f_zeroed && !force_overwrites(c)) {
     int rc = zero_f32(c, f, state_len(c));
     if (rc) return rc;
   }
-  return force_accumulate(c, u, f, force_overwrites(c), !force_overwrites(c), tl);
+  return force_accumulate(c, u, f, force_overwrites(c), !force_overwrites(c), tl, defer);
 }
 
 // The time loop stores the source force into f before the force pass (in
 // the bookkeeping launch) when the pass overwrites every node with
 // first-touch stores: the source nodes' first touch then reads and adds to
 // it, and no injection launch follows the pass.
+}  // namespace
+
 bool prestores(const semx_ctx* c) { return c->src.nsrc > 0 && c->src.nsn > 0 && force_overwrites(c); }
 
 // The time loop's first-touch bits: the bit of each source node's first
 // touch (in launch order) cleared, per element and per block.
 int build_first_tl(semx_ctx* c) {
-  std::vector<uint8_t> src(c->nglob, 0);
   for (int32_t g : c->h_src_nodes)
     if (g < 0 || g >= c->nglob) return fail(c, SEMX_ESTATE, "sources do not belong to the current mesh");
+  if (parts_active(c)) {
+    if (!c->srcbits_dirty) return SEMX_OK;
+    std::vector<uint32_t> bits((size_t)(c->nglob + 31) / 32, 0u);
+    for (int32_t g : c->h_src_nodes) bits[g >> 5] |= 1u << (g & 31);
+    int rc = dev_alloc(c, c->d_srcbits, sizeof(uint32_t) * bits.size());
+    if (rc) return rc;
+    SEMX_HIP(c, hipMemcpy(c->d_srcbits.p, bits.data(), sizeof(uint32_t) * bits.size(), hipMemcpyHostToDevice));
+    c->srcbits_dirty = false;
+    return SEMX_OK;
+  }
+  if (!blocks_active(c)) {
+    int rc = build_colored(c);
+    if (rc) return rc;
+  }
+  if (!c->first_tl_dirty) return SEMX_OK;
+  std::vector<uint8_t> src(c->nglob, 0);
   const int n3 = c->n3, fw = c->first_words;
   if (!c->h_first.empty()) {
     for (int32_t g : c->h_src_nodes) src[g] = 1;
     std::vector<uint32_t> bits = c->h_first;
-    for (const auto& L : c->colored_launches)
-      for (int64_t pos = L.pos0; pos < L.pos0 + L.count; ++pos) {
-        const int32_t* ib = &c->h_ibool[(size_t)c->h_order[pos] * n3];
-        for (int q = 0; q < n3; ++q)
-          if (src[ib[q]] == 1) {
-            src[ib[q]] = 0;
-            bits[pos * fw + q / 32] &= ~(1u << (q % 32));
-          }
-      }
+    for (int32_t pos : c->h_clist) {
+      const int32_t* ib = &c->h_ibool[(size_t)c->h_order[pos] * n3];
+      for (int q = 0; q < n3; ++q)
+        if (src[ib[q]] == 1) {
+          src[ib[q]] = 0;
+          bits[(size_t)pos * fw + q / 32] &= ~(1u << (q % 32));
+        }
+    }
     int rc = dev_alloc(c, c->d_first_tl, sizeof(uint32_t) * bits.size());
     if (rc) return rc;
     SEMX_HIP(c, hipMemcpy(c->d_first_tl.p, bits.data(), sizeof(uint32_t) * bits.size(), hipMemcpyHostToDevice));
@@ -1128,6 +1100,16 @@ int build_first_tl(semx_ctx* c) {
   return SEMX_OK;
 }
 
+int settle_force(semx_ctx* c) {
+  if (!c->f_in_part) return SEMX_OK;
+  c->f_in_part = false;
+  const uint32_t* bits = c->part_src ? c->d_srcbits.as<uint32_t>() : nullptr;
+  const hipError_t e = c->storage == SEMX_F64 ? launch_gather64(c, c->d_f.as<double>(), bits, c->stream)
+                                              : launch_gather(c, c->d_f.as<float>(), bits, c->stream);
+  return e == hipSuccess ? SEMX_OK : hip_fail(c, e, "nodal sum launch");
+}
+
+namespace {
 
 int inject_sources(semx_ctx* c, int64_t m, float* f, const int64_t* dstep = nullptr) {
   if (c->src.nsrc == 0 || c->src.nsn == 0) return SEMX_OK;
@@ -1143,6 +1125,8 @@ int inject_sources(semx_ctx* c, int64_t m, float* f, const int64_t* dstep = null
 int finalize_state(semx_ctx* c, float* seg_a = nullptr) {
   if (c->storage == SEMX_F64) return f64_finalize(c);
   if (!c->pending_correct) return SEMX_OK;
+  int rc = settle_force(c);
+  if (rc) return rc;
   const int64_t nn = (int64_t)c->nmodels * c->nglob;
   launch_newmark<kCorrect | kStoreA>(c, nn, grid_for(c->ncomp * nn), (float)c->dt, c->d_minv.as<float>(),
                                      c->d_u.as<float>(), c->d_v.as<float>(), c->d_a.as<float>(),
@@ -1155,6 +1139,7 @@ int finalize_state(semx_ctx* c, float* seg_a = nullptr) {
 int do_reset(semx_ctx* c) {
   c->run_gen++;
   c->ckpt_count = 0;
+  c->f_in_part = false;
   if (c->storage == SEMX_F64) return f64_reset(c);
   const int64_t len = state_len(c);
   for (auto* b : {&c->d_u, &c->d_v, &c->d_a, &c->d_f}) {
@@ -1222,7 +1207,16 @@ int step_once(semx_ctx* c, bool record, float* seg_u, float* seg_a, const int64_
     f_pe = c->d_work.as<float>();
   }
   const unsigned gb = grid_for(c->ncomp * nn, 1 << 30);  // one pass per lane (streams faster than grid-stride)
-  if (c->pending_correct) {
+  if (track || !force_overwrites(c)) {  // the energy pass reads f^n; other passes need f summed or cleared
+    int rc = settle_force(c);
+    if (rc) return rc;
+  }
+  if (c->f_in_part) {
+    c->f_in_part = false;
+    const hipError_t e = launch_newmark_parts(c, c->part_src ? c->d_srcbits.as<uint32_t>() : nullptr, seg_u, seg_a,
+                                              c->stream);
+    if (e != hipSuccess) return hip_fail(c, e, "Newmark pass launch");
+  } else if (c->pending_correct) {
     if (keep) launch_newmark<kCorrect | kPredict | kKeepF>(c, nn, gb, dt, minv, u, v, a, f, seg_u, seg_a);
     else launch_newmark<kCorrect | kPredict>(c, nn, gb, dt, minv, u, v, a, f, seg_u, seg_a);
   } else {
@@ -1238,12 +1232,12 @@ int step_once(semx_ctx* c, bool record, float* seg_u, float* seg_a, const int64_
   // source work and receivers read u^{n+1}, which the force pass leaves
   // alone; with prestores() the same launch stores f_src^{n+1} into f
   const bool pre = prestores(c);
-  int rc = pre && c->first_tl_dirty ? build_first_tl(c) : SEMX_OK;
+  int rc = pre ? build_first_tl(c) : SEMX_OK;
   if (!rc) rc = step_aux(c, c->it, track && src_in_f, record, dstep, pre);
   if (rc) return rc;
   // f is zero here only if the Newmark pass cleared it (untracked step on a
   // mesh the force pass does not overwrite)
-  rc = force_into(c, u, f, !track && !force_overwrites(c), pre);
+  rc = force_into(c, u, f, !track && !force_overwrites(c), pre, true);
   if (!rc && !pre) rc = inject_sources(c, c->it + 1, f, dstep);
   if (rc) return rc;
   if (dstep) {
@@ -1256,7 +1250,6 @@ int step_once(semx_ctx* c, bool record, float* seg_u, float* seg_a, const int64_
   return SEMX_OK;
 }
 
-int apply_force_accumulate(semx_ctx* c, const float* u, float* f) { return force_accumulate(c, u, f); }
 int fill_zero(semx_ctx* c, float* p, int64_t n) { return zero_f32(c, p, n); }
 int complete_step(semx_ctx* c, float* seg_a) { return finalize_state(c, seg_a); }
 // Point sources with the time function given in FP32 (stf32) or FP64
@@ -1266,11 +1259,14 @@ int set_sources_impl(semx_ctx* c, int nsrc, const int32_t* elem, const double* x
   if (!c) return SEMX_EINVAL;
   if (!c->have_mesh) return fail(c, SEMX_ESTATE, "set_sources: no mesh");
   if (nsrc < 0) return fail(c, SEMX_EINVAL, "set_sources: nsrc < 0");
+  int rs = settle_force(c);  // a pending force holds the old sources
+  if (rs) return rs;
   if (nsrc == 0) {
     c->src.nsrc = 0;
     c->src.nsn = 0;
     c->h_src_nodes.clear();
     c->first_tl_dirty = true;
+    c->srcbits_dirty = true;
     c->run_gen++;
     c->ckpt_count = 0;
     return c->have_model && c->d_u.p ? energy_reset(c) : SEMX_OK;
@@ -1319,12 +1315,12 @@ int set_sources_impl(semx_ctx* c, int nsrc, const int32_t* elem, const double* x
     if (nz) pts.push_back((int32_t)p);
   }
   if (pts.empty()) pts.push_back(0);
-  // the nodes that receive a source force in FP32, each with its (source,
+  // the nodes that receive a source force, each with its (source,
   // point) pairs in order: the injection's per-node sums
   std::vector<std::pair<int32_t, int32_t>> np_pairs;  // (node, s n3 + q)
   for (size_t p = 0; p < (size_t)nsrc * n3; ++p) {
     bool nz = false;
-    for (int d = 0; d < nc; ++d) nz |= wdir[p * nc + d] != 0.0f;
+    for (int d = 0; d < nc; ++d) nz |= wdir64[p * nc + d] != 0.0;
     if (nz) np_pairs.push_back({nodes[p], (int32_t)p});
   }
   std::sort(np_pairs.begin(), np_pairs.end());
@@ -1336,6 +1332,7 @@ int set_sources_impl(semx_ctx* c, int nsrc, const int32_t* elem, const double* x
   }
   c->h_src_nodes = snode;
   c->first_tl_dirty = true;
+  c->srcbits_dirty = true;
   sptr.push_back((int32_t)np_pairs.size());
   if (sidx.empty()) sidx.push_back(0);
   int rc = dev_alloc(c, c->src.nodes, nodes.size() * sizeof(int32_t));
@@ -1436,7 +1433,7 @@ int semx_destroy(semx_ctx* c) {
                     &c->rec.seis,
                     &c->src.wdir64, &c->src.stf64, &c->rec.wts64, &c->rec.seis64, &c->d_gam64, &c->d_mat64,
                     &c->d_minv64, &c->d_D64,
-                    &c->d_first, &c->d_aff})
+                    &c->d_first, &c->d_aff, &c->d_nptr, &c->d_nidx, &c->d_part, &c->d_srcbits, &c->d_clist})
     dev_free(*b);
   delete c;
   return SEMX_OK;
@@ -1464,6 +1461,8 @@ int semx_upload_mesh(semx_ctx* c, int64_t nspec, int64_t nglob, const int32_t* i
   int rc = set_device(c);
   if (rc) return rc;
   c->have_mesh = c->have_model = false;
+  c->user_colors = false;
+  c->f_in_part = false;
   // sources and receivers live in elements of the previous mesh
   c->src.nsrc = 0;
   c->src.nsn = 0;
@@ -1591,8 +1590,10 @@ int semx_set_coloring(semx_ctx* c, int ncolors, const int32_t* color_ptr, const 
   c->ncolors = ncolors;
   c->color_ptr.assign(color_ptr, color_ptr + ncolors + 1);
   c->elem_order.assign(elem_order, elem_order + c->nspec);
+  c->user_colors = true;
   // the device layout follows the colouring: rebuild it; the model must be uploaded again
   c->have_model = false;
+  c->f_in_part = false;
   return build_layout(c);
 }
 
@@ -1625,6 +1626,7 @@ int upload_model_impl(semx_ctx* c, int nmodels, const double* lambda, const doub
   int rc = set_device(c);
   if (rc) return rc;
   c->have_model = false;
+  c->f_in_part = false;
   c->nmodels = nmodels;
   c->vp_max = vpmax;
   DevBuf dl, dm, dr;
@@ -1642,6 +1644,11 @@ int upload_model_impl(semx_ctx* c, int nmodels, const double* lambda, const doub
   if (!rc) rc = dev_alloc(c, c->d_a, es * len);
   if (!rc) rc = dev_alloc(c, c->d_f, es * len);
   if (!rc) rc = dev_alloc(c, c->d_work, es * len);
+  // without room for the element-local forces the force runs colour by colour
+  if (!rc && (c->user_colors || dev_alloc(c, c->d_part, es * c->ncomp * npt) != SEMX_OK)) {
+    dev_free(c->d_part);
+    c->err.clear();
+  }
   if (!rc && c->storage == SEMX_F64) rc = dev_alloc(c, c->d_gam64, sizeof(double) * 9 * c->nspec * c->n3);
   if (!rc && c->storage != SEMX_F64)
     for (DevBuf* b : {&c->d_gam64, &c->d_mat64, &c->d_minv64}) dev_free(*b);
@@ -1654,21 +1661,8 @@ int upload_model_impl(semx_ctx* c, int nmodels, const double* lambda, const doub
   material_kernel<<<grid_for(npt, 8192), kThreads, 0, c->stream>>>(
       c->n3, c->nspec, nmodels, c->d_order.as<int32_t>(), dl.as<double>(), dm.as<double>(), dr.as<double>(),
       c->d_wdet.as<double>(), c->d_mat.as<float>(), c->d_wrho.as<float>());
-  fill_f64<<<grid_for(nmodels * c->nglob), kThreads, 0, c->stream>>>(c->d_mass64.as<double>(),
-                                                                     nmodels * c->nglob, 0.0);
-  // deterministic mass assembly, one coloured launch range at a time
-  if (c->ncolors > 0) {
-    for (const auto& L : c->colored_launches)
-      mass_color_kernel<<<grid_for((int64_t)nmodels * L.count * c->n3, 8192), kThreads, 0, c->stream>>>(
-          c->n3, c->nspec, c->nglob, nmodels, L.pos0, L.count, c->d_order.as<int32_t>(),
-          c->d_ibool.as<int32_t>(), dr.as<double>(), c->d_wdet.as<double>(), c->d_mass64.as<double>());
-  } else {
-    // no valid colouring (an element repeats a node): one thread walks the
-    // positions in order, which keeps the sum deterministic (tiny meshes only)
-    mass_serial_kernel<<<1, 1, 0, c->stream>>>(c->n3, c->nspec, c->nglob, nmodels, c->d_order.as<int32_t>(),
-                                               c->d_ibool.as<int32_t>(), dr.as<double>(), c->d_wdet.as<double>(),
-                                               c->d_mass64.as<double>());
-  }
+  e = launch_mass(c, dr.as<double>(), c->d_mass64.as<double>(), c->stream);
+  if (e != hipSuccess) { cleanup(); return hip_fail(c, e, "mass kernel launch"); }
   minv_kernel<<<grid_for(nmodels * c->nglob), kThreads, 0, c->stream>>>(nmodels * c->nglob,
                                                                         c->d_mass64.as<double>(),
                                                                         c->d_minv.as<float>());
@@ -1811,7 +1805,16 @@ int semx_force_skeleton(semx_ctx* c, const float* u_dev, float* f_dev, int reps,
   if (!u_dev || !f_dev || reps <= 0) return fail(c, SEMX_EINVAL, "force_skeleton: null pointer or reps <= 0");
   const int64_t len = state_len(c);
   if (u_dev < f_dev + len && f_dev < u_dev + len) return fail(c, SEMX_EINVAL, "force_skeleton: u and f overlap");
+  int rs = settle_force(c);
+  if (rs) return rs;
+  const bool parts = parts_active(c), colored = !parts && !blocks_active(c);
+  if (colored) {
+    int rc = build_colored(c);
+    if (rc) return rc;
+  }
   ForceArgs a = force_args(c, u_dev, f_dev, force_overwrites(c));
+  if (colored) a.list = c->d_clist.as<int32_t>();
+  if (parts) a.part = c->d_part.as<float>();
   auto pass = [&]() -> hipError_t {
     if (blocks_active(c)) {
       const int geo = c->blocks_irregular ? c->irregular_geo : kRegular;
@@ -1823,7 +1826,7 @@ int semx_force_skeleton(semx_ctx* c, const float* u_dev, float* f_dev, int reps,
       }
       return hipSuccess;
     }
-    for (const auto& L : c->colored_launches) {
+    for (const auto& L : colored ? c->colored_launches : c->kind_launches) {
       a.pos0 = L.pos0;
       a.count = L.count;
       const int geo = L.irregular ? c->irregular_geo : kRegular;
@@ -1831,7 +1834,7 @@ int semx_force_skeleton(semx_ctx* c, const float* u_dev, float* f_dev, int reps,
                                            : launch_force_skeleton(c->n, geo, L.naff, a, c->stream);
       if (e != hipSuccess) return e;
     }
-    return hipSuccess;
+    return parts ? launch_gather(c, f_dev, nullptr, c->stream) : hipSuccess;
   };
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipError_t e = pass();  // warm
@@ -2081,6 +2084,7 @@ int semx_set_state(semx_ctx* c, const float* u_dev, const float* v_dev, const fl
   if (rc) return rc;
   c->it = it;
   c->pending_correct = false;
+  c->f_in_part = false;
   c->run_gen++;  // earlier checkpoints belong to another run
   c->ckpt_count = 0;
   return energy_reset(c);
@@ -2213,6 +2217,7 @@ int semx_set_state_f64(semx_ctx* c, const double* u_dev, const double* v_dev, co
   SEMX_HIP(c, hipGetLastError());
   c->it = it;
   c->pending_correct = false;
+  c->f_in_part = false;
   return energy_reset(c);
 }
 

@@ -156,12 +156,26 @@ __device__ __forceinline__ void stress_flux(const float gr[3][3], float lamw, fl
 template <int N3>
 __device__ __forceinline__ bool first_touch(const ForceArgs& a, int pos) {
   constexpr int NW = (N3 + 31) / 32;
+  if (a.part) return true;  // nothing to add to: the node's points are summed afterwards
   if (!a.first) return false;
   const uint32_t* w = a.first + (size_t)pos * a.first_words;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const uint64_t lo = wave * 2 < NW ? w[wave * 2] : 0u;
   const uint64_t hi = wave * 2 + 1 < NW ? w[wave * 2 + 1] : 0u;
   return __builtin_amdgcn_inverse_ballot_w64(lo | (hi << 32));
+}
+
+// Launch position of the launch's element `grp`.
+__device__ __forceinline__ int elem_pos(const ForceArgs& a, int grp) {
+  return a.list ? a.list[a.pos0 + grp] : (int)a.pos0 + grp;
+}
+
+// The NC force components of local point q into the element-local forces.
+template <int NC>
+__device__ __forceinline__ void store_part(const ForceArgs& a, int model, int pos, int n3, int q, const float x[NC]) {
+  float* p = a.part + (((size_t)model * a.nspec + pos) * n3 + q) * NC;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) p[c] = x[c];
 }
 
 // Node number of local point pp of the element at launch position `pos`

@@ -132,18 +132,19 @@ __global__ __launch_bounds__(kT) void source_energy_kernel(int npt, int n3, int 
   source_energy_block<T>(npt, n3, nc, nstf, n, step, it0, pts, nodes, wdir, stf, u, hist, per, with_corr, acc, red);
 }
 
-// Receivers (FP32 storage): receiver r of model `model` is
+// Receivers: receiver r of model `model` is
 // sum_q l_q(x_r) u[node_q] per component (nc = 3 elastic, 1 acoustic),
 // stored as sample `it` of seis [nmodels][nrec][nc][nt_max].  One block of
 // kT lanes; the caller keeps samples outside [0, nt_max) away.
+template <class T>
 __device__ __forceinline__ void receiver_block(int r, int model, int nrec, int n3, int nc, int64_t nglob,
                                                int64_t nt_max, int64_t it, const int32_t* __restrict__ nodes,
-                                               const float* __restrict__ wts, const float* __restrict__ u,
-                                               float* __restrict__ seis, float (*red)[kT]) {
-  const float* um = u + (int64_t)model * nglob * nc;
-  float s[3] = {0.f, 0.f, 0.f};
+                                               const T* __restrict__ wts, const T* __restrict__ u,
+                                               T* __restrict__ seis, T (*red)[kT]) {
+  const T* um = u + (int64_t)model * nglob * nc;
+  T s[3] = {0, 0, 0};
   for (int q = threadIdx.x; q < n3; q += blockDim.x) {
-    const float wq = wts[(int64_t)r * n3 + q];
+    const T wq = wts[(int64_t)r * n3 + q];
     const int64_t g = nodes[(int64_t)r * n3 + q];
     for (int c = 0; c < nc; ++c) s[c] += wq * um[nc * g + c];
   }
@@ -164,16 +165,17 @@ __device__ __forceinline__ void receiver_block(int r, int model, int nrec, int n
 // thread per (model, source node, component) sums the (source, point) pairs
 // that reach the node in a fixed order, as the injection after a force pass
 // does, and stores the sum.
+template <class T>
 struct Prestore {
   int nsn;                    // source nodes; 0: nothing to store
   const int32_t* snode;       // [nsn] node numbers
   const int32_t* sptr;        // [nsn + 1]
   const int32_t* sidx;        // the points s n3 + q of each node
-  float* f;                   // [nmodels][nglob][nc]
+  T* f;                       // [nmodels][nglob][nc]
   int nmodels;
 };
 
-// The per-step bookkeeping before the force pass (FP32 storage), one launch
+// The per-step bookkeeping before the force pass, one launch
 // after the Newmark pass: blocks x < nrec_blocks record receiver x of model
 // y (sample it, or *step for graph-captured steps; nothing outside
 // [0, nt_max)); block x = nrec_blocks of row y = 0, when `src` is set, is
@@ -181,28 +183,29 @@ struct Prestore {
 // of sample it + 1 (P.nsn > 0).  All of them read u^{n+1}, which the force
 // pass that follows leaves alone; the stores to f touch only source nodes,
 // which nothing else in the launch reads.
+template <class T>
 __global__ __launch_bounds__(kT) void step_aux_kernel(int nrec_blocks, int nrec, int n3, int nc, int64_t nglob,
                                                       int64_t nt_max, int64_t it, const int64_t* step,
                                                       const int32_t* __restrict__ rnodes,
-                                                      const float* __restrict__ rwts, float* __restrict__ seis,
+                                                      const T* __restrict__ rwts, T* __restrict__ seis,
                                                       int src, int npt, int64_t nstf, int64_t it0,
                                                       const int32_t* __restrict__ pts,
                                                       const int32_t* __restrict__ snodes,
-                                                      const float* __restrict__ wdir, const float* __restrict__ stf,
-                                                      float* hist, size_t per, int with_corr,
-                                                      double* __restrict__ acc, const float* __restrict__ u,
-                                                      Prestore P) {
-  __shared__ float rred[3][kT];
+                                                      const T* __restrict__ wdir, const T* __restrict__ stf,
+                                                      T* hist, size_t per, int with_corr,
+                                                      double* __restrict__ acc, const T* __restrict__ u,
+                                                      Prestore<T> P) {
+  __shared__ T rred[3][kT];
   __shared__ double ered[kT];
   if ((int)blockIdx.x < nrec_blocks) {
     if (step) it = *step;
     if (it < 0 || it >= nt_max) return;  // uniform over the block
-    receiver_block(blockIdx.x, blockIdx.y, nrec, n3, nc, nglob, nt_max, it, rnodes, rwts, u, seis, rred);
+    receiver_block<T>(blockIdx.x, blockIdx.y, nrec, n3, nc, nglob, nt_max, it, rnodes, rwts, u, seis, rred);
     return;
   }
   if (blockIdx.y != 0) return;
   if (src && (int)blockIdx.x == nrec_blocks) {
-    source_energy_block<float>(npt, n3, nc, nstf, it, step, it0, pts, snodes, wdir, stf, u, hist, per, with_corr,
+    source_energy_block<T>(npt, n3, nc, nstf, it, step, it0, pts, snodes, wdir, stf, u, hist, per, with_corr,
                                acc, ered);
     return;
   }
@@ -212,10 +215,10 @@ __global__ __launch_bounds__(kT) void step_aux_kernel(int nrec_blocks, int nrec,
   if (t >= P.nmodels * per_m) return;
   const int64_t r = t % per_m;
   const int i = (int)(r / nc), cc = (int)(r % nc);
-  float sum = 0.0f;
+  T sum = 0;
   for (int k = P.sptr[i]; k < P.sptr[i + 1]; ++k) {
     const int p = P.sidx[k];
-    const float amp = (m >= 0 && m < nstf) ? stf[(int64_t)(p / n3) * nstf + m] : 0.0f;
+    const T amp = (m >= 0 && m < nstf) ? stf[(int64_t)(p / n3) * nstf + m] : (T)0;
     sum += amp * wdir[(int64_t)nc * p + cc];
   }
   P.f[((t / per_m) * nglob + P.snode[i]) * nc + cc] = sum;
@@ -287,28 +290,41 @@ int energy_reset(semx_ctx* c) {
   return SEMX_OK;
 }
 
-int step_aux(semx_ctx* c, int64_t n, bool with_corr, bool record, const int64_t* dstep, bool prestore) {
+namespace {
+
+template <class T>
+int step_aux_t(semx_ctx* c, int64_t n, bool with_corr, bool record, const int64_t* dstep, bool prestore, const T* rwts,
+               T* seis, const T* wdir, const T* stf) {
   const bool src = c->src.nsrc > 0 && c->d_ehist.p != nullptr;
   const bool rec = record && c->rec.nrec > 0 && (dstep || (n >= 0 && n < c->rec.nt_max));
   const bool pre = prestore && c->src.nsrc > 0 && c->src.nsn > 0;
   if (!src && !rec && !pre) return SEMX_OK;
   const int nrb = rec ? c->rec.nrec : 0;
-  Prestore P{};
+  Prestore<T> P{};
   int npb = 0;
   if (pre) {
-    P = {c->src.nsn, c->src.snode.as<int32_t>(), c->src.sptr.as<int32_t>(), c->src.sidx.as<int32_t>(),
-         c->d_f.as<float>(), c->nmodels};
+    P = {c->src.nsn, c->src.snode.as<int32_t>(), c->src.sptr.as<int32_t>(), c->src.sidx.as<int32_t>(), c->d_f.as<T>(),
+         c->nmodels};
     npb = (int)(((int64_t)c->nmodels * c->src.nsn * c->ncomp + kT - 1) / kT);
   }
   dim3 grid(nrb + (src ? 1 : 0) + npb, rec ? c->nmodels : 1);
   const size_t per = (size_t)c->src.npts * c->ncomp;
-  step_aux_kernel<<<grid, kT, 0, c->stream>>>(
-      nrb, c->rec.nrec, c->n3, c->ncomp, c->nglob, c->rec.nt_max, n, dstep, c->rec.nodes.as<int32_t>(),
-      c->rec.wts.as<float>(), c->rec.seis.as<float>(), src ? 1 : 0, c->src.npts, c->src.nstf, c->energy_it0,
-      c->src.pts.as<int32_t>(), c->src.nodes.as<int32_t>(), c->src.wdir.as<float>(), c->src.stf.as<float>(),
-      c->d_ehist.as<float>(), per, with_corr ? 1 : 0, c->d_eacc.as<double>(), c->d_u.as<float>(), P);
+  step_aux_kernel<T><<<grid, kT, 0, c->stream>>>(
+      nrb, c->rec.nrec, c->n3, c->ncomp, c->nglob, c->rec.nt_max, n, dstep, c->rec.nodes.as<int32_t>(), rwts, seis,
+      src ? 1 : 0, c->src.npts, c->src.nstf, c->energy_it0, c->src.pts.as<int32_t>(), c->src.nodes.as<int32_t>(), wdir,
+      stf, c->d_ehist.as<T>(), per, with_corr ? 1 : 0, c->d_eacc.as<double>(), c->d_u.as<T>(), P);
   SEMX_HIP(c, hipGetLastError());
   return SEMX_OK;
+}
+
+}  // namespace
+
+int step_aux(semx_ctx* c, int64_t n, bool with_corr, bool record, const int64_t* dstep, bool prestore) {
+  if (c->storage == SEMX_F64)
+    return step_aux_t<double>(c, n, with_corr, record, dstep, prestore, c->rec.wts64.as<double>(),
+                              c->rec.seis64.as<double>(), c->src.wdir64.as<double>(), c->src.stf64.as<double>());
+  return step_aux_t<float>(c, n, with_corr, record, dstep, prestore, c->rec.wts.as<float>(), c->rec.seis.as<float>(),
+                           c->src.wdir.as<float>(), c->src.stf.as<float>());
 }
 
 int energy_source_step(semx_ctx* c, int64_t n, bool with_corr, const int64_t* dstep) {

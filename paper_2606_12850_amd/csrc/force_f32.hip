@@ -49,7 +49,7 @@ __global__ __launch_bounds__(Shape<NG>::BLK) void force_f32_kernel(ForceArgs a) 
   const int ngrp = (int)a.count;
   const int grp = xcd_group(ngrp);
   if (grp >= ngrp) return;  // uniform over the block
-  const int pos = (int)a.pos0 + grp;
+  const int pos = elem_pos(a, grp);
 
   const int p = threadIdx.x;
   const bool act = p < N3;
@@ -150,7 +150,9 @@ __global__ __launch_bounds__(Shape<NG>::BLK) void force_f32_kernel(ForceArgs a) 
       }
     } else {
       const float out[3] = {fo[0] + F[0], fo[1] + F[1], fo[2] + F[2]};
-      if constexpr (AFF) {
+      if (a.part) {
+        store_part<3>(a, model, pos, N3, p, out);
+      } else if constexpr (AFF) {
         store_affine<3>(sp, out);
       } else {
         float* fg = f + 3 * (size_t)g;
@@ -199,7 +201,7 @@ __global__ __launch_bounds__(Shape<NG>::BLK) void force_skeleton_kernel(ForceArg
   if (grp >= ngrp) return;  // uniform over the block
   const int p = threadIdx.x;
   if (p >= N3) return;
-  const int pos = (int)a.pos0 + grp;
+  const int pos = elem_pos(a, grp);
   const int model = blockIdx.y;
   const float* __restrict__ u = a.u + (size_t)model * a.nglob * 3;
   float* f = a.f + (size_t)model * a.nglob * 3;
@@ -222,7 +224,8 @@ __global__ __launch_bounds__(Shape<NG>::BLK) void force_skeleton_kernel(ForceArg
     gather_affine<3>(sp, uo);
     prior_force_affine<3>(sp, first_touch<N3>(a, pos), fo);
     const float out[3] = {fo[0] + s * uo[0], fo[1] + s * uo[1], fo[2] + s * uo[2]};
-    store_affine<3>(sp, out);
+    if (a.part) store_part<3>(a, model, pos, N3, p, out);
+    else store_affine<3>(sp, out);
   } else {
     const int g = node_of<NG>(a, pos, p);
     uo[0] = u[3 * (size_t)g + 0];
@@ -233,7 +236,7 @@ __global__ __launch_bounds__(Shape<NG>::BLK) void force_skeleton_kernel(ForceArg
       fo[1] = f[3 * (size_t)g + 1];
       fo[2] = f[3 * (size_t)g + 2];
     }
-    float* fg = f + 3 * (size_t)g;
+    float* fg = a.part ? a.part + (((size_t)model * a.nspec + pos) * N3 + p) * 3 : f + 3 * (size_t)g;
     fg[0] = fo[0] + s * uo[0];
     fg[1] = fo[1] + s * uo[1];
     fg[2] = fo[2] + s * uo[2];

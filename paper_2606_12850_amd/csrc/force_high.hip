@@ -66,7 +66,7 @@ __global__ __launch_bounds__(ColShape<NG>::BLK) __attribute__((amdgpu_waves_per_
   const int ngrp = (int)a.count;
   const int grp = xcd_group(ngrp);
   if (grp >= ngrp) return;  // uniform over the block
-  const int pos = (int)a.pos0 + grp;
+  const int pos = elem_pos(a, grp);
 
   const int l = threadIdx.x;
   const bool act = l < N2;
@@ -243,7 +243,10 @@ __global__ __launch_bounds__(ColShape<NG>::BLK) __attribute__((amdgpu_waves_per_
         unsafeAtomicAdd(fg + 2, -acc[2][k]);
       } else {
         const bool first = a.first && ((a.first[(size_t)pos * a.first_words + (q >> 5)] >> (q & 31)) & 1u);
-        if (first) {
+        if (a.part) {
+          const float out[3] = {-acc[0][k], -acc[1][k], -acc[2][k]};
+          store_part<3>(a, model, pos, N3, q, out);
+        } else if (first) {
           fg[0] = -acc[0][k];
           fg[1] = -acc[1][k];
           fg[2] = -acc[2][k];
@@ -293,7 +296,7 @@ __global__ __launch_bounds__(ColShape<NG>::BLK) void force_col_skeleton_kernel(F
   const int ngrp = (int)a.count;
   const int grp = xcd_group(ngrp);
   if (grp >= ngrp) return;  // uniform over the block
-  const int pos = (int)a.pos0 + grp;
+  const int pos = elem_pos(a, grp);
   const int l = threadIdx.x;
   const int model = blockIdx.y;
   const float* __restrict__ u = a.u + (size_t)model * a.nglob * 3;
@@ -320,8 +323,8 @@ __global__ __launch_bounds__(ColShape<NG>::BLK) void force_col_skeleton_kernel(F
       for (int d = 0; d < 9; ++d) m += ldnt(gp + d * N3);
     }
     const float x0 = u[3 * (size_t)g + 0], x1 = u[3 * (size_t)g + 1], x2 = u[3 * (size_t)g + 2];
-    float* fg = f + 3 * (size_t)g;
-    const bool first = a.first && ((a.first[(size_t)pos * a.first_words + (q >> 5)] >> (q & 31)) & 1u);
+    float* fg = a.part ? a.part + (((size_t)model * a.nspec + pos) * N3 + q) * 3 : f + 3 * (size_t)g;
+    const bool first = a.part || (a.first && ((a.first[(size_t)pos * a.first_words + (q >> 5)] >> (q & 31)) & 1u));
     if (first) {
       fg[0] = m * x0;
       fg[1] = m * x1;

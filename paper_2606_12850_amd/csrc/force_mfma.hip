@@ -169,7 +169,7 @@ __global__ __launch_bounds__(Shape<NG>::BLK) void force_mfma_kernel(ForceArgs a)
 
   const int grp = xcd_group((int)a.count);
   if (grp >= a.count) return;
-  const int pos = (int)a.pos0 + grp;
+  const int pos = elem_pos(a, grp);
   const int p = threadIdx.x;
   const bool act = p < N3;
   const int pp = act ? p : 0;
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(Shape<NG>::BLK) void force_mfma_kernel(ForceArgs a)
   float uu[3], f0[3] = {0.f, 0.f, 0.f};
   bool first = false;  // first point to reach its node in launch order: store, no read
   if constexpr (!ATOMIC)
-    if (a.first) first = (a.first[(size_t)pos * a.first_words + (pp >> 5)] >> (pp & 31)) & 1u;
+    first = a.part || (a.first && ((a.first[(size_t)pos * a.first_words + (pp >> 5)] >> (pp & 31)) & 1u));
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     uu[c] = u[3 * (size_t)g + c];
@@ -288,6 +288,8 @@ __global__ __launch_bounds__(Shape<NG>::BLK) void force_mfma_kernel(ForceArgs a)
       unsafeAtomicAdd(fg + 0, F[0]);
       unsafeAtomicAdd(fg + 1, F[1]);
       unsafeAtomicAdd(fg + 2, F[2]);
+    } else if (a.part) {
+      store_part<3>(a, model, pos, N3, pp, F);
     } else {
       fg[0] = f0[0] + F[0];
       fg[1] = f0[1] + F[1];

@@ -304,9 +304,9 @@ __global__ __launch_bounds__(kBlk) void force_tile16_kernel(ForceArgs a) {
   }
 
   Ahead cur;
-  if constexpr (AHEAD) load_ahead<NG, ATOMIC, AFF, MAT_AHEAD, NC>(a, u, model, (int)a.pos0 + grp, P, g, c, w, cur);
+  if constexpr (AHEAD) load_ahead<NG, ATOMIC, AFF, MAT_AHEAD, NC>(a, u, model, elem_pos(a, grp), P, g, c, w, cur);
   for (;;) {
-    const int pos = (int)a.pos0 + grp;
+    const int pos = elem_pos(a, grp);
     if constexpr (!AHEAD) load_ahead<NG, ATOMIC, AFF, true, NC>(a, u, model, pos, P, g, c, w, cur);
     if constexpr (AHEAD && !MAT_AHEAD) load_mat<NG>(a, model, pos, P, cur);
     float fo[3][4];
@@ -314,7 +314,7 @@ __global__ __launch_bounds__(kBlk) void force_tile16_kernel(ForceArgs a) {
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         fo[0][t] = fo[1][t] = fo[2][t] = 0.0f;
-        if (!ATOMIC && P.real(t) && !((cur.fw >> t) & 1u)) {  // the point's values in one request
+        if (!ATOMIC && !a.part && P.real(t) && !((cur.fw >> t) & 1u)) {  // the point's values in one request
           const float* fp = f + NC * (size_t)cur.node[t];
 #pragma unroll
           for (int e = 0; e < NC; ++e) fo[e][t] = fp[e];
@@ -507,7 +507,7 @@ __global__ __launch_bounds__(kBlk) void force_tile16_kernel(ForceArgs a) {
     const bool more = AHEAD && nxt < xend;  // uniform over the block
     Ahead ahead;
     if constexpr (AHEAD) {
-      if (more) load_ahead<NG, ATOMIC, AFF, MAT_AHEAD, NC>(a, u, model, (int)a.pos0 + nxt, P, g, c, w, ahead);
+      if (more) load_ahead<NG, ATOMIC, AFF, MAT_AHEAD, NC>(a, u, model, elem_pos(a, nxt), P, g, c, w, ahead);
     }
     __syncthreads();  // B3: eta fluxes in R0, zeta fluxes in R2; R1 free
     if constexpr (LOW) {
@@ -557,7 +557,8 @@ __global__ __launch_bounds__(kBlk) void force_tile16_kernel(ForceArgs a) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       if (!P.real(t)) continue;
-      float* fg = f + NC * (size_t)cur.node[t];
+      float* fg = !ATOMIC && a.part ? a.part + (((size_t)model * a.nspec + pos) * E3 + P.q(t)) * NC
+                                    : f + NC * (size_t)cur.node[t];
 #pragma unroll
       for (int e = 0; e < NC; ++e) {
         if constexpr (ATOMIC) unsafeAtomicAdd(fg + e, -F[e][t]);

@@ -16,23 +16,22 @@
 // atomic adds).
 #include <hip/hip_runtime.h>
 
+#include "newmark.hpp"
 #include "semx_internal.hpp"
 
 namespace semx {
 namespace {
 
 constexpr int kT = 256;
-constexpr int kCorrect = 1, kPredict = 2, kStoreA = 4, kKeepF = 8;
-
 template <int NG>
-__global__ void force64_kernel(int64_t pos0, int64_t nspec, int64_t nglob, int atomic,
+__global__ void force64_kernel(int64_t pos0, const int32_t* __restrict__ list, int64_t nspec, int64_t nglob, int atomic,
                                const int32_t* __restrict__ ibool, const double* __restrict__ gam,
                                const double* __restrict__ mat, const double* __restrict__ Dg,
-                               const double* __restrict__ u, double* __restrict__ f) {
+                               const double* __restrict__ u, double* __restrict__ f, double* __restrict__ part) {
   constexpr int n3 = NG * NG * NG;
   __shared__ double D[NG * NG];  // D[a * NG + b] = l'_b(xi_a)
   __shared__ double s[3][n3];
-  const int64_t pos = pos0 + blockIdx.x;
+  const int64_t pos = list ? list[pos0 + blockIdx.x] : pos0 + blockIdx.x;
   const int64_t model = blockIdx.y;
   const int q = threadIdx.x;
   for (int t = q; t < NG * NG; t += blockDim.x) D[t] = Dg[t];
@@ -105,8 +104,12 @@ __global__ void force64_kernel(int64_t pos0, int64_t nspec, int64_t nglob, int a
     }
   }
   if (live) {
-    double* fm = f + (model * nglob + g) * 3;
-    if (atomic) {
+    double* fm = part ? part + ((model * nspec + pos) * n3 + q) * 3 : f + (model * nglob + g) * 3;
+    if (part) {
+      fm[0] = F[0];
+      fm[1] = F[1];
+      fm[2] = F[2];
+    } else if (atomic) {
       atomicAdd(fm + 0, F[0]);
       atomicAdd(fm + 1, F[1]);
       atomicAdd(fm + 2, F[2]);
@@ -262,12 +265,14 @@ hipError_t launch_force64_n(const semx_ctx* c, const double* u, double* f) {
   constexpr int n3 = NG * NG * NG;
   const unsigned threads = (unsigned)((n3 + 63) / 64 * 64);
   const bool atomic = c->assembly == SEMX_ASM_ATOMIC;
-  for (const auto& L : atomic ? c->atomic_launches : c->colored_launches) {
+  const bool parts = parts_active(c), colored = !atomic && !parts;
+  for (const auto& L : colored ? c->colored_launches : c->kind_launches) {
     if (L.count <= 0) continue;
     dim3 grid((unsigned)L.count, (unsigned)c->nmodels);
-    force64_kernel<NG><<<grid, threads, 0, c->stream>>>(L.pos0, c->nspec, c->nglob, atomic ? 1 : 0,
-                                                        c->d_ibool.as<int32_t>(), c->d_gam64.as<double>(),
-                                                        c->d_mat64.as<double>(), c->d_D64.as<double>(), u, f);
+    force64_kernel<NG><<<grid, threads, 0, c->stream>>>(
+        L.pos0, colored ? c->d_clist.as<int32_t>() : nullptr, c->nspec, c->nglob, atomic ? 1 : 0,
+        c->d_ibool.as<int32_t>(), c->d_gam64.as<double>(), c->d_mat64.as<double>(), c->d_D64.as<double>(), u, f,
+        parts ? c->d_part.as<double>() : nullptr);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -336,6 +341,18 @@ int f64_model_setup(semx_ctx* c, const double* lam_dev, const double* mu_dev) {
 }
 
 int f64_force_into(semx_ctx* c, const double* u, double* f, bool f_zeroed) {
+  int rs = settle_force(c);
+  if (rs) return rs;
+  if (parts_active(c)) {
+    hipError_t e = launch_force64(c, u, f);
+    if (e == hipSuccess) e = launch_gather64(c, f, nullptr, c->stream);
+    if (e != hipSuccess) return hip_fail(c, e, "FP64 force kernel launch");
+    return SEMX_OK;
+  }
+  if (c->assembly != SEMX_ASM_ATOMIC) {
+    int rc = build_colored(c);
+    if (rc) return rc;
+  }
   if (!f_zeroed) {
     int rc = zero64(c, f, len64(c));
     if (rc) return rc;
@@ -347,6 +364,8 @@ int f64_force_into(semx_ctx* c, const double* u, double* f, bool f_zeroed) {
 
 int f64_finalize(semx_ctx* c) {
   if (!c->pending_correct) return SEMX_OK;
+  int rc = settle_force(c);
+  if (rc) return rc;
   const int64_t nn = (int64_t)c->nmodels * c->nglob;
   newmark64_kernel<kCorrect | kStoreA><<<grid_1d(3 * nn), kT, 0, c->stream>>>(
       nn, c->dt, c->d_minv64.as<double>(), c->d_u.as<double>(), c->d_v.as<double>(), c->d_a.as<double>(),
@@ -386,6 +405,7 @@ int f64_step_once(semx_ctx* c, bool record) {
   double *u = c->d_u.as<double>(), *v = c->d_v.as<double>(), *a = c->d_a.as<double>(), *f = c->d_f.as<double>();
   const double* minv = c->d_minv64.as<double>();
   const bool track = c->track_energy;
+  const bool keep = track || parts_active(c);  // the gather overwrites f
   c->track_energy = false;
   // a tracked step keeps f^n through the Newmark pass for the potential
   // term, or computes -K u^n into the work vector when no force is pending
@@ -395,11 +415,20 @@ int f64_step_once(semx_ctx* c, bool record) {
     if (rc) return rc;
     f_pe = c->d_work.as<double>();
   }
-  if (c->pending_correct) {
-    if (track) newmark64_kernel<kCorrect | kPredict | kKeepF><<<grid_1d(3 * nn), kT, 0, c->stream>>>(nn, c->dt, minv, u, v, a, f);
+  const bool parts = parts_active(c);
+  if (track || !parts) {  // the energy pass reads f^n; other passes need f summed or cleared
+    int rc = settle_force(c);
+    if (rc) return rc;
+  }
+  if (c->f_in_part) {
+    c->f_in_part = false;
+    const hipError_t e = launch_newmark_parts64(c, c->part_src ? c->d_srcbits.as<uint32_t>() : nullptr, c->stream);
+    if (e != hipSuccess) return hip_fail(c, e, "Newmark pass launch");
+  } else if (c->pending_correct) {
+    if (keep) newmark64_kernel<kCorrect | kPredict | kKeepF><<<grid_1d(3 * nn), kT, 0, c->stream>>>(nn, c->dt, minv, u, v, a, f);
     else newmark64_kernel<kCorrect | kPredict><<<grid_1d(3 * nn), kT, 0, c->stream>>>(nn, c->dt, minv, u, v, a, f);
   } else {
-    if (track) newmark64_kernel<kPredict | kKeepF><<<grid_1d(3 * nn), kT, 0, c->stream>>>(nn, c->dt, minv, u, v, a, f);
+    if (keep) newmark64_kernel<kPredict | kKeepF><<<grid_1d(3 * nn), kT, 0, c->stream>>>(nn, c->dt, minv, u, v, a, f);
     else newmark64_kernel<kPredict><<<grid_1d(3 * nn), kT, 0, c->stream>>>(nn, c->dt, minv, u, v, a, f);
   }
   SEMX_HIP(c, hipGetLastError());
@@ -408,11 +437,25 @@ int f64_step_once(semx_ctx* c, bool record) {
     int rc = energy_track(c, f_pe, src_in_f);
     if (rc) return rc;
   }
-  int rc = energy_source_step(c, c->it, track && src_in_f);
-  if (!rc) rc = f64_force_into(c, u, f, !track);
-  if (!rc) rc = inject64(c, c->it + 1, f);
-  if (!rc && record) rc = record64(c, c->it);
-  if (rc) return rc;
+  int rc = SEMX_OK;
+  if (parts) {
+    // receivers, source work and the coming source force read u^{n+1}, which
+    // the force pass leaves alone: one launch before it
+    const bool pre = prestores(c);
+    if (pre) rc = build_first_tl(c);
+    if (!rc) rc = step_aux(c, c->it, track && src_in_f, record, nullptr, pre);
+    if (rc) return rc;
+    const hipError_t e = launch_force64(c, u, f);
+    if (e != hipSuccess) return hip_fail(c, e, "FP64 force kernel launch");
+    c->f_in_part = true;
+    c->part_src = pre;
+  } else {
+    rc = energy_source_step(c, c->it, track && src_in_f);
+    if (!rc) rc = f64_force_into(c, u, f, !track);
+    if (!rc) rc = inject64(c, c->it + 1, f);
+    if (!rc && record) rc = record64(c, c->it);
+    if (rc) return rc;
+  }
   c->it++;
   c->pending_correct = true;
   if (track) c->energy_it = c->it;

@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <array>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -32,12 +33,26 @@ struct DevBuf {
 };
 
 // One force launch: a contiguous range of launch positions (elements of one
-// colour and one geometry kind, or of one kind for atomic assembly).
+// geometry kind) or, for a pass colour by colour, of the colour list
+// (elements of one colour and one kind).
 struct Launch {
   int64_t pos0 = 0;
   int64_t count = 0;
   bool irregular = false;  // geometry path: kRegular, else the context's irregular path
   int64_t naff = 0;        // leading elements whose node numbers are affine in (i, j, k)
+};
+
+// Division of x < 2^31 by a constant: (mulhi(x, m) + x) >> s.
+struct FastDiv {
+  uint32_t m, s;
+};
+
+// A box of elements on one node lattice (gather.hip); n = 0: the mesh is none.
+struct Lattice {
+  int n = 0;
+  int Gx, Gy, nex, ney, nez;  // nodes per row and rows per plane; elements per axis
+  uint32_t txs, ntx, nty, ntiles;  // blocks of 2^txs x (256 >> txs) nodes, tiles per row, column and in all
+  FastDiv dn, drow, dplane;   // by n - 1, ntx, ntx nty
 };
 
 struct SourceSet {
@@ -100,7 +115,8 @@ struct semx_ctx {
   std::vector<int32_t> h_elem_vert;
   std::vector<double> h_vert;
   // per-element device arrays are stored by launch position; h_order[pos] =
-  // element, positions sorted by (geometry kind, colour, element)
+  // element, positions sorted by (geometry kind, affine numbering first,
+  // element): neighbours in the mesh are neighbours in memory
   std::vector<int32_t> h_order;
   semx::DevBuf d_order;     // int32 [nspec]
   std::vector<float> h_gam_el;  // [nspec][9] per-element Gamma of regular elements (user order)
@@ -118,7 +134,27 @@ struct semx_ctx {
   int64_t nregular = 0, nirregular = 0;
   double hmin = 0.0;               // min distance between adjacent GLL points
 
-  // first touch of each node in coloured launch order, per launch position:
+  // the points of each node: ids pos * n3 + q in the order in which a pass
+  // colour by colour reaches them, at d_nidx[d_nptr[g] .. d_nptr[g + 1])
+  semx::DevBuf d_nptr;  // int32 [nglob + 1]
+  semx::DevBuf d_nidx;  // int32 [nspec * n3]
+  std::vector<semx::Launch> kind_launches;  // whole mesh: regular, irregular elements
+  // element-local forces of one pass, [nmodels][nspec][n3][ncomp] in the
+  // storage precision; without it (no memory left) and with a colouring given
+  // by the caller the force runs colour by colour
+  semx::DevBuf d_part;
+  semx::Lattice lattice;
+  // the pending force f^n lies in d_part (and, where part_src, in f at the
+  // source nodes) and has not been summed into f
+  bool f_in_part = false, part_src = false;
+  bool user_colors = false;
+  // one bit per node that receives a source force (the time loop's gather
+  // starts those nodes from the source force stored in f)
+  semx::DevBuf d_srcbits;
+  bool srcbits_dirty = true;
+
+  // first touch of each node in coloured launch order, per launch position
+  // (built when a pass first runs colour by colour):
   // bit q of d_first[pos * first_words + q / 32] set when local point q is the
   // first to reach its node; elem_cover = every node is reached by an element
   semx::DevBuf d_first;
@@ -140,8 +176,9 @@ struct semx_ctx {
   // colouring
   int ncolors = 0;
   std::vector<int32_t> color_ptr, elem_order;
-  std::vector<semx::Launch> colored_launches;  // per colour: regular then irregular
-  std::vector<semx::Launch> atomic_launches;   // regular list, irregular list
+  std::vector<semx::Launch> colored_launches;  // ranges of d_clist, per colour: regular then irregular
+  std::vector<int32_t> h_clist;                // launch positions, colour by colour
+  semx::DevBuf d_clist;
   // 2 x 2 x 2 element blocks (FP32 elastic force, NGLL <= 5, coloured):
   // built when every element is affine-numbered with common strides, of one
   // geometry kind, and belongs to a block; nblocks = 0 otherwise
@@ -246,6 +283,8 @@ struct ForceArgs {
                          // reach their node first in launch order (store, no read), or null
   int first_words;       // 32-bit words per position in `first`
   int excl_interior;     // atomic assembly: element-interior points own their nodes (plain store)
+  const int32_t* list;   // the launch's elements are list[pos0 ..] (colour by colour), or null: pos0 ..
+  float* part;           // element-local forces [nmodels][nspec][n3][ncomp]: store there, f is not touched; or null
   int64_t pos0;          // first launch position of this launch
   int64_t count;
   int64_t nspec, nglob;
@@ -316,7 +355,6 @@ bool mfma_supported(int n, int prec);
 // (the step-indexed kernels read it; the step advances it), else null.
 int step_once(semx_ctx* c, bool record, float* seg_u = nullptr, float* seg_a = nullptr,
               const int64_t* dstep = nullptr);
-int apply_force_accumulate(semx_ctx* c, const float* u, float* f);
 int fill_zero(semx_ctx* c, float* p, int64_t n);
 // Apply the pending correction (a = M^{-1} f, v += dt/2 a); seg_a, if given,
 // receives a as well.
@@ -324,6 +362,29 @@ int complete_step(semx_ctx* c, float* seg_a = nullptr);
 unsigned grid_1d(int64_t n, int cap = 1 << 16);
 // adjoint.hip
 int save_checkpoint(semx_ctx* c);
+// The force runs as one launch per geometry kind into d_part, then a gather.
+bool parts_active(const semx_ctx* c);
+// Sums a pending force that lies in d_part into f (before d_part, f, the
+// sources or the state change otherwise).
+int settle_force(semx_ctx* c);
+// The time loop stores the source force into f before the force pass.
+bool prestores(const semx_ctx* c);
+int build_first_tl(semx_ctx* c);
+// Tables of a pass colour by colour on the device (no-op once built).
+int build_colored(semx_ctx* c);
+
+// gather.hip: node tables, and the sum of the element-local forces per node
+int build_node_points(semx_ctx* c);
+void find_lattice(semx_ctx* c, const std::vector<std::array<int32_t, 4>>& aff);
+// f[model][g][c] = sum over the node's points of part, in their order; a node without points gets 0.  srcbits: nodes whose sum starts from
+// the value f holds, or null.
+hipError_t launch_gather(const semx_ctx* c, float* f, const uint32_t* srcbits, hipStream_t s);
+hipError_t launch_gather64(const semx_ctx* c, double* f, const uint32_t* srcbits, hipStream_t s);
+// One Newmark step (correct, predict) whose force is the nodal sum of part.
+hipError_t launch_newmark_parts(const semx_ctx* c, const uint32_t* srcbits, float* seg_u, float* seg_a, hipStream_t s);
+hipError_t launch_newmark_parts64(const semx_ctx* c, const uint32_t* srcbits, hipStream_t s);
+// mass[model][g] = sum over the node's points of rho wdet (rho by element, wdet by position)
+hipError_t launch_mass(const semx_ctx* c, const double* rho, double* mass, hipStream_t s);
 
 // scratch layout: [0..7] doubles for reductions, then int flags
 inline double* scratch_doubles(semx_ctx* c) { return c->d_scratch.as<double>(); }
