@@ -803,6 +803,7 @@ ForceArgs force_args(const semx_ctx* c, const float* u, float* f, bool first_tou
   a.u = u;
   a.f = f;
   a.D = c->d_D.as<float>();
+  a.eo = c->d_eo.as<float>();
   a.Dh = c->d_Dh.p;
   a.nspec = c->nspec;
   a.nglob = c->nglob;
@@ -918,6 +919,30 @@ int build_colored(semx_ctx* c) {
 
 namespace {
 
+// True when a launch of geometry path `geo` runs on the line kernel
+// (force_line.hpp), FP32 with element-local forces.  Where the lines lie
+// (us per apply, line / kernel it replaces, 2e5 and 3e6 nodes):
+//   * from 2^18 points, a chip's worth of lines: below, a line's longer chain
+//     costs more than its fewer instructions give (NGLL 5, 4^3: 8.1 / 8.2,
+//     NGLL 10, 2^3: 13 / 10.5; NGLL 5, 15^3 10.6 / 11.6; 36^3 trilinear
+//     62 / 84; NGLL 8, 21^3 53 / 78);
+//   * at NGLL 2 and from 11 at any size: 8 points leave seven eighths of the
+//     per-point kernel's lanes idle (58^3: 19 / 60), and the slices of the
+//     column kernel follow each other (NGLL 11, one element: 11 / 24, 14^3:
+//     54 / 90; NGLL 12, 13^3: 70 / 99 for the padded tile);
+//   * stored geometry at NGLL 3-5 stays on the per-point kernel, whose many
+//     small workgroups keep more of the 36 bytes a point in flight (NGLL 4,
+//     48^3: 101 / 94, NGLL 6, 29^3: 94 / 107);
+//   * a run with checkpoints stays on the kernels whose arithmetic the
+//     adjoint repeats point by point, so that forward and adjoint apply the
+//     same discrete operator to the bit.
+bool use_line(const semx_ctx* c, bool parts, int geo) {
+  if (!parts || c->contraction != SEMX_C_F32 || c->n > kLineMaxN || c->ckpt_every > 0) return false;
+  if (c->n == 2 || c->n > kMaxNLow) return true;
+  if (geo == kStored && c->n <= 5) return false;
+  return (int64_t)c->nmodels * c->nspec * c->n3 >= (1 << 18);
+}
+
 // `tl`: the time loop's pass after the source force was stored into f
 // (prestores()): the first-touch bits with the source nodes cleared.
 int force_accumulate(semx_ctx* c, const float* u, float* f, bool first_touch = false, bool f_zero = false,
@@ -961,7 +986,10 @@ int force_accumulate(semx_ctx* c, const float* u, float* f, bool first_touch = f
     a.count = L.count;
     hipError_t e;
     const int geo = L.irregular ? c->irregular_geo : kRegular;
-    if (c->physics == SEMX_ACOUSTIC && c->n >= kTileMinNAcoustic)
+    if (use_line(c, parts, geo))
+      e = c->physics == SEMX_ACOUSTIC ? launch_force_line_acoustic(c->n, geo, L.naff, a, c->stream)
+                                      : launch_force_line(c->n, geo, L.naff, a, c->stream);
+    else if (c->physics == SEMX_ACOUSTIC && c->n >= kTileMinNAcoustic)
       e = launch_force_tile16_acoustic(c->n, geo, atomic, L.naff, a, c->stream);
     else if (c->physics == SEMX_ACOUSTIC)
       e = launch_force_acoustic(c->n, geo, atomic, L.naff, a, c->stream);
@@ -1394,7 +1422,16 @@ int semx_create(semx_ctx** out, int ngll, void* hip_stream) {
   gll_nodes_weights(ngll, c->xi, c->w);
   deriv_matrix(ngll, c->xi, c->D);
   std::vector<float> Df(c->D.begin(), c->D.end());
+  // even-odd form of D (force_line.hpp): A, B, middle column, middle row
+  std::vector<float> eo;
+  const int h = ngll / 2, m = ngll - 1;
+  for (int sgn = -1; sgn <= 1; sgn += 2)
+    for (int i = 0; i < h; ++i)
+      for (int j = 0; j < h; ++j) eo.push_back((float)(0.5 * (c->D[i * ngll + j] + sgn * c->D[i * ngll + m - j])));
+  for (int i = 0; i < h; ++i) eo.push_back((float)c->D[i * ngll + h]);
+  for (int j = 0; j < h; ++j) eo.push_back((float)c->D[h * ngll + j]);
   int rc = dev_alloc(c, c->d_D, Df.size() * sizeof(float));
+  if (!rc) rc = dev_alloc(c, c->d_eo, eo.size() * sizeof(float));
   if (!rc) rc = dev_alloc(c, c->d_xi64, ngll * sizeof(double));
   if (!rc) rc = dev_alloc(c, c->d_w64, ngll * sizeof(double));
   if (!rc) rc = dev_alloc(c, c->d_xi32, ngll * sizeof(float));
@@ -1404,6 +1441,7 @@ int semx_create(semx_ctx** out, int ngll, void* hip_stream) {
     return rc;
   }
   e = hipMemcpy(c->d_D.p, Df.data(), Df.size() * sizeof(float), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemcpy(c->d_eo.p, eo.data(), eo.size() * sizeof(float), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(c->d_xi64.p, c->xi.data(), ngll * sizeof(double), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(c->d_w64.p, c->w.data(), ngll * sizeof(double), hipMemcpyHostToDevice);
   std::vector<float> xi32(c->xi.begin(), c->xi.end());
@@ -1425,7 +1463,7 @@ int semx_destroy(semx_ctx* c) {
   for (DevBuf* b : {&c->d_bpos, &c->d_baff, &c->d_bfirst, &c->d_step, &c->d_first_tl, &c->d_bfirst_tl}) dev_free(*b);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
   c->cap_stream = nullptr;
-  for (DevBuf* b : {&c->d_D, &c->d_Dh, &c->d_xi64, &c->d_w64, &c->d_ibool, &c->d_vert, &c->d_elem_vert,
+  for (DevBuf* b : {&c->d_D, &c->d_eo, &c->d_Dh, &c->d_xi64, &c->d_w64, &c->d_ibool, &c->d_vert, &c->d_elem_vert,
                     &c->d_gam_pt, &c->d_gam_el, &c->d_tri, &c->d_xi32, &c->d_wdet, &c->d_order, &c->d_mat, &c->d_minv,
                     &c->d_mass64, &c->d_wrho, &c->d_u, &c->d_v, &c->d_a, &c->d_f, &c->d_work, &c->d_scratch,
                     &c->src.nodes, &c->src.wdir, &c->src.stf, &c->src.pts, &c->src.snode, &c->src.sptr,

@@ -1,0 +1,404 @@
+// Element force kernel with one lane per line of points (FP32; NC = 3 elastic,
+// NC = 1 acoustic): element-local forces for the nodal sum.
+//
+// The per-point kernels (one lane per GLL point) read n values per component
+// and direction from LDS for each point and fetch D with them; at NGLL 5 they
+// are bound by vector instructions (316 a point, 62 % of the ALU time of a
+// force pass at 64^3 elements) before they are bound by memory.  Here a lane
+// owns a whole line of n points: a derivative of the line is a small product
+// whose coefficients are the same for every lane (scalar registers), and it
+// takes the even-odd form (the derivative matrix on symmetric nodes is
+// centro-antisymmetric, D[n-1-i][n-1-j] = -D[i][j], so the sums and
+// differences of mirrored points halve the multiplications: 48 instead of 64
+// operations a line at NGLL 8).
+//
+//   home layout: lane c = (i, j) of its element holds the points k = 0..n-1
+//     (the zeta line): gather, pointwise stage, result; the zeta derivative
+//     and its transpose stay in registers;
+//   xi lines (lane (j, k)) and eta lines (lane (i, k)): the same lane number
+//     read across; values cross through LDS, each written once and read once
+//     per direction (45 LDS accesses a point, against some 110 before).
+//
+// A workgroup takes as many elements as fill its wavefronts (5 elements of 25
+// lines in two waves at NGLL 5: 125 of 128 lanes); where an element's lines
+// fit one wave (NGLL 2-4, 8) the workgroup is that wave and its barriers cost
+// nothing.  LDS lines are padded to an odd stride so that the lines of a wave
+// start on different banks.
+#pragma once
+#include "elem_common.hpp"
+
+namespace semx {
+namespace {
+
+template <int NG>
+struct LineShape {
+  static constexpr int N2 = NG * NG;
+  static constexpr int N3 = NG * NG * NG;
+  static constexpr int P = NG | 1;          // LDS stride of a xi line
+  static constexpr int ESZ = P * NG * NG;   // LDS words of one field of one element
+  // elements per workgroup (NGLL 10: one in 100 of 128 lanes; three in 300 of
+  // 320 leave two workgroups a compute unit and took 79 instead of 59 us per
+  // apply at 16^3 elements), lanes
+  static constexpr int EPW = NG == 2 ? 16 : NG == 3 ? 7 : NG == 4 ? 4 : NG <= 7 ? 5 : NG == 9 ? 3 : 1;
+  static constexpr int BLK = (EPW * N2 + 63) / 64 * 64;
+};
+
+// Even-odd tables of D: A[i][j] = (D[i][j] - D[i][n-1-j]) / 2, B[i][j] = (D[i][j] +
+// D[i][n-1-j]) / 2 for i, j < n / 2, then the middle column D[i][n/2] and the
+// middle row D[n/2][j] (odd n).
+template <int NG>
+struct EvenOdd {
+  static constexpr int H = NG / 2;
+  static constexpr bool ODD = NG & 1;
+  const float* __restrict__ t;
+  __device__ __forceinline__ float A(int i, int j) const { return t[i * H + j]; }
+  __device__ __forceinline__ float B(int i, int j) const { return t[H * H + i * H + j]; }
+  __device__ __forceinline__ float col(int i) const { return t[2 * H * H + i]; }
+  __device__ __forceinline__ float row(int j) const { return t[2 * H * H + H + j]; }
+
+  // y = D x
+  __device__ __forceinline__ void apply(float x[NG]) const {
+    float e[H], o[H];
+#pragma unroll
+    for (int j = 0; j < H; ++j) {
+      e[j] = x[j] + x[NG - 1 - j];
+      o[j] = x[j] - x[NG - 1 - j];
+    }
+    const float mid = x[H];
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      float s = A(i, 0) * o[0], t_ = B(i, 0) * e[0];
+#pragma unroll
+      for (int j = 1; j < H; ++j) {
+        s += A(i, j) * o[j];
+        t_ += B(i, j) * e[j];
+      }
+      if constexpr (ODD) t_ += col(i) * mid;
+      x[i] = s + t_;
+      x[NG - 1 - i] = s - t_;
+    }
+    if constexpr (ODD) {
+      float s = row(0) * o[0];
+#pragma unroll
+      for (int j = 1; j < H; ++j) s += row(j) * o[j];
+      x[H] = s;
+    }
+  }
+
+  // z = D^T q
+  __device__ __forceinline__ void apply_t(float q[NG]) const {
+    float e[H], o[H];
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      e[i] = q[i] + q[NG - 1 - i];
+      o[i] = q[i] - q[NG - 1 - i];
+    }
+    const float mid = q[H];
+#pragma unroll
+    for (int j = 0; j < H; ++j) {
+      float s = B(0, j) * o[0], t_ = A(0, j) * e[0];
+#pragma unroll
+      for (int i = 1; i < H; ++i) {
+        s += B(i, j) * o[i];
+        t_ += A(i, j) * e[i];
+      }
+      if constexpr (ODD) t_ += row(j) * mid;
+      q[j] = s + t_;
+      q[NG - 1 - j] = s - t_;
+    }
+    if constexpr (ODD) {
+      float s = col(0) * o[0];
+#pragma unroll
+      for (int i = 1; i < H; ++i) s += col(i) * o[i];
+      q[H] = s;
+    }
+  }
+};
+
+// Geometry of the points of one zeta line.  kTrilinear: along the line the
+// first two columns of J are linear in zeta and the third is constant.
+template <int GEO>
+struct LineGeom {
+  float g[GEO == kStored ? 1 : GEO == kRegular ? 9 : 15];
+
+  __device__ __forceinline__ void load(const ForceArgs& a, int pos, float rx, float ry) {
+    if constexpr (GEO == kRegular) {
+#pragma unroll
+      for (int d = 0; d < 9; ++d) g[d] = a.gam_el[(size_t)pos * 9 + d];
+    } else if constexpr (GEO == kTrilinear) {
+      const float4* src = reinterpret_cast<const float4*>(a.tri + (size_t)pos * 24);
+#pragma unroll
+      for (int ax = 0; ax < 3; ++ax) {
+        const float4 lo = src[2 * ax], hi = src[2 * ax + 1];  // c0 c1 c2 c3, c4 c5 c6 c7
+        const float b0 = hi.y + hi.w * ry;
+        g[5 * ax + 0] = lo.y + hi.x * ry;            // dx/dxi   = g0 + g1 zeta
+        g[5 * ax + 1] = b0;
+        g[5 * ax + 2] = lo.z + hi.x * rx;            // dx/deta  = g2 + g3 zeta
+        g[5 * ax + 3] = hi.z + hi.w * rx;
+        g[5 * ax + 4] = lo.w + hi.z * ry + rx * b0;  // dx/dzeta
+      }
+    }
+  }
+  // Mg and scale as in geom_map_from (G: the point's Gamma on the stored path)
+  __device__ __forceinline__ void at(float rz, const float G[9], float Mg[9], float& scale) const {
+    scale = 1.0f;
+    if constexpr (GEO == kStored) {
+#pragma unroll
+      for (int d = 0; d < 9; ++d) Mg[d] = G[d];
+    } else if constexpr (GEO == kRegular) {
+#pragma unroll
+      for (int d = 0; d < 9; ++d) Mg[d] = g[d];
+    } else {
+      float J[3][3];
+#pragma unroll
+      for (int ax = 0; ax < 3; ++ax) {
+        J[ax][0] = g[5 * ax + 0] + g[5 * ax + 1] * rz;
+        J[ax][1] = g[5 * ax + 2] + g[5 * ax + 3] * rz;
+        J[ax][2] = g[5 * ax + 4];
+      }
+      Mg[0] = J[1][1] * J[2][2] - J[1][2] * J[2][1];
+      Mg[3] = J[1][2] * J[2][0] - J[1][0] * J[2][2];
+      Mg[6] = J[1][0] * J[2][1] - J[1][1] * J[2][0];
+      Mg[1] = J[0][2] * J[2][1] - J[0][1] * J[2][2];
+      Mg[4] = J[0][0] * J[2][2] - J[0][2] * J[2][0];
+      Mg[7] = J[0][1] * J[2][0] - J[0][0] * J[2][1];
+      Mg[2] = J[0][1] * J[1][2] - J[0][2] * J[1][1];
+      Mg[5] = J[0][2] * J[1][0] - J[0][0] * J[1][2];
+      Mg[8] = J[0][0] * J[1][1] - J[0][1] * J[1][0];
+      const float det = J[0][0] * Mg[0] + J[0][1] * Mg[3] + J[0][2] * Mg[6];
+      const float id = __builtin_amdgcn_rcpf(det);
+      scale = id * id;
+    }
+  }
+};
+
+// Weighted fluxes of one point in place of its reference derivatives d[c][dir].
+__device__ __forceinline__ void point_flux(float d[3][3], const float Mg[9], float scale, float lamw, float muw) {
+  float gr[3][3];
+  apply_map(d, Mg, gr);
+  const float ls = lamw * scale, ms = muw * scale, ms2 = 2.0f * ms;
+  const float ltr = ls * (gr[0][0] + gr[1][1] + gr[2][2]);
+  float sg[3][3];
+  sg[0][0] = ltr + ms2 * gr[0][0];
+  sg[1][1] = ltr + ms2 * gr[1][1];
+  sg[2][2] = ltr + ms2 * gr[2][2];
+  sg[0][1] = sg[1][0] = ms * (gr[0][1] + gr[1][0]);
+  sg[0][2] = sg[2][0] = ms * (gr[0][2] + gr[2][0]);
+  sg[1][2] = sg[2][1] = ms * (gr[1][2] + gr[2][1]);
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) d[c][q] = sg[c][0] * Mg[q * 3 + 0] + sg[c][1] * Mg[q * 3 + 1] + sg[c][2] * Mg[q * 3 + 2];
+}
+
+__device__ __forceinline__ void scalar_flux(float d[3], const float Mg[9], float scale, float w) {
+  float g[3];
+#pragma unroll
+  for (int b = 0; b < 3; ++b) g[b] = d[0] * Mg[0 * 3 + b] + d[1] * Mg[1 * 3 + b] + d[2] * Mg[2 * 3 + b];
+  const float s = w * scale;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) d[q] = s * (g[0] * Mg[q * 3 + 0] + g[1] * Mg[q * 3 + 1] + g[2] * Mg[q * 3 + 2]);
+}
+
+template <int NG, int NC, int GEO, bool AFF>
+__global__ __launch_bounds__(LineShape<NG>::BLK) void force_line_kernel(ForceArgs a) {
+  using S = LineShape<NG>;
+  constexpr int N2 = S::N2, N3 = S::N3, P = S::P, EPW = S::EPW;
+  constexpr int AS = EPW * S::ESZ;  // words of one field
+  __shared__ float s[2 * NC * AS];
+
+  const int ngrp = ((int)a.count + EPW - 1) / EPW;
+  const int grp = xcd_group(ngrp);
+  if (grp >= ngrp) return;  // uniform over the block
+  // spare lanes repeat the last line (the same values to the same places),
+  // spare elements of the last group the last element; neither stores a result
+  const int l = min((int)threadIdx.x, EPW * N2 - 1);
+  const int e = l / N2, c = l - e * N2;
+  const int i = c % NG, j = c / NG;
+  const int el = grp * EPW + e;
+  const bool act = (int)threadIdx.x < EPW * N2 && el < (int)a.count;
+  const int pos = (int)a.pos0 + min(el, (int)a.count - 1);
+
+  const int model = blockIdx.y;
+  const float* __restrict__ u = a.u + (size_t)model * a.nglob * NC;
+  const float* __restrict__ mat = a.mat + ((size_t)model * a.nspec + pos) * 2 * N3 + c;
+  const EvenOdd<NG> D{a.eo};
+
+  // the line's nodes, u and material; the element's geometry
+  float uc[NC][NG], lam[NG], mu[NC == 3 ? NG : 1];
+  if constexpr (AFF) {
+    const int4 r = *reinterpret_cast<const int4*>(a.aff + (size_t)pos * 4);
+    const float* p = u + (int64_t)(r.x + i * r.y + j * r.z) * NC;
+    const int64_t step = (int64_t)r.w * NC;
+#pragma unroll
+    for (int k = 0; k < NG; ++k)
+#pragma unroll
+      for (int q = 0; q < NC; ++q) uc[q][k] = p[k * step + q];
+  } else {
+    const int32_t* ib = a.ibool + (size_t)pos * N3 + c;
+    int node[NG];
+#pragma unroll
+    for (int k = 0; k < NG; ++k) node[k] = ldnt(ib + k * N2);
+#pragma unroll
+    for (int k = 0; k < NG; ++k)
+#pragma unroll
+      for (int q = 0; q < NC; ++q) uc[q][k] = u[(int64_t)node[k] * NC + q];
+  }
+  LineGeom<GEO> geo;
+  geo.load(a, pos, GEO == kTrilinear ? a.xi[i] : 0.0f, GEO == kTrilinear ? a.xi[j] : 0.0f);
+#pragma unroll
+  for (int k = 0; k < NG; ++k) {
+    lam[k] = ldnt(mat + k * N2);
+    if constexpr (NC == 3) mu[k] = ldnt(mat + N3 + k * N2);
+  }
+  const float* __restrict__ gp = GEO == kStored ? a.gam_pt + (size_t)pos * 9 * N3 + c : nullptr;
+  // Gamma of the next PD points of the line (a stored-path pass is bound by
+  // the bytes in flight)
+  constexpr int PD = NG <= 5 ? NG : 2;
+  float Gn[PD][9];
+  if constexpr (GEO == kStored) {
+#pragma unroll
+    for (int k = 0; k < PD; ++k)
+#pragma unroll
+      for (int d = 0; d < 9; ++d) Gn[k][d] = ldnt(gp + d * N3 + k * N2);
+  }
+
+  float* const sz = s + e * S::ESZ + i + P * j;       // home: + k P n
+  float* const sx = s + e * S::ESZ + P * c;           // xi line (j, k) = c: + b
+  float* const sy = s + e * S::ESZ + i + P * NG * j;  // eta line (i, k = j): + b P
+#pragma unroll
+  for (int q = 0; q < NC; ++q)
+#pragma unroll
+    for (int k = 0; k < NG; ++k) sz[q * AS + k * P * NG] = uc[q][k];
+  __syncthreads();
+
+  // ---- forward contractions: xi and eta derivatives take the place of u ----
+  {
+    float x[NC][NG], y[NC][NG];
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+#pragma unroll
+      for (int b = 0; b < NG; ++b) {
+        x[q][b] = sx[q * AS + b];
+        y[q][b] = sy[q * AS + b * P];
+      }
+#pragma unroll
+    for (int q = 0; q < NC; ++q) D.apply(uc[q]);  // zeta derivatives
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      D.apply(x[q]);
+      D.apply(y[q]);
+#pragma unroll
+      for (int b = 0; b < NG; ++b) {
+        sx[q * AS + b] = x[q][b];
+        sy[(NC + q) * AS + b * P] = y[q][b];
+      }
+    }
+  }
+  __syncthreads();
+
+  // ---- pointwise: geometry map, stress, weighted fluxes in place ----
+#pragma unroll
+  for (int k = 0; k < NG; ++k) {
+    float G[9];
+    if constexpr (GEO == kStored) {
+#pragma unroll
+      for (int d = 0; d < 9; ++d) G[d] = Gn[k % PD][d];
+      if (k + PD < NG) {
+#pragma unroll
+        for (int d = 0; d < 9; ++d) Gn[k % PD][d] = ldnt(gp + d * N3 + (k + PD) * N2);
+      }
+    }
+    float Mg[9], scale;
+    geo.at(GEO == kTrilinear ? a.xi[k] : 0.0f, G, Mg, scale);
+    float d[NC][3];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      d[q][0] = sz[q * AS + k * P * NG];
+      d[q][1] = sz[(NC + q) * AS + k * P * NG];
+      d[q][2] = uc[q][k];
+    }
+    if constexpr (NC == 3) point_flux(d, Mg, scale, lam[k], mu[k]);
+    else scalar_flux(d[0], Mg, scale, lam[k]);
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      sz[q * AS + k * P * NG] = d[q][0];
+      sz[(NC + q) * AS + k * P * NG] = d[q][1];
+      uc[q][k] = d[q][2];
+    }
+  }
+  __syncthreads();
+
+  // ---- transpose contractions, each line in place ----
+#pragma unroll
+  for (int q = 0; q < NC; ++q) {
+    float x[NG], y[NG];
+#pragma unroll
+    for (int b = 0; b < NG; ++b) {
+      x[b] = sx[q * AS + b];
+      y[b] = sy[(NC + q) * AS + b * P];
+    }
+    D.apply_t(x);
+    D.apply_t(y);
+#pragma unroll
+    for (int b = 0; b < NG; ++b) {
+      sx[q * AS + b] = x[b];
+      sy[(NC + q) * AS + b * P] = y[b];
+    }
+    D.apply_t(uc[q]);
+  }
+  __syncthreads();
+
+  if (!act) return;
+  float* out = a.part + (((size_t)model * a.nspec + pos) * N3 + c) * NC;
+#pragma unroll
+  for (int k = 0; k < NG; ++k)
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+      out[k * N2 * NC + q] = -(uc[q][k] + (sz[q * AS + k * P * NG] + sz[(NC + q) * AS + k * P * NG]));
+}
+
+template <int NG, int NC, int GEO>
+hipError_t launch_line(bool aff, const ForceArgs& a, hipStream_t s) {
+  using S = LineShape<NG>;
+  const int64_t ngrp = (a.count + S::EPW - 1) / S::EPW;
+  const dim3 grid((unsigned)((ngrp + kNumXcd - 1) / kNumXcd * kNumXcd), (unsigned)a.nmodels);
+  if (aff) force_line_kernel<NG, NC, GEO, true><<<grid, S::BLK, 0, s>>>(a);
+  else force_line_kernel<NG, NC, GEO, false><<<grid, S::BLK, 0, s>>>(a);
+  return hipGetLastError();
+}
+
+template <int NG, int NC>
+hipError_t launch_line_n(int geo, bool aff, const ForceArgs& a, hipStream_t s) {
+  switch (geo) {
+    case kRegular: return launch_line<NG, NC, kRegular>(aff, a, s);
+    case kStored: return launch_line<NG, NC, kStored>(aff, a, s);
+    case kTrilinear: return launch_line<NG, NC, kTrilinear>(aff, a, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <int NC>
+hipError_t launch_line_any(int n, int geo, int64_t naff, const ForceArgs& a, hipStream_t s) {
+  if (!a.part || a.list || !a.eo) return hipErrorInvalidValue;
+  return split_affine(naff, a, [&](const ForceArgs& b, bool aff) -> hipError_t {
+    switch (n) {
+      case 2: return launch_line_n<2, NC>(geo, aff, b, s);
+      case 3: return launch_line_n<3, NC>(geo, aff, b, s);
+      case 4: return launch_line_n<4, NC>(geo, aff, b, s);
+      case 5: return launch_line_n<5, NC>(geo, aff, b, s);
+      case 6: return launch_line_n<6, NC>(geo, aff, b, s);
+      case 7: return launch_line_n<7, NC>(geo, aff, b, s);
+      case 8: return launch_line_n<8, NC>(geo, aff, b, s);
+      case 9: return launch_line_n<9, NC>(geo, aff, b, s);
+      case 10: return launch_line_n<10, NC>(geo, aff, b, s);
+      case 11: return launch_line_n<11, NC>(geo, aff, b, s);
+      case 12: return launch_line_n<12, NC>(geo, aff, b, s);
+      default: return hipErrorInvalidValue;
+    }
+  });
+}
+
+}  // namespace
+}  // namespace semx

@@ -105,6 +105,7 @@ struct semx_ctx {
   // GLL data (library's own, FP64 on host)
   std::vector<double> xi, w, D;  // D[a*n+b] = l'_b(xi_a)
   semx::DevBuf d_D;              // float [n][n]
+  semx::DevBuf d_eo;             // float, even-odd form of D (force_line.hpp)
   semx::DevBuf d_Dh;             // packed half/bfloat D tables for the MFMA paths
   semx::DevBuf d_xi64, d_w64;    // double [n]
 
@@ -278,6 +279,7 @@ struct ForceArgs {
   const float* u;        // [nmodels][nglob][3]
   float* f;              // [nmodels][nglob][3]
   const float* D;        // [n][n] FP32
+  const float* eo;       // even-odd form of D (force_line.hpp)
   const void* Dh;        // packed low-precision D tables (MFMA paths)
   const uint32_t* first; // coloured per-element paths: per-position bitmask of the points that
                          // reach their node first in launch order (store, no read), or null
@@ -313,6 +315,12 @@ struct BlockArgs {
 hipError_t launch_force_block(int n, int geo, const ForceArgs& a, const BlockArgs& b, hipStream_t s);
 hipError_t launch_force_block_skeleton(int n, int geo, const ForceArgs& a, const BlockArgs& b, hipStream_t s);
 constexpr int kBlockMaxN = 5;  // eight elements of n^3 points in one 1024-lane workgroup
+
+// force_line.hpp: one lane per line of points, element-local forces only
+// (a.part set, no list), NGLL 2..12.
+hipError_t launch_force_line(int n, int geo, int64_t naff, const ForceArgs& a, hipStream_t s);
+hipError_t launch_force_line_acoustic(int n, int geo, int64_t naff, const ForceArgs& a, hipStream_t s);
+constexpr int kLineMaxN = 12;
 
 hipError_t launch_force_mfma(int n, int prec, int geo, bool atomic, const ForceArgs& a, hipStream_t s);
 // force_high.hip: NGLL 11..16 (one lane per (i, j) column; the FP32 force pass uses it for 11..12)

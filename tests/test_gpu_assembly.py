@@ -6,7 +6,8 @@ colour by colour, one launch per colour with read-modify-write.  Without it
 the force is one launch over the mesh and a sum per node, in the order in
 which the coloured pass reaches the node: the same additions, so the FP32
 results agree to the bit, and so do the time loops (whose Newmark pass sums
-the node's points itself).
+the node's points itself).  Elastic FP32 runs are made with checkpoints on:
+those keep the element kernels of the coloured pass at every size.
 """
 import numpy as np
 import pytest
@@ -49,6 +50,8 @@ def _run(P, mesh, n, colours, geometry, mode=None, storage=0, acoustic=False, mo
     if mode is not None:
         s.set_mode(mode)
     f64 = storage == P.SEMX_F64
+    if not f64 and not acoustic:
+        P.semx_set_checkpointing(s.ctx, 6)
     u = s.empty_field()
     u.copy_(torch.from_numpy(np.random.default_rng(3).uniform(-1, 1, tuple(u.shape))))
     out = [s.apply_force(u).cpu().numpy()]
@@ -84,7 +87,7 @@ CASES = [  # n, elements, mesh, geometry (0 stored, 1 trilinear), mode, physics 
     (4, (4, 4, 5), "periodic", 0, None, "elastic"), (16, (2, 1, 2), "scrambled", 0, None, "elastic"),
     (5, (3, 4, 2), "jittered", 0, "bf16", "elastic"), (8, (2, 3, 2), "regular", 0, "f16", "elastic"),
     (12, (2, 3, 2), "regular", 0, "bf16", "elastic"), (14, (2, 1, 2), "jittered", 1, "f16", "elastic"),
-    *((n, (3, 2, 2), "jittered", n % 2, None, "acoustic") for n in (2, 5, 10, 11, 12, 16)),
+    *((n, (3, 2, 2), "jittered", n % 2, None, "acoustic") for n in (3, 5, 10, 13, 16)),
     (8, (19, 1, 1), "regular", 0, None, "acoustic"), (5, (4, 5, 3), "scrambled", 0, None, "acoustic"),
     *((n, (3, 2, 2), "jittered", 0, None, "f64") for n in (2, 5, 10)), (4, (4, 4, 4), "scrambled", 0, None, "f64"),
 ]
