@@ -14,6 +14,7 @@
 #include <cstdint>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "semx_internal.hpp"
@@ -27,7 +28,7 @@ struct semx_mlp {
   int64_t nparam = 0;
   std::vector<int64_t> woff, boff;
   semx::DevBuf theta, theta_bf, grad, m, v;
-  std::vector<semx::DevBuf> Z, H;  // Z[l] [B][w[l+1]], H[l] (l >= 1) [B][w[l]]
+  std::vector<semx::DevBuf> Z, H;  // Z[l] [B][w[l+1]] FP32, H[l] (l >= 1) [B][w[l]] BF16 (only ever a GEMM operand)
   semx::DevBuf g0, g1;             // backward work [B][max width]
   semx::DevBuf scratch;
   semx::DevBuf splitk;             // split-K partial sums
@@ -40,9 +41,10 @@ namespace semx {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int BM = 64, BN = 64, BK = 32, PADK = 8;
+constexpr int BK = 32, PADK = 8;
 constexpr int64_t kSplitWs = 2 << 20;  // floats of split-K partial sums per network (8 MB)
 
 // Workspace of semx_mlp_forward_noalloc: two activation buffers of
@@ -69,135 +71,280 @@ hipError_t noalloc_setup(int dev) {
   return g_scratch_err[dev];
 }
 
-__device__ __forceinline__ float to_f(float x) { return x; }
-__device__ __forceinline__ float to_f(__bf16 x) { return (float)x; }
-
-// Eight consecutive elements starting at p (16-byte aligned when `vec`).
+// Eight elements of an operand as they lie in memory: a request that stays in
+// flight until the values are converted into LDS.
 template <class T>
-__device__ __forceinline__ void load8(const T* p, float v[8]);
+struct Raw8;
 template <>
-__device__ __forceinline__ void load8<float>(const float* p, float v[8]) {
-  const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
-  v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-}
-template <>
-__device__ __forceinline__ void load8<__bf16>(const __bf16* p, float v[8]) {
-  const bf16x8 a = *reinterpret_cast<const bf16x8*>(p);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = (float)a[e];
-}
-
-// One operand tile T[r][k] (64 rows x BK) of X(r, k) = X[r * sr + k * sk],
-// rows r0 .. r0+63, k in [k0, kend).  KC: X is contiguous along k (sk = 1),
-// a thread loads 8 consecutive k of one row; otherwise it is contiguous
-// along r (sr = 1) and a thread loads 8 consecutive rows of one k.  `vec`
-// allows 16-byte vector loads (checked alignment); ragged edges use scalar
-// loads with bounds.
-template <class T, bool KC>
-__device__ __forceinline__ void load_tile(__bf16 (*Ts)[BK + PADK], const T* __restrict__ X, int64_t sr, int64_t sk,
-                                          int R, int r0, int k0, int kend, bool vec, int t) {
-  float v[8];
-  if constexpr (KC) {
-    const int rr = t >> 2, kk = (t & 3) * 8;
-    const int r = r0 + rr, k = k0 + kk;
-    if (vec && r < R && k + 8 <= kend) {
-      load8<T>(X + (int64_t)r * sr + k, v);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = (r < R && k + e < kend) ? to_f(X[(int64_t)r * sr + (int64_t)(k + e) * sk]) : 0.0f;
-    }
-    bf16x8 w;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) w[e] = (__bf16)v[e];
-    *reinterpret_cast<bf16x8*>(&Ts[rr][kk]) = w;
-  } else {
-    const int kk = t >> 3, rr = (t & 7) * 8;
-    const int r = r0 + rr, k = k0 + kk;
-    if (vec && k < kend && r + 8 <= R) {
-      load8<T>(X + r + (int64_t)k * sk, v);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = (r + e < R && k < kend) ? to_f(X[(int64_t)(r + e) * sr + (int64_t)k * sk]) : 0.0f;
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) Ts[rr + e][kk] = (__bf16)v[e];
+struct Raw8<float> {
+  float4 a, b;
+  __device__ __forceinline__ void load(const float* p) {
+    a = *reinterpret_cast<const float4*>(p);
+    b = *reinterpret_cast<const float4*>(p + 4);
   }
+  __device__ __forceinline__ void set(int e, float x) {
+    if (e == 0) a.x = x; else if (e == 1) a.y = x; else if (e == 2) a.z = x; else if (e == 3) a.w = x;
+    else if (e == 4) b.x = x; else if (e == 5) b.y = x; else if (e == 6) b.z = x; else b.w = x;
+  }
+  __device__ __forceinline__ bf16x8 bf16() const {
+    return bf16x8{(__bf16)a.x, (__bf16)a.y, (__bf16)a.z, (__bf16)a.w, (__bf16)b.x, (__bf16)b.y, (__bf16)b.z, (__bf16)b.w};
+  }
+};
+template <>
+struct Raw8<__bf16> {
+  bf16x8 v;
+  __device__ __forceinline__ void load(const __bf16* p) { v = *reinterpret_cast<const bf16x8*>(p); }
+  __device__ __forceinline__ void set(int e, __bf16 x) { v[e] = x; }
+  __device__ __forceinline__ bf16x8 bf16() const { return v; }
+};
+
+// A thread's share of one operand tile T[r][k] (ROWS rows x BK, 256 threads,
+// ROWS / 64 chunks of eight a thread) of X(r, k) = X[r * sr + k * sk], rows
+// r0 .. r0+ROWS-1, k in [k0, kend).  KC: X is contiguous along k (sk = 1), a
+// chunk is 8 consecutive k of one row; otherwise it is contiguous along r
+// (sr = 1) and a chunk is 8 consecutive rows of one k.
+// VEC: every chunk lies wholly inside or wholly outside the operand and is
+// 16-byte aligned (the launch checks it): one vector load at an address that
+// is clamped into the operand, zeroed on the way into LDS where it lies past
+// kend (rows past R give sums that are not stored).  Otherwise element by
+// element, with bounds.
+template <class T, bool KC, int ROWS, bool VEC>
+struct Tile {
+  static constexpr int C = ROWS / 64;
+  Raw8<T> raw[C];
+
+  __device__ static __forceinline__ int row(int c, int t) {
+    return KC ? (t >> 2) + 64 * c : (t + 256 * c) % (ROWS / 8) * 8;
+  }
+  __device__ static __forceinline__ int kof(int c, int t) { return KC ? (t & 3) * 8 : (t + 256 * c) / (ROWS / 8); }
+
+  __device__ __forceinline__ void load(const T* __restrict__ X, int64_t sr, int64_t sk, int R, int r0, int k0, int kend,
+                                       int t) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const int r = r0 + row(c, t), k = k0 + kof(c, t);
+      if constexpr (VEC) {
+        if constexpr (KC) raw[c].load(X + (int64_t)min(r, R - 1) * sr + min(k, kend - 8));
+        else raw[c].load(X + min(r, R - 8) + (int64_t)min(k, kend - 1) * sk);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int re = KC ? r : r + e, ke = KC ? k + e : k;
+          raw[c].set(e, (re < R && ke < kend) ? X[(int64_t)re * sr + (int64_t)ke * sk] : (T)0.0f);
+        }
+      }
+    }
+  }
+  template <bool TAIL>
+  __device__ __forceinline__ void store(__bf16 (*Ts)[BK + PADK], int k0, int kend, int t) const {
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      bf16x8 w = raw[c].bf16();
+      if (VEC && TAIL && k0 + kof(c, t) >= kend) w = bf16x8{};
+      if constexpr (KC) {
+        *reinterpret_cast<bf16x8*>(&Ts[row(c, t)][kof(c, t)]) = w;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) Ts[row(c, t) + e][kof(c, t)] = w[e];
+      }
+    }
+  }
+};
+
+__device__ __forceinline__ float silu(float v) { return v / (1.0f + expf(-v)); }
+__device__ __forceinline__ float silu_grad(float z) {
+  const float s = 1.0f / (1.0f + expf(-z));
+  return s * (1.0f + z * (1.0f - s));
 }
 
-// C[m][n] (+)= sum_k A(m,k) B(k,n), A(m,k) = A[m*sam + k*sak], B(k,n) = B[k*sbk + n*sbn].
-// EPI 1: + bias[n]; EPI 2: + bias[n] and H[m][n] = SiLU(C[m][n]); EPI 3:
-// C[m][n] = SiLU(sum + bias[n]) (inference: the pre-activation is not kept).
-// Split-K (gridDim.z > 1, EPI 0 only): slice z covers k in [z kchunk,
-// (z+1) kchunk) and stores its partial sums to C + z M N (row stride N).
-template <class TA, class TB, int EPI, bool AKC, bool BKC>
-__global__ __launch_bounds__(256) void gemm_kernel(int M, int N, int K, int kchunk, const TA* __restrict__ A,
-                                                   int64_t sam, int64_t sak, int veca, const TB* __restrict__ B,
-                                                   int64_t sbk, int64_t sbn, int vecb, float* __restrict__ C,
-                                                   int64_t ldc, const float* __restrict__ bias, float* __restrict__ H,
-                                                   int accumulate) {
-  __shared__ __attribute__((aligned(16))) __bf16 As[BM][BK + PADK];
-  __shared__ __attribute__((aligned(16))) __bf16 Bs[BN][BK + PADK];
+// What a GEMM does with its sums.
+constexpr int kPlain = 0;     // C = sum; split-K slices store their partial sums
+constexpr int kBias = 1;      // C = sum + bias[n]
+constexpr int kSiluKeep = 2;  // C = sum + bias[n] (the pre-activation), Hb = SiLU(C) in BF16
+constexpr int kSilu = 3;      // Hb = SiLU(sum + bias[n]) in BF16 (inference: the pre-activation is not kept)
+constexpr int kGradZ = 4;     // C = sum * SiLU'(Z[m][n]); split-K as kPlain (the reduction applies Z)
+constexpr int kBiasStream = 6;  // kBias, the output past the caches
+constexpr int kGradW = 5;     // C = sum; db[m] = sum of A over k
+
+// C[m][n] = sum_k A(m,k) B(k,n), A(m,k) = A[m*sam + k*sak], B(k,n) = B[k*sbk + n*sbn].
+// Split-K (gridDim.z > 1): slice z covers k in [z kchunk, (z+1) kchunk) and
+// stores its partial sums to C + z M N (row stride N).
+//
+// One workgroup of four waves per tile of 32 WT x 32 WT outputs, a wave WT x WT
+// matrix-core tiles; k in steps of 32 through two LDS buffers (one barrier a
+// step).  The network's products are short in k and often small: what bounds
+// them is the latency of the operand loads, a round trip per step when a step
+// waits for its own.  The loads of PF steps are therefore in flight at a time,
+// held as they came from memory and converted on the way into LDS (64 x 64
+// tiles that waited for each step: the hidden layers' products at batch 128 18
+// us, now 7; the input gradient of 24576 outputs 22 -> 10).  WT = 2 (64 x 64)
+// where few tiles would leave compute units idle, WT = 4 (128 x 128: half the
+// operand traffic and LDS reads per product) from 512 tiles: the 4096 x 24576
+// x 512 output layer 344 -> 172 us, 600 TFLOP/s; its floor is the 402 MB
+// written (70 us).  The order of the sum over k is the same in both.
+template <class TA, class TB, int EPI, bool AKC, bool BKC, int WT, bool VEC>
+__global__ __launch_bounds__(256, WT == 2 ? 4 : 2) void gemm_kernel(int M, int N, int K, int kchunk,
+                                                                    const TA* __restrict__ A, int64_t sam, int64_t sak,
+                                                                    const TB* __restrict__ B, int64_t sbk, int64_t sbn,
+                                                                    float* __restrict__ C, int64_t ldc,
+                                                                    const float* __restrict__ bias,
+                                                                    __bf16* __restrict__ Hb,
+                                                                    const float* __restrict__ Z,
+                                                                    float* __restrict__ db, int outv) {
+  constexpr int ROWS = 32 * WT, PF = !VEC ? 1 : WT == 2 ? 4 : 2;
+  __shared__ __attribute__((aligned(16))) __bf16 As[2][ROWS][BK + PADK];
+  __shared__ __attribute__((aligned(16))) __bf16 Bs[2][ROWS][BK + PADK];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int bm = blockIdx.y * BM, bn = blockIdx.x * BN;
-  const int wm = wv >> 1, wn = wv & 1;
+  const int bm = blockIdx.y * ROWS, bn = blockIdx.x * ROWS;
+  const int wu = __builtin_amdgcn_readfirstlane(wv), wm = wu >> 1, wn = wu & 1;
   const bool split = gridDim.z > 1;
   const int kbeg = blockIdx.z * kchunk;
   const int kend = min(K, kbeg + kchunk);
-  f32x4 acc[2][2];
+  const int steps = (kend - kbeg + BK - 1) / BK;
+  f32x4 acc[WT][WT];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < WT; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  for (int k0 = kbeg; k0 < kend; k0 += BK) {
-    load_tile<TA, AKC>(As, A, sam, sak, M, bm, k0, kend, veca != 0, t);
-    load_tile<TB, BKC>(Bs, B, sbn, sbk, N, bn, k0, kend, vecb != 0, t);
-    __syncthreads();
-    bf16x8 av[2], bv[2];
+    for (int b = 0; b < WT; ++b) acc[a][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  Tile<TA, AKC, ROWS, VEC> ta[PF];
+  Tile<TB, BKC, ROWS, VEC> tb[PF];
 #pragma unroll
-    for (int a = 0; a < 2; ++a) av[a] = *reinterpret_cast<const bf16x8*>(&As[wm * 32 + a * 16 + (lane & 15)][8 * (lane >> 4)]);
-#pragma unroll
-    for (int b = 0; b < 2; ++b) bv[b] = *reinterpret_cast<const bf16x8*>(&Bs[wn * 32 + b * 16 + (lane & 15)][8 * (lane >> 4)]);
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[a], bv[b], acc[a][b], 0, 0, 0);
-    __syncthreads();
+  for (int p = 0; p < PF; ++p) {
+    ta[p].load(A, sam, sak, M, bm, kbeg + p * BK, kend, t);
+    tb[p].load(B, sbn, sbk, N, bn, kbeg + p * BK, kend, t);
   }
-  float* Cz = split ? C + (int64_t)blockIdx.z * M * N : C;
+  if constexpr (EPI == kGradW) {
+    // the blocks of the first column also sum their rows of A over k, in order
+    if (blockIdx.x == 0 && blockIdx.z == 0 && t < ROWS && bm + t < M) {
+      const TA* p = A + (int64_t)(bm + t) * sam;
+      float s = 0.0f;
+      int k = 0;
+      for (; k + 16 <= K; k += 16) {
+        float v[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = (float)p[(int64_t)(k + e) * sak];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s += v[e];
+      }
+      for (; k < K; ++k) s += (float)p[(int64_t)k * sak];
+      db[bm + t] = s;
+    }
+  }
+  // One step: tile p to LDS, the tile PF steps ahead requested in its place
+  // (LOAD), products.  The loop's loads are unconditional, so that the compiler
+  // counts them and a step waits for its own tile alone; the last PF steps
+  // request nothing, and only there can a tile end inside.
+  auto step = [&](auto load, auto p_, int s) {
+    constexpr bool LOAD = decltype(load)::value;
+    constexpr int p = decltype(p_)::value;
+    // buffer s & 1 was last read in step s - 2, before the barrier of step s - 1
+    __bf16(*as)[BK + PADK] = As[s & 1];
+    __bf16(*bs)[BK + PADK] = Bs[s & 1];
+    ta[p].template store<!LOAD>(as, kbeg + s * BK, kend, t);
+    tb[p].template store<!LOAD>(bs, kbeg + s * BK, kend, t);
+    if constexpr (LOAD) {
+      ta[p].load(A, sam, sak, M, bm, kbeg + (s + PF) * BK, kend, t);
+      tb[p].load(B, sbn, sbk, N, bn, kbeg + (s + PF) * BK, kend, t);
+    }
+    __syncthreads();
+    bf16x8 av[WT], bv[WT];
+#pragma unroll
+    for (int a = 0; a < WT; ++a)
+      av[a] = *reinterpret_cast<const bf16x8*>(&as[wm * 16 * WT + a * 16 + (lane & 15)][8 * (lane >> 4)]);
+#pragma unroll
+    for (int b = 0; b < WT; ++b)
+      bv[b] = *reinterpret_cast<const bf16x8*>(&bs[wn * 16 * WT + b * 16 + (lane & 15)][8 * (lane >> 4)]);
+#pragma unroll
+    for (int a = 0; a < WT; ++a)
+#pragma unroll
+      for (int b = 0; b < WT; ++b)
+        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv[b], av[a], acc[a][b], 0, 0, 0);
+  };
+  auto group = [&](auto load, int s0) {
+    constexpr bool LOAD = decltype(load)::value;
+    step(load, std::integral_constant<int, 0>{}, s0);
+    if constexpr (PF > 1)
+      if (LOAD || s0 + 1 < steps) step(load, std::integral_constant<int, 1>{}, s0 + 1);
+    if constexpr (PF > 2) {
+      if (LOAD || s0 + 2 < steps) step(load, std::integral_constant<int, 2>{}, s0 + 2);
+      if (LOAD || s0 + 3 < steps) step(load, std::integral_constant<int, 3>{}, s0 + 3);
+    }
+  };
+  int s0 = 0;
+  for (; s0 + PF < steps; s0 += PF) group(std::true_type{}, s0);
+  group(std::false_type{}, s0);
+  // The product is taken transposed (B's columns as the rows of the matrix-core
+  // tile): a lane holds four consecutive n of one m, one 16-byte store.
+  // Outputs of 64 MB and more go past the caches (402 MB at batch 4096: 257 ->
+  // 210 us for the network, 202 with the 16-byte stores).
   const int64_t ldz = split ? N : ldc;
+  float* Cz = split ? C + (int64_t)blockIdx.z * M * N : C;
+  const int m0 = bm + wm * 16 * WT + (lane & 15), n0 = bn + wn * 16 * WT + 4 * (lane >> 4);
+  constexpr bool BIAS = EPI == kBias || EPI == kBiasStream || EPI == kSiluKeep || EPI == kSilu;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int b = 0; b < WT; ++b) {
+    const int n = n0 + 16 * b;
+    if (n >= N) continue;
+    float add[4] = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (BIAS) {
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+      for (int r = 0; r < 4; ++r) add[r] = n + r < N ? bias[n + r] : 0.0f;
+    }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = bm + wm * 32 + a * 16 + 4 * (lane >> 4) + r;
-        const int n = bn + wn * 32 + b * 16 + (lane & 15);
-        if (m < M && n < N) {
-          float v = acc[a][b][r];
-          const int64_t o = (int64_t)m * ldz + n;
+    for (int a = 0; a < WT; ++a) {
+      const int m = m0 + 16 * a;
+      if (m >= M) continue;
+      const int64_t o = (int64_t)m * ldz + n;
+      f32x4 v = acc[a][b];
+      if constexpr (BIAS) v += (f32x4){add[0], add[1], add[2], add[3]};
+      if (outv) {
+        if constexpr (EPI == kGradZ)
           if (!split) {
-            if (accumulate) v += Cz[o];
-            if (EPI >= 1) v += bias[n];
+            const f32x4 z = *reinterpret_cast<const f32x4*>(Z + o);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] *= silu_grad(z[r]);
           }
-          if (EPI == 3) {
-            Cz[o] = v / (1.0f + expf(-v));
-          } else {
-            Cz[o] = v;
-            if (EPI == 2) H[o] = v / (1.0f + expf(-v));
-          }
+        if constexpr (EPI == kBiasStream) __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(Cz + o));
+        else if constexpr (EPI != kSilu) *reinterpret_cast<f32x4*>(Cz + o) = v;
+        if constexpr (EPI == kSiluKeep || EPI == kSilu) {
+          bf16x4 h;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) h[r] = (__bf16)silu(v[r]);
+          *reinterpret_cast<bf16x4*>(Hb + o) = h;
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if (n + r >= N) continue;
+          float x = v[r];
+          if (EPI == kGradZ && !split) x *= silu_grad(Z[o + r]);
+          if (EPI != kSilu) Cz[o + r] = x;
+          if (EPI == kSiluKeep || EPI == kSilu) Hb[o + r] = (__bf16)silu(x);
         }
       }
+    }
+  }
 }
 
-// C[m][n] = sum over the nz slices of P (fixed order: deterministic).
-__global__ void splitk_reduce_kernel(int M, int N, int nz, const float* __restrict__ P, float* __restrict__ C,
-                                     int64_t ldc) {
+// C[m][n] = sum over the nz slices of P (fixed order: deterministic), times
+// SiLU'(Z) when Z is given.
+__global__ void splitk_reduce_kernel(int M, int N, int nz, const float* __restrict__ P, const float* __restrict__ Z,
+                                     float* __restrict__ C, int64_t ldc) {
   const int64_t MN = (int64_t)M * N;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < MN; t += (int64_t)gridDim.x * blockDim.x) {
     float s = 0.0f;
-    for (int z = 0; z < nz; ++z) s += P[z * MN + t];
-    C[(t / N) * ldc + t % N] = s;
+    int z = 0;
+    for (; z + 8 <= nz; z += 8) {
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = P[(z + e) * MN + t];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s += v[e];
+    }
+    for (; z < nz; ++z) s += P[z * MN + t];
+    const int64_t o = (t / N) * ldc + t % N;
+    if (Z) s *= silu_grad(Z[o]);
+    C[o] = s;
   }
 }
 
@@ -206,16 +353,27 @@ bool aligned16(const T* p, int64_t stride) {
   return (reinterpret_cast<uintptr_t>(p) % 16 == 0) && ((stride * (int64_t)sizeof(T)) % 16 == 0);
 }
 
+// The outputs a GEMM may write and what its epilogue reads.
+struct GemmOut {
+  float* C = nullptr;
+  int64_t ldc = 0;
+  const float* bias = nullptr;
+  __bf16* Hb = nullptr;
+  const float* Z = nullptr;
+  float* db = nullptr;
+  float* ws = nullptr;  // split-K partial sums
+};
+
 template <class TA, class TB, int EPI, bool AKC, bool BKC>
 hipError_t gemm_launch(hipStream_t s, int M, int N, int K, const TA* A, int64_t sam, int64_t sak, const TB* B,
-                       int64_t sbk, int64_t sbn, float* C, int64_t ldc, const float* bias, float* H, int accumulate,
-                       float* ws) {
-  // vector loads need unit stride along the loaded direction and 16-byte alignment
-  const int veca = (AKC ? sak == 1 : sam == 1) && aligned16(A, AKC ? sam : sak);
-  const int vecb = (BKC ? sbk == 1 : sbn == 1) && aligned16(B, BKC ? sbn : sbk);
-  const int tiles = ((N + BN - 1) / BN) * ((M + BM - 1) / BM);
+                       int64_t sbk, int64_t sbn, const GemmOut& O) {
+  // whole vectors: 16-byte alignment and eights along the contiguous direction
+  const bool vec = aligned16(A, AKC ? sam : sak) && aligned16(B, BKC ? sbn : sbk) &&
+                   (AKC ? sak == 1 && K % 8 == 0 : sam == 1 && M % 8 == 0) &&
+                   (BKC ? sbk == 1 && K % 8 == 0 : sbn == 1 && N % 8 == 0);
+  const int tiles = ((N + 63) / 64) * ((M + 63) / 64);
   int nz = 1, kchunk = K;
-  if (EPI == 0 && !accumulate && ws && tiles < 128 && K >= 1024) {
+  if ((EPI == kPlain || EPI == kGradZ || EPI == kGradW) && O.ws && tiles < 128 && K >= 1024) {
     nz = std::min<int>(32, (512 + tiles - 1) / tiles);
     kchunk = (((K + nz - 1) / nz + BK - 1) / BK) * BK;
     nz = (K + kchunk - 1) / kchunk;
@@ -224,60 +382,39 @@ hipError_t gemm_launch(hipStream_t s, int M, int N, int K, const TA* A, int64_t 
       nz = (K + kchunk - 1) / kchunk;
     }
   }
-  dim3 grid((N + BN - 1) / BN, (M + BM - 1) / BM, nz), block(256);
-  gemm_kernel<TA, TB, EPI, AKC, BKC><<<grid, block, 0, s>>>(M, N, K, kchunk, A, sam, sak, veca, B, sbk, sbn, vecb,
-                                                            nz > 1 ? ws : C, ldc, bias, H, accumulate);
+  const bool wide = vec && (int64_t)((N + 127) / 128) * ((M + 127) / 128) >= 512;
+  const int rows = wide ? 128 : 64;
+  const dim3 grid((N + rows - 1) / rows, (M + rows - 1) / rows, nz), block(256);
+  float* C = nz > 1 ? O.ws : O.C;
+  // outputs in fours along n
+  const int outv = (nz > 1 ? N : O.ldc) % 4 == 0 && N % 4 == 0 && reinterpret_cast<uintptr_t>(C) % 16 == 0 &&
+                   reinterpret_cast<uintptr_t>(O.Hb) % 8 == 0 && reinterpret_cast<uintptr_t>(O.Z) % 16 == 0;
+  auto go = [&](auto kernel) {
+    kernel<<<grid, block, 0, s>>>(M, N, K, kchunk, A, sam, sak, B, sbk, sbn, C, O.ldc, O.bias, O.Hb, O.Z, O.db, outv);
+  };
+  if (wide) go(gemm_kernel<TA, TB, EPI, AKC, BKC, 4, true>);
+  else if (vec) go(gemm_kernel<TA, TB, EPI, AKC, BKC, 2, true>);
+  else go(gemm_kernel<TA, TB, EPI, AKC, BKC, 2, false>);
   if (nz > 1) {
     const int64_t MN = (int64_t)M * N;
     const unsigned nb = (unsigned)std::min<int64_t>((MN + 255) / 256, 4096);
-    splitk_reduce_kernel<<<nb, 256, 0, s>>>(M, N, nz, ws, C, ldc);
+    splitk_reduce_kernel<<<nb, 256, 0, s>>>(M, N, nz, O.ws, EPI == kGradZ ? O.Z : nullptr, O.C, O.ldc);
   }
   return hipGetLastError();
 }
 
-// Dispatch on operand layout: contiguous along k (stride 1) or along m / n.
-template <class TA, class TB, int EPI>
-hipError_t gemm(hipStream_t s, int M, int N, int K, const TA* A, int64_t sam, int64_t sak, const TB* B, int64_t sbk,
-                int64_t sbn, float* C, int64_t ldc, const float* bias, float* H, int accumulate, float* ws = nullptr) {
-  const bool akc = sak == 1 || sam != 1;
-  const bool bkc = sbk == 1 || sbn != 1;
-  if (akc && bkc)
-    return gemm_launch<TA, TB, EPI, true, true>(s, M, N, K, A, sam, sak, B, sbk, sbn, C, ldc, bias, H, accumulate, ws);
-  if (akc)
-    return gemm_launch<TA, TB, EPI, true, false>(s, M, N, K, A, sam, sak, B, sbk, sbn, C, ldc, bias, H, accumulate, ws);
-  if (bkc)
-    return gemm_launch<TA, TB, EPI, false, true>(s, M, N, K, A, sam, sak, B, sbk, sbn, C, ldc, bias, H, accumulate, ws);
-  return gemm_launch<TA, TB, EPI, false, false>(s, M, N, K, A, sam, sak, B, sbk, sbn, C, ldc, bias, H, accumulate, ws);
-}
-
-// g *= SiLU'(z)
-__global__ void silu_bwd_kernel(int64_t n, const float* __restrict__ z, float* __restrict__ g) {
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
-    const float s = 1.0f / (1.0f + expf(-z[t]));
-    g[t] *= s * (1.0f + z[t] * (1.0f - s));
-  }
-}
-
-// db[n] = sum_m g[m][n]
-__global__ void colsum_kernel(int M, int N, const float* __restrict__ g, float* __restrict__ db) {
-  for (int n = blockIdx.x * blockDim.x + threadIdx.x; n < N; n += gridDim.x * blockDim.x) {
-    float s = 0.0f;
-    for (int m = 0; m < M; ++m) s += g[(int64_t)m * N + n];
-    db[n] = s;
-  }
-}
-
-// loss += sum (y - t)^2 / n (FP64), dy = 2 (y - t) / n
-__global__ void mse_kernel(int64_t n, const float* __restrict__ y, const float* __restrict__ t, float* __restrict__ dy,
-                           double* __restrict__ loss) {
+// dy = 2 (y - t) / n and, when `loss` is given, loss += sum (y - t)^2 / n (FP64)
+__global__ __launch_bounds__(256) void mse_kernel(int64_t n, const float* __restrict__ y, const float* __restrict__ t,
+                                                  float* __restrict__ dy, double* __restrict__ loss) {
   __shared__ double red[256];
   double s = 0.0;
   const float inv = 1.0f / (float)n;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     const float d = y[i] - t[i];
     if (dy) dy[i] = 2.0f * d * inv;
-    s += (double)d * (double)d;
+    if (loss) s += (double)d * (double)d;
   }
+  if (!loss) return;
   red[threadIdx.x] = s;
   __syncthreads();
   for (int st = blockDim.x / 2; st > 0; st >>= 1) {
@@ -356,6 +493,25 @@ __global__ void adam_kernel(int64_t n, float lr, float b1, float b2, float eps, 
 __global__ void to_bf16_kernel(int64_t n, const float* __restrict__ x, __bf16* __restrict__ y) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     y[i] = (__bf16)x[i];
+}
+
+// Layer l of the forward pass: A(m,k) = h[m*in + k] (the input x at l = 0, BF16
+// activations after it), B(k,n) = W[n*in + k].
+template <int EPI>
+hipError_t layer(semx_mlp* p, int l, int batch, const float* x, const __bf16* h, GemmOut& O) {
+  const int in = p->w[l], out = p->w[l + 1];
+  const __bf16* W = p->theta_bf.as<__bf16>() + p->woff[l];
+  O.ldc = out;
+  O.bias = p->theta.as<float>() + p->boff[l];
+  return l == 0 ? gemm_launch<float, __bf16, EPI, true, true>(p->stream, batch, out, in, x, in, 1, W, 1, in, O)
+                : gemm_launch<__bf16, __bf16, EPI, true, true>(p->stream, batch, out, in, h, in, 1, W, 1, in, O);
+}
+
+// The network's output, past the caches where they would not hold it until its
+// reader comes.
+hipError_t output_layer(semx_mlp* p, int l, int batch, const float* x, const __bf16* h, GemmOut& O) {
+  return (int64_t)batch * p->w[l + 1] * 4 >= (int64_t(64) << 20) ? layer<kBiasStream>(p, l, batch, x, h, O)
+                                                                  : layer<kBias>(p, l, batch, x, h, O);
 }
 
 unsigned g1(int64_t n) {
@@ -441,7 +597,7 @@ int semx_mlp_create(semx_mlp** out, int nlayers, const int* widths, int max_batc
   p->H.resize(nlayers + 1);
   for (int l = 0; l < nlayers && !rc; ++l) {
     rc = malloc_buf(p, p->Z[l], sizeof(float) * max_batch * p->w[l + 1]);
-    if (!rc && l + 1 < nlayers) rc = malloc_buf(p, p->H[l + 1], sizeof(float) * max_batch * p->w[l + 1]);
+    if (!rc && l + 1 < nlayers) rc = malloc_buf(p, p->H[l + 1], sizeof(__bf16) * max_batch * p->w[l + 1]);
   }
   if (rc) {
     semx_mlp_destroy(p);
@@ -497,23 +653,14 @@ int semx_mlp_get_grads(semx_mlp* p, float* grads) {
 int semx_mlp_forward(semx_mlp* p, const float* x_dev, int batch, float* y_dev) {
   if (!p || !x_dev || !y_dev) return SEMX_EINVAL;
   if (batch < 1 || batch > p->max_batch) return mfail(p, SEMX_EINVAL, "forward: batch outside [1, max_batch]");
-  const __bf16* W = p->theta_bf.as<__bf16>();
-  const float* th = p->theta.as<float>();
-  const float* h = x_dev;
   for (int l = 0; l < p->nl; ++l) {
-    const int in = p->w[l], out = p->w[l + 1];
     const bool last = l + 1 == p->nl;
-    float* z = last ? y_dev : p->Z[l].as<float>();
-    hipError_t e;
-    // A(m,k) = h[m*in + k], B(k,n) = W[n*in + k]
-    if (last)
-      e = gemm<float, __bf16, 1>(p->stream, batch, out, in, h, in, 1, W + p->woff[l], 1, in, z, out, th + p->boff[l],
-                                 nullptr, 0);
-    else
-      e = gemm<float, __bf16, 2>(p->stream, batch, out, in, h, in, 1, W + p->woff[l], 1, in, z, out, th + p->boff[l],
-                                 p->H[l + 1].as<float>(), 0);
+    GemmOut O;
+    O.C = last ? y_dev : p->Z[l].as<float>();
+    if (!last) O.Hb = p->H[l + 1].as<__bf16>();
+    const __bf16* h = l > 0 ? p->H[l].as<__bf16>() : nullptr;
+    const hipError_t e = last ? output_layer(p, l, batch, x_dev, h, O) : layer<kSiluKeep>(p, l, batch, x_dev, h, O);
     if (e != hipSuccess) return mhip(p, e, "mlp forward gemm");
-    if (!last) h = p->H[l + 1].as<float>();
   }
   // the output layer's pre-activation is y itself; keep a copy for backward bookkeeping
   p->x_saved = x_dev;
@@ -532,22 +679,15 @@ int semx_mlp_forward_noalloc(semx_mlp* p, const float* x_dev, int batch, float* 
   float* ws = (p->device >= 0 && p->device < kMaxDevices) ? g_scratch_dev[p->device] : nullptr;
   if (!ws) return mfail(p, SEMX_ESTATE, "forward_noalloc: workspace address not resolved on this device");
   float* buf[2] = {ws, ws + kNoAllocFloats / 2};
-  const __bf16* W = p->theta_bf.as<__bf16>();
-  const float* th = p->theta.as<float>();
-  const float* h = x_dev;
+  const __bf16* h = nullptr;
   for (int l = 0; l < p->nl; ++l) {
-    const int in = p->w[l], out = p->w[l + 1];
     const bool last = l + 1 == p->nl;
-    float* z = last ? y_dev : buf[l & 1];
-    hipError_t e;
-    if (last)
-      e = gemm<float, __bf16, 1>(p->stream, batch, out, in, h, in, 1, W + p->woff[l], 1, in, z, out, th + p->boff[l],
-                                 nullptr, 0);
-    else
-      e = gemm<float, __bf16, 3>(p->stream, batch, out, in, h, in, 1, W + p->woff[l], 1, in, z, out, th + p->boff[l],
-                                 nullptr, 0);
+    GemmOut O;
+    O.C = y_dev;
+    O.Hb = reinterpret_cast<__bf16*>(buf[l & 1]);
+    const hipError_t e = last ? output_layer(p, l, batch, x_dev, h, O) : layer<kSilu>(p, l, batch, x_dev, h, O);
     if (e != hipSuccess) return mhip(p, e, "mlp forward_noalloc gemm");
-    h = z;
+    h = O.Hb;
   }
   return SEMX_OK;
 }
@@ -563,20 +703,27 @@ int semx_mlp_backward(semx_mlp* p, const float* dy_dev, int batch) {
   int cur = 0;
   for (int l = p->nl - 1; l >= 0; --l) {
     const int in = p->w[l], out = p->w[l + 1];
-    const float* h = (l == 0) ? p->x_saved : p->H[l].as<float>();
-    // dW = G^T H : C[n_out][k_in] = sum_b G[b][n_out] H[b][k_in]
-    hipError_t e = gemm<float, float, 0>(p->stream, out, in, batch, g, 1, out, h, in, 1, gr + p->woff[l], in, nullptr,
-                                          nullptr, 0, p->splitk.as<float>());
+    // dW = G^T H : C[n_out][k_in] = sum_b G[b][n_out] H[b][k_in]; db = sum_b G
+    GemmOut O;
+    O.C = gr + p->woff[l];
+    O.ldc = in;
+    O.db = gr + p->boff[l];
+    O.ws = p->splitk.as<float>();
+    hipError_t e = l == 0 ? gemm_launch<float, float, kGradW, false, false>(p->stream, out, in, batch, g, 1, out,
+                                                                            p->x_saved, in, 1, O)
+                          : gemm_launch<float, __bf16, kGradW, false, false>(p->stream, out, in, batch, g, 1, out,
+                                                                             p->H[l].as<__bf16>(), in, 1, O);
     if (e != hipSuccess) return mhip(p, e, "mlp wgrad gemm");
-    colsum_kernel<<<g1(out), 256, 0, p->stream>>>(batch, out, g, gr + p->boff[l]);
     if (l == 0) break;
-    // dH = G W : C[b][k_in] = sum_o G[b][o] W[o][k_in]
-    float* dh = bufs[cur];
-    e = gemm<float, __bf16, 0>(p->stream, batch, in, out, g, out, 1, W + p->woff[l], in, 1, dh, in, nullptr, nullptr, 0,
-                               p->splitk.as<float>());
+    // dL/dZ = (G W) SiLU'(Z) : C[b][k_in] = sum_o G[b][o] W[o][k_in]
+    GemmOut D;
+    D.C = bufs[cur];
+    D.ldc = in;
+    D.Z = p->Z[l - 1].as<float>();
+    D.ws = p->splitk.as<float>();
+    e = gemm_launch<float, __bf16, kGradZ, true, false>(p->stream, batch, in, out, g, out, 1, W + p->woff[l], in, 1, D);
     if (e != hipSuccess) return mhip(p, e, "mlp dgrad gemm");
-    silu_bwd_kernel<<<g1((int64_t)batch * in), 256, 0, p->stream>>>((int64_t)batch * in, p->Z[l - 1].as<float>(), dh);
-    g = dh;
+    g = bufs[cur];
     cur ^= 1;
   }
   MLP_HIP(p, hipGetLastError());
@@ -585,9 +732,12 @@ int semx_mlp_backward(semx_mlp* p, const float* dy_dev, int batch) {
 
 int semx_mlp_mse(semx_mlp* p, const float* y_dev, const float* t_dev, int64_t n, float* dy_dev, double* loss) {
   if (!p || !y_dev || !t_dev || n < 1) return SEMX_EINVAL;
-  double* d = p->scratch.as<double>();
-  MLP_HIP(p, hipMemsetAsync(d, 0, sizeof(double), p->stream));
-  mse_kernel<<<g1(n) > 1024 ? 1024 : g1(n), 256, 0, p->stream>>>(n, y_dev, t_dev, dy_dev, d);
+  if (!dy_dev && !loss) return SEMX_OK;
+  double* d = loss ? p->scratch.as<double>() : nullptr;
+  if (d) MLP_HIP(p, hipMemsetAsync(d, 0, sizeof(double), p->stream));
+  // the FP64 sum ends in one atomic a block: few blocks; dy alone: all
+  const unsigned top = d ? 1024 : 8192;
+  mse_kernel<<<std::min(g1(n), top), 256, 0, p->stream>>>(n, y_dev, t_dev, dy_dev, d);
   MLP_HIP(p, hipGetLastError());
   if (loss) {
     MLP_HIP(p, hipMemcpyAsync(loss, d, sizeof(double), hipMemcpyDeviceToHost, p->stream));
