@@ -26,6 +26,7 @@
 #include <string>
 
 #include "elem_common.hpp"
+#include "nodal.hpp"
 
 namespace semx {
 namespace {
@@ -79,7 +80,8 @@ __global__ __launch_bounds__(Shape<NG>::BLK) void adjoint_force_kernel(AdjArgs A
     ps[c] = psi[3 * (size_t)g + c];
     uu[c] = A.uscale * A.um[vofs + 3 * (size_t)g + c];
     aa[c] = A.uscale * A.am[vofs + 3 * (size_t)g + c];
-    if constexpr (!ATOMIC) f0[c] = f[3 * (size_t)g + c];
+    if constexpr (!ATOMIC)
+      if (!a.part) f0[c] = f[3 * (size_t)g + c];
   }
   if (p < NG * NG) s_D[p] = a.D[p];
   if (act) {
@@ -130,6 +132,8 @@ __global__ __launch_bounds__(Shape<NG>::BLK) void adjoint_force_kernel(AdjArgs A
       unsafeAtomicAdd(fg + 0, F[0]);
       unsafeAtomicAdd(fg + 1, F[1]);
       unsafeAtomicAdd(fg + 2, F[2]);
+    } else if (a.part) {
+      store_part<3>(a, model, pos, N3, p, F);
     } else {
       fg[0] = f0[0] + F[0];
       fg[1] = f0[1] + F[1];
@@ -353,6 +357,9 @@ __global__ __launch_bounds__(AdjCol<NG>::BLK) __attribute__((amdgpu_waves_per_eu
         unsafeAtomicAdd(fg + 0, -acc[0][k]);
         unsafeAtomicAdd(fg + 1, -acc[1][k]);
         unsafeAtomicAdd(fg + 2, -acc[2][k]);
+      } else if (a.part) {
+        const float out[3] = {-acc[0][k], -acc[1][k], -acc[2][k]};
+        store_part<3>(a, model, pos, N3, ll + N2 * k, out);
       } else {
         fg[0] = fg[0] - acc[0][k];
         fg[1] = fg[1] - acc[1][k];
@@ -426,17 +433,7 @@ __device__ __forceinline__ float adj_entry(float p1, float p0, float dt2, float 
   return 2.0f * p1 - p0 + dt2 * m * f;
 }
 
-__global__ void adj_update_kernel(int64_t nnodes, float dt2, const float* __restrict__ minv,
-                                  const float* __restrict__ p1, const float* __restrict__ p0,
-                                  float* __restrict__ p2, float* __restrict__ fb) {
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < 3 * nnodes;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    p2[t] = adj_entry(p1[t], p0[t], dt2, minv[t / 3], fb[t]);
-    fb[t] = 0.0f;
-  }
-}
-
-// The same with four consecutive entries per lane (16-byte accesses; every
+// The update with four consecutive entries per lane (16-byte accesses; every
 // array 16-byte aligned).  The last (3 nnodes) % 4 entries go to the first
 // lanes.
 typedef float adj_f4 __attribute__((ext_vector_type(4)));
@@ -463,6 +460,67 @@ __global__ void adj_update4_kernel(int64_t nnodes, float dt2, const float* __res
   }
 }
 
+// The nodes that receivers read (ascending), and for node i its (receiver,
+// point) pairs r n3 + q at idx[ptr[i] .. ptr[i + 1]).
+struct RecNodes {
+  const uint32_t* bits;  // one bit per node
+  const int32_t* node;
+  const int32_t* ptr;
+  const int32_t* idx;
+  int count;
+};
+
+// The update on element-local forces: one lane per node sums its points of
+// -K psi^{m+1} (none at the last step, part null), adds the adjoint sources
+// that reach it, and applies the recursion: fb is neither cleared, written nor
+// read, and a step is two launches (this one and the element pass, which is
+// one launch over the mesh: 24^3, NGLL 5, 8 x 9.4 us before).
+template <class MAP>
+__global__ __launch_bounds__(kNodeT) void adj_update_parts_kernel(MAP m, int64_t nglob, int64_t npt, float dt2,
+                                                                  const float* __restrict__ part, RecNodes R, int nrec,
+                                                                  int n3, int64_t nt_max, int64_t sample, float inv_dt2,
+                                                                  const float* __restrict__ wts,
+                                                                  const float* __restrict__ gseis,
+                                                                  const float* __restrict__ minv,
+                                                                  const float* __restrict__ p1,
+                                                                  const float* __restrict__ p0, float* __restrict__ p2) {
+  int64_t g;
+  if (!m.locate(g)) return;
+  const int64_t at = (int64_t)blockIdx.y * nglob + g;
+  const float mi = minv[at];
+  float a[3], b[3], s[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    a[c] = p1[at * 3 + c];
+    b[c] = p0[at * 3 + c];
+  }
+  if (part) m.template sum<float, 3>(part + (int64_t)blockIdx.y * npt * 3, g, s);
+  if (has_bit(R.bits, g)) {
+    int lo = 0, hi = R.count - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi) / 2;
+      if (R.node[mid] < (int32_t)g) lo = mid + 1;
+      else hi = mid;
+    }
+    // receivers may share a node: their terms are added in FP64, so that the
+    // sum has no order
+    double d[3] = {s[0], s[1], s[2]};
+    for (int32_t k = R.ptr[lo]; k < R.ptr[lo + 1]; ++k) {
+      const int32_t rq = R.idx[k];
+      const float w = wts[rq] * inv_dt2;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const float add = w * gseis[(((int64_t)blockIdx.y * nrec + rq / n3) * 3 + c) * nt_max + sample];
+        d[c] += (double)add;
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) s[c] = (float)d[c];
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) p2[at * 3 + c] = adj_entry(a[c], b[c], dt2, mi, s[c]);
+}
+
 // kr += -W psi^1 . (uscale u^1) at every element-local point (start-up term)
 __global__ void adj_rho_start_kernel(int n3, int64_t nspec, int nmodels, int64_t nglob,
                                      const int32_t* __restrict__ ibool, const double* __restrict__ wdet,
@@ -480,12 +538,27 @@ __global__ void adj_rho_start_kernel(int n3, int64_t nspec, int nmodels, int64_t
   }
 }
 
-// max |x| into *out (bit pattern of a non-negative float orders like an int)
-__global__ void maxabs_kernel(int64_t n, const float* __restrict__ x, unsigned int* __restrict__ out) {
+// max |x| into *out (bit pattern of a non-negative float orders like an int):
+// one atomic per block
+__global__ __launch_bounds__(256) void maxabs_kernel(int64_t n, const float* __restrict__ x,
+                                                     unsigned int* __restrict__ out) {
+  __shared__ float red[4];
   float mx = 0.0f;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x)
-    mx = fmaxf(mx, fabsf(x[t]));
-  if (mx > 0.0f) atomicMax(out, __float_as_uint(mx));
+  const int64_t gid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t n4 = (reinterpret_cast<uintptr_t>(x) & 15) == 0 ? n / 4 : 0;
+  for (int64_t q = gid; q < n4; q += (int64_t)gridDim.x * blockDim.x) {
+    const adj_f4 v = reinterpret_cast<const adj_f4*>(x)[q];
+    mx = fmaxf(fmaxf(mx, fmaxf(fabsf(v[0]), fabsf(v[1]))), fmaxf(fabsf(v[2]), fabsf(v[3])));
+  }
+  for (int64_t t = 4 * n4 + gid; t < n; t += (int64_t)gridDim.x * blockDim.x) mx = fmaxf(mx, fabsf(x[t]));
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    if (mx > 0.0f) atomicMax(out, __float_as_uint(mx));
+  }
 }
 
 // out[model][order[pos]][q] = scale * acc[model][pos][q]   (FP64 output: the
@@ -525,6 +598,41 @@ int max_abs(semx_ctx* c, const float* x, int64_t n, unsigned int* dword, float* 
 float pow2_normaliser(float x) {
   if (!(x > 0.0f) || !std::isfinite(x)) return 1.0f;
   return std::ldexp(1.0f, -std::ilogb(x));
+}
+
+// Device tables of the nodes that receivers read (until the receivers change).
+int build_rec_nodes(semx_ctx* c) {
+  ReceiverSet& R = c->rec;
+  if (!R.nodes_dirty) return SEMX_OK;
+  std::vector<std::pair<int32_t, int32_t>> pairs;
+  for (size_t p = 0; p < R.h_nodes.size(); ++p)
+    if (R.h_wts[p] != 0.0f) pairs.push_back({R.h_nodes[p], (int32_t)p});
+  std::sort(pairs.begin(), pairs.end());
+  std::vector<int32_t> node, ptr, idx;
+  std::vector<uint32_t> bits((size_t)(c->nglob + 31) / 32, 0u);
+  for (size_t k = 0; k < pairs.size(); ++k) {
+    if (k == 0 || pairs[k].first != pairs[k - 1].first) {
+      node.push_back(pairs[k].first);
+      ptr.push_back((int32_t)k);
+      bits[pairs[k].first >> 5] |= 1u << (pairs[k].first & 31);
+    }
+    idx.push_back(pairs[k].second);
+  }
+  ptr.push_back((int32_t)pairs.size());
+  R.nrn = (int)node.size();
+  if (node.empty()) node.push_back(0), idx.push_back(0);
+  auto put = [&](DevBuf& b, const void* src, size_t bytes) {
+    int rc = dev_alloc(c, b, bytes);
+    if (!rc && hipMemcpy(b.p, src, bytes, hipMemcpyHostToDevice) != hipSuccess)
+      rc = fail(c, SEMX_EHIP, "receiver node tables: copy failed");
+    return rc;
+  };
+  int rc = put(R.rbits, bits.data(), bits.size() * sizeof(uint32_t));
+  if (!rc) rc = put(R.rnode, node.data(), node.size() * sizeof(int32_t));
+  if (!rc) rc = put(R.rptr, ptr.data(), ptr.size() * sizeof(int32_t));
+  if (!rc) rc = put(R.ridx, idx.data(), idx.size() * sizeof(int32_t));
+  if (!rc) R.nodes_dirty = false;
+  return rc;
 }
 
 }  // namespace
@@ -671,12 +779,20 @@ int semx_adjoint(semx_ctx* c, const float* gseis_dev, int64_t nt, double* g_lamb
   const float dt = (float)c->dt;
   A.coef = -dt * dt;
   const bool atomic = c->ncolors == 0;
-  if (!atomic) {
+  // element-local forces and nodal sums as in the forward pass (parts_active),
+  // whichever assembly the forward run uses
+  const bool parts = !atomic && !c->user_colors && c->d_part.p;
+  if (parts) {
+    rc = build_rec_nodes(c);
+    A.fa.part = c->d_part.as<float>();
+  } else if (!atomic) {
     rc = build_colored(c);
-    if (rc) { cleanup(); return rc; }
     A.fa.list = c->d_clist.as<int32_t>();
   }
-  const auto& launches = atomic ? c->kind_launches : c->colored_launches;
+  if (rc) { cleanup(); return rc; }
+  const RecNodes R{c->rec.rbits.as<uint32_t>(), c->rec.rnode.as<int32_t>(), c->rec.rptr.as<int32_t>(),
+                   c->rec.ridx.as<int32_t>(), c->rec.nrn};
+  const auto& launches = atomic || parts ? c->kind_launches : c->colored_launches;
   int i0 = 0, i1 = 1, i2 = 2;  // p[i0] = psi^{m+2}, p[i1] = psi^{m+1}, p[i2] = psi^m
 
   for (int64_t seg = nseg - 1; seg >= 0 && !rc; --seg) {
@@ -723,12 +839,22 @@ int semx_adjoint(semx_ctx* c, const float* gseis_dev, int64_t nt, double* g_lamb
         }
         if (rc) break;
       }
-      const int64_t total = (int64_t)c->nmodels * c->rec.nrec * c->n3;
-      adj_source_kernel<<<grid_1d(total), 256, 0, c->stream>>>(
-          c->rec.nrec, c->n3, c->rec.nt_max, m - 1, c->nmodels, c->nglob, sg / (dt * dt),
-          c->rec.nodes.as<int32_t>(), c->rec.wts.as<float>(), gseis_dev, fb.as<float>());
-      adj_update4_kernel<<<grid_1d((3 * nn + 3) / 4), 256, 0, c->stream>>>(nn, dt * dt, c->d_minv.as<float>(),
-                                                                           p[i1], p[i0], p[i2], fb.as<float>());
+      if (parts) {
+        const float* part = m <= nt - 1 ? c->d_part.as<float>() : nullptr;
+        const hipError_t el = with_map(c, [&](auto map, dim3 grid) {
+          adj_update_parts_kernel<decltype(map)><<<grid, kNodeT, 0, c->stream>>>(
+              map, c->nglob, c->nspec * c->n3, dt * dt, part, R, c->rec.nrec, c->n3, c->rec.nt_max, m - 1,
+              sg / (dt * dt), c->rec.wts.as<float>(), gseis_dev, c->d_minv.as<float>(), p[i1], p[i0], p[i2]);
+        });
+        if (el != hipSuccess) { rc = hip_fail(c, el, "adjoint update"); break; }
+      } else {
+        const int64_t total = (int64_t)c->nmodels * c->rec.nrec * c->n3;
+        adj_source_kernel<<<grid_1d(total), 256, 0, c->stream>>>(
+            c->rec.nrec, c->n3, c->rec.nt_max, m - 1, c->nmodels, c->nglob, sg / (dt * dt),
+            c->rec.nodes.as<int32_t>(), c->rec.wts.as<float>(), gseis_dev, fb.as<float>());
+        adj_update4_kernel<<<grid_1d((3 * nn + 3) / 4), 256, 0, c->stream>>>(nn, dt * dt, c->d_minv.as<float>(),
+                                                                             p[i1], p[i0], p[i2], fb.as<float>());
+      }
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) { rc = hip_fail(c, e, "adjoint update"); break; }
       const int t = i0;

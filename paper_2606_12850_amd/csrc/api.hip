@@ -1471,7 +1471,8 @@ int semx_destroy(semx_ctx* c) {
                     &c->rec.seis,
                     &c->src.wdir64, &c->src.stf64, &c->rec.wts64, &c->rec.seis64, &c->d_gam64, &c->d_mat64,
                     &c->d_minv64, &c->d_D64,
-                    &c->d_first, &c->d_aff, &c->d_nptr, &c->d_nidx, &c->d_part, &c->d_srcbits, &c->d_clist})
+                    &c->d_first, &c->d_aff, &c->d_nptr, &c->d_nidx, &c->d_part, &c->d_srcbits, &c->d_clist, &c->rec.rbits, &c->rec.rnode, &c->rec.rptr,
+                    &c->rec.ridx})
     dev_free(*b);
   delete c;
   return SEMX_OK;
@@ -2009,6 +2010,9 @@ int semx_set_receivers(semx_ctx* c, int nrec, const int32_t* elem, const double*
   SEMX_HIP(c, hipMemcpy(c->rec.nodes.p, nodes.data(), nodes.size() * sizeof(int32_t), hipMemcpyHostToDevice));
   SEMX_HIP(c, hipMemcpy(c->rec.wts.p, wts.data(), wts.size() * sizeof(float), hipMemcpyHostToDevice));
   SEMX_HIP(c, hipMemcpy(c->rec.wts64.p, wts64.data(), wts64.size() * sizeof(double), hipMemcpyHostToDevice));
+  c->rec.h_nodes = std::move(nodes);
+  c->rec.h_wts = std::move(wts);
+  c->rec.nodes_dirty = true;
   c->rec.nrec = nrec;
   c->rec.nt_max = nt_max;
   return alloc_seismograms(c);

@@ -78,6 +78,12 @@ struct ReceiverSet {
   DevBuf wts;     // float [nrec][n3]
   DevBuf seis;    // float [nmodels][nrec][3][nt_max] (FP32 storage)
   DevBuf wts64;   // double [nrec][n3]
+  // the nodes that receivers read, for the adjoint sources (adjoint.hip)
+  std::vector<int32_t> h_nodes;
+  std::vector<float> h_wts;
+  DevBuf rbits, rnode, rptr, ridx;
+  int nrn = 0;
+  bool nodes_dirty = true;
   DevBuf seis64;  // double [nmodels][nrec][3][nt_max] (FP64 storage)
 };
 
