@@ -55,8 +55,10 @@ __global__ __launch_bounds__(Shape<NG>::BLK) void force_ac_kernel(ForceArgs a) {
   __shared__ float s_q[3 * N3];
   __shared__ float s_D[ND + NG];  // D (row-major), then the GLL nodes
 
+  if constexpr (!ATOMIC)
+    if (run_aux(a.aux)) return;  // uniform over the block
   const int ngrp = (int)a.count;
-  const int grp = xcd_group(ngrp);
+  const int grp = xcd_group(ngrp, ATOMIC ? 0 : a.aux.blocks);
   if (grp >= ngrp) return;  // uniform over the block
   const int pos = elem_pos(a, grp);
 
@@ -292,8 +294,10 @@ template <int NG, int GEO, bool ATOMIC, bool AFF>
 hipError_t launch_ac(const ForceArgs& a, hipStream_t s) {
   const int64_t nb = ((a.count + kNumXcd - 1) / kNumXcd) * kNumXcd;
   if constexpr (NG <= kMaxNLow) {
-    dim3 grid((unsigned)nb, (unsigned)a.nmodels), block(Shape<NG>::BLK);
-    force_ac_kernel<NG, GEO, ATOMIC, AFF><<<grid, block, 0, s>>>(a);
+    ForceArgs b = a;
+    b.aux.blocks = (int)aux_blocks(a.aux, Shape<NG>::BLK, kNumXcd);
+    dim3 grid((unsigned)nb + b.aux.blocks, (unsigned)a.nmodels), block(Shape<NG>::BLK);
+    force_ac_kernel<NG, GEO, ATOMIC, AFF><<<grid, block, 0, s>>>(b);
   } else {
     dim3 grid((unsigned)nb, (unsigned)a.nmodels), block(AcColShape<NG>::BLK);
     force_ac_col_kernel<NG, GEO, ATOMIC><<<grid, block, 0, s>>>(a);

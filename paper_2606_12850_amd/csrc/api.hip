@@ -943,10 +943,31 @@ bool use_line(const semx_ctx* c, bool parts, int geo) {
   return (int64_t)c->nmodels * c->nspec * c->n3 >= (1 << 18);
 }
 
+// The kernel of a launch of geometry path `geo`.
+enum ForceKernel { kLine, kTileAcoustic, kAcoustic, kTile, kColumn, kPoint, kMixed };
+ForceKernel kernel_for(const semx_ctx* c, bool parts, int geo) {
+  if (use_line(c, parts, geo)) return kLine;
+  if (c->physics == SEMX_ACOUSTIC) return c->n >= kTileMinNAcoustic ? kTileAcoustic : kAcoustic;
+  if (c->n >= kTileMinN || (c->n >= kTileMinNMixed && c->contraction != SEMX_C_F32) ||
+      (c->n == kTileRegularN && geo == kRegular))
+    return kTile;
+  if (c->contraction != SEMX_C_F32) return kMixed;
+  return c->n > kMaxNLow ? kColumn : kPoint;
+}
+
+// True when the first launch of the force pass can take the step's bookkeeping
+// along (element-local forces; not the column kernels and the 16-bit kernel of
+// the low orders).
+bool carries_aux(const semx_ctx* c) {
+  if (!parts_active(c) || c->kind_launches.empty()) return false;
+  const ForceKernel k = kernel_for(c, true, c->kind_launches[0].irregular ? c->irregular_geo : kRegular);
+  return k != kColumn && k != kMixed && !(k == kAcoustic && c->n > kMaxNLow);
+}
+
 // `tl`: the time loop's pass after the source force was stored into f
 // (prestores()): the first-touch bits with the source nodes cleared.
 int force_accumulate(semx_ctx* c, const float* u, float* f, bool first_touch = false, bool f_zero = false,
-                     bool tl = false, bool defer = false) {
+                     bool tl = false, bool defer = false, const AuxArgs<float>* aux = nullptr) {
   const bool atomic = c->assembly == SEMX_ASM_ATOMIC;
   const bool parts = parts_active(c), colored = !atomic && !parts && !blocks_active(c);
   if (colored) {
@@ -974,6 +995,7 @@ int force_accumulate(semx_ctx* c, const float* u, float* f, bool first_touch = f
   }
   if (colored) a.list = c->d_clist.as<int32_t>();
   if (parts) a.part = c->d_part.as<float>();
+  if (parts && aux) a.aux = *aux;
   const auto& launches = colored ? c->colored_launches : c->kind_launches;
   hipEvent_t e1 = nullptr;
   if (!launches.empty() && c->timing_stride > 0 && (c->timing_seq++ % c->timing_stride) == 0) {
@@ -984,24 +1006,21 @@ int force_accumulate(semx_ctx* c, const float* u, float* f, bool first_touch = f
   for (const auto& L : launches) {
     a.pos0 = L.pos0;
     a.count = L.count;
-    hipError_t e;
     const int geo = L.irregular ? c->irregular_geo : kRegular;
-    if (use_line(c, parts, geo))
-      e = c->physics == SEMX_ACOUSTIC ? launch_force_line_acoustic(c->n, geo, L.naff, a, c->stream)
-                                      : launch_force_line(c->n, geo, L.naff, a, c->stream);
-    else if (c->physics == SEMX_ACOUSTIC && c->n >= kTileMinNAcoustic)
-      e = launch_force_tile16_acoustic(c->n, geo, atomic, L.naff, a, c->stream);
-    else if (c->physics == SEMX_ACOUSTIC)
-      e = launch_force_acoustic(c->n, geo, atomic, L.naff, a, c->stream);
-    else if (c->n >= kTileMinN || (c->n >= kTileMinNMixed && c->contraction != SEMX_C_F32) ||
-             (c->n == kTileRegularN && geo == kRegular))
-      e = launch_force_tile16(c->n, c->contraction, geo, atomic, L.naff, a, c->stream);
-    else if (c->contraction == SEMX_C_F32 && c->n > kMaxNLow)
-      e = launch_force_high(c->n, geo, atomic, a, c->stream);
-    else if (c->contraction == SEMX_C_F32)
-      e = launch_force_f32_split(c->n, geo, atomic, L.naff, a, c->stream);
-    else
-      e = launch_force_mfma(c->n, c->contraction, geo, atomic, a, c->stream);
+    hipError_t e = hipErrorInvalidValue;
+    switch (kernel_for(c, parts, geo)) {
+      case kLine:
+        e = c->physics == SEMX_ACOUSTIC ? launch_force_line_acoustic(c->n, geo, L.naff, a, c->stream)
+                                        : launch_force_line(c->n, geo, L.naff, a, c->stream);
+        break;
+      case kTileAcoustic: e = launch_force_tile16_acoustic(c->n, geo, atomic, L.naff, a, c->stream); break;
+      case kAcoustic: e = launch_force_acoustic(c->n, geo, atomic, L.naff, a, c->stream); break;
+      case kTile: e = launch_force_tile16(c->n, c->contraction, geo, atomic, L.naff, a, c->stream); break;
+      case kColumn: e = launch_force_high(c->n, geo, atomic, a, c->stream); break;
+      case kPoint: e = launch_force_f32_split(c->n, geo, atomic, L.naff, a, c->stream); break;
+      case kMixed: e = launch_force_mfma(c->n, c->contraction, geo, atomic, a, c->stream); break;
+    }
+    a.aux.units = 0;  // rode in the first launch
     if (e != hipSuccess) return hip_fail(c, e, "force kernel launch");
   }
   if (parts && defer) {
@@ -1050,14 +1069,16 @@ bool force_overwrites(const semx_ctx* c) {
 
 // f = -K u.  `f_zeroed`: f already holds zeros.  `tl`: see force_accumulate.
 // `defer`: element-local forces may stay unsummed (the time loop's own f).
-int force_into(semx_ctx* c, const float* u, float* f, bool f_zeroed, bool tl = false, bool defer = false) {
+// `aux`: the step's bookkeeping, where the pass carries it (carries_aux).
+int force_into(semx_ctx* c, const float* u, float* f, bool f_zeroed, bool tl = false, bool defer = false,
+               const AuxArgs<float>* aux = nullptr) {
   int rs = settle_force(c);
   if (rs) return rs;
   if (!f_zeroed && !force_overwrites(c)) {
     int rc = zero_f32(c, f, state_len(c));
     if (rc) return rc;
   }
-  return force_accumulate(c, u, f, force_overwrites(c), !force_overwrites(c), tl, defer);
+  return force_accumulate(c, u, f, force_overwrites(c), !force_overwrites(c), tl, defer, aux);
 }
 
 // The time loop stores the source force into f before the force pass (in
@@ -1261,11 +1282,13 @@ int step_once(semx_ctx* c, bool record, float* seg_u, float* seg_a, const int64_
   // alone; with prestores() the same launch stores f_src^{n+1} into f
   const bool pre = prestores(c);
   int rc = pre ? build_first_tl(c) : SEMX_OK;
-  if (!rc) rc = step_aux(c, c->it, track && src_in_f, record, dstep, pre);
+  const bool ride = carries_aux(c);
+  const AuxArgs<float> aux = ride ? aux_args(c, c->it, track && src_in_f, record, dstep, pre) : AuxArgs<float>{};
+  if (!rc && !ride) rc = step_aux(c, c->it, track && src_in_f, record, dstep, pre);
   if (rc) return rc;
   // f is zero here only if the Newmark pass cleared it (untracked step on a
   // mesh the force pass does not overwrite)
-  rc = force_into(c, u, f, !track && !force_overwrites(c), pre, true);
+  rc = force_into(c, u, f, !track && !force_overwrites(c), pre, true, ride ? &aux : nullptr);
   if (!rc && !pre) rc = inject_sources(c, c->it + 1, f, dstep);
   if (rc) return rc;
   if (dstep) {

@@ -306,6 +306,7 @@ inline hipError_t split_affine(int64_t naff, const ForceArgs& a, F launch) {
   b.count = naff;
   hipError_t e = naff > 0 ? launch(b, true) : hipSuccess;
   if (e != hipSuccess || naff == a.count) return e;
+  if (naff > 0) b.aux.units = 0;
   b.pos0 = a.pos0 + naff;
   b.count = a.count - naff;
   return launch(b, false);
@@ -314,9 +315,10 @@ inline hipError_t split_affine(int64_t naff, const ForceArgs& a, F launch) {
 // XCD-aware group index: blocks are dispatched round-robin over the XCDs, so
 // block b runs on XCD b % 8; groups are dealt so that each XCD walks one
 // contiguous eighth of the launch range (elements sharing nodes meet in one L2).
-__device__ __forceinline__ int xcd_group(int ngrp) {
-  const int gpx = (ngrp + kNumXcd - 1) / kNumXcd;
-  return (blockIdx.x % kNumXcd) * gpx + blockIdx.x / kNumXcd;
+// `lead` blocks (a multiple of the XCD count) come before the groups' own.
+__device__ __forceinline__ int xcd_group(int ngrp, int lead = 0) {
+  const int gpx = (ngrp + kNumXcd - 1) / kNumXcd, b = (int)blockIdx.x - lead;
+  return (b % kNumXcd) * gpx + b / kNumXcd;
 }
 
 }  // namespace semx

@@ -46,8 +46,10 @@ __global__ __launch_bounds__(Shape<NG>::BLK) void force_f32_kernel(ForceArgs a) 
   __shared__ float s_q[9 * N3];
   __shared__ float s_D[ND + NG];  // D (row-major), then the GLL nodes
 
+  if constexpr (!ATOMIC)
+    if (run_aux(a.aux)) return;  // uniform over the block
   const int ngrp = (int)a.count;
-  const int grp = xcd_group(ngrp);
+  const int grp = xcd_group(ngrp, ATOMIC ? 0 : a.aux.blocks);
   if (grp >= ngrp) return;  // uniform over the block
   const int pos = elem_pos(a, grp);
 
@@ -167,8 +169,10 @@ __global__ __launch_bounds__(Shape<NG>::BLK) void force_f32_kernel(ForceArgs a) 
 template <int NG, int GEO, bool ATOMIC, bool AFF>
 hipError_t launch_one(const ForceArgs& a, hipStream_t s) {
   const int64_t nb = ((a.count + kNumXcd - 1) / kNumXcd) * kNumXcd;
-  dim3 grid((unsigned)nb, (unsigned)a.nmodels), block(Shape<NG>::BLK);
-  force_f32_kernel<NG, GEO, ATOMIC, AFF><<<grid, block, 0, s>>>(a);
+  ForceArgs b = a;
+  b.aux.blocks = (int)aux_blocks(a.aux, Shape<NG>::BLK, kNumXcd);
+  dim3 grid((unsigned)nb + b.aux.blocks, (unsigned)a.nmodels), block(Shape<NG>::BLK);
+  force_f32_kernel<NG, GEO, ATOMIC, AFF><<<grid, block, 0, s>>>(b);
   return hipGetLastError();
 }
 

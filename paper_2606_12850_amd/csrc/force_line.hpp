@@ -207,8 +207,9 @@ __global__ __launch_bounds__(LineShape<NG>::BLK) void force_line_kernel(ForceArg
   constexpr int AS = EPW * S::ESZ;  // words of one field
   __shared__ float s[2 * NC * AS];
 
+  if (run_aux(a.aux)) return;  // uniform over the block
   const int ngrp = ((int)a.count + EPW - 1) / EPW;
-  const int grp = xcd_group(ngrp);
+  const int grp = xcd_group(ngrp, a.aux.blocks);
   if (grp >= ngrp) return;  // uniform over the block
   // spare lanes repeat the last line (the same values to the same places),
   // spare elements of the last group the last element; neither stores a result
@@ -363,9 +364,11 @@ template <int NG, int NC, int GEO>
 hipError_t launch_line(bool aff, const ForceArgs& a, hipStream_t s) {
   using S = LineShape<NG>;
   const int64_t ngrp = (a.count + S::EPW - 1) / S::EPW;
-  const dim3 grid((unsigned)((ngrp + kNumXcd - 1) / kNumXcd * kNumXcd), (unsigned)a.nmodels);
-  if (aff) force_line_kernel<NG, NC, GEO, true><<<grid, S::BLK, 0, s>>>(a);
-  else force_line_kernel<NG, NC, GEO, false><<<grid, S::BLK, 0, s>>>(a);
+  ForceArgs b = a;
+  b.aux.blocks = (int)aux_blocks(a.aux, S::BLK, kNumXcd);
+  const dim3 grid((unsigned)((ngrp + kNumXcd - 1) / kNumXcd * kNumXcd) + b.aux.blocks, (unsigned)a.nmodels);
+  if (aff) force_line_kernel<NG, NC, GEO, true><<<grid, S::BLK, 0, s>>>(b);
+  else force_line_kernel<NG, NC, GEO, false><<<grid, S::BLK, 0, s>>>(b);
   return hipGetLastError();
 }
 

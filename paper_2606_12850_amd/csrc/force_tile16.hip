@@ -267,12 +267,15 @@ __global__ __launch_bounds__(kBlk) void force_tile16_kernel(ForceArgs a) {
   __shared__ __attribute__((aligned(16))) float r2[NC * kN3];
   __shared__ float s_red[2][kWaves];  // FP16: per-wave maxima of the operands
 
+  if constexpr (!ATOMIC)
+    if (run_aux(a.aux)) return;  // uniform over the block
+  const int lead = ATOMIC ? 0 : a.aux.blocks;
   const int ngrp = (int)a.count;
   const int gpx = (ngrp + kNumXcd - 1) / kNumXcd;
-  const int per_xcd = (int)gridDim.x / kNumXcd;
-  const int xbeg = ((int)blockIdx.x % kNumXcd) * gpx;
+  const int per_xcd = ((int)gridDim.x - lead) / kNumXcd;
+  const int xbeg = (((int)blockIdx.x - lead) % kNumXcd) * gpx;
   const int xend = min(xbeg + gpx, ngrp);
-  int grp = xbeg + (int)blockIdx.x / kNumXcd;
+  int grp = xbeg + ((int)blockIdx.x - lead) / kNumXcd;
   if (grp >= xend) return;  // uniform over the block
 
   const int w = threadIdx.x >> 6;
@@ -589,8 +592,10 @@ template <int NG, int GEO, bool ATOMIC, bool AFF, int PREC, int NC>
 hipError_t launch_t16(const ForceArgs& a, hipStream_t s) {
   int64_t nb = ((a.count + kNumXcd - 1) / kNumXcd) * kNumXcd;
   if (tile_persistent<NG, GEO, PREC, NC>()) nb = std::min<int64_t>(nb, resident_groups());
-  dim3 grid((unsigned)nb, (unsigned)a.nmodels), block(kBlk);
-  force_tile16_kernel<NG, GEO, ATOMIC, AFF, PREC, NC><<<grid, block, 0, s>>>(a);
+  ForceArgs b = a;
+  b.aux.blocks = ATOMIC ? 0 : (int)aux_blocks(a.aux, kBlk, kNumXcd);
+  dim3 grid((unsigned)nb + b.aux.blocks, (unsigned)a.nmodels), block(kBlk);
+  force_tile16_kernel<NG, GEO, ATOMIC, AFF, PREC, NC><<<grid, block, 0, s>>>(b);
   return hipGetLastError();
 }
 
@@ -620,6 +625,7 @@ hipError_t launch_t16_split(int geo, bool atomic, int64_t naff, const ForceArgs&
   b.count = naff;
   hipError_t e = launch_t16_geo<NG, true, PREC, NC>(geo, atomic, b, s);
   if (e != hipSuccess || naff == a.count) return e;
+  if (naff > 0) b.aux.units = 0;
   b.pos0 = a.pos0 + naff;
   b.count = a.count - naff;
   return launch_t16_geo<NG, false, PREC, NC>(geo, atomic, b, s);

@@ -27,11 +27,14 @@ template <int NG>
 __global__ void force64_kernel(int64_t pos0, const int32_t* __restrict__ list, int64_t nspec, int64_t nglob, int atomic,
                                const int32_t* __restrict__ ibool, const double* __restrict__ gam,
                                const double* __restrict__ mat, const double* __restrict__ Dg,
-                               const double* __restrict__ u, double* __restrict__ f, double* __restrict__ part) {
+                               const double* __restrict__ u, double* __restrict__ f, double* __restrict__ part,
+                               AuxArgs<double> aux) {
+  if (run_aux(aux)) return;  // uniform over the block
   constexpr int n3 = NG * NG * NG;
   __shared__ double D[NG * NG];  // D[a * NG + b] = l'_b(xi_a)
   __shared__ double s[3][n3];
-  const int64_t pos = list ? list[pos0 + blockIdx.x] : pos0 + blockIdx.x;
+  const int64_t slot = pos0 + (blockIdx.x - aux.blocks);
+  const int64_t pos = list ? list[slot] : slot;
   const int64_t model = blockIdx.y;
   const int q = threadIdx.x;
   for (int t = q; t < NG * NG; t += blockDim.x) D[t] = Dg[t];
@@ -261,35 +264,38 @@ __global__ void finite64_kernel(int64_t n, const double* __restrict__ x, int* __
 }
 
 template <int NG>
-hipError_t launch_force64_n(const semx_ctx* c, const double* u, double* f) {
+hipError_t launch_force64_n(const semx_ctx* c, const double* u, double* f, AuxArgs<double> aux) {
   constexpr int n3 = NG * NG * NG;
   const unsigned threads = (unsigned)((n3 + 63) / 64 * 64);
   const bool atomic = c->assembly == SEMX_ASM_ATOMIC;
   const bool parts = parts_active(c), colored = !atomic && !parts;
   for (const auto& L : colored ? c->colored_launches : c->kind_launches) {
     if (L.count <= 0) continue;
-    dim3 grid((unsigned)L.count, (unsigned)c->nmodels);
+    aux.blocks = (int)aux_blocks(aux, (int)threads, kNumXcd);
+    dim3 grid((unsigned)L.count + aux.blocks, (unsigned)c->nmodels);
     force64_kernel<NG><<<grid, threads, 0, c->stream>>>(
         L.pos0, colored ? c->d_clist.as<int32_t>() : nullptr, c->nspec, c->nglob, atomic ? 1 : 0,
         c->d_ibool.as<int32_t>(), c->d_gam64.as<double>(), c->d_mat64.as<double>(), c->d_D64.as<double>(), u, f,
-        parts ? c->d_part.as<double>() : nullptr);
+        parts ? c->d_part.as<double>() : nullptr, aux);
+    aux.units = 0;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
-hipError_t launch_force64(const semx_ctx* c, const double* u, double* f) {
+// aux: bookkeeping waves of the step that ride in the pass (element-local forces only)
+hipError_t launch_force64(const semx_ctx* c, const double* u, double* f, const AuxArgs<double>& aux = {}) {
   switch (c->n) {
-    case 2: return launch_force64_n<2>(c, u, f);
-    case 3: return launch_force64_n<3>(c, u, f);
-    case 4: return launch_force64_n<4>(c, u, f);
-    case 5: return launch_force64_n<5>(c, u, f);
-    case 6: return launch_force64_n<6>(c, u, f);
-    case 7: return launch_force64_n<7>(c, u, f);
-    case 8: return launch_force64_n<8>(c, u, f);
-    case 9: return launch_force64_n<9>(c, u, f);
-    case 10: return launch_force64_n<10>(c, u, f);
+    case 2: return launch_force64_n<2>(c, u, f, aux);
+    case 3: return launch_force64_n<3>(c, u, f, aux);
+    case 4: return launch_force64_n<4>(c, u, f, aux);
+    case 5: return launch_force64_n<5>(c, u, f, aux);
+    case 6: return launch_force64_n<6>(c, u, f, aux);
+    case 7: return launch_force64_n<7>(c, u, f, aux);
+    case 8: return launch_force64_n<8>(c, u, f, aux);
+    case 9: return launch_force64_n<9>(c, u, f, aux);
+    case 10: return launch_force64_n<10>(c, u, f, aux);
     default: return hipErrorInvalidValue;
   }
 }
@@ -439,13 +445,11 @@ int f64_step_once(semx_ctx* c, bool record) {
   }
   int rc = SEMX_OK;
   if (parts) {
-    // receivers, source work and the coming source force read u^{n+1}, which
-    // the force pass leaves alone: one launch before it
+    // receivers, source work and the coming source force ride in the force launch
     const bool pre = prestores(c);
     if (pre) rc = build_first_tl(c);
-    if (!rc) rc = step_aux(c, c->it, track && src_in_f, record, nullptr, pre);
     if (rc) return rc;
-    const hipError_t e = launch_force64(c, u, f);
+    const hipError_t e = launch_force64(c, u, f, aux_args64(c, c->it, track && src_in_f, record, pre));
     if (e != hipSuccess) return hip_fail(c, e, "FP64 force kernel launch");
     c->f_in_part = true;
     c->part_src = pre;
