@@ -109,27 +109,39 @@ __device__ __forceinline__ void aux_energy(const AuxArgs<T>& A, int lane) {
   const int64_t n = A.step ? *A.step : A.it;
   T* slot = A.hist + (size_t)((n + 1) & 1) * A.per;
   const bool with_work = n > A.it0;
-  double work[4] = {0, 0, 0, 0}, corr[4] = {0, 0, 0, 0};
-  for (int k0 = lane; k0 < A.npt; k0 += 256) {
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const int k = k0 + 64 * w;
-      if (k >= A.npt) break;
-      const int p = A.pts[k];
-      const int s = p / A.n3;
-      const double amp = (n >= 0 && n < A.nstf) ? (double)A.stf[(int64_t)s * A.nstf + n] : 0.0;
-      const int64_t g = A.snodes[p];
+  const bool live = n >= 0 && n < A.nstf;
+  // two points a lane at a time: their indices, then their values, in one
+  // round trip each (no more: the force kernel that carries this wave lives on
+  // its occupancy)
+  auto pass = [&](int first, double& work0, double& work1, double& corr0, double& corr1) {
+    for (int k0 = lane + first; k0 < A.npt; k0 += 256) {
+      const bool two = k0 + 64 < A.npt;
+      const int k1 = two ? k0 + 64 : k0;
+      const int p0 = A.pts[k0], p1 = A.pts[k1];
+      const int g0 = A.snodes[p0] * A.nc, g1 = A.snodes[p1] * A.nc;
+      const T amp0 = live ? A.stf[(int64_t)(p0 / A.n3) * A.nstf + n] : (T)0;
+      const T amp1 = live ? A.stf[(int64_t)(p1 / A.n3) * A.nstf + n] : (T)0;
+#pragma unroll 1
       for (int c = 0; c < A.nc; ++c) {
-        const double un = A.u[A.nc * g + c];
-        const double fs = amp * (double)A.wdir[(int64_t)A.nc * p + c];
-        work[w] += 0.5 * (un - (double)slot[(int64_t)A.nc * k + c]) * fs;
-        corr[w] += un * fs;
-        slot[(int64_t)A.nc * k + c] = (T)un;
+        const T u0 = A.u[g0 + c], u1 = A.u[g1 + c];
+        const double fs0 = (double)amp0 * (double)A.wdir[A.nc * p0 + c];
+        const double fs1 = (double)amp1 * (double)A.wdir[A.nc * p1 + c];
+        const T old0 = slot[A.nc * k0 + c], old1 = slot[A.nc * k1 + c];
+        work0 += 0.5 * ((double)u0 - (double)old0) * fs0;
+        corr0 += (double)u0 * fs0;
+        slot[A.nc * k0 + c] = u0;
+        if (two) {
+          work1 += 0.5 * ((double)u1 - (double)old1) * fs1;
+          corr1 += (double)u1 * fs1;
+          slot[A.nc * k1 + c] = u1;
+        }
       }
     }
-  }
-  const double ws = tree_sum(work[0], work[1], work[2], work[3]);
-  const double cs = tree_sum(corr[0], corr[1], corr[2], corr[3]);
+  };
+  double w0 = 0, w1 = 0, w2 = 0, w3 = 0, c0 = 0, c1 = 0, c2 = 0, c3 = 0;
+  pass(0, w0, w1, c0, c1);
+  pass(128, w2, w3, c2, c3);
+  const double ws = tree_sum(w0, w1, w2, w3), cs = tree_sum(c0, c1, c2, c3);
   if (lane == 0) {
     if (with_work) A.acc[3] += ws;
     if (A.with_corr) A.acc[2] = cs;

@@ -48,6 +48,9 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// assembly: read-modify-write inside a colour, atomic adds, element-local forces
+constexpr int kRmw = 0, kAtomicAdd = 1, kPart = 2;
+
 constexpr int kN = 16;
 constexpr int kN3 = kN * kN * kN;
 constexpr int kWaves = 16;
@@ -177,7 +180,7 @@ __device__ __forceinline__ void load_mat(const ForceArgs& a, int model, int pos,
   }
 }
 
-template <int NG, bool ATOMIC, bool AFF, bool MAT, int NC = 3>
+template <int NG, int ASM, bool AFF, bool MAT, int NC = 3>
 __device__ __forceinline__ void load_ahead(const ForceArgs& a, const float* __restrict__ u, int model, int pos,
                                            const OwnPts<NG>& P, int g, int c, int w, Ahead& h) {
   constexpr int E3 = NG * NG * NG;
@@ -197,7 +200,7 @@ __device__ __forceinline__ void load_ahead(const ForceArgs& a, const float* __re
     for (int t = 0; t < 4; ++t) h.node[t] = P.real(t) ? a.ibool[(size_t)pos * E3 + P.q(t)] : 0;
   }
   h.fw = 0;
-  if constexpr (!ATOMIC) {
+  if constexpr (ASM == kRmw) {
     if (a.first) {
       const uint32_t* fb = a.first + (size_t)pos * a.first_words;
       if constexpr (NG == kN) {
@@ -245,20 +248,20 @@ __device__ __forceinline__ void load_ahead(const ForceArgs& a, const float* __re
 // form spills 84-176 bytes and loses up to 50 %.  The scalar operator
 // (NC = 1) has the room: it gains 5-14 % on every geometry path.  The launch
 // sizes the grid by the same rule.
-template <int NG, int GEO, int PREC, int NC>
+template <int NG, int GEO, int ASM, int PREC, int NC>
 constexpr bool tile_persistent() {
-  return NC == 1 || (GEO == kRegular && (NG == kN || PREC != SEMX_C_F16));
+  return NC == 1 || (GEO == kRegular && (ASM == kPart || NG == kN || PREC != SEMX_C_F16));
 }
 
-template <int NG, int GEO, bool ATOMIC, bool AFF, int PREC, int NC>
+template <int NG, int GEO, int ASM, bool AFF, int PREC, int NC>
 __global__ __launch_bounds__(kBlk) void force_tile16_kernel(ForceArgs a) {
   static_assert(NC == 3 || PREC == SEMX_C_F32, "the scalar (acoustic) operator runs in FP32");
   constexpr int E3 = NG * NG * NG;
   // persistent, next element requested ahead
-  constexpr bool AHEAD = tile_persistent<NG, GEO, PREC, NC>();
+  constexpr bool AHEAD = tile_persistent<NG, GEO, ASM, PREC, NC>();
   constexpr bool LOW = PREC == SEMX_C_BF16 || PREC == SEMX_C_F16;
   // 16-bit operands and padded tiles need the registers: material at the start
-  constexpr bool MAT_AHEAD = AHEAD && !LOW && NG == kN;
+  constexpr bool MAT_AHEAD = AHEAD && (ASM == kPart ? NC == 1 || PREC != SEMX_C_F16 : !LOW && NG == kN);
   constexpr bool SCALE = PREC == SEMX_C_F16;  // BF16 has the FP32 exponent range
   using L = Low<PREC>;
   using lvec = typename L::vec;
@@ -267,9 +270,9 @@ __global__ __launch_bounds__(kBlk) void force_tile16_kernel(ForceArgs a) {
   __shared__ __attribute__((aligned(16))) float r2[NC * kN3];
   __shared__ float s_red[2][kWaves];  // FP16: per-wave maxima of the operands
 
-  if constexpr (!ATOMIC)
+  if constexpr (ASM == kPart)
     if (run_aux(a.aux)) return;  // uniform over the block
-  const int lead = ATOMIC ? 0 : a.aux.blocks;
+  const int lead = ASM == kPart ? a.aux.blocks : 0;
   const int ngrp = (int)a.count;
   const int gpx = (ngrp + kNumXcd - 1) / kNumXcd;
   const int per_xcd = ((int)gridDim.x - lead) / kNumXcd;
@@ -307,17 +310,19 @@ __global__ __launch_bounds__(kBlk) void force_tile16_kernel(ForceArgs a) {
   }
 
   Ahead cur;
-  if constexpr (AHEAD) load_ahead<NG, ATOMIC, AFF, MAT_AHEAD, NC>(a, u, model, elem_pos(a, grp), P, g, c, w, cur);
+  if constexpr (AHEAD) load_ahead<NG, ASM, AFF, MAT_AHEAD, NC>(a, u, model, elem_pos(a, grp), P, g, c, w, cur);
   for (;;) {
     const int pos = elem_pos(a, grp);
-    if constexpr (!AHEAD) load_ahead<NG, ATOMIC, AFF, true, NC>(a, u, model, pos, P, g, c, w, cur);
+    if constexpr (!AHEAD) load_ahead<NG, ASM, AFF, true, NC>(a, u, model, pos, P, g, c, w, cur);
     if constexpr (AHEAD && !MAT_AHEAD) load_mat<NG>(a, model, pos, P, cur);
     float fo[3][4];
     auto read_prior = [&]() {
+      if constexpr (ASM != kRmw) return;
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        fo[0][t] = fo[1][t] = fo[2][t] = 0.0f;
-        if (!ATOMIC && !a.part && P.real(t) && !((cur.fw >> t) & 1u)) {  // the point's values in one request
+#pragma unroll
+        for (int e = 0; e < NC; ++e) fo[e][t] = 0.0f;
+        if (P.real(t) && !((cur.fw >> t) & 1u)) {  // the point's values in one request
           const float* fp = f + NC * (size_t)cur.node[t];
 #pragma unroll
           for (int e = 0; e < NC; ++e) fo[e][t] = fp[e];
@@ -510,7 +515,7 @@ __global__ __launch_bounds__(kBlk) void force_tile16_kernel(ForceArgs a) {
     const bool more = AHEAD && nxt < xend;  // uniform over the block
     Ahead ahead;
     if constexpr (AHEAD) {
-      if (more) load_ahead<NG, ATOMIC, AFF, MAT_AHEAD, NC>(a, u, model, elem_pos(a, nxt), P, g, c, w, ahead);
+      if (more) load_ahead<NG, ASM, AFF, MAT_AHEAD, NC>(a, u, model, elem_pos(a, nxt), P, g, c, w, ahead);
     }
     __syncthreads();  // B3: eta fluxes in R0, zeta fluxes in R2; R1 free
     if constexpr (LOW) {
@@ -557,15 +562,30 @@ __global__ __launch_bounds__(kBlk) void force_tile16_kernel(ForceArgs a) {
     for (int e = 0; e < NC; ++e) F[e] += ld4(r1 + e * kN3 + sS);
 
     // ---- assembly ----
+    if constexpr (ASM == kPart) {
+      float* fp = a.part + (((size_t)model * a.nspec + pos) * E3 + P.q0) * NC;
+      if constexpr (NG == kN && NC == 3) {  // the four points' twelve values: 16-byte aligned
+        st4(fp, f32x4{-F[0][0], -F[1][0], -F[2][0], -F[0][1]});
+        st4(fp + 4, f32x4{-F[1][1], -F[2][1], -F[0][2], -F[1][2]});
+        st4(fp + 8, f32x4{-F[2][2], -F[0][3], -F[1][3], -F[2][3]});
+      } else {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      if (!P.real(t)) continue;
-      float* fg = !ATOMIC && a.part ? a.part + (((size_t)model * a.nspec + pos) * E3 + P.q(t)) * NC
-                                    : f + NC * (size_t)cur.node[t];
+        for (int t = 0; t < 4; ++t)
+          if (P.real(t)) {
 #pragma unroll
-      for (int e = 0; e < NC; ++e) {
-        if constexpr (ATOMIC) unsafeAtomicAdd(fg + e, -F[e][t]);
-        else fg[e] = fo[e][t] - F[e][t];
+            for (int e = 0; e < NC; ++e) fp[t * NC + e] = -F[e][t];
+          }
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        if (!P.real(t)) continue;
+        float* fg = f + NC * (size_t)cur.node[t];
+#pragma unroll
+        for (int e = 0; e < NC; ++e) {
+          if constexpr (ASM == kAtomicAdd) unsafeAtomicAdd(fg + e, -F[e][t]);
+          else fg[e] = fo[e][t] - F[e][t];
+        }
       }
     }
     if (!AHEAD || !more) break;
@@ -588,32 +608,31 @@ int64_t resident_groups() {
   return cache[dev];
 }
 
-template <int NG, int GEO, bool ATOMIC, bool AFF, int PREC, int NC>
+template <int NG, int GEO, int ASM, bool AFF, int PREC, int NC>
 hipError_t launch_t16(const ForceArgs& a, hipStream_t s) {
   int64_t nb = ((a.count + kNumXcd - 1) / kNumXcd) * kNumXcd;
-  if (tile_persistent<NG, GEO, PREC, NC>()) nb = std::min<int64_t>(nb, resident_groups());
+  if (tile_persistent<NG, GEO, ASM, PREC, NC>()) nb = std::min<int64_t>(nb, resident_groups());
   ForceArgs b = a;
-  b.aux.blocks = ATOMIC ? 0 : (int)aux_blocks(a.aux, kBlk, kNumXcd);
+  b.aux.blocks = ASM == kPart ? (int)aux_blocks(a.aux, kBlk, kNumXcd) : 0;
   dim3 grid((unsigned)nb + b.aux.blocks, (unsigned)a.nmodels), block(kBlk);
-  force_tile16_kernel<NG, GEO, ATOMIC, AFF, PREC, NC><<<grid, block, 0, s>>>(b);
+  force_tile16_kernel<NG, GEO, ASM, AFF, PREC, NC><<<grid, block, 0, s>>>(b);
   return hipGetLastError();
+}
+
+template <int NG, int GEO, bool AFF, int PREC, int NC>
+hipError_t launch_t16_asm(bool atomic, const ForceArgs& a, hipStream_t s) {
+  if (atomic) return launch_t16<NG, GEO, kAtomicAdd, AFF, PREC, NC>(a, s);
+  return a.part ? launch_t16<NG, GEO, kPart, AFF, PREC, NC>(a, s) : launch_t16<NG, GEO, kRmw, AFF, PREC, NC>(a, s);
 }
 
 template <int NG, bool AFF, int PREC, int NC>
 hipError_t launch_t16_geo(int geo, bool atomic, const ForceArgs& a, hipStream_t s) {
   if (a.count <= 0) return hipSuccess;
   switch (geo) {
-    case kRegular:
-      return atomic ? launch_t16<NG, kRegular, true, AFF, PREC, NC>(a, s)
-                    : launch_t16<NG, kRegular, false, AFF, PREC, NC>(a, s);
-    case kStored:
-      return atomic ? launch_t16<NG, kStored, true, AFF, PREC, NC>(a, s)
-                    : launch_t16<NG, kStored, false, AFF, PREC, NC>(a, s);
-    case kTrilinear:
-      return atomic ? launch_t16<NG, kTrilinear, true, AFF, PREC, NC>(a, s)
-                    : launch_t16<NG, kTrilinear, false, AFF, PREC, NC>(a, s);
-    default:
-      return hipErrorInvalidValue;
+    case kRegular: return launch_t16_asm<NG, kRegular, AFF, PREC, NC>(atomic, a, s);
+    case kStored: return launch_t16_asm<NG, kStored, AFF, PREC, NC>(atomic, a, s);
+    case kTrilinear: return launch_t16_asm<NG, kTrilinear, AFF, PREC, NC>(atomic, a, s);
+    default: return hipErrorInvalidValue;
   }
 }
 
