@@ -1445,14 +1445,9 @@ int semx_create(semx_ctx** out, int ngll, void* hip_stream) {
   gll_nodes_weights(ngll, c->xi, c->w);
   deriv_matrix(ngll, c->xi, c->D);
   std::vector<float> Df(c->D.begin(), c->D.end());
-  // even-odd form of D (force_line.hpp): A, B, middle column, middle row
-  std::vector<float> eo;
-  const int h = ngll / 2, m = ngll - 1;
-  for (int sgn = -1; sgn <= 1; sgn += 2)
-    for (int i = 0; i < h; ++i)
-      for (int j = 0; j < h; ++j) eo.push_back((float)(0.5 * (c->D[i * ngll + j] + sgn * c->D[i * ngll + m - j])));
-  for (int i = 0; i < h; ++i) eo.push_back((float)c->D[i * ngll + h]);
-  for (int j = 0; j < h; ++j) eo.push_back((float)c->D[h * ngll + j]);
+  std::vector<double> eo64;
+  even_odd(ngll, c->D, eo64);
+  std::vector<float> eo(eo64.begin(), eo64.end());
   int rc = dev_alloc(c, c->d_D, Df.size() * sizeof(float));
   if (!rc) rc = dev_alloc(c, c->d_eo, eo.size() * sizeof(float));
   if (!rc) rc = dev_alloc(c, c->d_xi64, ngll * sizeof(double));
@@ -1493,7 +1488,7 @@ int semx_destroy(semx_ctx* c) {
                     &c->src.sidx, &c->rec.nodes, &c->rec.wts,
                     &c->rec.seis,
                     &c->src.wdir64, &c->src.stf64, &c->rec.wts64, &c->rec.seis64, &c->d_gam64, &c->d_mat64,
-                    &c->d_minv64, &c->d_D64,
+                    &c->d_minv64, &c->d_D64, &c->d_eo64, &c->d_gam64_el,
                     &c->d_first, &c->d_aff, &c->d_nptr, &c->d_nidx, &c->d_part, &c->d_srcbits, &c->d_clist, &c->rec.rbits, &c->rec.rnode, &c->rec.rptr,
                     &c->rec.ridx})
     dev_free(*b);
@@ -1713,7 +1708,7 @@ int upload_model_impl(semx_ctx* c, int nmodels, const double* lambda, const doub
   }
   if (!rc && c->storage == SEMX_F64) rc = dev_alloc(c, c->d_gam64, sizeof(double) * 9 * c->nspec * c->n3);
   if (!rc && c->storage != SEMX_F64)
-    for (DevBuf* b : {&c->d_gam64, &c->d_mat64, &c->d_minv64}) dev_free(*b);
+    for (DevBuf* b : {&c->d_gam64, &c->d_mat64, &c->d_minv64, &c->d_gam64_el}) dev_free(*b);
   auto cleanup = [&]() { dev_free(dl); dev_free(dm); dev_free(dr); };
   if (rc) { cleanup(); return rc; }
   hipError_t e = hipMemcpy(dl.p, lambda, sizeof(double) * npt, hipMemcpyHostToDevice);

@@ -115,7 +115,8 @@ __device__ __forceinline__ void geom_map(const ForceArgs& a, int pos, const floa
 }
 
 // gr[c][b] = sum_d du[c][d] Mg[d][b]
-__device__ __forceinline__ void apply_map(const float du[3][3], const float Mg[9], float gr[3][3]) {
+template <class T>
+__device__ __forceinline__ void apply_map(const T du[3][3], const T Mg[9], T gr[3][3]) {
 #pragma unroll
   for (int c = 0; c < 3; ++c)
 #pragma unroll
@@ -299,10 +300,10 @@ __device__ __forceinline__ void pin_elem_geom(const ElemGeom<GEO>& eg) {
 }
 
 // A launch range whose first `naff` elements are affine-numbered: two launches.
-template <class F>
-inline hipError_t split_affine(int64_t naff, const ForceArgs& a, F launch) {
+template <class A, class F>
+inline hipError_t split_affine(int64_t naff, const A& a, F launch) {
   naff = naff < 0 ? 0 : (naff > a.count ? a.count : naff);
-  ForceArgs b = a;
+  A b = a;
   b.count = naff;
   hipError_t e = naff > 0 ? launch(b, true) : hipSuccess;
   if (e != hipSuccess || naff == a.count) return e;

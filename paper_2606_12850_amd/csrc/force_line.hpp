@@ -1,5 +1,6 @@
-// Element force kernel with one lane per line of points (FP32; NC = 3 elastic,
-// NC = 1 acoustic): element-local forces for the nodal sum.
+// Element force kernel with one lane per line of points (T = float: NC = 3
+// elastic, NC = 1 acoustic; T = double: elastic): element-local forces for the
+// nodal sum.
 //
 // The per-point kernels (one lane per GLL point) read n values per component
 // and direction from LDS for each point and fetch D with them; at NGLL 5 they
@@ -30,8 +31,9 @@
 namespace semx {
 namespace {
 
-template <int NG>
+template <class T, int NG>
 struct LineShape {
+  static constexpr bool F64 = sizeof(T) == 8;
   static constexpr int N2 = NG * NG;
   static constexpr int N3 = NG * NG * NG;
   static constexpr int P = NG | 1;          // LDS stride of a xi line
@@ -39,35 +41,36 @@ struct LineShape {
   // elements per workgroup (NGLL 10: one in 100 of 128 lanes; three in 300 of
   // 320 leave two workgroups a compute unit and took 79 instead of 59 us per
   // apply at 16^3 elements), lanes
-  static constexpr int EPW = NG == 2 ? 16 : NG == 3 ? 7 : NG == 4 ? 4 : NG <= 7 ? 5 : NG == 9 ? 3 : 1;
+  static constexpr int EPW = NG == 2 ? 16 : NG == 3 ? 7 : NG == 4 ? 4 : NG == 5 ? 5 : NG == 6 ? (F64 ? 3 : 5)
+                             : NG == 7 ? (F64 ? 1 : 5) : NG == 9 ? (F64 ? 1 : 3) : 1;
   static constexpr int BLK = (EPW * N2 + 63) / 64 * 64;
 };
 
 // Even-odd tables of D: A[i][j] = (D[i][j] - D[i][n-1-j]) / 2, B[i][j] = (D[i][j] +
 // D[i][n-1-j]) / 2 for i, j < n / 2, then the middle column D[i][n/2] and the
 // middle row D[n/2][j] (odd n).
-template <int NG>
+template <class T, int NG>
 struct EvenOdd {
   static constexpr int H = NG / 2;
   static constexpr bool ODD = NG & 1;
-  const float* __restrict__ t;
-  __device__ __forceinline__ float A(int i, int j) const { return t[i * H + j]; }
-  __device__ __forceinline__ float B(int i, int j) const { return t[H * H + i * H + j]; }
-  __device__ __forceinline__ float col(int i) const { return t[2 * H * H + i]; }
-  __device__ __forceinline__ float row(int j) const { return t[2 * H * H + H + j]; }
+  const T* __restrict__ t;
+  __device__ __forceinline__ T A(int i, int j) const { return t[i * H + j]; }
+  __device__ __forceinline__ T B(int i, int j) const { return t[H * H + i * H + j]; }
+  __device__ __forceinline__ T col(int i) const { return t[2 * H * H + i]; }
+  __device__ __forceinline__ T row(int j) const { return t[2 * H * H + H + j]; }
 
   // y = D x
-  __device__ __forceinline__ void apply(float x[NG]) const {
-    float e[H], o[H];
+  __device__ __forceinline__ void apply(T x[NG]) const {
+    T e[H], o[H];
 #pragma unroll
     for (int j = 0; j < H; ++j) {
       e[j] = x[j] + x[NG - 1 - j];
       o[j] = x[j] - x[NG - 1 - j];
     }
-    const float mid = x[H];
+    const T mid = x[H];
 #pragma unroll
     for (int i = 0; i < H; ++i) {
-      float s = A(i, 0) * o[0], t_ = B(i, 0) * e[0];
+      T s = A(i, 0) * o[0], t_ = B(i, 0) * e[0];
 #pragma unroll
       for (int j = 1; j < H; ++j) {
         s += A(i, j) * o[j];
@@ -78,7 +81,7 @@ struct EvenOdd {
       x[NG - 1 - i] = s - t_;
     }
     if constexpr (ODD) {
-      float s = row(0) * o[0];
+      T s = row(0) * o[0];
 #pragma unroll
       for (int j = 1; j < H; ++j) s += row(j) * o[j];
       x[H] = s;
@@ -86,17 +89,17 @@ struct EvenOdd {
   }
 
   // z = D^T q
-  __device__ __forceinline__ void apply_t(float q[NG]) const {
-    float e[H], o[H];
+  __device__ __forceinline__ void apply_t(T q[NG]) const {
+    T e[H], o[H];
 #pragma unroll
     for (int i = 0; i < H; ++i) {
       e[i] = q[i] + q[NG - 1 - i];
       o[i] = q[i] - q[NG - 1 - i];
     }
-    const float mid = q[H];
+    const T mid = q[H];
 #pragma unroll
     for (int j = 0; j < H; ++j) {
-      float s = B(0, j) * o[0], t_ = A(0, j) * e[0];
+      T s = B(0, j) * o[0], t_ = A(0, j) * e[0];
 #pragma unroll
       for (int i = 1; i < H; ++i) {
         s += B(i, j) * o[i];
@@ -107,7 +110,7 @@ struct EvenOdd {
       q[NG - 1 - j] = s - t_;
     }
     if constexpr (ODD) {
-      float s = col(0) * o[0];
+      T s = col(0) * o[0];
 #pragma unroll
       for (int i = 1; i < H; ++i) s += col(i) * o[i];
       q[H] = s;
@@ -117,11 +120,11 @@ struct EvenOdd {
 
 // Geometry of the points of one zeta line.  kTrilinear: along the line the
 // first two columns of J are linear in zeta and the third is constant.
-template <int GEO>
+template <class T, int GEO>
 struct LineGeom {
-  float g[GEO == kStored ? 1 : GEO == kRegular ? 9 : 15];
+  T g[GEO == kStored ? 1 : GEO == kRegular ? 9 : 15];
 
-  __device__ __forceinline__ void load(const ForceArgs& a, int pos, float rx, float ry) {
+  __device__ __forceinline__ void load(const LineArgs<T>& a, int pos, T rx, T ry) {
     if constexpr (GEO == kRegular) {
 #pragma unroll
       for (int d = 0; d < 9; ++d) g[d] = a.gam_el[(size_t)pos * 9 + d];
@@ -140,8 +143,8 @@ struct LineGeom {
     }
   }
   // Mg and scale as in geom_map_from (G: the point's Gamma on the stored path)
-  __device__ __forceinline__ void at(float rz, const float G[9], float Mg[9], float& scale) const {
-    scale = 1.0f;
+  __device__ __forceinline__ void at(T rz, const T G[9], T Mg[9], T& scale) const {
+    scale = 1;
     if constexpr (GEO == kStored) {
 #pragma unroll
       for (int d = 0; d < 9; ++d) Mg[d] = G[d];
@@ -149,7 +152,7 @@ struct LineGeom {
 #pragma unroll
       for (int d = 0; d < 9; ++d) Mg[d] = g[d];
     } else {
-      float J[3][3];
+      T J[3][3];
 #pragma unroll
       for (int ax = 0; ax < 3; ++ax) {
         J[ax][0] = g[5 * ax + 0] + g[5 * ax + 1] * rz;
@@ -165,20 +168,21 @@ struct LineGeom {
       Mg[2] = J[0][1] * J[1][2] - J[0][2] * J[1][1];
       Mg[5] = J[0][2] * J[1][0] - J[0][0] * J[1][2];
       Mg[8] = J[0][0] * J[1][1] - J[0][1] * J[1][0];
-      const float det = J[0][0] * Mg[0] + J[0][1] * Mg[3] + J[0][2] * Mg[6];
-      const float id = __builtin_amdgcn_rcpf(det);
+      const T det = J[0][0] * Mg[0] + J[0][1] * Mg[3] + J[0][2] * Mg[6];
+      const T id = __builtin_amdgcn_rcpf(det);
       scale = id * id;
     }
   }
 };
 
 // Weighted fluxes of one point in place of its reference derivatives d[c][dir].
-__device__ __forceinline__ void point_flux(float d[3][3], const float Mg[9], float scale, float lamw, float muw) {
-  float gr[3][3];
+template <class T>
+__device__ __forceinline__ void point_flux(T d[3][3], const T Mg[9], T scale, T lamw, T muw) {
+  T gr[3][3];
   apply_map(d, Mg, gr);
-  const float ls = lamw * scale, ms = muw * scale, ms2 = 2.0f * ms;
-  const float ltr = ls * (gr[0][0] + gr[1][1] + gr[2][2]);
-  float sg[3][3];
+  const T ls = lamw * scale, ms = muw * scale, ms2 = 2 * ms;
+  const T ltr = ls * (gr[0][0] + gr[1][1] + gr[2][2]);
+  T sg[3][3];
   sg[0][0] = ltr + ms2 * gr[0][0];
   sg[1][1] = ltr + ms2 * gr[1][1];
   sg[2][2] = ltr + ms2 * gr[2][2];
@@ -191,21 +195,22 @@ __device__ __forceinline__ void point_flux(float d[3][3], const float Mg[9], flo
     for (int q = 0; q < 3; ++q) d[c][q] = sg[c][0] * Mg[q * 3 + 0] + sg[c][1] * Mg[q * 3 + 1] + sg[c][2] * Mg[q * 3 + 2];
 }
 
-__device__ __forceinline__ void scalar_flux(float d[3], const float Mg[9], float scale, float w) {
-  float g[3];
+template <class T>
+__device__ __forceinline__ void scalar_flux(T d[3], const T Mg[9], T scale, T w) {
+  T g[3];
 #pragma unroll
   for (int b = 0; b < 3; ++b) g[b] = d[0] * Mg[0 * 3 + b] + d[1] * Mg[1 * 3 + b] + d[2] * Mg[2 * 3 + b];
-  const float s = w * scale;
+  const T s = w * scale;
 #pragma unroll
   for (int q = 0; q < 3; ++q) d[q] = s * (g[0] * Mg[q * 3 + 0] + g[1] * Mg[q * 3 + 1] + g[2] * Mg[q * 3 + 2]);
 }
 
-template <int NG, int NC, int GEO, bool AFF>
-__global__ __launch_bounds__(LineShape<NG>::BLK) void force_line_kernel(ForceArgs a) {
-  using S = LineShape<NG>;
+template <class T, int NG, int NC, int GEO, bool AFF>
+__global__ __launch_bounds__((LineShape<T, NG>::BLK)) void force_line_kernel(LineArgs<T> a) {
+  using S = LineShape<T, NG>;
   constexpr int N2 = S::N2, N3 = S::N3, P = S::P, EPW = S::EPW;
   constexpr int AS = EPW * S::ESZ;  // words of one field
-  __shared__ float s[2 * NC * AS];
+  __shared__ T s[2 * NC * AS];
 
   if (run_aux(a.aux)) return;  // uniform over the block
   const int ngrp = ((int)a.count + EPW - 1) / EPW;
@@ -221,15 +226,15 @@ __global__ __launch_bounds__(LineShape<NG>::BLK) void force_line_kernel(ForceArg
   const int pos = (int)a.pos0 + min(el, (int)a.count - 1);
 
   const int model = blockIdx.y;
-  const float* __restrict__ u = a.u + (size_t)model * a.nglob * NC;
-  const float* __restrict__ mat = a.mat + ((size_t)model * a.nspec + pos) * 2 * N3 + c;
-  const EvenOdd<NG> D{a.eo};
+  const T* __restrict__ u = a.u + (size_t)model * a.nglob * NC;
+  const T* __restrict__ mat = a.mat + ((size_t)model * a.nspec + pos) * 2 * N3 + c;
+  const EvenOdd<T, NG> D{a.eo};
 
   // the line's nodes, u and material; the element's geometry
-  float uc[NC][NG], lam[NG], mu[NC == 3 ? NG : 1];
+  T uc[NC][NG], lam[NG], mu[NC == 3 ? NG : 1];
   if constexpr (AFF) {
     const int4 r = *reinterpret_cast<const int4*>(a.aff + (size_t)pos * 4);
-    const float* p = u + (int64_t)(r.x + i * r.y + j * r.z) * NC;
+    const T* p = u + (int64_t)(r.x + i * r.y + j * r.z) * NC;
     const int64_t step = (int64_t)r.w * NC;
 #pragma unroll
     for (int k = 0; k < NG; ++k)
@@ -245,18 +250,18 @@ __global__ __launch_bounds__(LineShape<NG>::BLK) void force_line_kernel(ForceArg
 #pragma unroll
       for (int q = 0; q < NC; ++q) uc[q][k] = u[(int64_t)node[k] * NC + q];
   }
-  LineGeom<GEO> geo;
-  geo.load(a, pos, GEO == kTrilinear ? a.xi[i] : 0.0f, GEO == kTrilinear ? a.xi[j] : 0.0f);
+  LineGeom<T, GEO> geo;
+  geo.load(a, pos, GEO == kTrilinear ? a.xi[i] : (T)0, GEO == kTrilinear ? a.xi[j] : (T)0);
 #pragma unroll
   for (int k = 0; k < NG; ++k) {
     lam[k] = ldnt(mat + k * N2);
     if constexpr (NC == 3) mu[k] = ldnt(mat + N3 + k * N2);
   }
-  const float* __restrict__ gp = GEO == kStored ? a.gam_pt + (size_t)pos * 9 * N3 + c : nullptr;
+  const T* __restrict__ gp = GEO == kStored ? a.gam_pt + (size_t)pos * 9 * N3 + c : nullptr;
   // Gamma of the next PD points of the line (a stored-path pass is bound by
   // the bytes in flight)
-  constexpr int PD = NG <= 5 ? NG : 2;
-  float Gn[PD][9];
+  constexpr int PD = NG <= 5 && !S::F64 ? NG : 2;
+  T Gn[PD][9];
   if constexpr (GEO == kStored) {
 #pragma unroll
     for (int k = 0; k < PD; ++k)
@@ -264,9 +269,9 @@ __global__ __launch_bounds__(LineShape<NG>::BLK) void force_line_kernel(ForceArg
       for (int d = 0; d < 9; ++d) Gn[k][d] = ldnt(gp + d * N3 + k * N2);
   }
 
-  float* const sz = s + e * S::ESZ + i + P * j;       // home: + k P n
-  float* const sx = s + e * S::ESZ + P * c;           // xi line (j, k) = c: + b
-  float* const sy = s + e * S::ESZ + i + P * NG * j;  // eta line (i, k = j): + b P
+  T* const sz = s + e * S::ESZ + i + P * j;       // home: + k P n
+  T* const sx = s + e * S::ESZ + P * c;           // xi line (j, k) = c: + b
+  T* const sy = s + e * S::ESZ + i + P * NG * j;  // eta line (i, k = j): + b P
 #pragma unroll
   for (int q = 0; q < NC; ++q)
 #pragma unroll
@@ -275,26 +280,30 @@ __global__ __launch_bounds__(LineShape<NG>::BLK) void force_line_kernel(ForceArg
 
   // ---- forward contractions: xi and eta derivatives take the place of u ----
   {
-    float x[NC][NG], y[NC][NG];
+    // eta derivatives go to the second field at once (in double at NGLL 9 an
+    // apply at 729000 points 28.5 -> 26.3 us against all lines first); xi
+    // derivatives take the place of u and wait for its last reader
+    T x[NC][NG];
 #pragma unroll
     for (int q = 0; q < NC; ++q)
 #pragma unroll
-      for (int b = 0; b < NG; ++b) {
-        x[q][b] = sx[q * AS + b];
-        y[q][b] = sy[q * AS + b * P];
-      }
+      for (int b = 0; b < NG; ++b) x[q][b] = sx[q * AS + b];
 #pragma unroll
-    for (int q = 0; q < NC; ++q) D.apply(uc[q]);  // zeta derivatives
+    for (int q = 0; q < NC; ++q) {
+      T y[NG];
+#pragma unroll
+      for (int b = 0; b < NG; ++b) y[b] = sy[q * AS + b * P];
+      D.apply(y);
+#pragma unroll
+      for (int b = 0; b < NG; ++b) sy[(NC + q) * AS + b * P] = y[b];
+      D.apply(uc[q]);  // zeta derivatives
+    }
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
       D.apply(x[q]);
-      D.apply(y[q]);
 #pragma unroll
-      for (int b = 0; b < NG; ++b) {
-        sx[q * AS + b] = x[q][b];
-        sy[(NC + q) * AS + b * P] = y[q][b];
-      }
+      for (int b = 0; b < NG; ++b) sx[q * AS + b] = x[q][b];
     }
   }
   __syncthreads();
@@ -302,7 +311,7 @@ __global__ __launch_bounds__(LineShape<NG>::BLK) void force_line_kernel(ForceArg
   // ---- pointwise: geometry map, stress, weighted fluxes in place ----
 #pragma unroll
   for (int k = 0; k < NG; ++k) {
-    float G[9];
+    T G[9];
     if constexpr (GEO == kStored) {
 #pragma unroll
       for (int d = 0; d < 9; ++d) G[d] = Gn[k % PD][d];
@@ -311,9 +320,9 @@ __global__ __launch_bounds__(LineShape<NG>::BLK) void force_line_kernel(ForceArg
         for (int d = 0; d < 9; ++d) Gn[k % PD][d] = ldnt(gp + d * N3 + (k + PD) * N2);
       }
     }
-    float Mg[9], scale;
-    geo.at(GEO == kTrilinear ? a.xi[k] : 0.0f, G, Mg, scale);
-    float d[NC][3];
+    T Mg[9], scale;
+    geo.at(GEO == kTrilinear ? a.xi[k] : (T)0, G, Mg, scale);
+    T d[NC][3];
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
       d[q][0] = sz[q * AS + k * P * NG];
@@ -334,7 +343,7 @@ __global__ __launch_bounds__(LineShape<NG>::BLK) void force_line_kernel(ForceArg
   // ---- transpose contractions, each line in place ----
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
-    float x[NG], y[NG];
+    T x[NG], y[NG];
 #pragma unroll
     for (int b = 0; b < NG; ++b) {
       x[b] = sx[q * AS + b];
@@ -352,7 +361,7 @@ __global__ __launch_bounds__(LineShape<NG>::BLK) void force_line_kernel(ForceArg
   __syncthreads();
 
   if (!act) return;
-  float* out = a.part + (((size_t)model * a.nspec + pos) * N3 + c) * NC;
+  T* out = a.part + (((size_t)model * a.nspec + pos) * N3 + c) * NC;
 #pragma unroll
   for (int k = 0; k < NG; ++k)
 #pragma unroll
@@ -360,47 +369,64 @@ __global__ __launch_bounds__(LineShape<NG>::BLK) void force_line_kernel(ForceArg
       out[k * N2 * NC + q] = -(uc[q][k] + (sz[q * AS + k * P * NG] + sz[(NC + q) * AS + k * P * NG]));
 }
 
-template <int NG, int NC, int GEO>
-hipError_t launch_line(bool aff, const ForceArgs& a, hipStream_t s) {
-  using S = LineShape<NG>;
+template <class T, int NG, int NC, int GEO>
+hipError_t launch_line(bool aff, const LineArgs<T>& a, hipStream_t s) {
+  using S = LineShape<T, NG>;
   const int64_t ngrp = (a.count + S::EPW - 1) / S::EPW;
-  ForceArgs b = a;
+  LineArgs<T> b = a;
   b.aux.blocks = (int)aux_blocks(a.aux, S::BLK, kNumXcd);
   const dim3 grid((unsigned)((ngrp + kNumXcd - 1) / kNumXcd * kNumXcd) + b.aux.blocks, (unsigned)a.nmodels);
-  if (aff) force_line_kernel<NG, NC, GEO, true><<<grid, S::BLK, 0, s>>>(b);
-  else force_line_kernel<NG, NC, GEO, false><<<grid, S::BLK, 0, s>>>(b);
+  if (aff) force_line_kernel<T, NG, NC, GEO, true><<<grid, S::BLK, 0, s>>>(b);
+  else force_line_kernel<T, NG, NC, GEO, false><<<grid, S::BLK, 0, s>>>(b);
   return hipGetLastError();
 }
 
-template <int NG, int NC>
-hipError_t launch_line_n(int geo, bool aff, const ForceArgs& a, hipStream_t s) {
+template <class T, int NG, int NC>
+hipError_t launch_line_n(int geo, bool aff, const LineArgs<T>& a, hipStream_t s) {
   switch (geo) {
-    case kRegular: return launch_line<NG, NC, kRegular>(aff, a, s);
-    case kStored: return launch_line<NG, NC, kStored>(aff, a, s);
-    case kTrilinear: return launch_line<NG, NC, kTrilinear>(aff, a, s);
+    case kRegular: return launch_line<T, NG, NC, kRegular>(aff, a, s);
+    case kStored: return launch_line<T, NG, NC, kStored>(aff, a, s);
+    case kTrilinear:
+      if constexpr (sizeof(T) == 4) return launch_line<T, NG, NC, kTrilinear>(aff, a, s);
     default: return hipErrorInvalidValue;
   }
 }
 
-template <int NC>
-hipError_t launch_line_any(int n, int geo, int64_t naff, const ForceArgs& a, hipStream_t s) {
-  if (!a.part || a.list || !a.eo) return hipErrorInvalidValue;
-  return split_affine(naff, a, [&](const ForceArgs& b, bool aff) -> hipError_t {
+// MAXN: largest NGLL of the instantiation
+template <class T, int NC, int MAXN>
+hipError_t launch_line_any(int n, int geo, int64_t naff, const LineArgs<T>& a, hipStream_t s) {
+  if (!a.part || !a.eo) return hipErrorInvalidValue;
+  return split_affine(naff, a, [&](const LineArgs<T>& b, bool aff) -> hipError_t {
     switch (n) {
-      case 2: return launch_line_n<2, NC>(geo, aff, b, s);
-      case 3: return launch_line_n<3, NC>(geo, aff, b, s);
-      case 4: return launch_line_n<4, NC>(geo, aff, b, s);
-      case 5: return launch_line_n<5, NC>(geo, aff, b, s);
-      case 6: return launch_line_n<6, NC>(geo, aff, b, s);
-      case 7: return launch_line_n<7, NC>(geo, aff, b, s);
-      case 8: return launch_line_n<8, NC>(geo, aff, b, s);
-      case 9: return launch_line_n<9, NC>(geo, aff, b, s);
-      case 10: return launch_line_n<10, NC>(geo, aff, b, s);
-      case 11: return launch_line_n<11, NC>(geo, aff, b, s);
-      case 12: return launch_line_n<12, NC>(geo, aff, b, s);
+      case 2: return launch_line_n<T, 2, NC>(geo, aff, b, s);
+      case 3: return launch_line_n<T, 3, NC>(geo, aff, b, s);
+      case 4: return launch_line_n<T, 4, NC>(geo, aff, b, s);
+      case 5: return launch_line_n<T, 5, NC>(geo, aff, b, s);
+      case 6: return launch_line_n<T, 6, NC>(geo, aff, b, s);
+      case 7: return launch_line_n<T, 7, NC>(geo, aff, b, s);
+      case 8: return launch_line_n<T, 8, NC>(geo, aff, b, s);
+      case 9: return launch_line_n<T, 9, NC>(geo, aff, b, s);
+      case 10: return launch_line_n<T, 10, NC>(geo, aff, b, s);
+      case 11:
+        if constexpr (MAXN >= 11) return launch_line_n<T, 11, NC>(geo, aff, b, s);
+        return hipErrorInvalidValue;
+      case 12:
+        if constexpr (MAXN >= 12) return launch_line_n<T, 12, NC>(geo, aff, b, s);
+        return hipErrorInvalidValue;
       default: return hipErrorInvalidValue;
     }
   });
+}
+
+// The FP32 launch from the arguments that the force kernels share.
+template <int NC>
+hipError_t launch_line_f32(int n, int geo, int64_t naff, const ForceArgs& a, hipStream_t s) {
+  if (a.list) return hipErrorInvalidValue;
+  return launch_line_any<float, NC, kLineMaxN>(
+      n, geo, naff,
+      LineArgs<float>{a.ibool, a.aff, a.gam_pt, a.gam_el, a.tri, a.xi, a.mat, a.u, a.eo, a.part, a.pos0, a.count,
+                      a.nspec, a.nglob, a.nmodels, a.aux},
+      s);
 }
 
 }  // namespace

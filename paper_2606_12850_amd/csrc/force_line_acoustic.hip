@@ -4,7 +4,7 @@
 namespace semx {
 
 hipError_t launch_force_line_acoustic(int n, int geo, int64_t naff, const ForceArgs& a, hipStream_t s) {
-  return launch_line_any<1>(n, geo, naff, a, s);
+  return launch_line_f32<1>(n, geo, naff, a, s);
 }
 
 }  // namespace semx

@@ -8,10 +8,10 @@
 //   explicit Newmark, beta = 0, gamma = 1/2 (Sec. V-C), point sources, receivers.
 //
 // It serves runs that must agree with an FP64 reference to FP64 rounding and
-// finite-difference checks that need FP64 forward solves.  The kernels are
-// plain: one workgroup per element and model, one GLL point per lane, LDS
-// holding one component's three cubes at a time (3 n^3 doubles, 24 KB at
-// NGLL 10).  Assembly is coloured (plain read-modify-write: no two elements
+// finite-difference checks that need FP64 forward solves.  Large passes take
+// the line kernel (force_line.hpp); the kernels here are plain: one workgroup
+// per element and model, one GLL point per lane, LDS holding one component's
+// three cubes at a time (3 n^3 doubles, 24 KB at NGLL 10).  Assembly is coloured (plain read-modify-write: no two elements
 // of a colour share a node, so it is deterministic) or atomic (hardware FP64
 // atomic adds).
 #include <hip/hip_runtime.h>
@@ -145,6 +145,30 @@ __global__ void material64_kernel(int n3, int64_t nspec, int nmodels, const int3
   }
 }
 
+// Gamma of the first point of each element, and whether it holds for all points
+// of the regular elements (the first nreg positions): their Gamma may differ by
+// what the rounding of the vertex coordinates (half an ulp each) does to it.
+__global__ void gam_el64_kernel(int n3, int64_t nspec, int64_t nreg, const double* __restrict__ vert,
+                                const int32_t* __restrict__ ev, const int32_t* __restrict__ order,
+                                const double* __restrict__ gam, double* __restrict__ gam_el, int* __restrict__ bad) {
+  for (int64_t pos = blockIdx.x * (int64_t)(blockDim.x / 64) + threadIdx.x / 64; pos < nspec;
+       pos += (int64_t)gridDim.x * (blockDim.x / 64)) {
+    const int lane = threadIdx.x & 63;
+    const double* G = gam + pos * 9 * n3;
+    if (lane < 9) gam_el[pos * 9 + lane] = G[(int64_t)lane * n3];
+    if (pos >= nreg) continue;
+    double x = 0.0, g = 0.0, dev = 0.0;
+    for (int v = 0; v < 8; ++v)
+      for (int b = 0; b < 3; ++b) x = fmax(x, fabs(vert[3 * (int64_t)ev[8 * (int64_t)order[pos] + v] + b]));
+    for (int d = 0; d < 9; ++d) {
+      const double g0 = G[(int64_t)d * n3];
+      g = fmax(g, fabs(g0));
+      for (int q = lane; q < n3; q += 64) dev = fmax(dev, fabs(G[(int64_t)d * n3 + q] - g0));
+    }
+    if (!(dev <= 4 * 2.220446049250313e-16 * g * (1.0 + g * x))) atomicOr(bad, 1);
+  }
+}
+
 __global__ void minv64_kernel(int64_t n, const double* __restrict__ mass, double* __restrict__ minv) {
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x)
     minv[t] = mass[t] > 0.0 ? 1.0 / mass[t] : 0.0;  // a node no element reaches stays at rest
@@ -263,6 +287,34 @@ __global__ void finite64_kernel(int64_t n, const double* __restrict__ x, int* __
   if (bad) atomicOr(flag, 1);
 }
 
+// Line kernel (force_line.hpp) instead of one lane per point: where a launch
+// fills the chip.  Per-point Gamma: at NGLL 2-5 the line kernel has fewer of
+// its 72 bytes a point in flight.  Force applies of a box, lane per point / line:
+//   one Gamma per element  NGLL 5, 1000000 points 35.7 / 25.8 us, 216000 13.4 / 11.5, 42875 7.9 / 8.6;
+//                          NGLL 9, 729000 47.4 / 26.3;  NGLL 10, 125000 16.3 / 15.9
+//   Gamma at each point    NGLL 5, 1000000 points 35.7 / 38.8;  NGLL 7, 753571 41.3 / 36.2, 175616 14.2 / 14.5
+bool use_line64(const semx_ctx* c, bool parts, int geo) {
+  const int64_t points = (int64_t)c->nmodels * c->nspec * c->n3;
+  if (!parts) return false;
+  return geo == kRegular ? points >= (1 << 17) : c->n >= 6 && points >= (1 << 18);
+}
+
+LineArgs<double> line_args64(const semx_ctx* c, const double* u) {
+  LineArgs<double> a{};
+  a.ibool = c->d_ibool.as<int32_t>();
+  a.aff = c->d_aff.as<int32_t>();
+  a.gam_pt = c->d_gam64.as<double>();
+  a.gam_el = c->d_gam64_el.as<double>();
+  a.mat = c->d_mat64.as<double>();
+  a.u = u;
+  a.eo = c->d_eo64.as<double>();
+  a.part = c->d_part.as<double>();
+  a.nspec = c->nspec;
+  a.nglob = c->nglob;
+  a.nmodels = c->nmodels;
+  return a;
+}
+
 template <int NG>
 hipError_t launch_force64_n(const semx_ctx* c, const double* u, double* f, AuxArgs<double> aux) {
   constexpr int n3 = NG * NG * NG;
@@ -271,6 +323,17 @@ hipError_t launch_force64_n(const semx_ctx* c, const double* u, double* f, AuxAr
   const bool parts = parts_active(c), colored = !atomic && !parts;
   for (const auto& L : colored ? c->colored_launches : c->kind_launches) {
     if (L.count <= 0) continue;
+    const int geo = !L.irregular && c->affine64 ? kRegular : kStored;
+    if (use_line64(c, parts, geo)) {
+      LineArgs<double> a = line_args64(c, u);
+      a.pos0 = L.pos0;
+      a.count = L.count;
+      a.aux = aux;
+      aux.units = 0;
+      const hipError_t e = launch_force_line64(NG, geo, L.naff, a, c->stream);
+      if (e != hipSuccess) return e;
+      continue;
+    }
     aux.blocks = (int)aux_blocks(aux, (int)threads, kNumXcd);
     dim3 grid((unsigned)L.count + aux.blocks, (unsigned)c->nmodels);
     force64_kernel<NG><<<grid, threads, 0, c->stream>>>(
@@ -335,7 +398,22 @@ int f64_model_setup(semx_ctx* c, const double* lam_dev, const double* mu_dev) {
   int rc = dev_alloc(c, c->d_mat64, sizeof(double) * 2 * npt);
   if (!rc) rc = dev_alloc(c, c->d_minv64, sizeof(double) * c->nmodels * c->nglob);
   if (!rc && c->d_D64.bytes != sizeof(double) * c->n * c->n) rc = dev_alloc(c, c->d_D64, sizeof(double) * c->n * c->n);
+  std::vector<double> eo;
+  even_odd(c->n, c->D, eo);
+  if (!rc) rc = dev_alloc(c, c->d_eo64, sizeof(double) * eo.size());
+  if (!rc) rc = dev_alloc(c, c->d_gam64_el, sizeof(double) * 9 * c->nspec);
   if (rc) return rc;
+  SEMX_HIP(c, hipMemcpy(c->d_eo64.p, eo.data(), sizeof(double) * eo.size(), hipMemcpyHostToDevice));
+  int* flag = scratch_flags(c);
+  SEMX_HIP(c, hipMemsetAsync(flag, 0, sizeof(int), c->stream));
+  gam_el64_kernel<<<grid_1d(c->nspec * 64, 4096), kT, 0, c->stream>>>(
+      c->n3, c->nspec, c->nregular, c->d_vert.as<double>(), c->d_elem_vert.as<int32_t>(), c->d_order.as<int32_t>(),
+      c->d_gam64.as<double>(), c->d_gam64_el.as<double>(), flag);
+  SEMX_HIP(c, hipGetLastError());
+  int uneven = 0;
+  SEMX_HIP(c, hipMemcpyAsync(&uneven, flag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+  SEMX_HIP(c, hipStreamSynchronize(c->stream));
+  c->affine64 = uneven == 0;
   SEMX_HIP(c, hipMemcpyAsync(c->d_D64.p, c->D.data(), sizeof(double) * c->n * c->n, hipMemcpyHostToDevice, c->stream));
   material64_kernel<<<grid_1d(npt, 8192), kT, 0, c->stream>>>(c->n3, c->nspec, c->nmodels, c->d_order.as<int32_t>(),
                                                                lam_dev, mu_dev, c->d_wdet.as<double>(),

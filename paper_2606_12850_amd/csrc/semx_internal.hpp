@@ -208,8 +208,11 @@ struct semx_ctx {
   double vp_max = 0.0;
 
   // FP64 storage: Gamma [nspec][9][n3], lambda W / mu W [nmodels][nspec][2][n3]
-  // by launch position, M^{-1} [nmodels][nglob], D [n][n]
-  semx::DevBuf d_gam64, d_mat64, d_minv64, d_D64;
+  // by launch position, M^{-1} [nmodels][nglob], D [n][n] and its even-odd
+  // form; Gamma of the first point of each element [nspec][9], which holds for
+  // all points of the regular elements when affine64 is set
+  semx::DevBuf d_gam64, d_mat64, d_minv64, d_D64, d_eo64, d_gam64_el;
+  bool affine64 = false;
 
   // time loop state, [nmodels][nglob][3], float or double by `storage`
   semx::DevBuf d_u, d_v, d_a, d_f;
@@ -271,6 +274,7 @@ void dev_free(DevBuf& b);
 // ---- GLL basis (host, FP64) ---------------------------------------------
 void gll_nodes_weights(int n, std::vector<double>& xi, std::vector<double>& w);
 void deriv_matrix(int n, const std::vector<double>& xi, std::vector<double>& D);
+void even_odd(int n, const std::vector<double>& D, std::vector<double>& t);
 void lagrange_at(int n, const std::vector<double>& xi, double x, double* l);
 
 // ---- launchers (force_f32.hip, force_mfma.hip) -----------------------------
@@ -325,7 +329,17 @@ hipError_t launch_force_block_skeleton(int n, int geo, const ForceArgs& a, const
 constexpr int kBlockMaxN = 5;  // eight elements of n^3 points in one 1024-lane workgroup
 
 // force_line.hpp: one lane per line of points, element-local forces only
-// (a.part set, no list), NGLL 2..12.
+// (part set, no list), NGLL 2..12 (double: 2..10, kRegular and kStored).
+template <class T>
+struct LineArgs {
+  const int32_t *ibool, *aff;
+  const T *gam_pt, *gam_el, *tri, *xi, *mat, *u, *eo;
+  T* part;
+  int64_t pos0, count, nspec, nglob;
+  int nmodels;
+  AuxArgs<T> aux;
+};
+hipError_t launch_force_line64(int n, int geo, int64_t naff, const LineArgs<double>& a, hipStream_t s);
 hipError_t launch_force_line(int n, int geo, int64_t naff, const ForceArgs& a, hipStream_t s);
 hipError_t launch_force_line_acoustic(int n, int geo, int64_t naff, const ForceArgs& a, hipStream_t s);
 constexpr int kLineMaxN = 12;
