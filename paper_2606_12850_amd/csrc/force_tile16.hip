@@ -223,31 +223,29 @@ __device__ __forceinline__ void load_ahead(const ForceArgs& a, const float* __re
   if constexpr (MAT) load_mat<NG>(a, model, pos, P, h);
 }
 
-// Element loop.  Regular path (tile_persistent): the grid holds one
+// Element loop.  Persistent form (tile_persistent): the grid holds one
 // workgroup per compute unit (one fills its LDS or its registers) and each
 // walks its share of the launch, dealt XCD by XCD as in xcd_group (the
 // workgroups on XCD x take the x-th eighth of the range, in steps of the
-// number of workgroups there); the next element's node numbers and u (and
-// at NGLL 16 with FP32 operands its material) are requested before the
-// current one's last two barriers, so that their latency hides behind its
-// transpose contractions and assembly.  With per-point geometry (and FP16
-// operands on padded tiles) one element per workgroup, its loads requested
-// at its start.  Inside a colour no other workgroup of the launch touches
-// the element's nodes, so the prior f there may be read at any time before
-// the assembly: at the start of the arithmetic in general, and in the
-// persistent elastic form after the pointwise stage, just before the next
-// element's loads, so that the 12 values are not held through the stress
-// computation (this removed the 8-40 bytes per lane that the padded orders
-// spilled there with FP32 and BF16 operands, and took 4-21 % off an apply
-// at NGLL 11-15).
-// The persistent form (the next element requested ahead).  Elastic: on the
-// regular path only, and with FP16 operands only at NGLL 16; on padded
-// tiles FP16 needs more registers (36-60 bytes per lane spilled) and,
-// measured per apply at 2e7 nodes, loses 20-35 %, so it keeps one element
-// per workgroup there; with per-point or trilinear geometry the persistent
-// form spills 84-176 bytes and loses up to 50 %.  The scalar operator
-// (NC = 1) has the room: it gains 5-14 % on every geometry path.  The launch
-// sizes the grid by the same rule.
+// number of workgroups there); the next element's node numbers and u are
+// requested before the current one's last two barriers, so that their latency
+// hides behind its transpose contractions and assembly.  Otherwise one element
+// per workgroup, its loads requested at its start.  Inside a colour (kRmw) no
+// other workgroup of the launch touches the element's nodes, so the prior f may
+// be read at any time before the assembly: in the persistent elastic form after
+// the pointwise stage, just before the next element's loads, so that the 12
+// values are not held through the stress computation.  Element-local forces
+// (kPart) have no prior f and no node numbers to hold; the form is a template
+// argument so that the registers are free, and the next element's material is
+// requested along with its u: with a runtime choice of the two forms 12-20
+// bytes a lane spilled, and an apply at 11 x 10 x 10 elements of NGLL 16 took 86
+// instead of 79 us, 13 x 14 x 13 of NGLL 12 in BF16 95 instead of 84.
+// The persistent form is taken where it does not spill.  Elastic: on the
+// regular path (with prior f and FP16 operands only at NGLL 16: on padded tiles
+// that form spills 36-60 bytes a lane and loses 20-35 %); with per-point or
+// trilinear geometry it spills 16-176 bytes and loses up to 50 %.  The scalar
+// operator (NC = 1) has the room: it gains 5-14 % on every geometry path.  The
+// launch sizes the grid by the same rule.
 template <int NG, int GEO, int ASM, int PREC, int NC>
 constexpr bool tile_persistent() {
   return NC == 1 || (GEO == kRegular && (ASM == kPart || NG == kN || PREC != SEMX_C_F16));
