@@ -98,11 +98,10 @@ struct Raw8<__bf16> {
   __device__ __forceinline__ bf16x8 bf16() const { return v; }
 };
 
-// A thread's share of one operand tile T[r][k] (ROWS rows x BK, 256 threads,
-// ROWS / 64 chunks of eight a thread) of X(r, k) = X[r * sr + k * sk], rows
-// r0 .. r0+ROWS-1, k in [k0, kend).  KC: X is contiguous along k (sk = 1), a
-// chunk is 8 consecutive k of one row; otherwise it is contiguous along r
-// (sr = 1) and a chunk is 8 consecutive rows of one k.
+// A thread's share of one operand tile T[r][k] (ROWS rows x BK, 256 threads) of
+// X(r, k) = X[r * sr + k * sk], rows r0 .. r0+ROWS-1, k in [k0, kend).
+// KC: X is contiguous along k (sk = 1), a thread takes ROWS / 64 chunks of 8
+// consecutive k of one row.
 // VEC: every chunk lies wholly inside or wholly outside the operand and is
 // 16-byte aligned (the launch checks it): one vector load at an address that
 // is clamped into the operand, zeroed on the way into LDS where it lies past
@@ -113,25 +112,17 @@ struct Tile {
   static constexpr int C = ROWS / 64;
   Raw8<T> raw[C];
 
-  __device__ static __forceinline__ int row(int c, int t) {
-    return KC ? (t >> 2) + 64 * c : (t + 256 * c) % (ROWS / 8) * 8;
-  }
-  __device__ static __forceinline__ int kof(int c, int t) { return KC ? (t & 3) * 8 : (t + 256 * c) / (ROWS / 8); }
-
   __device__ __forceinline__ void load(const T* __restrict__ X, int64_t sr, int64_t sk, int R, int r0, int k0, int kend,
                                        int t) {
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-      const int r = r0 + row(c, t), k = k0 + kof(c, t);
+      const int r = r0 + (t >> 2) + 64 * c, k = k0 + (t & 3) * 8;
       if constexpr (VEC) {
-        if constexpr (KC) raw[c].load(X + (int64_t)min(r, R - 1) * sr + min(k, kend - 8));
-        else raw[c].load(X + min(r, R - 8) + (int64_t)min(k, kend - 1) * sk);
+        raw[c].load(X + (int64_t)min(r, R - 1) * sr + min(k, kend - 8));
       } else {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int re = KC ? r : r + e, ke = KC ? k + e : k;
-          raw[c].set(e, (re < R && ke < kend) ? X[(int64_t)re * sr + (int64_t)ke * sk] : (T)0.0f);
-        }
+        for (int e = 0; e < 8; ++e)
+          raw[c].set(e, (r < R && k + e < kend) ? X[(int64_t)r * sr + (int64_t)(k + e) * sk] : (T)0.0f);
       }
     }
   }
@@ -139,14 +130,54 @@ struct Tile {
   __device__ __forceinline__ void store(__bf16 (*Ts)[BK + PADK], int k0, int kend, int t) const {
 #pragma unroll
     for (int c = 0; c < C; ++c) {
+      const int kk = (t & 3) * 8;
       bf16x8 w = raw[c].bf16();
-      if (VEC && TAIL && k0 + kof(c, t) >= kend) w = bf16x8{};
-      if constexpr (KC) {
-        *reinterpret_cast<bf16x8*>(&Ts[row(c, t)][kof(c, t)]) = w;
+      if (VEC && TAIL && k0 + kk >= kend) w = bf16x8{};
+      *reinterpret_cast<bf16x8*>(&Ts[(t >> 2) + 64 * c][kk]) = w;
+    }
+  }
+};
+
+// X contiguous along r (sr = 1): a thread takes a block of 4 rows x KQ
+// consecutive k, turns it in its registers and writes KQ elements of a row at a
+// time.  The lanes of a wave run over k first, so that their writes (rows 80
+// bytes apart) fall on different banks; with eight rows of one k a thread,
+// written element by element, up to 16 lanes met on a bank: the weight gradient
+// of 24576 outputs at batch 128 took 34.5 us, now 23 (its 50 MB of output alone 10),
+// the input gradient 28, now 23.
+template <class T, int ROWS, bool VEC>
+struct Tile<T, false, ROWS, VEC> {
+  static constexpr int KQ = ROWS / 32;  // 4 or 2
+  typedef T T4 __attribute__((ext_vector_type(4)));
+  typedef __bf16 BK4 __attribute__((ext_vector_type(KQ)));
+  T4 raw[KQ];
+
+  __device__ static __forceinline__ int kof(int t) { return t % (BK / KQ) * KQ; }
+  __device__ static __forceinline__ int row(int t) { return t / (BK / KQ) * 4; }
+
+  __device__ __forceinline__ void load(const T* __restrict__ X, int64_t sr, int64_t sk, int R, int r0, int k0, int kend,
+                                       int t) {
+    const int r = r0 + row(t), k = k0 + kof(t);
+#pragma unroll
+    for (int j = 0; j < KQ; ++j) {
+      if constexpr (VEC) {
+        raw[j] = *reinterpret_cast<const T4*>(X + min(r, R - 4) + (int64_t)min(k + j, kend - 1) * sk);
       } else {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) Ts[row(c, t) + e][kof(c, t)] = w[e];
+        for (int e = 0; e < 4; ++e)
+          raw[j][e] = (r + e < R && k + j < kend) ? X[(int64_t)(r + e) * sr + (int64_t)(k + j) * sk] : (T)0.0f;
       }
+    }
+  }
+  template <bool TAIL>
+  __device__ __forceinline__ void store(__bf16 (*Ts)[BK + PADK], int k0, int kend, int t) const {
+    const int r = row(t), k = kof(t);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      BK4 w;
+#pragma unroll
+      for (int j = 0; j < KQ; ++j) w[j] = VEC && TAIL && k0 + k + j >= kend ? (__bf16)0.0f : (__bf16)raw[j][e];
+      *reinterpret_cast<BK4*>(&Ts[r + e][k]) = w;
     }
   }
 };
@@ -195,10 +226,21 @@ __global__ __launch_bounds__(256, WT == 2 ? 4 : 2) void gemm_kernel(int M, int N
   __shared__ __attribute__((aligned(16))) __bf16 As[2][ROWS][BK + PADK];
   __shared__ __attribute__((aligned(16))) __bf16 Bs[2][ROWS][BK + PADK];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int bm = blockIdx.y * ROWS, bn = blockIdx.x * ROWS;
+  // A split-K slice on one XCD (consecutive blocks go to the eight XCDs in
+  // turn), so that its tiles meet the operands' slices in one L2: the input
+  // gradient of 24576 outputs at batch 128 23.1 -> 18.8 us
+  int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
+  if (EPI == kGradZ && gridDim.z % kNumXcd == 0) {
+    const int tiles = gridDim.x * gridDim.y, L = bx + gridDim.x * (by + gridDim.y * bz);
+    const int tile = L / kNumXcd % tiles;
+    bz = L % kNumXcd + kNumXcd * (L / kNumXcd / tiles);
+    bx = tile % gridDim.x;
+    by = tile / gridDim.x;
+  }
+  const int bm = by * ROWS, bn = bx * ROWS;
   const int wu = __builtin_amdgcn_readfirstlane(wv), wm = wu >> 1, wn = wu & 1;
   const bool split = gridDim.z > 1;
-  const int kbeg = blockIdx.z * kchunk;
+  const int kbeg = bz * kchunk;
   const int kend = min(K, kbeg + kchunk);
   const int steps = (kend - kbeg + BK - 1) / BK;
   f32x4 acc[WT][WT];
@@ -215,16 +257,16 @@ __global__ __launch_bounds__(256, WT == 2 ? 4 : 2) void gemm_kernel(int M, int N
   }
   if constexpr (EPI == kGradW) {
     // the blocks of the first column also sum their rows of A over k, in order
-    if (blockIdx.x == 0 && blockIdx.z == 0 && t < ROWS && bm + t < M) {
+    if (bx == 0 && bz == 0 && t < ROWS && bm + t < M) {
       const TA* p = A + (int64_t)(bm + t) * sam;
       float s = 0.0f;
       int k = 0;
-      for (; k + 16 <= K; k += 16) {
-        float v[16];
+      for (; k + 32 <= K; k += 32) {
+        float v[32];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) v[e] = (float)p[(int64_t)(k + e) * sak];
+        for (int e = 0; e < 32; ++e) v[e] = (float)p[(int64_t)(k + e) * sak];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) s += v[e];
+        for (int e = 0; e < 32; ++e) s += v[e];
       }
       for (; k < K; ++k) s += (float)p[(int64_t)k * sak];
       db[bm + t] = s;
@@ -278,7 +320,7 @@ __global__ __launch_bounds__(256, WT == 2 ? 4 : 2) void gemm_kernel(int M, int N
   // Outputs of 64 MB and more go past the caches (402 MB at batch 4096: 257 ->
   // 210 us for the network, 202 with the 16-byte stores).
   const int64_t ldz = split ? N : ldc;
-  float* Cz = split ? C + (int64_t)blockIdx.z * M * N : C;
+  float* Cz = split ? C + (int64_t)bz * M * N : C;
   const int m0 = bm + wm * 16 * WT + (lane & 15), n0 = bn + wn * 16 * WT + 4 * (lane >> 4);
   constexpr bool BIAS = EPI == kBias || EPI == kBiasStream || EPI == kSiluKeep || EPI == kSilu;
 #pragma unroll
@@ -409,7 +451,22 @@ __global__ __launch_bounds__(256) void mse_kernel(int64_t n, const float* __rest
   __shared__ double red[256];
   double s = 0.0;
   const float inv = 1.0f / (float)n;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+  const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+  const bool vec = (reinterpret_cast<uintptr_t>(y) | reinterpret_cast<uintptr_t>(t) | reinterpret_cast<uintptr_t>(dy)) % 16 == 0;
+  const int64_t nv = vec ? n / 4 : 0;
+  for (int64_t i = i0; i < nv; i += stride) {
+    const f32x4 d = reinterpret_cast<const f32x4*>(y)[i] - reinterpret_cast<const f32x4*>(t)[i];
+    if (dy) {
+      f32x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = 2.0f * d[e] * inv;
+      reinterpret_cast<f32x4*>(dy)[i] = o;
+    }
+    if (loss)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s += (double)d[e] * (double)d[e];
+  }
+  for (int64_t i = 4 * nv + i0; i < n; i += stride) {
     const float d = y[i] - t[i];
     if (dy) dy[i] = 2.0f * d * inv;
     if (loss) s += (double)d * (double)d;
