@@ -8,10 +8,13 @@
 //   dW_l = G^T H_l,  db_l = sum over the batch of G,  dH_l = G W_l,
 //   dL/dZ_{l-1} = dH_l * SiLU'(Z_{l-1}).
 #include <hip/hip_runtime.h>
+#include <sys/mman.h>
+#include <unistd.h>
 
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <cstring>
 #include <mutex>
 #include <string>
 #include <type_traits>
@@ -32,6 +35,8 @@ struct semx_mlp {
   semx::DevBuf g0, g1;             // backward work [B][max width]
   semx::DevBuf scratch;
   semx::DevBuf splitk;             // split-K partial sums
+  char* stage = nullptr;           // pinned, kStageSlots pieces of kStageBytes (download)
+  hipEvent_t staged[2] = {nullptr, nullptr};
   const float* x_saved = nullptr;
   int batch_saved = 0;
   int device = 0;                  // device current at creation (allocation-free forward)
@@ -599,6 +604,60 @@ int malloc_buf(semx_mlp* p, DevBuf& b, size_t bytes) {
   return SEMX_OK;
 }
 
+// Device to host copy of a whole parameter vector, complete on return.  Copied
+// straight into pageable memory, 53 MB took 3.1 ms, and 2 ms more where the
+// pages were new; the device's share is 0.9.  So the destination's pages are
+// made present first, while the kernels queued on the stream still run, and the
+// data comes through two pinned pieces, one on its way while the other is
+// copied out.  Anything unusual (small, pinned or device memory, a stream under
+// capture, pages that cannot be written) goes the direct way.
+constexpr int kStageSlots = 2;
+constexpr int64_t kStageBytes = 4 << 20;
+
+int download(semx_mlp* p, float* dst, const float* src) {
+  const int64_t bytes = sizeof(float) * p->nparam;
+  char* d = reinterpret_cast<char*>(dst);
+  const char* s = reinterpret_cast<const char*>(src);
+  bool staged = p->stage && bytes >= kStageBytes;
+  if (staged) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
+    hipPointerAttribute_t at{};
+    staged = hipStreamIsCapturing(p->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+    if (staged && hipPointerGetAttributes(&at, dst) == hipSuccess) staged = at.type == hipMemoryTypeUnregistered;
+    (void)hipGetLastError();  // an ordinary host pointer may be reported as an invalid value
+  }
+  if (staged) {
+    const uintptr_t page = (uintptr_t)sysconf(_SC_PAGESIZE);
+    const uintptr_t beg = reinterpret_cast<uintptr_t>(d) / page * page;
+    const uintptr_t end = (reinterpret_cast<uintptr_t>(d) + bytes + page - 1) / page * page;
+    staged = madvise(reinterpret_cast<void*>(beg), end - beg, MADV_POPULATE_WRITE) == 0;
+  }
+  if (!staged) {
+    hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, p->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
+    return e == hipSuccess ? SEMX_OK : mhip(p, e, "parameter download");
+  }
+  const int64_t pieces = (bytes + kStageBytes - 1) / kStageBytes;
+  hipError_t e = hipSuccess;
+  for (int64_t k = 0; k < pieces + kStageSlots - 1 && e == hipSuccess; ++k) {
+    if (k < pieces) {
+      const int64_t n = std::min(kStageBytes, bytes - k * kStageBytes);
+      e = hipMemcpyAsync(p->stage + k % kStageSlots * kStageBytes, s + k * kStageBytes, n, hipMemcpyDeviceToHost, p->stream);
+      if (e == hipSuccess) e = hipEventRecord(p->staged[k % kStageSlots], p->stream);
+    }
+    const int64_t o = k - (kStageSlots - 1);  // the piece to copy out
+    if (o < 0 || e != hipSuccess) continue;
+    e = hipEventSynchronize(p->staged[o % kStageSlots]);
+    if (e == hipSuccess)
+      std::memcpy(d + o * kStageBytes, p->stage + o % kStageSlots * kStageBytes, std::min(kStageBytes, bytes - o * kStageBytes));
+  }
+  if (e != hipSuccess) {
+    (void)hipStreamSynchronize(p->stream);  // nothing of this call is on its way on return
+    return mhip(p, e, "parameter download");
+  }
+  return SEMX_OK;
+}
+
 }  // namespace
 }  // namespace semx
 
@@ -660,6 +719,16 @@ int semx_mlp_create(semx_mlp** out, int nlayers, const int* widths, int max_batc
     semx_mlp_destroy(p);
     return rc;
   }
+  // without the pinned pieces downloads go the direct way
+  if (sizeof(float) * off >= kStageBytes) {
+    void* st = nullptr;
+    bool ok = hipHostMalloc(&st, kStageSlots * kStageBytes, hipHostMallocDefault) == hipSuccess;
+    for (int k = 0; k < kStageSlots && ok; ++k)
+      ok = hipEventCreateWithFlags(&p->staged[k], hipEventDisableTiming) == hipSuccess;
+    if (ok) p->stage = static_cast<char*>(st);
+    else if (st) (void)hipHostFree(st);
+    (void)hipGetLastError();
+  }
   *out = p;
   return SEMX_OK;
 }
@@ -669,6 +738,9 @@ int semx_mlp_destroy(semx_mlp* p) {
   (void)hipStreamSynchronize(p->stream);
   for (DevBuf* b : {&p->theta, &p->theta_bf, &p->grad, &p->m, &p->v, &p->g0, &p->g1, &p->scratch, &p->splitk})
     dev_free(*b);
+  if (p->stage) (void)hipHostFree(p->stage);
+  for (hipEvent_t ev : p->staged)
+    if (ev) (void)hipEventDestroy(ev);
   for (auto& b : p->Z) dev_free(b);
   for (auto& b : p->H) dev_free(b);
   delete p;
@@ -695,16 +767,12 @@ int semx_mlp_set_params(semx_mlp* p, const float* params) {
 
 int semx_mlp_get_params(semx_mlp* p, float* params) {
   if (!p || !params) return SEMX_EINVAL;
-  MLP_HIP(p, hipMemcpyAsync(params, p->theta.p, sizeof(float) * p->nparam, hipMemcpyDeviceToHost, p->stream));
-  MLP_HIP(p, hipStreamSynchronize(p->stream));
-  return SEMX_OK;
+  return download(p, params, p->theta.as<float>());
 }
 
 int semx_mlp_get_grads(semx_mlp* p, float* grads) {
   if (!p || !grads) return SEMX_EINVAL;
-  MLP_HIP(p, hipMemcpyAsync(grads, p->grad.p, sizeof(float) * p->nparam, hipMemcpyDeviceToHost, p->stream));
-  MLP_HIP(p, hipStreamSynchronize(p->stream));
-  return SEMX_OK;
+  return download(p, grads, p->grad.as<float>());
 }
 
 int semx_mlp_forward(semx_mlp* p, const float* x_dev, int batch, float* y_dev) {
