@@ -49,7 +49,21 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int BK = 32, PADK = 8;
+constexpr int BK = 32;
+// LDS place of element (r, k) of a tile.  SWZ (both operands contiguous along
+// k): rows of 64 bytes, whose four 16-byte pieces are permuted by the row so
+// that neither the writes nor the reads of a wave meet on a bank (with rows
+// padded to 80 bytes half the LDS cycles of the output layer were conflicts).
+// Otherwise rows of 80 bytes, which suit the pieces that Tile's turned form
+// writes (training at batch 128 is 3 % slower with permuted rows).
+template <bool SWZ>
+constexpr int kPitch = SWZ ? BK : BK + 8;
+template <bool SWZ>
+__device__ __forceinline__ int lds_at(int r, int k) {
+  return r * kPitch<SWZ> + (SWZ ? (((k >> 3) ^ (r >> 1)) & 3) * 8 + (k & 7) : k);
+}
+// columns of tiles that share an XCD's L2 (gemm_kernel)
+constexpr int kGroup = 16;
 constexpr int64_t kSplitWs = 2 << 20;  // floats of split-K partial sums per network (8 MB)
 
 // Workspace of semx_mlp_forward_noalloc: two activation buffers of
@@ -131,14 +145,14 @@ struct Tile {
       }
     }
   }
-  template <bool TAIL>
-  __device__ __forceinline__ void store(__bf16 (*Ts)[BK + PADK], int k0, int kend, int t) const {
+  template <bool TAIL, bool SWZ>
+  __device__ __forceinline__ void store(__bf16* Ts, int k0, int kend, int t) const {
 #pragma unroll
     for (int c = 0; c < C; ++c) {
       const int kk = (t & 3) * 8;
       bf16x8 w = raw[c].bf16();
       if (VEC && TAIL && k0 + kk >= kend) w = bf16x8{};
-      *reinterpret_cast<bf16x8*>(&Ts[(t >> 2) + 64 * c][kk]) = w;
+      *reinterpret_cast<bf16x8*>(Ts + lds_at<SWZ>((t >> 2) + 64 * c, kk)) = w;
     }
   }
 };
@@ -174,15 +188,15 @@ struct Tile<T, false, ROWS, VEC> {
       }
     }
   }
-  template <bool TAIL>
-  __device__ __forceinline__ void store(__bf16 (*Ts)[BK + PADK], int k0, int kend, int t) const {
+  template <bool TAIL, bool SWZ>
+  __device__ __forceinline__ void store(__bf16* Ts, int k0, int kend, int t) const {
     const int r = row(t), k = kof(t);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       BK4 w;
 #pragma unroll
       for (int j = 0; j < KQ; ++j) w[j] = VEC && TAIL && k0 + k + j >= kend ? (__bf16)0.0f : (__bf16)raw[j][e];
-      *reinterpret_cast<BK4*>(&Ts[r + e][k]) = w;
+      *reinterpret_cast<BK4*>(Ts + lds_at<SWZ>(r + e, k)) = w;
     }
   }
 };
@@ -213,11 +227,13 @@ constexpr int kGradW = 5;     // C = sum; db[m] = sum of A over k
 // waits for its own.  The loads of PF steps are therefore in flight at a time,
 // held as they came from memory and converted on the way into LDS (64 x 64
 // tiles that waited for each step: the hidden layers' products at batch 128 18
-// us, now 7; the input gradient of 24576 outputs 22 -> 10).  WT = 2 (64 x 64)
-// where few tiles would leave compute units idle, WT = 4 (128 x 128: half the
-// operand traffic and LDS reads per product) from 512 tiles: the 4096 x 24576
-// x 512 output layer 344 -> 172 us, 600 TFLOP/s; its floor is the 402 MB
-// written (70 us).  The order of the sum over k is the same in both.
+// us, now 7).  WT = 2 (64 x 64) where few tiles would leave compute units idle,
+// WT = 4 (128 x 128: half the operand traffic and LDS reads per product) from
+// 512 tiles: the 4096 x 24576 x 512 output layer 344 -> 172 us, with permuted
+// LDS rows, whole-line stores and tile order below (L2 misses 8.7 -> 3.8
+// million lines) 162, 640 TFLOP/s.  Its products alone take 115 us, its 402 MB
+// of stores alone 74: the two hardly overlap.  The order of the sum over k is
+// the same in both.
 template <class TA, class TB, int EPI, bool AKC, bool BKC, int WT, bool VEC>
 __global__ __launch_bounds__(256, WT == 2 ? 4 : 2) void gemm_kernel(int M, int N, int K, int kchunk,
                                                                     const TA* __restrict__ A, int64_t sam, int64_t sak,
@@ -227,9 +243,10 @@ __global__ __launch_bounds__(256, WT == 2 ? 4 : 2) void gemm_kernel(int M, int N
                                                                     __bf16* __restrict__ Hb,
                                                                     const float* __restrict__ Z,
                                                                     float* __restrict__ db, int outv) {
+  constexpr bool SWZ = AKC && BKC;
   constexpr int ROWS = 32 * WT, PF = !VEC ? 1 : WT == 2 ? 4 : 2;
-  __shared__ __attribute__((aligned(16))) __bf16 As[2][ROWS][BK + PADK];
-  __shared__ __attribute__((aligned(16))) __bf16 Bs[2][ROWS][BK + PADK];
+  __shared__ __attribute__((aligned(16))) __bf16 As[2][ROWS * kPitch<SWZ>];
+  __shared__ __attribute__((aligned(16))) __bf16 Bs[2][ROWS * kPitch<SWZ>];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   // A split-K slice on one XCD (consecutive blocks go to the eight XCDs in
   // turn), so that its tiles meet the operands' slices in one L2: the input
@@ -241,6 +258,18 @@ __global__ __launch_bounds__(256, WT == 2 ? 4 : 2) void gemm_kernel(int M, int N
     bz = L % kNumXcd + kNumXcd * (L / kNumXcd / tiles);
     bx = tile % gridDim.x;
     by = tile / gridDim.x;
+  }
+  // Many tiles: columns of tiles in groups of kGroup, row by row inside a group,
+  // an eighth of that order to each XCD, so that what its L2 holds of B is used
+  // by all of A before the next group
+  if (WT == 4 && gridDim.z == 1 && EPI != kGradW) {
+    const int nx = gridDim.x, ny = gridDim.y, n = nx * ny, L = bx + nx * by;
+    if (n % kNumXcd == 0) {
+      const int T = L % kNumXcd * (n / kNumXcd) + L / kNumXcd, g = T / (kGroup * ny), r = T - g * kGroup * ny;
+      const int w = min(kGroup, nx - g * kGroup);
+      bx = g * kGroup + r % w;
+      by = r / w;
+    }
   }
   const int bm = by * ROWS, bn = bx * ROWS;
   const int wu = __builtin_amdgcn_readfirstlane(wv), wm = wu >> 1, wn = wu & 1;
@@ -285,10 +314,10 @@ __global__ __launch_bounds__(256, WT == 2 ? 4 : 2) void gemm_kernel(int M, int N
     constexpr bool LOAD = decltype(load)::value;
     constexpr int p = decltype(p_)::value;
     // buffer s & 1 was last read in step s - 2, before the barrier of step s - 1
-    __bf16(*as)[BK + PADK] = As[s & 1];
-    __bf16(*bs)[BK + PADK] = Bs[s & 1];
-    ta[p].template store<!LOAD>(as, kbeg + s * BK, kend, t);
-    tb[p].template store<!LOAD>(bs, kbeg + s * BK, kend, t);
+    __bf16* as = As[s & 1];
+    __bf16* bs = Bs[s & 1];
+    ta[p].template store<!LOAD, SWZ>(as, kbeg + s * BK, kend, t);
+    tb[p].template store<!LOAD, SWZ>(bs, kbeg + s * BK, kend, t);
     if constexpr (LOAD) {
       ta[p].load(A, sam, sak, M, bm, kbeg + (s + PF) * BK, kend, t);
       tb[p].load(B, sbn, sbk, N, bn, kbeg + (s + PF) * BK, kend, t);
@@ -297,10 +326,10 @@ __global__ __launch_bounds__(256, WT == 2 ? 4 : 2) void gemm_kernel(int M, int N
     bf16x8 av[WT], bv[WT];
 #pragma unroll
     for (int a = 0; a < WT; ++a)
-      av[a] = *reinterpret_cast<const bf16x8*>(&as[wm * 16 * WT + a * 16 + (lane & 15)][8 * (lane >> 4)]);
+      av[a] = *reinterpret_cast<const bf16x8*>(as + lds_at<SWZ>(wm * 16 * WT + a * 16 + (lane & 15), 8 * (lane >> 4)));
 #pragma unroll
     for (int b = 0; b < WT; ++b)
-      bv[b] = *reinterpret_cast<const bf16x8*>(&bs[wn * 16 * WT + b * 16 + (lane & 15)][8 * (lane >> 4)]);
+      bv[b] = *reinterpret_cast<const bf16x8*>(bs + lds_at<SWZ>(wn * 16 * WT + b * 16 + (lane & 15), 8 * (lane >> 4)));
 #pragma unroll
     for (int a = 0; a < WT; ++a)
 #pragma unroll
@@ -328,6 +357,49 @@ __global__ __launch_bounds__(256, WT == 2 ? 4 : 2) void gemm_kernel(int M, int N
   float* Cz = split ? C + (int64_t)bz * M * N : C;
   const int m0 = bm + wm * 16 * WT + (lane & 15), n0 = bn + wn * 16 * WT + 4 * (lane >> 4);
   constexpr bool BIAS = EPI == kBias || EPI == kBiasStream || EPI == kSiluKeep || EPI == kSilu;
+  if constexpr (EPI == kBias || EPI == kBiasStream) {
+    // Whole 128-byte lines: a store of one tile holds 64 bytes of 16 rows; lanes
+    // eight rows apart exchange halves of a pair of tiles, so that a store holds
+    // the 128 bytes of both in 8 rows.
+    if (outv) {
+      const bool hi = lane & 8;
+      const int mr = bm + wm * 16 * WT + (lane & 7);
+#pragma unroll
+      for (int b = 0; b < WT; b += 2) {
+        const int n = n0 + 16 * (b + (hi ? 1 : 0));
+        f32x4 add0, add1;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          add0[r] = bias[min(n0 + 16 * b + r, N - 1)];
+          add1[r] = bias[min(n0 + 16 * (b + 1) + r, N - 1)];
+        }
+#pragma unroll
+        for (int a = 0; a < WT; ++a) {
+          f32x4 lo = acc[a][b] + add0, up = acc[a][b + 1] + add1;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float x = hi ? lo[r] : up[r];
+            // row_ror:8, the lane eight away in its row of sixteen
+            const float y = __builtin_bit_cast(
+                float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x128, 0xf, 0xf, false));
+            if (hi) lo[r] = y;
+            else up[r] = y;
+          }
+          const int m = n < N ? mr + 16 * a : M;
+          f32x4* o = reinterpret_cast<f32x4*>(Cz + (int64_t)m * ldz + n);
+          f32x4* o8 = reinterpret_cast<f32x4*>(Cz + (int64_t)(m + 8) * ldz + n);
+          if constexpr (EPI == kBiasStream) {
+            if (m < M) __builtin_nontemporal_store(lo, o);
+            if (m + 8 < M) __builtin_nontemporal_store(up, o8);
+          } else {
+            if (m < M) *o = lo;
+            if (m + 8 < M) *o8 = up;
+          }
+        }
+      }
+      return;
+    }
+  }
 #pragma unroll
   for (int b = 0; b < WT; ++b) {
     const int n = n0 + 16 * b;

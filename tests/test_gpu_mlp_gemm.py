@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 TOL = 3e-4
 
 SHAPES = [((27, 33, 7), 1), ((64, 200, 4433), 17), ((8, 8, 16), 3), ((64, 72, 136), 65), ((27, 256, 256, 1102), 130),
-          ((512, 129, 48), 64), ((40, 512, 24576), 100), ((64, 512, 512, 8320), 1100), ((16, 1000, 64), 260)]
+          ((512, 129, 48), 64), ((40, 512, 24576), 100), ((64, 512, 512, 8320), 1100), ((64, 512, 8320), 1000),
+          ((16, 1000, 64), 260)]
 
 
 def _bf(x):
