@@ -737,6 +737,7 @@ int build_layout(semx_ctx* c) {
     c->interior_exclusive = excl;
     c->elem_cover = c->ncolors > 0;
     for (int64_t g = 0; g < c->nglob && c->elem_cover; ++g) c->elem_cover = refs[g] != 0;
+    c->one_point_nodes = c->elem_cover && nspec * n3 == c->nglob;
   }
   int rc = dev_alloc(c, c->d_order, sizeof(int32_t) * nspec);
   if (!rc) rc = dev_alloc(c, c->d_ibool, sizeof(int32_t) * nspec * n3);
@@ -757,6 +758,10 @@ int build_layout(semx_ctx* c) {
   rc = build_blocks(c, pos_of, aff, order);
   find_lattice(c, aff);
   if (!rc) rc = build_node_points(c);
+  if (!rc && c->one_point_nodes && build_colored(c) != SEMX_OK) {  // stores_direct does without
+    dev_free(c->d_clist);
+    c->err.clear();
+  }
   if (rc) return rc;
   int* bad = scratch_i(c);
   SEMX_HIP(c, hipMemsetAsync(bad, 0, sizeof(int), c->stream));
@@ -964,17 +969,32 @@ bool carries_aux(const semx_ctx* c) {
   return k != kColumn && k != kMixed && !(k == kAcoustic && c->n > kMaxNLow);
 }
 
+// True when a pass with nothing to sum stores into f at once: every node has
+// one element point (elements that touch nowhere; a mesh of one).  The nodal
+// sum would be a second launch that only copies, some 2 us on applies of 7 to
+// 11 us.  The tables are there from the upload.  The line kernel has no such
+// form; it gives more than the launch costs.
+bool stores_direct(const semx_ctx* c) {
+  return parts_active(c) && c->one_point_nodes && c->d_clist.p && !c->kind_launches.empty() &&
+         kernel_for(c, true, c->kind_launches[0].irregular ? c->irregular_geo : kRegular) != kLine;
+}
+
 // `tl`: the time loop's pass after the source force was stored into f
 // (prestores()): the first-touch bits with the source nodes cleared.
 int force_accumulate(semx_ctx* c, const float* u, float* f, bool first_touch = false, bool f_zero = false,
                      bool tl = false, bool defer = false, const AuxArgs<float>* aux = nullptr) {
   const bool atomic = c->assembly == SEMX_ASM_ATOMIC;
-  const bool parts = parts_active(c), colored = !atomic && !parts && !blocks_active(c);
+  const bool direct = first_touch && !defer && !tl && stores_direct(c);
+  const bool parts = parts_active(c) && !direct, colored = !atomic && !parts && !direct && !blocks_active(c);
   if (colored) {
     int rc = build_colored(c);
     if (rc) return rc;
   }
   ForceArgs a = force_args(c, u, f, first_touch);
+  if (direct) {
+    a.first = c->d_first.as<uint32_t>();
+    a.first_words = c->first_words;
+  }
   if (tl && a.first) a.first = c->d_first_tl.as<uint32_t>();
   a.excl_interior = atomic && f_zero && c->interior_exclusive ? 1 : 0;
   if (blocks_active(c)) {

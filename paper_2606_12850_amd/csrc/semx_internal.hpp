@@ -176,6 +176,7 @@ struct semx_ctx {
   bool first_tl_dirty = true;
   std::vector<int32_t> h_src_nodes;  // nodes with a source force (FP32 weights), ascending
   bool elem_cover = false;
+  bool one_point_nodes = false;  // every node has one element point
   // every element-interior GLL point (local indices 1..n-2 in all three
   // directions) is the only reference to its node, as in any conforming mesh:
   // atomic assembly stores those points' forces without an atomic
@@ -345,7 +346,8 @@ hipError_t launch_force_line_acoustic(int n, int geo, int64_t naff, const ForceA
 constexpr int kLineMaxN = 12;
 
 hipError_t launch_force_mfma(int n, int prec, int geo, bool atomic, const ForceArgs& a, hipStream_t s);
-// force_high.hip: NGLL 11..16 (one lane per (i, j) column; the FP32 force pass uses it for 11..12)
+// force_high.hip: NGLL 11..16 (one lane per (i, j) column; the FP32 force pass uses it for 11..12
+// where the line kernel does not run)
 hipError_t launch_force_high(int n, int geo, bool atomic, const ForceArgs& a, hipStream_t s);
 // Memory skeleton of the coloured launch_force_high (same loads and stores, no arithmetic).
 hipError_t launch_force_high_skeleton(int n, int geo, const ForceArgs& a, hipStream_t s);
@@ -353,12 +355,12 @@ hipError_t launch_force_high_skeleton(int n, int geo, const ForceArgs& a, hipStr
 // contractions on the matrix cores; prec SEMX_C_F32 / SEMX_C_MFMA_F32 (FP32
 // operands), SEMX_C_BF16, SEMX_C_F16 (the launch's first naff elements have
 // an affine numbering).  FP32 contractions take it from kTileMinN (below,
-// the column kernel is faster: at NGLL 11-12 the padded tile does 2.4-3x the
-// useful matrix work), the matrix-core modes from kTileMinNMixed.
+// the line and column kernels are faster: at NGLL 11-12 the padded tile does
+// 2.4-3x the useful matrix work), the matrix-core modes from kTileMinNMixed.
 constexpr int kTileMinN = 13;
 constexpr int kTileMinNMixed = 11;
-// FP32 at NGLL 12: the tile kernel for launches of regular elements (its
-// persistent form, 0.754 against 0.917 ms per apply for the column kernel
+// FP32 at NGLL 12 where the line kernel does not run (assembly into f): the
+// tile kernel for launches of regular elements (its persistent form, 0.754 against 0.917 ms per apply for the column kernel
 // at 2e7 nodes); with per-point or trilinear geometry the column kernel
 // stays faster (0.98 against 1.05-1.19 ms), as at NGLL 11 on every path.
 constexpr int kTileRegularN = 12;

@@ -9,6 +9,8 @@ results agree to the bit, and so do the time loops (whose Newmark pass sums
 the node's points itself).  Elastic FP32 runs are made with checkpoints on:
 those keep the element kernels of the coloured pass at every size.
 """
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 
@@ -149,3 +151,22 @@ def test_adjoint_on_nodal_sums(n, ne, kind, geometry):
         # the terms of receivers at one node are added in another order: a rounding of 2^-24 a step, carried through
         # 24 steps of a recursion that preserves it
         assert np.linalg.norm(a - b) <= 24 * 6e-8 * 4 * np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("n,mode", [(2, "F32"), (5, "F32"), (10, "F32"), (12, "BF16"), (16, "F16"), (16, "F32"), (5, "BF16")])
+@pytest.mark.parametrize("acoustic", [False, True])
+@pytest.mark.parametrize("elements", [1, 3])
+def test_nothing_to_sum(n, mode, acoustic, elements):
+    """Elements that touch nowhere: an apply stores into f at once."""
+    import paper_2606_12850_amd as P
+    if acoustic and (mode != "F32" or n == 2):
+        pytest.skip("no 16-bit contractions; the line kernel at NGLL 2")
+    mesh = W.box_mesh((1, 1, 1), n, 1000.0)
+    k = np.arange(elements)[:, None]
+    mesh = SimpleNamespace(n=n, nspec=elements, nglob=elements * mesh.nglob,
+                           ibool=(mesh.ibool + k * mesh.nglob).astype(np.int32),
+                           elem_vert=(mesh.elem_vert + k * len(mesh.vert)).astype(np.int32),
+                           vert=np.concatenate([mesh.vert + [2000.0 * e, 0.0, 0.0] for e in range(elements)]))
+    kw = {"mode": None if mode == "F32" else getattr(P, "SEMX_C_" + mode), "acoustic": acoustic}
+    for a, b in zip(_run(P, mesh, n, True, 0, **kw), _run(P, mesh, n, False, 0, **kw)):
+        np.testing.assert_array_equal(a, b)
