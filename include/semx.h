@@ -24,10 +24,11 @@
  *     call that returns data to host memory synchronises that stream.
  *     A context is not thread-safe; use one context per host thread.
  *   - ngll = n = N+1 GLL points per direction, 2 <= n <= 16 (N = polynomial
- *     degree up to 15).  From NGLL 11 the FP32 operator runs on a
- *     column-per-lane kernel (NGLL 11, and 12 on irregular elements) or on
- *     matrix-core tiles (the rest; the acoustic operator from 12), the
- *     adjoint on column-per-lane kernels; FP64 storage supports n <= 10
+ *     degree up to 15).  Up to NGLL 12 the FP32 operator runs one lane per
+ *     point or per line of points by the size of the pass, from 13 on
+ *     matrix-core tiles; passes that assemble into f and runs with checkpoints
+ *     take a column-per-lane kernel at NGLL 11 (and at 12 on irregular
+ *     elements), as does the adjoint from 11; FP64 storage supports n <= 10
  *     (SEMX_EINVAL above), the 16-bit matrix-core contractions 4 <= n <= 8
  *     and 11 <= n <= 16.  Element-local point q = i + n*(j + n*k), i fastest
  *     (i along xi, j along eta, k along zeta).

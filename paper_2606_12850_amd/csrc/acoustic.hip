@@ -12,10 +12,11 @@
 // Two layouts, as for the elastic operator:
 //   force_ac_kernel      NGLL <= 10: one workgroup per element, one lane per
 //                        point, p and the three flux cubes in LDS;
-//   force_ac_col_kernel  NGLL 11..16: one lane per (i, j) column, the
-//                        column of p and its force accumulators in registers,
-//                        the element walked slice by slice in k (at NGLL 16
-//                        the xi contractions on DPP row rotations).
+//   force_ac_col_kernel  NGLL 11 where the line kernel does not run
+//                        (assembly into f, runs with checkpoints): one lane
+//                        per (i, j) column, the column of p and its force
+//                        accumulators in registers, the element walked slice
+//                        by slice in k.
 // Geometry paths, first-touch coloured stores and atomic assembly follow
 // the elastic kernels.
 #include "dpp_rows.hpp"

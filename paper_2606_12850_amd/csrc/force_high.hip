@@ -1,6 +1,8 @@
 // FP32 element internal-force kernel for high orders (NGLL 11..16).  The
-// force pass takes it at NGLL 11 and for irregular elements at 12; the
-// matrix-core tile kernel (force_tile16.hip) is faster elsewhere.
+// force pass takes it at NGLL 11 and for irregular elements at 12 where it
+// assembles into f (colours, atomics) and in runs with checkpoints; with
+// element-local forces the line kernel (force_line.hpp) runs there, and the
+// matrix-core tile kernel (force_tile16.hip) is faster at the other orders.
 //
 // Same operator as force_f32.hip (Sec. II-B weak form: three forward and
 // three transpose sum-factorised contractions around the pointwise
