@@ -1015,8 +1015,9 @@ def main():
 
     # ---- time loop: warmup, then exactly `steps` timed steps.  The force
     # kernel's launch duration is measured over the same region: one HIP
-    # event pair around the force pass (all colour launches back to back) of
-    # every second step, divided by its launches.  An event pair around every
+    # event pair around the force pass of every second step, divided by the
+    # launches that a pass colour by colour takes (element-local forces run it
+    # as one launch, its nodal sum inside the Newmark pass).  An event pair around every
     # launch would add the event-to-kernel latency to each duration and slow
     # the step itself by about 9 %.
     stride = 2
@@ -1088,8 +1089,13 @@ def main():
                    "nregular": info["nregular"], "nirregular": info["nirregular"], "ncolors": info["ncolors"]},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                     "kernel": f"force_f32_kernel<5, {args.geometry}, {args.assembly}"
-                               + (", affine numbering>" if args.assembly == "colored" else ">"),
+                     "kernel": f"FP32 force pass, NGLL 5, {args.geometry}, {args.assembly}"
+                               + (" (one launch of element-local forces on a box, the nodal sum in the Newmark pass)"
+                                  if args.assembly == "colored" and args.geometry == "trilinear" else ""),
+                     "note": "achieved and frac price the pass at the model's bytes, which the trilinear path does "
+                             "not move (no Gamma or det J per point): frac may exceed 1, frac_impl counts what its "
+                             "inputs and forces need; per-launch figures are the pass divided by the mesh's colours; "
+                             "the skeleton includes the nodal sum, the pass in the loop does not",
                      "bytes_model": "4 n^3 + 10 s n^3 + 2 s n^3 + 6 s G/E (node numbers, Gamma and det J per "
                                     "point, lambda and mu, u read and f written once per unique node; s = 4)",
                      "bytes_per_element": b_model, "bytes_per_launch": bytes_per_launch,
