@@ -730,8 +730,6 @@ int semx_adjoint(semx_ctx* c, const float* gseis_dev, int64_t nt, double* g_lamb
   if (!rc) rc = dev_alloc(c, acc, 3 * sizeof(double) * npt);
   if (rc) { cleanup(); return rc; }
   // keep the caller's forward state
-  rc = settle_force(c);
-  if (rc) { cleanup(); return rc; }
   const int64_t it_saved = c->it;
   const bool pend_saved = c->pending_correct;
   char* sv = saved.as<char>();

@@ -1092,8 +1092,6 @@ bool force_overwrites(const semx_ctx* c) {
 // `aux`: the step's bookkeeping, where the pass carries it (carries_aux).
 int force_into(semx_ctx* c, const float* u, float* f, bool f_zeroed, bool tl = false, bool defer = false,
                const AuxArgs<float>* aux = nullptr) {
-  int rs = settle_force(c);
-  if (rs) return rs;
   if (!f_zeroed && !force_overwrites(c)) {
     int rc = zero_f32(c, f, state_len(c));
     if (rc) return rc;
@@ -1330,8 +1328,6 @@ int set_sources_impl(semx_ctx* c, int nsrc, const int32_t* elem, const double* x
   if (!c) return SEMX_EINVAL;
   if (!c->have_mesh) return fail(c, SEMX_ESTATE, "set_sources: no mesh");
   if (nsrc < 0) return fail(c, SEMX_EINVAL, "set_sources: nsrc < 0");
-  int rs = settle_force(c);  // a pending force holds the old sources
-  if (rs) return rs;
   if (nsrc == 0) {
     c->src.nsrc = 0;
     c->src.nsn = 0;
@@ -1882,8 +1878,6 @@ int semx_force_skeleton(semx_ctx* c, const float* u_dev, float* f_dev, int reps,
   if (!u_dev || !f_dev || reps <= 0) return fail(c, SEMX_EINVAL, "force_skeleton: null pointer or reps <= 0");
   const int64_t len = state_len(c);
   if (u_dev < f_dev + len && f_dev < u_dev + len) return fail(c, SEMX_EINVAL, "force_skeleton: u and f overlap");
-  int rs = settle_force(c);
-  if (rs) return rs;
   const bool parts = parts_active(c), colored = !parts && !blocks_active(c);
   if (colored) {
     int rc = build_colored(c);
@@ -2062,19 +2056,18 @@ int semx_reset(semx_ctx* c) {
   return do_reset(c);
 }
 
-int semx_step(semx_ctx* c, int64_t nsteps) {
-  if (!c) return SEMX_EINVAL;
-  if (!c->have_mesh || !c->have_model) return fail(c, SEMX_ESTATE, "step: mesh and model required");
-  if (!c->have_dt) return fail(c, SEMX_ESTATE, "step: dt not set");
-  if (nsteps < 0) return fail(c, SEMX_EINVAL, "step: nsteps < 0");
+namespace {
+
+int step_many(semx_ctx* c, int64_t nsteps) {
   // Graph-captured chunks for the untracked middle of a long call: FP32
   // storage, no force timing, no checkpoints, no watchdog; the first step
-  // (if no corrector is pending) and the last (energy tracking) run directly.
+  // (unless the state is the one that a chunk leaves: a corrector pending, its
+  // force where this pass leaves it) and the last (energy tracking) run directly.
   const int64_t G = c->graph_chunk;
   if (G > 0 && c->storage == SEMX_F32 && c->timing_stride == 0 && c->ckpt_every == 0 &&
       c->watchdog_every == 0 && nsteps >= 2 * G + 2) {
     int64_t done = 0;
-    if (!c->pending_correct) {
+    if (!c->pending_correct || c->f_in_part != parts_active(c)) {
       c->track_energy = false;
       int rc = step_once(c, true);
       if (rc) return rc;
@@ -2119,6 +2112,21 @@ int semx_step(semx_ctx* c, int64_t nsteps) {
     }
   }
   return SEMX_OK;
+}
+
+}  // namespace
+
+int semx_step(semx_ctx* c, int64_t nsteps) {
+  if (!c) return SEMX_EINVAL;
+  if (!c->have_mesh || !c->have_model) return fail(c, SEMX_ESTATE, "step: mesh and model required");
+  if (!c->have_dt) return fail(c, SEMX_ESTATE, "step: dt not set");
+  if (nsteps < 0) return fail(c, SEMX_EINVAL, "step: nsteps < 0");
+  const int rc = step_many(c, nsteps);
+  // Between calls the pending force lies in f, whatever form the last step
+  // had: the modes may change, a force apply (also one replayed from a caller's
+  // graph) writes the element-local forces.
+  const int rs = settle_force(c);
+  return rc ? rc : rs;
 }
 
 int semx_time_index(semx_ctx* c, int64_t* it) {

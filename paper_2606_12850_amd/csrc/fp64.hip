@@ -425,8 +425,6 @@ int f64_model_setup(semx_ctx* c, const double* lam_dev, const double* mu_dev) {
 }
 
 int f64_force_into(semx_ctx* c, const double* u, double* f, bool f_zeroed) {
-  int rs = settle_force(c);
-  if (rs) return rs;
   if (parts_active(c)) {
     hipError_t e = launch_force64(c, u, f);
     if (e == hipSuccess) e = launch_gather64(c, f, nullptr, c->stream);

@@ -152,8 +152,9 @@ struct semx_ctx {
   // by the caller the force runs colour by colour
   semx::DevBuf d_part;
   semx::Lattice lattice;
-  // the pending force f^n lies in d_part (and, where part_src, in f at the
-  // source nodes) and has not been summed into f
+  // inside a semx_step call: the pending force f^n lies in d_part (and, where
+  // part_src, in f at the source nodes) and has not been summed into f.  On
+  // return of the call it has: d_part keeps nothing from one call to the next
   bool f_in_part = false, part_src = false;
   bool user_colors = false;
   // one bit per node that receives a source force (the time loop's gather
@@ -396,8 +397,8 @@ unsigned grid_1d(int64_t n, int cap = 1 << 16);
 int save_checkpoint(semx_ctx* c);
 // The force runs as one launch per geometry kind into d_part, then a gather.
 bool parts_active(const semx_ctx* c);
-// Sums a pending force that lies in d_part into f (before d_part, f, the
-// sources or the state change otherwise).
+// Sums a pending force that lies in d_part into f (at the end of a semx_step
+// call and where a step of it needs f).
 int settle_force(semx_ctx* c);
 // The time loop stores the source force into f before the force pass.
 bool prestores(const semx_ctx* c);
