@@ -758,10 +758,10 @@ int build_layout(semx_ctx* c) {
   rc = build_blocks(c, pos_of, aff, order);
   find_lattice(c, aff);
   if (!rc) rc = build_node_points(c);
-  if (!rc && c->one_point_nodes && build_colored(c) != SEMX_OK) {  // stores_direct does without
-    dev_free(c->d_clist);
-    c->err.clear();
-  }
+  // a pass that runs colour by colour finds its tables whatever call comes
+  // first (it may be captured into a graph, where nothing can be allocated)
+  if (!rc && c->user_colors) rc = build_colored(c);
+  if (!rc && c->one_point_nodes && build_colored(c) != SEMX_OK) c->err.clear();  // stores_direct does without
   if (rc) return rc;
   int* bad = scratch_i(c);
   SEMX_HIP(c, hipMemsetAsync(bad, 0, sizeof(int), c->stream));
@@ -913,9 +913,16 @@ int build_colored(semx_ctx* c) {
   }
   int rc = dev_alloc(c, c->d_first, sizeof(uint32_t) * first.size());
   if (!rc) rc = dev_alloc(c, c->d_clist, sizeof(int32_t) * c->nspec);
-  if (rc) return rc;
-  SEMX_HIP(c, hipMemcpy(c->d_first.p, first.data(), sizeof(uint32_t) * first.size(), hipMemcpyHostToDevice));
-  SEMX_HIP(c, hipMemcpy(c->d_clist.p, c->h_clist.data(), sizeof(int32_t) * c->nspec, hipMemcpyHostToDevice));
+  hipError_t e = hipSuccess;
+  if (!rc) e = hipMemcpy(c->d_first.p, first.data(), sizeof(uint32_t) * first.size(), hipMemcpyHostToDevice);
+  if (!rc && e == hipSuccess)
+    e = hipMemcpy(c->d_clist.p, c->h_clist.data(), sizeof(int32_t) * c->nspec, hipMemcpyHostToDevice);
+  if (e != hipSuccess) rc = hip_fail(c, e, "colour tables");
+  if (rc) {  // d_clist says that they are there
+    dev_free(c->d_clist);
+    dev_free(c->d_first);
+    return rc;
+  }
   c->h_first = std::move(first);
   c->first_words = fw;
   c->first_tl_dirty = true;
@@ -1721,6 +1728,7 @@ int upload_model_impl(semx_ctx* c, int nmodels, const double* lambda, const doub
   if (!rc && (c->user_colors || dev_alloc(c, c->d_part, es * c->ncomp * npt) != SEMX_OK)) {
     dev_free(c->d_part);
     c->err.clear();
+    rc = build_colored(c);
   }
   if (!rc && c->storage == SEMX_F64) rc = dev_alloc(c, c->d_gam64, sizeof(double) * 9 * c->nspec * c->n3);
   if (!rc && c->storage != SEMX_F64)

@@ -135,3 +135,35 @@ def test_replayed_applies_leave_the_run():
     for fn in (between, captured_only):
         for x, y in zip(plain, _run(fn, 0)):
             np.testing.assert_array_equal(x, y)
+
+
+def _captured_first_apply(f64):
+    """On a caller's colouring, the first force pass of all is recorded into a graph."""
+    import torch
+    import paper_2606_12850_amd as P
+    mesh = W.box_mesh((3, 2, 3), N, 4000.0, jitter=0.1, seed=4)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        s = P.Solver(N, storage=P.SEMX_F64 if f64 else P.SEMX_F32)
+        s.upload_mesh(mesh)
+        P.semx_set_coloring(s.ctx, *P.semx_get_coloring(s.ctx, mesh.nspec))
+        s.upload_model(*W.layered_model(mesh))
+        s.ug, s.fg, s.side = s.empty_field(), s.empty_field(), side
+        s.ug += torch.arange(mesh.nglob, device="cuda")[:, None] * 1e-3
+        s.ug *= s.ug
+        g = _capture(s)
+        s.fg.fill_(1.0)
+        g.replay()
+        first = s.fg.clone()
+        s.apply_force(s.ug, s.fg)
+        side.synchronize()
+        out = first.cpu().numpy(), s.fg.cpu().numpy()
+    s.close()
+    return out
+
+
+@pytest.mark.parametrize("f64", [False, True], ids=["f32", "f64"])
+def test_first_pass_captured(f64):
+    graph, direct = _captured_first_apply(f64)
+    assert np.abs(direct).max() > 0
+    np.testing.assert_array_equal(graph, direct)
