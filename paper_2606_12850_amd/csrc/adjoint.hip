@@ -649,7 +649,7 @@ int save_checkpoint(semx_ctx* c) {
     c->ckpt_gen.resize(k + 1, -1);
   }
   if (c->ckpts[k].bytes != 3 * vb) {
-    rc = dev_alloc(c, c->ckpts[k], 3 * vb);
+    rc = run_alloc(c, c->ckpts[k], 3 * vb);
     if (rc) return rc;
   }
   char* base = c->ckpts[k].as<char>();
@@ -722,12 +722,12 @@ int semx_adjoint(semx_ctx* c, const float* gseis_dev, int64_t nt, double* g_lamb
   auto cleanup = [&]() {
     for (DevBuf* b : {&saved, &segu, &sega, &psi, &fb, &acc}) dev_free(*b);
   };
-  int rc = dev_alloc(c, saved, 4 * vb);
-  if (!rc) rc = dev_alloc(c, segu, (K + 1) * vbp);
-  if (!rc) rc = dev_alloc(c, sega, (K + 1) * vbp);
-  if (!rc) rc = dev_alloc(c, psi, 3 * vbp);
-  if (!rc) rc = dev_alloc(c, fb, vb);
-  if (!rc) rc = dev_alloc(c, acc, 3 * sizeof(double) * npt);
+  int rc = run_alloc(c, saved, 4 * vb);
+  if (!rc) rc = run_alloc(c, segu, (K + 1) * vbp);
+  if (!rc) rc = run_alloc(c, sega, (K + 1) * vbp);
+  if (!rc) rc = run_alloc(c, psi, 3 * vbp);
+  if (!rc) rc = run_alloc(c, fb, vb);
+  if (!rc) rc = run_alloc(c, acc, 3 * sizeof(double) * npt);
   if (rc) { cleanup(); return rc; }
   // keep the caller's forward state
   const int64_t it_saved = c->it;

@@ -42,6 +42,17 @@ int dev_alloc(semx_ctx* c, DevBuf& b, size_t bytes) {
   return SEMX_OK;
 }
 
+int run_alloc(semx_ctx* c, DevBuf& b, size_t bytes) {
+  int rc = dev_alloc(c, b, bytes);
+  if (rc != SEMX_ENOMEM || !c->d_part.p || !c->have_model || c->part_captured) return rc;
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || free_b + c->d_part.bytes < bytes) return rc;
+  dev_free(c->d_part);
+  c->err.clear();
+  rc = build_colored(c);
+  return rc ? rc : dev_alloc(c, b, bytes);
+}
+
 void dev_free(DevBuf& b) {
   if (b.p) (void)hipFree(b.p);
   b.p = nullptr;
@@ -931,6 +942,13 @@ int build_colored(semx_ctx* c) {
 
 namespace {
 
+// A caller who captures force passes keeps the address of d_part in a graph.
+void note_capture(semx_ctx* c) {
+  if (!c->stream || c->part_captured || !c->d_part.p) return;  // the null stream cannot be captured
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  c->part_captured = hipStreamIsCapturing(c->stream, &st) == hipSuccess && st == hipStreamCaptureStatusActive;
+}
+
 // True when a launch of geometry path `geo` runs on the line kernel
 // (force_line.hpp), FP32 with element-local forces.  Where the lines lie
 // (us per apply, line / kernel it replaces, 2e5 and 3e6 nodes):
@@ -1075,14 +1093,14 @@ int alloc_seismograms(semx_ctx* c) {
   const int64_t cnt = (int64_t)nm * c->rec.nrec * c->ncomp * c->rec.nt_max;
   if (c->storage == SEMX_F64) {
     dev_free(c->rec.seis);
-    int rc = dev_alloc(c, c->rec.seis64, sizeof(double) * cnt);
+    int rc = run_alloc(c, c->rec.seis64, sizeof(double) * cnt);
     if (rc) return rc;
     fill_f64<<<grid_for(cnt), kThreads, 0, c->stream>>>(c->rec.seis64.as<double>(), cnt, 0.0);
     SEMX_HIP(c, hipGetLastError());
     return SEMX_OK;
   }
   dev_free(c->rec.seis64);
-  int rc = dev_alloc(c, c->rec.seis, sizeof(float) * cnt);
+  int rc = run_alloc(c, c->rec.seis, sizeof(float) * cnt);
   if (rc) return rc;
   return zero_f32(c, c->rec.seis.as<float>(), cnt);
 }
@@ -1409,15 +1427,15 @@ int set_sources_impl(semx_ctx* c, int nsrc, const int32_t* elem, const double* x
   c->srcbits_dirty = true;
   sptr.push_back((int32_t)np_pairs.size());
   if (sidx.empty()) sidx.push_back(0);
-  int rc = dev_alloc(c, c->src.nodes, nodes.size() * sizeof(int32_t));
-  if (!rc) rc = dev_alloc(c, c->src.snode, sizeof(int32_t) * std::max<size_t>(1, snode.size()));
-  if (!rc) rc = dev_alloc(c, c->src.sptr, sizeof(int32_t) * sptr.size());
-  if (!rc) rc = dev_alloc(c, c->src.sidx, sizeof(int32_t) * sidx.size());
-  if (!rc) rc = dev_alloc(c, c->src.pts, pts.size() * sizeof(int32_t));
-  if (!rc) rc = dev_alloc(c, c->src.wdir, wdir.size() * sizeof(float));
-  if (!rc) rc = dev_alloc(c, c->src.stf, sizeof(float) * ns);
-  if (!rc) rc = dev_alloc(c, c->src.wdir64, wdir64.size() * sizeof(double));
-  if (!rc) rc = dev_alloc(c, c->src.stf64, sizeof(double) * ns);
+  int rc = run_alloc(c, c->src.nodes, nodes.size() * sizeof(int32_t));
+  if (!rc) rc = run_alloc(c, c->src.snode, sizeof(int32_t) * std::max<size_t>(1, snode.size()));
+  if (!rc) rc = run_alloc(c, c->src.sptr, sizeof(int32_t) * sptr.size());
+  if (!rc) rc = run_alloc(c, c->src.sidx, sizeof(int32_t) * sidx.size());
+  if (!rc) rc = run_alloc(c, c->src.pts, pts.size() * sizeof(int32_t));
+  if (!rc) rc = run_alloc(c, c->src.wdir, wdir.size() * sizeof(float));
+  if (!rc) rc = run_alloc(c, c->src.stf, sizeof(float) * ns);
+  if (!rc) rc = run_alloc(c, c->src.wdir64, wdir64.size() * sizeof(double));
+  if (!rc) rc = run_alloc(c, c->src.stf64, sizeof(double) * ns);
   if (rc) return rc;
   SEMX_HIP(c, hipMemcpy(c->src.nodes.p, nodes.data(), nodes.size() * sizeof(int32_t), hipMemcpyHostToDevice));
   if (!snode.empty())
@@ -1543,6 +1561,7 @@ int semx_upload_mesh(semx_ctx* c, int64_t nspec, int64_t nglob, const int32_t* i
   c->have_mesh = c->have_model = false;
   c->user_colors = false;
   c->f_in_part = false;
+  dev_free(c->d_part);
   // sources and receivers live in elements of the previous mesh
   c->src.nsrc = 0;
   c->src.nsn = 0;
@@ -1674,6 +1693,7 @@ int semx_set_coloring(semx_ctx* c, int ncolors, const int32_t* color_ptr, const 
   // the device layout follows the colouring: rebuild it; the model must be uploaded again
   c->have_model = false;
   c->f_in_part = false;
+  dev_free(c->d_part);
   return build_layout(c);
 }
 
@@ -1707,8 +1727,10 @@ int upload_model_impl(semx_ctx* c, int nmodels, const double* lambda, const doub
   if (rc) return rc;
   c->have_model = false;
   c->f_in_part = false;
+  c->part_captured = false;
   c->nmodels = nmodels;
   c->vp_max = vpmax;
+  dev_free(c->d_part);
   DevBuf dl, dm, dr;
   rc = dev_alloc(c, dl, sizeof(double) * npt);
   if (!rc) rc = dev_alloc(c, dm, sizeof(double) * npt);
@@ -1724,12 +1746,6 @@ int upload_model_impl(semx_ctx* c, int nmodels, const double* lambda, const doub
   if (!rc) rc = dev_alloc(c, c->d_a, es * len);
   if (!rc) rc = dev_alloc(c, c->d_f, es * len);
   if (!rc) rc = dev_alloc(c, c->d_work, es * len);
-  // without room for the element-local forces the force runs colour by colour
-  if (!rc && (c->user_colors || dev_alloc(c, c->d_part, es * c->ncomp * npt) != SEMX_OK)) {
-    dev_free(c->d_part);
-    c->err.clear();
-    rc = build_colored(c);
-  }
   if (!rc && c->storage == SEMX_F64) rc = dev_alloc(c, c->d_gam64, sizeof(double) * 9 * c->nspec * c->n3);
   if (!rc && c->storage != SEMX_F64)
     for (DevBuf* b : {&c->d_gam64, &c->d_mat64, &c->d_minv64, &c->d_gam64_el}) dev_free(*b);
@@ -1768,7 +1784,14 @@ int upload_model_impl(semx_ctx* c, int nmodels, const double* lambda, const doub
     rc = alloc_seismograms(c);
     if (rc) return rc;
   }
-  return do_reset(c);
+  rc = do_reset(c);
+  // Last, and only if there is room: without the element-local forces the pass
+  // runs colour by colour.
+  if (!rc && !c->user_colors && c->ncolors > 0 && dev_alloc(c, c->d_part, es * c->ncomp * npt) != SEMX_OK) {
+    c->err.clear();
+    rc = build_colored(c);
+  }
+  return rc;
 }
 
 }  // namespace
@@ -1874,6 +1897,7 @@ int semx_apply_force(semx_ctx* c, const float* u_dev, float* f_dev) {
   if (!u_dev || !f_dev) return fail(c, SEMX_EINVAL, "apply_force: null pointer");
   const int64_t len = state_len(c);
   if (u_dev < f_dev + len && f_dev < u_dev + len) return fail(c, SEMX_EINVAL, "apply_force: u and f overlap");
+  note_capture(c);
   return force_into(c, u_dev, f_dev, false);
 }
 
@@ -1960,8 +1984,8 @@ int semx_max_eigenvalue(semx_ctx* c, int iters, double* lambda_max) {
   const int saved_models = c->nmodels;
   const int64_t n3g = c->ncomp * c->nglob;
   DevBuf x, y;
-  int rc = dev_alloc(c, x, sizeof(float) * n3g * saved_models);
-  if (!rc) rc = dev_alloc(c, y, sizeof(float) * n3g * saved_models);
+  int rc = run_alloc(c, x, sizeof(float) * n3g * saved_models);
+  if (!rc) rc = run_alloc(c, y, sizeof(float) * n3g * saved_models);
   if (rc) { dev_free(x); dev_free(y); return rc; }
   // deterministic pseudo-random start vector (hash of the index)
   std::vector<float> h(n3g * saved_models, 0.0f);
@@ -2043,9 +2067,9 @@ int semx_set_receivers(semx_ctx* c, int nrec, const int32_t* elem, const double*
           wts[(size_t)r * n3 + q] = (float)wts64[(size_t)r * n3 + q];
         }
   }
-  int rc = dev_alloc(c, c->rec.nodes, nodes.size() * sizeof(int32_t));
-  if (!rc) rc = dev_alloc(c, c->rec.wts, wts.size() * sizeof(float));
-  if (!rc) rc = dev_alloc(c, c->rec.wts64, wts64.size() * sizeof(double));
+  int rc = run_alloc(c, c->rec.nodes, nodes.size() * sizeof(int32_t));
+  if (!rc) rc = run_alloc(c, c->rec.wts, wts.size() * sizeof(float));
+  if (!rc) rc = run_alloc(c, c->rec.wts64, wts64.size() * sizeof(double));
   if (rc) return rc;
   SEMX_HIP(c, hipMemcpy(c->rec.nodes.p, nodes.data(), nodes.size() * sizeof(int32_t), hipMemcpyHostToDevice));
   SEMX_HIP(c, hipMemcpy(c->rec.wts.p, wts.data(), wts.size() * sizeof(float), hipMemcpyHostToDevice));
@@ -2129,6 +2153,7 @@ int semx_step(semx_ctx* c, int64_t nsteps) {
   if (!c->have_mesh || !c->have_model) return fail(c, SEMX_ESTATE, "step: mesh and model required");
   if (!c->have_dt) return fail(c, SEMX_ESTATE, "step: dt not set");
   if (nsteps < 0) return fail(c, SEMX_EINVAL, "step: nsteps < 0");
+  note_capture(c);
   const int rc = step_many(c, nsteps);
   // Between calls the pending force lies in f, whatever form the last step
   // had: the modes may change, a force apply (also one replayed from a caller's
@@ -2273,6 +2298,7 @@ int semx_apply_force_f64(semx_ctx* c, const double* u_dev, double* f_dev) {
   if (!u_dev || !f_dev) return fail(c, SEMX_EINVAL, "apply_force_f64: null pointer");
   const int64_t len = state_len(c);
   if (u_dev < f_dev + len && f_dev < u_dev + len) return fail(c, SEMX_EINVAL, "apply_force_f64: u and f overlap");
+  note_capture(c);
   return f64_force_into(c, u_dev, f_dev, false);
 }
 

@@ -151,6 +151,7 @@ struct semx_ctx {
   // storage precision; without it (no memory left) and with a colouring given
   // by the caller the force runs colour by colour
   semx::DevBuf d_part;
+  bool part_captured = false;  // a force pass was captured by the caller since the model upload
   semx::Lattice lattice;
   // inside a semx_step call: the pending force f^n lies in d_part (and, where
   // part_src, in f at the source nodes) and has not been summed into f.  On
@@ -271,6 +272,10 @@ int hip_fail(semx_ctx* c, hipError_t e, const char* what);
   } while (0)
 
 int dev_alloc(semx_ctx* c, DevBuf& b, size_t bytes);
+// The same for what a run needs besides the model: where it does not fit, the
+// element-local forces make room (the force then runs colour by colour).  Not
+// while a pass is under way, and not where a caller's graph holds their address.
+int run_alloc(semx_ctx* c, DevBuf& b, size_t bytes);
 void dev_free(DevBuf& b);
 
 // ---- GLL basis (host, FP64) ---------------------------------------------

@@ -32,8 +32,8 @@ extern "C" int semx_stream_bandwidth(semx_ctx* c, int64_t nbytes, int reps, doub
   const int64_t n = nbytes / 16;
   if ((n + 255) / 256 > 0x7fffffffLL) return fail(c, SEMX_EINVAL, "stream_bandwidth: nbytes too large");
   DevBuf a, b;
-  int rc = dev_alloc(c, a, (size_t)nbytes);
-  if (!rc) rc = dev_alloc(c, b, (size_t)nbytes);
+  int rc = run_alloc(c, a, (size_t)nbytes);
+  if (!rc) rc = run_alloc(c, b, (size_t)nbytes);
   if (rc) {
     dev_free(a);
     dev_free(b);
