@@ -819,7 +819,7 @@ ForceArgs force_args(const semx_ctx* c, const float* u, float* f, bool first_tou
   a.u = u;
   a.f = f;
   a.D = c->d_D.as<float>();
-  a.eo = c->d_eo.as<float>();
+  a.dtab = c->d_dtab.as<float>();
   a.Dh = c->d_Dh.p;
   a.nspec = c->nspec;
   a.nglob = c->nglob;
@@ -1486,11 +1486,11 @@ int semx_create(semx_ctx** out, int ngll, void* hip_stream) {
   gll_nodes_weights(ngll, c->xi, c->w);
   deriv_matrix(ngll, c->xi, c->D);
   std::vector<float> Df(c->D.begin(), c->D.end());
-  std::vector<double> eo64;
-  even_odd(ngll, c->D, eo64);
-  std::vector<float> eo(eo64.begin(), eo64.end());
+  std::vector<double> tab64;
+  line_table(ngll, c->D, tab64);
+  std::vector<float> tab(tab64.begin(), tab64.end());
   int rc = dev_alloc(c, c->d_D, Df.size() * sizeof(float));
-  if (!rc) rc = dev_alloc(c, c->d_eo, eo.size() * sizeof(float));
+  if (!rc) rc = dev_alloc(c, c->d_dtab, tab.size() * sizeof(float));
   if (!rc) rc = dev_alloc(c, c->d_xi64, ngll * sizeof(double));
   if (!rc) rc = dev_alloc(c, c->d_w64, ngll * sizeof(double));
   if (!rc) rc = dev_alloc(c, c->d_xi32, ngll * sizeof(float));
@@ -1500,7 +1500,7 @@ int semx_create(semx_ctx** out, int ngll, void* hip_stream) {
     return rc;
   }
   e = hipMemcpy(c->d_D.p, Df.data(), Df.size() * sizeof(float), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(c->d_eo.p, eo.data(), eo.size() * sizeof(float), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemcpy(c->d_dtab.p, tab.data(), tab.size() * sizeof(float), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(c->d_xi64.p, c->xi.data(), ngll * sizeof(double), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(c->d_w64.p, c->w.data(), ngll * sizeof(double), hipMemcpyHostToDevice);
   std::vector<float> xi32(c->xi.begin(), c->xi.end());
@@ -1522,14 +1522,14 @@ int semx_destroy(semx_ctx* c) {
   for (DevBuf* b : {&c->d_bpos, &c->d_baff, &c->d_bfirst, &c->d_step, &c->d_first_tl, &c->d_bfirst_tl}) dev_free(*b);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
   c->cap_stream = nullptr;
-  for (DevBuf* b : {&c->d_D, &c->d_eo, &c->d_Dh, &c->d_xi64, &c->d_w64, &c->d_ibool, &c->d_vert, &c->d_elem_vert,
+  for (DevBuf* b : {&c->d_D, &c->d_dtab, &c->d_Dh, &c->d_xi64, &c->d_w64, &c->d_ibool, &c->d_vert, &c->d_elem_vert,
                     &c->d_gam_pt, &c->d_gam_el, &c->d_tri, &c->d_xi32, &c->d_wdet, &c->d_order, &c->d_mat, &c->d_minv,
                     &c->d_mass64, &c->d_wrho, &c->d_u, &c->d_v, &c->d_a, &c->d_f, &c->d_work, &c->d_scratch,
                     &c->src.nodes, &c->src.wdir, &c->src.stf, &c->src.pts, &c->src.snode, &c->src.sptr,
                     &c->src.sidx, &c->rec.nodes, &c->rec.wts,
                     &c->rec.seis,
                     &c->src.wdir64, &c->src.stf64, &c->rec.wts64, &c->rec.seis64, &c->d_gam64, &c->d_mat64,
-                    &c->d_minv64, &c->d_D64, &c->d_eo64, &c->d_gam64_el,
+                    &c->d_minv64, &c->d_D64, &c->d_dtab64, &c->d_gam64_el,
                     &c->d_first, &c->d_aff, &c->d_nptr, &c->d_nidx, &c->d_part, &c->d_srcbits, &c->d_clist, &c->rec.rbits, &c->rec.rnode, &c->rec.rptr,
                     &c->rec.ridx})
     dev_free(*b);

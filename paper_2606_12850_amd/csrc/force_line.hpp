@@ -7,11 +7,7 @@
 // are bound by vector instructions (316 a point, 62 % of the ALU time of a
 // force pass at 64^3 elements) before they are bound by memory.  Here a lane
 // owns a whole line of n points: a derivative of the line is a small product
-// whose coefficients are the same for every lane (scalar registers), and it
-// takes the even-odd form (the derivative matrix on symmetric nodes is
-// centro-antisymmetric, D[n-1-i][n-1-j] = -D[i][j], so the sums and
-// differences of mirrored points halve the multiplications: 48 instead of 64
-// operations a line at NGLL 8).
+// whose coefficients are the same for every lane (scalar registers).
 //
 //   home layout: lane c = (i, j) of its element holds the points k = 0..n-1
 //     (the zeta line): gather, pointwise stage, result; the zeta derivative
@@ -46,75 +42,112 @@ struct LineShape {
   static constexpr int BLK = (EPW * N2 + 63) / 64 * 64;
 };
 
-// Even-odd tables of D: A[i][j] = (D[i][j] - D[i][n-1-j]) / 2, B[i][j] = (D[i][j] +
-// D[i][n-1-j]) / 2 for i, j < n / 2, then the middle column D[i][n/2] and the
-// middle row D[n/2][j] (odd n).
+// D on a line, from the tables of line_table(): the upper half of its rows,
+// the left half of the middle row (odd n; D is centro-antisymmetric, so these
+// are all of it), and the halves A[i][j] = (D[i][j] - D[i][n-1-j]) / 2, B[i][j] =
+// (D[i][j] + D[i][n-1-j]) / 2.
+//
+// y = D x takes the rows as they are.  The even-odd form (the sums and
+// differences of mirrored points times A and B) has a quarter fewer operations,
+// but its parts cancel: forces of 5-30 nodes per wavelength came out up to 1.5
+// times as far from FP64 as the per-point kernels' (NGLL 5; 2.4 times at 40 nodes
+// and more), which the rows do not (0.88-1.03 times).  Terms are added from the
+// far end of the line, the large ones last, but at NGLL 3, where the small ones
+// go last.  z = D^T q holds fluxes, which do not cancel so: it takes the even-odd
+// form from NGLL 6, the rows below (1.00 against 1.03-1.05 times the error at
+// NGLL 4 and 5).  All in even-odd form an apply took 0-2 % less up to NGLL 6, 2-5 %
+// to 9, 3-10 % from 10.
 template <class T, int NG>
-struct EvenOdd {
+struct LineD {
   static constexpr int H = NG / 2;
   static constexpr bool ODD = NG & 1;
   const T* __restrict__ t;
-  __device__ __forceinline__ T A(int i, int j) const { return t[i * H + j]; }
-  __device__ __forceinline__ T B(int i, int j) const { return t[H * H + i * H + j]; }
-  __device__ __forceinline__ T col(int i) const { return t[2 * H * H + i]; }
-  __device__ __forceinline__ T row(int j) const { return t[2 * H * H + H + j]; }
+  __device__ __forceinline__ T D(int i, int j) const { return t[i * NG + j]; }
+  __device__ __forceinline__ T mid(int j) const { return t[H * NG + j]; }
+  __device__ __forceinline__ T A(int i, int j) const { return t[H * (NG + 1) + i * H + j]; }
+  __device__ __forceinline__ T B(int i, int j) const { return t[H * (NG + 1) + H * H + i * H + j]; }
 
-  // y = D x
+  // x = D x
   __device__ __forceinline__ void apply(T x[NG]) const {
-    T e[H], o[H];
-#pragma unroll
-    for (int j = 0; j < H; ++j) {
-      e[j] = x[j] + x[NG - 1 - j];
-      o[j] = x[j] - x[NG - 1 - j];
-    }
-    const T mid = x[H];
+    T y[NG];
 #pragma unroll
     for (int i = 0; i < H; ++i) {
-      T s = A(i, 0) * o[0], t_ = B(i, 0) * e[0];
+      T s, r;
+      if constexpr (NG == 3) {
+        s = D(i, 0) * x[0];
+        r = D(i, NG - 1) * x[0];
 #pragma unroll
-      for (int j = 1; j < H; ++j) {
-        s += A(i, j) * o[j];
-        t_ += B(i, j) * e[j];
+        for (int j = 1; j < NG; ++j) {
+          s += D(i, j) * x[j];
+          r += D(i, NG - 1 - j) * x[j];
+        }
+      } else {
+        s = D(i, NG - 1) * x[NG - 1];
+        r = D(i, NG - 1) * x[0];
+#pragma unroll
+        for (int j = NG - 2; j >= 0; --j) {
+          s += D(i, j) * x[j];
+          r += D(i, j) * x[NG - 1 - j];
+        }
       }
-      if constexpr (ODD) t_ += col(i) * mid;
-      x[i] = s + t_;
-      x[NG - 1 - i] = s - t_;
+      y[i] = s;
+      y[NG - 1 - i] = -r;
     }
     if constexpr (ODD) {
-      T s = row(0) * o[0];
+      T s = mid(0) * (x[0] - x[NG - 1]);
 #pragma unroll
-      for (int j = 1; j < H; ++j) s += row(j) * o[j];
-      x[H] = s;
+      for (int j = 1; j < H; ++j) s += mid(j) * (x[j] - x[NG - 1 - j]);
+      y[H] = s;
     }
+#pragma unroll
+    for (int i = 0; i < NG; ++i) x[i] = y[i];
   }
 
-  // z = D^T q
+  // q = D^T q
   __device__ __forceinline__ void apply_t(T q[NG]) const {
-    T e[H], o[H];
+    T z[NG];
+    if constexpr (NG <= 5) {
 #pragma unroll
-    for (int i = 0; i < H; ++i) {
-      e[i] = q[i] + q[NG - 1 - i];
-      o[i] = q[i] - q[NG - 1 - i];
-    }
-    const T mid = q[H];
+      for (int j = 0; j < NG; ++j) {
+        T s = D(0, j) * q[0];
 #pragma unroll
-    for (int j = 0; j < H; ++j) {
-      T s = B(0, j) * o[0], t_ = A(0, j) * e[0];
+        for (int i = 1; i < H; ++i) s += D(i, j) * q[i];
+        if constexpr (ODD) {
+          if (j < H) s += mid(j) * q[H];
+          if (j > H) s -= mid(NG - 1 - j) * q[H];
+        }
 #pragma unroll
-      for (int i = 1; i < H; ++i) {
-        s += B(i, j) * o[i];
-        t_ += A(i, j) * e[i];
+        for (int i = H - 1; i >= 0; --i) s -= D(i, NG - 1 - j) * q[NG - 1 - i];
+        z[j] = s;
       }
-      if constexpr (ODD) t_ += row(j) * mid;
-      q[j] = s + t_;
-      q[NG - 1 - j] = s - t_;
-    }
-    if constexpr (ODD) {
-      T s = col(0) * o[0];
+    } else {
+      T e[H], o[H];
 #pragma unroll
-      for (int i = 1; i < H; ++i) s += col(i) * o[i];
-      q[H] = s;
+      for (int i = 0; i < H; ++i) {
+        e[i] = q[i] + q[NG - 1 - i];
+        o[i] = q[i] - q[NG - 1 - i];
+      }
+#pragma unroll
+      for (int j = 0; j < H; ++j) {
+        T s = B(0, j) * o[0], r = A(0, j) * e[0];
+#pragma unroll
+        for (int i = 1; i < H; ++i) {
+          s += B(i, j) * o[i];
+          r += A(i, j) * e[i];
+        }
+        if constexpr (ODD) r += mid(j) * q[H];
+        z[j] = s + r;
+        z[NG - 1 - j] = s - r;
+      }
+      if constexpr (ODD) {
+        T s = D(0, H) * o[0];
+#pragma unroll
+        for (int i = 1; i < H; ++i) s += D(i, H) * o[i];
+        z[H] = s;
+      }
     }
+#pragma unroll
+    for (int i = 0; i < NG; ++i) q[i] = z[i];
   }
 };
 
@@ -228,7 +261,7 @@ __global__ __launch_bounds__((LineShape<T, NG>::BLK)) void force_line_kernel(Lin
   const int model = blockIdx.y;
   const T* __restrict__ u = a.u + (size_t)model * a.nglob * NC;
   const T* __restrict__ mat = a.mat + ((size_t)model * a.nspec + pos) * 2 * N3 + c;
-  const EvenOdd<T, NG> D{a.eo};
+  const LineD<T, NG> D{a.dtab};
 
   // the line's nodes, u and material; the element's geometry
   T uc[NC][NG], lam[NG], mu[NC == 3 ? NG : 1];
@@ -395,7 +428,7 @@ hipError_t launch_line_n(int geo, bool aff, const LineArgs<T>& a, hipStream_t s)
 // MAXN: largest NGLL of the instantiation
 template <class T, int NC, int MAXN>
 hipError_t launch_line_any(int n, int geo, int64_t naff, const LineArgs<T>& a, hipStream_t s) {
-  if (!a.part || !a.eo) return hipErrorInvalidValue;
+  if (!a.part || !a.dtab) return hipErrorInvalidValue;
   return split_affine(naff, a, [&](const LineArgs<T>& b, bool aff) -> hipError_t {
     switch (n) {
       case 2: return launch_line_n<T, 2, NC>(geo, aff, b, s);
@@ -424,7 +457,7 @@ hipError_t launch_line_f32(int n, int geo, int64_t naff, const ForceArgs& a, hip
   if (a.list) return hipErrorInvalidValue;
   return launch_line_any<float, NC, kLineMaxN>(
       n, geo, naff,
-      LineArgs<float>{a.ibool, a.aff, a.gam_pt, a.gam_el, a.tri, a.xi, a.mat, a.u, a.eo, a.part, a.pos0, a.count,
+      LineArgs<float>{a.ibool, a.aff, a.gam_pt, a.gam_el, a.tri, a.xi, a.mat, a.u, a.dtab, a.part, a.pos0, a.count,
                       a.nspec, a.nglob, a.nmodels, a.aux},
       s);
 }

@@ -307,7 +307,7 @@ LineArgs<double> line_args64(const semx_ctx* c, const double* u) {
   a.gam_el = c->d_gam64_el.as<double>();
   a.mat = c->d_mat64.as<double>();
   a.u = u;
-  a.eo = c->d_eo64.as<double>();
+  a.dtab = c->d_dtab64.as<double>();
   a.part = c->d_part.as<double>();
   a.nspec = c->nspec;
   a.nglob = c->nglob;
@@ -398,12 +398,12 @@ int f64_model_setup(semx_ctx* c, const double* lam_dev, const double* mu_dev) {
   int rc = dev_alloc(c, c->d_mat64, sizeof(double) * 2 * npt);
   if (!rc) rc = dev_alloc(c, c->d_minv64, sizeof(double) * c->nmodels * c->nglob);
   if (!rc && c->d_D64.bytes != sizeof(double) * c->n * c->n) rc = dev_alloc(c, c->d_D64, sizeof(double) * c->n * c->n);
-  std::vector<double> eo;
-  even_odd(c->n, c->D, eo);
-  if (!rc) rc = dev_alloc(c, c->d_eo64, sizeof(double) * eo.size());
+  std::vector<double> tab;
+  line_table(c->n, c->D, tab);
+  if (!rc) rc = dev_alloc(c, c->d_dtab64, sizeof(double) * tab.size());
   if (!rc) rc = dev_alloc(c, c->d_gam64_el, sizeof(double) * 9 * c->nspec);
   if (rc) return rc;
-  SEMX_HIP(c, hipMemcpy(c->d_eo64.p, eo.data(), sizeof(double) * eo.size(), hipMemcpyHostToDevice));
+  SEMX_HIP(c, hipMemcpy(c->d_dtab64.p, tab.data(), sizeof(double) * tab.size(), hipMemcpyHostToDevice));
   int* flag = scratch_flags(c);
   SEMX_HIP(c, hipMemsetAsync(flag, 0, sizeof(int), c->stream));
   gam_el64_kernel<<<grid_1d(c->nspec * 64, 4096), kT, 0, c->stream>>>(

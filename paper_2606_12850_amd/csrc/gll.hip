@@ -93,15 +93,14 @@ void deriv_matrix(int n, const std::vector<double>& xi, std::vector<double>& D) 
   }
 }
 
-// Even-odd form of D (force_line.hpp): A, B, middle column, middle row.
-void even_odd(int n, const std::vector<double>& D, std::vector<double>& t) {
+// Tables of D for a line of points (force_line.hpp).
+void line_table(int n, const std::vector<double>& D, std::vector<double>& t) {
   const int h = n / 2, m = n - 1;
-  t.clear();
+  t.assign(D.begin(), D.begin() + h * n);
+  for (int j = 0; j < h; ++j) t.push_back(D[h * n + j]);
   for (int sgn = -1; sgn <= 1; sgn += 2)
     for (int i = 0; i < h; ++i)
       for (int j = 0; j < h; ++j) t.push_back(0.5 * (D[i * n + j] + sgn * D[i * n + m - j]));
-  for (int i = 0; i < h; ++i) t.push_back(D[i * n + h]);
-  for (int j = 0; j < h; ++j) t.push_back(D[h * n + j]);
 }
 
 }  // namespace semx

@@ -112,7 +112,7 @@ struct semx_ctx {
   // GLL data (library's own, FP64 on host)
   std::vector<double> xi, w, D;  // D[a*n+b] = l'_b(xi_a)
   semx::DevBuf d_D;              // float [n][n]
-  semx::DevBuf d_eo;             // float, even-odd form of D (force_line.hpp)
+  semx::DevBuf d_dtab;             // float, tables of D for a line of points (force_line.hpp)
   semx::DevBuf d_Dh;             // packed half/bfloat D tables for the MFMA paths
   semx::DevBuf d_xi64, d_w64;    // double [n]
 
@@ -214,7 +214,7 @@ struct semx_ctx {
   // by launch position, M^{-1} [nmodels][nglob], D [n][n] and its even-odd
   // form; Gamma of the first point of each element [nspec][9], which holds for
   // all points of the regular elements when affine64 is set
-  semx::DevBuf d_gam64, d_mat64, d_minv64, d_D64, d_eo64, d_gam64_el;
+  semx::DevBuf d_gam64, d_mat64, d_minv64, d_D64, d_dtab64, d_gam64_el;
   bool affine64 = false;
 
   // time loop state, [nmodels][nglob][3], float or double by `storage`
@@ -281,7 +281,7 @@ void dev_free(DevBuf& b);
 // ---- GLL basis (host, FP64) ---------------------------------------------
 void gll_nodes_weights(int n, std::vector<double>& xi, std::vector<double>& w);
 void deriv_matrix(int n, const std::vector<double>& xi, std::vector<double>& D);
-void even_odd(int n, const std::vector<double>& D, std::vector<double>& t);
+void line_table(int n, const std::vector<double>& D, std::vector<double>& t);
 void lagrange_at(int n, const std::vector<double>& xi, double x, double* l);
 
 // ---- launchers (force_f32.hip, force_mfma.hip) -----------------------------
@@ -297,7 +297,7 @@ struct ForceArgs {
   const float* u;        // [nmodels][nglob][3]
   float* f;              // [nmodels][nglob][3]
   const float* D;        // [n][n] FP32
-  const float* eo;       // even-odd form of D (force_line.hpp)
+  const float* dtab;     // tables of D for a line of points (force_line.hpp)
   const void* Dh;        // packed low-precision D tables (MFMA paths)
   const uint32_t* first; // coloured per-element paths: per-position bitmask of the points that
                          // reach their node first in launch order (store, no read), or null
@@ -340,7 +340,7 @@ constexpr int kBlockMaxN = 5;  // eight elements of n^3 points in one 1024-lane 
 template <class T>
 struct LineArgs {
   const int32_t *ibool, *aff;
-  const T *gam_pt, *gam_el, *tri, *xi, *mat, *u, *eo;
+  const T *gam_pt, *gam_el, *tri, *xi, *mat, *u, *dtab;
   T* part;
   int64_t pos0, count, nspec, nglob;
   int nmodels;
