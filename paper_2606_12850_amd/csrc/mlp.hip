@@ -31,7 +31,8 @@ struct semx_mlp {
   int64_t nparam = 0;
   std::vector<int64_t> woff, boff;
   semx::DevBuf theta, theta_bf, grad, m, v;
-  std::vector<semx::DevBuf> Z, H;  // Z[l] [B][w[l+1]] FP32, H[l] (l >= 1) [B][w[l]] BF16 (only ever a GEMM operand)
+  std::vector<semx::DevBuf> Z, H;  // Z[l] [B][w[l+1]], H[l] (l >= 1) [B][w[l]], both FP32
+  semx::DevBuf Hb[2];              // BF16 copies of a layer's H: the next product's operand, layers in turn
   semx::DevBuf g0, g1;             // backward work [B][max width]
   semx::DevBuf scratch;
   semx::DevBuf splitk;             // split-K partial sums
@@ -210,8 +211,8 @@ __device__ __forceinline__ float silu_grad(float z) {
 // What a GEMM does with its sums.
 constexpr int kPlain = 0;     // C = sum; split-K slices store their partial sums
 constexpr int kBias = 1;      // C = sum + bias[n]
-constexpr int kSiluKeep = 2;  // C = sum + bias[n] (the pre-activation), Hb = SiLU(C) in BF16
-constexpr int kSilu = 3;      // Hb = SiLU(sum + bias[n]) in BF16 (inference: the pre-activation is not kept)
+constexpr int kSiluKeep = 2;  // C = sum + bias[n] (the pre-activation), H = SiLU(C), Hb the same in BF16 (the next product's operand)
+constexpr int kSilu = 3;      // H = SiLU(sum + bias[n]) (inference: the pre-activation is not kept)
 constexpr int kGradZ = 4;     // C = sum * SiLU'(Z[m][n]); split-K as kPlain (the reduction applies Z)
 constexpr int kBiasStream = 6;  // kBias, the output past the caches
 constexpr int kGradW = 5;     // C = sum; db[m] = sum of A over k
@@ -240,6 +241,7 @@ __global__ __launch_bounds__(256, WT == 2 ? 4 : 2) void gemm_kernel(int M, int N
                                                                     const TB* __restrict__ B, int64_t sbk, int64_t sbn,
                                                                     float* __restrict__ C, int64_t ldc,
                                                                     const float* __restrict__ bias,
+                                                                    float* __restrict__ H,
                                                                     __bf16* __restrict__ Hb,
                                                                     const float* __restrict__ Z,
                                                                     float* __restrict__ db, int outv) {
@@ -426,10 +428,12 @@ __global__ __launch_bounds__(256, WT == 2 ? 4 : 2) void gemm_kernel(int M, int N
         if constexpr (EPI == kBiasStream) __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(Cz + o));
         else if constexpr (EPI != kSilu) *reinterpret_cast<f32x4*>(Cz + o) = v;
         if constexpr (EPI == kSiluKeep || EPI == kSilu) {
-          bf16x4 h;
+          f32x4 h;
 #pragma unroll
-          for (int r = 0; r < 4; ++r) h[r] = (__bf16)silu(v[r]);
-          *reinterpret_cast<bf16x4*>(Hb + o) = h;
+          for (int r = 0; r < 4; ++r) h[r] = silu(v[r]);
+          *reinterpret_cast<f32x4*>(H + o) = h;
+          if constexpr (EPI == kSiluKeep)
+            if (Hb) *reinterpret_cast<bf16x4*>(Hb + o) = bf16x4{(__bf16)h[0], (__bf16)h[1], (__bf16)h[2], (__bf16)h[3]};
         }
       } else {
 #pragma unroll
@@ -438,7 +442,8 @@ __global__ __launch_bounds__(256, WT == 2 ? 4 : 2) void gemm_kernel(int M, int N
           float x = v[r];
           if (EPI == kGradZ && !split) x *= silu_grad(Z[o + r]);
           if (EPI != kSilu) Cz[o + r] = x;
-          if (EPI == kSiluKeep || EPI == kSilu) Hb[o + r] = (__bf16)silu(x);
+          if (EPI == kSiluKeep || EPI == kSilu) H[o + r] = silu(x);
+          if (EPI == kSiluKeep && Hb) Hb[o + r] = (__bf16)silu(x);
         }
       }
     }
@@ -477,6 +482,7 @@ struct GemmOut {
   float* C = nullptr;
   int64_t ldc = 0;
   const float* bias = nullptr;
+  float* H = nullptr;
   __bf16* Hb = nullptr;
   const float* Z = nullptr;
   float* db = nullptr;
@@ -507,9 +513,9 @@ hipError_t gemm_launch(hipStream_t s, int M, int N, int K, const TA* A, int64_t 
   float* C = nz > 1 ? O.ws : O.C;
   // outputs in fours along n
   const int outv = (nz > 1 ? N : O.ldc) % 4 == 0 && N % 4 == 0 && reinterpret_cast<uintptr_t>(C) % 16 == 0 &&
-                   reinterpret_cast<uintptr_t>(O.Hb) % 8 == 0 && reinterpret_cast<uintptr_t>(O.Z) % 16 == 0;
+                   reinterpret_cast<uintptr_t>(O.H) % 16 == 0 && reinterpret_cast<uintptr_t>(O.Hb) % 8 == 0 && reinterpret_cast<uintptr_t>(O.Z) % 16 == 0;
   auto go = [&](auto kernel) {
-    kernel<<<grid, block, 0, s>>>(M, N, K, kchunk, A, sam, sak, B, sbk, sbn, C, O.ldc, O.bias, O.Hb, O.Z, O.db, outv);
+    kernel<<<grid, block, 0, s>>>(M, N, K, kchunk, A, sam, sak, B, sbk, sbn, C, O.ldc, O.bias, O.H, O.Hb, O.Z, O.db, outv);
   };
   if (wide) go(gemm_kernel<TA, TB, EPI, AKC, BKC, 4, true>);
   else if (vec) go(gemm_kernel<TA, TB, EPI, AKC, BKC, 2, true>);
@@ -629,23 +635,29 @@ __global__ void to_bf16_kernel(int64_t n, const float* __restrict__ x, __bf16* _
     y[i] = (__bf16)x[i];
 }
 
-// Layer l of the forward pass: A(m,k) = h[m*in + k] (the input x at l = 0, BF16
-// activations after it), B(k,n) = W[n*in + k].
-template <int EPI>
-hipError_t layer(semx_mlp* p, int l, int batch, const float* x, const __bf16* h, GemmOut& O) {
+// Layer l of the forward pass: A(m,k) = h[m*in + k] (FP32, rounded to BF16 on its
+// way into LDS, or already BF16), B(k,n) = W[n*in + k].
+template <int EPI, class TA>
+hipError_t layer(semx_mlp* p, int l, int batch, const TA* h, GemmOut& O) {
   const int in = p->w[l], out = p->w[l + 1];
   const __bf16* W = p->theta_bf.as<__bf16>() + p->woff[l];
   O.ldc = out;
   O.bias = p->theta.as<float>() + p->boff[l];
-  return l == 0 ? gemm_launch<float, __bf16, EPI, true, true>(p->stream, batch, out, in, x, in, 1, W, 1, in, O)
-                : gemm_launch<__bf16, __bf16, EPI, true, true>(p->stream, batch, out, in, h, in, 1, W, 1, in, O);
+  return gemm_launch<TA, __bf16, EPI, true, true>(p->stream, batch, out, in, h, in, 1, W, 1, in, O);
 }
+
+// Whether the product after a hidden layer of this width reads its BF16 copy: half
+// the bytes where whole rows of it are 16-byte aligned (512 wide, 4096 x 24576
+// outputs: 185 us against 202), else the FP32 activations load faster (516 wide:
+// 1000 us against 1365).
+bool bf16_rows(int width) { return width % 8 == 0; }
 
 // The network's output, past the caches where they would not hold it until its
 // reader comes.
-hipError_t output_layer(semx_mlp* p, int l, int batch, const float* x, const __bf16* h, GemmOut& O) {
-  return (int64_t)batch * p->w[l + 1] * 4 >= (int64_t(64) << 20) ? layer<kBiasStream>(p, l, batch, x, h, O)
-                                                                  : layer<kBias>(p, l, batch, x, h, O);
+template <class TA>
+hipError_t output_layer(semx_mlp* p, int l, int batch, const TA* h, GemmOut& O) {
+  return (int64_t)batch * p->w[l + 1] * 4 >= (int64_t(64) << 20) ? layer<kBiasStream>(p, l, batch, h, O)
+                                                                  : layer<kBias>(p, l, batch, h, O);
 }
 
 unsigned g1(int64_t n) {
@@ -785,8 +797,11 @@ int semx_mlp_create(semx_mlp** out, int nlayers, const int* widths, int max_batc
   p->H.resize(nlayers + 1);
   for (int l = 0; l < nlayers && !rc; ++l) {
     rc = malloc_buf(p, p->Z[l], sizeof(float) * max_batch * p->w[l + 1]);
-    if (!rc && l + 1 < nlayers) rc = malloc_buf(p, p->H[l + 1], sizeof(__bf16) * max_batch * p->w[l + 1]);
+    if (!rc && l + 1 < nlayers) rc = malloc_buf(p, p->H[l + 1], sizeof(float) * max_batch * p->w[l + 1]);
   }
+  int widest = 0;  // hidden layer
+  for (int l = 1; l < nlayers; ++l) widest = std::max(widest, p->w[l]);
+  for (int k = 0; k < 2 && k + 1 < nlayers && !rc; ++k) rc = malloc_buf(p, p->Hb[k], sizeof(__bf16) * max_batch * widest);
   if (rc) {
     semx_mlp_destroy(p);
     return rc;
@@ -808,7 +823,8 @@ int semx_mlp_create(semx_mlp** out, int nlayers, const int* widths, int max_batc
 int semx_mlp_destroy(semx_mlp* p) {
   if (!p) return SEMX_OK;
   (void)hipStreamSynchronize(p->stream);
-  for (DevBuf* b : {&p->theta, &p->theta_bf, &p->grad, &p->m, &p->v, &p->g0, &p->g1, &p->scratch, &p->splitk})
+  for (DevBuf* b : {&p->theta, &p->theta_bf, &p->grad, &p->m, &p->v, &p->g0, &p->g1, &p->scratch, &p->splitk,
+                    &p->Hb[0], &p->Hb[1]})
     dev_free(*b);
   if (p->stage) (void)hipHostFree(p->stage);
   for (hipEvent_t ev : p->staged)
@@ -854,9 +870,18 @@ int semx_mlp_forward(semx_mlp* p, const float* x_dev, int batch, float* y_dev) {
     const bool last = l + 1 == p->nl;
     GemmOut O;
     O.C = last ? y_dev : p->Z[l].as<float>();
-    if (!last) O.Hb = p->H[l + 1].as<__bf16>();
-    const __bf16* h = l > 0 ? p->H[l].as<__bf16>() : nullptr;
-    const hipError_t e = last ? output_layer(p, l, batch, x_dev, h, O) : layer<kSiluKeep>(p, l, batch, x_dev, h, O);
+    if (!last) {
+      O.H = p->H[l + 1].as<float>();
+      if (bf16_rows(p->w[l + 1])) O.Hb = p->Hb[l & 1].as<__bf16>();
+    }
+    hipError_t e;
+    if (l > 0 && bf16_rows(p->w[l])) {
+      const __bf16* h = p->Hb[(l + 1) & 1].as<__bf16>();  // the layer before wrote it
+      e = last ? output_layer(p, l, batch, h, O) : layer<kSiluKeep>(p, l, batch, h, O);
+    } else {
+      const float* h = l > 0 ? p->H[l].as<float>() : x_dev;
+      e = last ? output_layer(p, l, batch, h, O) : layer<kSiluKeep>(p, l, batch, h, O);
+    }
     if (e != hipSuccess) return mhip(p, e, "mlp forward gemm");
   }
   // the output layer's pre-activation is y itself; keep a copy for backward bookkeeping
@@ -876,15 +901,15 @@ int semx_mlp_forward_noalloc(semx_mlp* p, const float* x_dev, int batch, float* 
   float* ws = (p->device >= 0 && p->device < kMaxDevices) ? g_scratch_dev[p->device] : nullptr;
   if (!ws) return mfail(p, SEMX_ESTATE, "forward_noalloc: workspace address not resolved on this device");
   float* buf[2] = {ws, ws + kNoAllocFloats / 2};
-  const __bf16* h = nullptr;
+  const float* h = x_dev;
   for (int l = 0; l < p->nl; ++l) {
     const bool last = l + 1 == p->nl;
     GemmOut O;
     O.C = y_dev;
-    O.Hb = reinterpret_cast<__bf16*>(buf[l & 1]);
-    const hipError_t e = last ? output_layer(p, l, batch, x_dev, h, O) : layer<kSilu>(p, l, batch, x_dev, h, O);
+    O.H = buf[l & 1];
+    const hipError_t e = last ? output_layer(p, l, batch, h, O) : layer<kSilu>(p, l, batch, h, O);
     if (e != hipSuccess) return mhip(p, e, "mlp forward_noalloc gemm");
-    h = O.Hb;
+    h = O.H;
   }
   return SEMX_OK;
 }
@@ -906,10 +931,8 @@ int semx_mlp_backward(semx_mlp* p, const float* dy_dev, int batch) {
     O.ldc = in;
     O.db = gr + p->boff[l];
     O.ws = p->splitk.as<float>();
-    hipError_t e = l == 0 ? gemm_launch<float, float, kGradW, false, false>(p->stream, out, in, batch, g, 1, out,
-                                                                            p->x_saved, in, 1, O)
-                          : gemm_launch<float, __bf16, kGradW, false, false>(p->stream, out, in, batch, g, 1, out,
-                                                                             p->H[l].as<__bf16>(), in, 1, O);
+    const float* h = l == 0 ? p->x_saved : p->H[l].as<float>();
+    hipError_t e = gemm_launch<float, float, kGradW, false, false>(p->stream, out, in, batch, g, 1, out, h, in, 1, O);
     if (e != hipSuccess) return mhip(p, e, "mlp wgrad gemm");
     if (l == 0) break;
     // dL/dZ = (G W) SiLU'(Z) : C[b][k_in] = sum_o G[b][o] W[o][k_in]
