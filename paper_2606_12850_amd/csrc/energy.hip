@@ -11,11 +11,12 @@
 //    half-step velocity, f_pe the force f^n = -K u^n + f_src^n), one pass
 //    sums v^T M v and u^{n+1} . f_pe in fixed-size blocks, reduced in a fixed
 //    order (deterministic);
-//  * energy_source_step(): every step, one workgroup over the source points
-//    adds 1/2 (u^{n+1} - u^{n-1}) . f_src^n to the running source work and,
-//    on tracked steps, sums u^{n+1} . f_src^n (the source part of f^n, which
-//    the potential term must not see); it keeps u at the source points of
-//    the last two steps.
+//  * every step, one wave of the force launch (aux.hpp), or one block of
+//    step_aux_kernel where the force pass carries no such waves, goes over the
+//    source points: it adds 1/2 (u^{n+1} - u^{n-1}) . f_src^n to the running
+//    source work and, on tracked steps, sums u^{n+1} . f_src^n (the source part
+//    of f^n, which the potential term must not see); it keeps u at the source
+//    points of the last two steps.
 // acc (double[8]): 0 sum M v^2, 1 sum u . f_pe, 2 sum u . f_src, 3 running
 // source work.  The caller's state and kernels are not touched.
 #include <algorithm>
@@ -78,9 +79,69 @@ __global__ void energy_reduce_kernel(int nblk, const double* __restrict__ part, 
   }
 }
 
+// The bookkeeping of a step in a launch of its own: a block per receiver and one
+// for the source work, whose 256 lanes take what a single wave of aux.hpp takes
+// in four parts (the same sums in the same order).  At NGLL 16 (4096 points) the
+// waves' launch took 25 us more than this one.
 template <class T>
 __global__ __launch_bounds__(kT) void step_aux_kernel(AuxArgs<T> A) {
-  (void)run_aux(A);
+  __shared__ double red[kT];
+  __shared__ T rred[3][kT];
+  const int unit = blockIdx.x, model = blockIdx.y, lane = threadIdx.x;
+  if (unit < A.nrec) {  // uniform over the block, as are all branches here
+    const int64_t it = A.step ? *A.step : A.it;
+    if (it < 0 || it >= A.nt_max) return;
+    const T* um = A.u + (int64_t)model * A.nglob * A.nc;
+    const int32_t* nodes = A.rnodes + (int64_t)unit * A.n3;
+    const T* wts = A.rwts + (int64_t)unit * A.n3;
+    T s[3] = {0, 0, 0};
+#pragma unroll 4
+    for (int q = lane; q < A.n3; q += kT) {
+      const T w = wts[q];
+      const int64_t g = nodes[q];
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        if (c < A.nc) s[c] += w * um[A.nc * g + c];
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) rred[c][lane] = s[c];
+    __syncthreads();
+    for (int st = kT / 2; st > 0; st >>= 1) {
+      if (lane < st)
+        for (int c = 0; c < A.nc; ++c) rred[c][lane] += rred[c][lane + st];
+      __syncthreads();
+    }
+    if (lane < A.nc) A.seis[(((int64_t)model * A.nrec + unit) * A.nc + lane) * A.nt_max + it] = rred[lane][0];
+    return;
+  }
+  if (model != 0) return;
+  const int rest = unit - A.nrec;
+  if (!A.energy || rest > 0) {
+    aux_source(A, (int64_t)(rest - A.energy) * kT + lane);
+    return;
+  }
+  const int64_t n = A.step ? *A.step : A.it;
+  T* slot = A.hist + (size_t)((n + 1) & 1) * A.per;
+  const bool live = n >= 0 && n < A.nstf;
+  double work = 0.0, corr = 0.0;
+  for (int k = lane; k < A.npt; k += kT) {
+    const int p = A.pts[k];
+    const int64_t g = (int64_t)A.snodes[p] * A.nc;
+    const T amp = live ? A.stf[(int64_t)(p / A.n3) * A.nstf + n] : (T)0;
+    for (int c = 0; c < A.nc; ++c) {
+      const T un = A.u[g + c], old = slot[(int64_t)A.nc * k + c];
+      const double fs = (double)amp * (double)A.wdir[(int64_t)A.nc * p + c];
+      work += 0.5 * ((double)un - (double)old) * fs;
+      corr += (double)un * fs;
+      slot[(int64_t)A.nc * k + c] = un;
+    }
+  }
+  work = block_sum(work, red);
+  corr = block_sum(corr, red);
+  if (lane == 0) {
+    if (n > A.it0) A.acc[3] += work;
+    if (A.with_corr) A.acc[2] = corr;
+  }
 }
 
 // u at the source points (model 0) into hist (at a reset or a new state).
@@ -176,7 +237,7 @@ AuxArgs<T> aux_args_t(semx_ctx* c, int64_t n, bool with_corr, bool record, const
 template <class T>
 int launch_aux(semx_ctx* c, AuxArgs<T> A) {
   if (A.units == 0) return SEMX_OK;
-  A.blocks = (int)aux_blocks(A, kT, 1);
+  A.blocks = A.nrec + A.energy + (int)(((int64_t)c->nmodels * A.nsn * c->ncomp + kT - 1) / kT);
   step_aux_kernel<T><<<dim3((unsigned)A.blocks, A.nrec > 0 ? (unsigned)c->nmodels : 1u), kT, 0, c->stream>>>(A);
   SEMX_HIP(c, hipGetLastError());
   return SEMX_OK;
