@@ -785,7 +785,7 @@ int semx_adjoint(semx_ctx* c, const float* gseis_dev, int64_t nt, double* g_lamb
     A.fa.part = c->d_part.as<float>();
   } else if (!atomic) {
     rc = build_colored(c);
-    A.fa.list = c->d_clist.as<int32_t>();
+    A.fa.list = colour_list(c);
   }
   if (rc) { cleanup(); return rc; }
   const RecNodes R{c->rec.rbits.as<uint32_t>(), c->rec.rnode.as<int32_t>(), c->rec.rptr.as<int32_t>(),

@@ -650,8 +650,12 @@ int build_blocks(semx_ctx* c, const std::vector<int32_t>& pos_of, const std::vec
 // positions sorted by (geometry kind, affine numbering first, element), so
 // that a launch over one kind streams one contiguous range and elements that
 // share nodes run close together.  A pass colour by colour takes its elements
-// from a list of positions.  Then the node tables, and the FP64 geometry
-// kernel fills Gamma and W det J in that order.
+// from a list of positions, and so does atomic assembly, whose concurrent
+// elements had better not share nodes.  With a colouring of the caller's every
+// pass runs colour by colour: positions are sorted by (kind, colour, affine
+// numbering first), and the launches stream contiguous ranges (from lists they
+// took 2-4 % more).  Then the node tables, and the FP64 geometry kernel fills
+// Gamma and W det J in that order.
 int build_layout(semx_ctx* c) {
   const int n3 = c->n3;
   const int64_t nspec = c->nspec;
@@ -677,22 +681,43 @@ int build_layout(semx_ctx* c) {
     aff[e] = ok ? std::array<int32_t, 4>{(int32_t)g0, (int32_t)sx, (int32_t)sy, (int32_t)sz}
                 : std::array<int32_t, 4>{-1, 0, 0, 0};
   }
-  std::vector<int32_t> order;
-  order.reserve(nspec);
+  const int ncol = std::max(c->ncolors, 1);
+  std::vector<int32_t> seq(nspec), color(nspec, 0);
+  for (int64_t e = 0; e < nspec; ++e) seq[e] = (int32_t)e;
+  for (int k = 0; k < c->ncolors; ++k)
+    for (int32_t t = c->color_ptr[k]; t < c->color_ptr[k + 1]; ++t) color[c->elem_order[t]] = k;
+  auto irregular = [&](int32_t e) { return c->h_regular[e] == 0 ? 1 : 0; };
+  auto scattered = [&](int32_t e) { return aff[e][0] >= 0 ? 0 : 1; };
+  // seq sorted by a key in [0, keys), equal keys in their order
+  auto sort_by = [&](const std::vector<int32_t>& in, int keys, auto key) {
+    std::vector<int64_t> at(keys + 1, 0);
+    for (int32_t e : in) at[key(e) + 1]++;
+    for (int k = 0; k < keys; ++k) at[k + 1] += at[k];
+    std::vector<int32_t> out(in.size());
+    for (int32_t e : in) out[at[key(e)]++] = e;
+    return out;
+  };
+  const std::vector<int32_t> order =
+      c->user_colors ? sort_by(c->elem_order, 4 * ncol,
+                               [&](int32_t e) { return (irregular(e) * ncol + color[e]) * 2 + scattered(e); })
+                     : sort_by(seq, 4, [&](int32_t e) { return irregular(e) * 2 + scattered(e); });
   c->kind_launches.clear();
-  for (int irr = 0; irr < 2; ++irr) {
-    const int64_t beg = (int64_t)order.size();
+  for (int64_t beg = 0, end = 0; beg < nspec; beg = end) {
+    const int irr = irregular(order[beg]);
     int64_t naff = 0;
-    for (int affine = 1; affine >= 0; --affine) {
-      for (int64_t e = 0; e < nspec; ++e)
-        if ((c->h_regular[e] == 0) == (irr == 1) && (aff[e][0] >= 0) == (affine == 1)) order.push_back((int32_t)e);
-      if (affine) naff = (int64_t)order.size() - beg;
-    }
-    if ((int64_t)order.size() > beg) c->kind_launches.push_back({beg, (int64_t)order.size() - beg, irr == 1, naff});
+    for (end = beg; end < nspec && irregular(order[end]) == irr; ++end)
+      if (!scattered(order[end]) && naff == end - beg) ++naff;
+    c->kind_launches.push_back({beg, end - beg, irr == 1, naff});
   }
   c->h_order = order;
   std::vector<int32_t> pos_of(nspec);
   for (int64_t pos = 0; pos < nspec; ++pos) pos_of[order[pos]] = (int32_t)pos;
+  // the launches over a kind, colour after colour, for atomic assembly
+  std::vector<int32_t> alist;
+  if (c->ncolors > 0 && !c->user_colors) {
+    alist = sort_by(seq, 4 * ncol, [&](int32_t e) { return (irregular(e) * 2 + scattered(e)) * ncol + color[e]; });
+    for (int32_t& e : alist) e = pos_of[e];
+  }
   // colour by colour: regular before irregular, affine-numbered first
   c->h_clist.clear();
   c->colored_launches.clear();
@@ -710,7 +735,9 @@ int build_layout(semx_ctx* c) {
       auto mid = std::stable_partition(c->h_clist.begin() + beg, c->h_clist.end(),
                                        [&](int32_t pos) { return aff[order[pos]][0] >= 0; });
       const int64_t cnt = (int64_t)c->h_clist.size() - beg;
-      if (cnt) c->colored_launches.push_back({beg, cnt, irr == 1, mid - (c->h_clist.begin() + beg)});
+      if (cnt)
+        c->colored_launches.push_back({c->user_colors ? c->h_clist[beg] : beg, cnt, irr == 1,
+                                       mid - (c->h_clist.begin() + beg)});
     }
 
   std::vector<int32_t> ib((size_t)nspec * n3), affpos((size_t)nspec * 4);
@@ -751,6 +778,7 @@ int build_layout(semx_ctx* c) {
     c->one_point_nodes = c->elem_cover && nspec * n3 == c->nglob;
   }
   int rc = dev_alloc(c, c->d_order, sizeof(int32_t) * nspec);
+  if (!rc) rc = dev_alloc(c, c->d_alist, sizeof(int32_t) * alist.size());
   if (!rc) rc = dev_alloc(c, c->d_ibool, sizeof(int32_t) * nspec * n3);
   if (!rc) rc = dev_alloc(c, c->d_aff, sizeof(int32_t) * 4 * nspec);
   if (!rc) rc = dev_alloc(c, c->d_gam_el, sizeof(float) * 9 * nspec);
@@ -760,6 +788,8 @@ int build_layout(semx_ctx* c) {
   if (!rc && c->nirregular == 0) dev_free(c->d_gam_pt);
   if (rc) return rc;
   SEMX_HIP(c, hipMemcpy(c->d_order.p, order.data(), sizeof(int32_t) * nspec, hipMemcpyHostToDevice));
+  if (!alist.empty())
+    SEMX_HIP(c, hipMemcpy(c->d_alist.p, alist.data(), sizeof(int32_t) * alist.size(), hipMemcpyHostToDevice));
   SEMX_HIP(c, hipMemcpy(c->d_ibool.p, ib.data(), sizeof(int32_t) * nspec * n3, hipMemcpyHostToDevice));
   SEMX_HIP(c, hipMemcpy(c->d_aff.p, affpos.data(), sizeof(int32_t) * 4 * nspec, hipMemcpyHostToDevice));
   c->first_tl_dirty = true;
@@ -1038,7 +1068,8 @@ int force_accumulate(semx_ctx* c, const float* u, float* f, bool first_touch = f
     if (e1) SEMX_HIP(c, hipEventRecord(e1, c->stream));
     return SEMX_OK;
   }
-  if (colored) a.list = c->d_clist.as<int32_t>();
+  if (colored) a.list = colour_list(c);
+  if (atomic) a.list = c->d_alist.as<int32_t>();
   if (parts) a.part = c->d_part.as<float>();
   if (parts && aux) a.aux = *aux;
   const auto& launches = colored ? c->colored_launches : c->kind_launches;
@@ -1523,7 +1554,7 @@ int semx_destroy(semx_ctx* c) {
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
   c->cap_stream = nullptr;
   for (DevBuf* b : {&c->d_D, &c->d_dtab, &c->d_Dh, &c->d_xi64, &c->d_w64, &c->d_ibool, &c->d_vert, &c->d_elem_vert,
-                    &c->d_gam_pt, &c->d_gam_el, &c->d_tri, &c->d_xi32, &c->d_wdet, &c->d_order, &c->d_mat, &c->d_minv,
+                    &c->d_gam_pt, &c->d_gam_el, &c->d_tri, &c->d_xi32, &c->d_wdet, &c->d_order, &c->d_alist, &c->d_mat, &c->d_minv,
                     &c->d_mass64, &c->d_wrho, &c->d_u, &c->d_v, &c->d_a, &c->d_f, &c->d_work, &c->d_scratch,
                     &c->src.nodes, &c->src.wdir, &c->src.stf, &c->src.pts, &c->src.snode, &c->src.sptr,
                     &c->src.sidx, &c->rec.nodes, &c->rec.wts,
@@ -1916,7 +1947,7 @@ int semx_force_skeleton(semx_ctx* c, const float* u_dev, float* f_dev, int reps,
     if (rc) return rc;
   }
   ForceArgs a = force_args(c, u_dev, f_dev, force_overwrites(c));
-  if (colored) a.list = c->d_clist.as<int32_t>();
+  if (colored) a.list = colour_list(c);
   if (parts) a.part = c->d_part.as<float>();
   auto pass = [&]() -> hipError_t {
     if (blocks_active(c)) {

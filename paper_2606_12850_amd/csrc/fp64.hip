@@ -337,7 +337,7 @@ hipError_t launch_force64_n(const semx_ctx* c, const double* u, double* f, AuxAr
     aux.blocks = (int)aux_blocks(aux, (int)threads, kNumXcd);
     dim3 grid((unsigned)L.count + aux.blocks, (unsigned)c->nmodels);
     force64_kernel<NG><<<grid, threads, 0, c->stream>>>(
-        L.pos0, colored ? c->d_clist.as<int32_t>() : nullptr, c->nspec, c->nglob, atomic ? 1 : 0,
+        L.pos0, colored ? colour_list(c) : atomic ? c->d_alist.as<int32_t>() : nullptr, c->nspec, c->nglob, atomic ? 1 : 0,
         c->d_ibool.as<int32_t>(), c->d_gam64.as<double>(), c->d_mat64.as<double>(), c->d_D64.as<double>(), u, f,
         parts ? c->d_part.as<double>() : nullptr, aux);
     aux.units = 0;

@@ -264,7 +264,7 @@ void find_lattice(semx_ctx* c, const std::vector<std::array<int32_t, 4>>& aff) {
   c->lattice = Lattice{};
   const int N = c->n - 1;
   const int64_t nspec = c->nspec;
-  if (c->kind_launches.size() != 1 || c->ncolors == 0 || aff[0][0] != 0 || aff[0][1] != 1) return;
+  if (c->kind_launches.size() != 1 || c->ncolors == 0 || c->user_colors || aff[0][0] != 0 || aff[0][1] != 1) return;
   const int64_t Gx = aff[0][2], gy = aff[0][3];
   if (Gx < 2 || (Gx - 1) % N != 0 || gy % Gx != 0) return;
   const int64_t Gy = gy / Gx;

@@ -124,7 +124,8 @@ struct semx_ctx {
   std::vector<double> h_vert;
   // per-element device arrays are stored by launch position; h_order[pos] =
   // element, positions sorted by (geometry kind, affine numbering first,
-  // element): neighbours in the mesh are neighbours in memory
+  // element): neighbours in the mesh are neighbours in memory (a caller's
+  // colouring comes before the numbering)
   std::vector<int32_t> h_order;
   semx::DevBuf d_order;     // int32 [nspec]
   std::vector<float> h_gam_el;  // [nspec][9] per-element Gamma of regular elements (user order)
@@ -187,9 +188,12 @@ struct semx_ctx {
   // colouring
   int ncolors = 0;
   std::vector<int32_t> color_ptr, elem_order;
-  std::vector<semx::Launch> colored_launches;  // ranges of d_clist, per colour: regular then irregular
+  // per colour: regular then irregular; ranges of d_clist, or of positions
+  // with a colouring given by the caller
+  std::vector<semx::Launch> colored_launches;
   std::vector<int32_t> h_clist;                // launch positions, colour by colour
   semx::DevBuf d_clist;
+  semx::DevBuf d_alist;  // positions kind by kind, colour after colour: atomic assembly (a caller's colouring has none)
   // 2 x 2 x 2 element blocks (FP32 elastic force, NGLL <= 5, coloured):
   // built when every element is affine-numbered with common strides, of one
   // geometry kind, and belongs to a block; nblocks = 0 otherwise
@@ -410,6 +414,8 @@ bool prestores(const semx_ctx* c);
 int build_first_tl(semx_ctx* c);
 // Tables of a pass colour by colour on the device (no-op once built).
 int build_colored(semx_ctx* c);
+// The list that its launches index, or null: positions.
+inline const int32_t* colour_list(const semx_ctx* c) { return c->user_colors ? nullptr : c->d_clist.as<int32_t>(); }
 
 // gather.hip: node tables, and the sum of the element-local forces per node
 int build_node_points(semx_ctx* c);
