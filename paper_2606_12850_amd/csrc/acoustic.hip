@@ -48,18 +48,17 @@ __device__ __forceinline__ bool first_bit(const ForceArgs& a, int pos, int q) {
 // affine-numbered element (AFF) gathers, reads its prior force and stores
 // through buffers over its node span, the prior force as one unconditional
 // request issued after the flux.
-template <int NG, int GEO, bool ATOMIC, bool AFF>
-__global__ __launch_bounds__(Shape<NG>::BLK) void force_ac_kernel(ForceArgs a) {
+template <int NG, int GEO, bool ATOMIC, bool AFF, class X>
+__global__ __launch_bounds__(Shape<NG>::BLK) void force_ac_kernel(ForceArgs a, X aux) {
   constexpr int N3 = Shape<NG>::N3;
   constexpr int ND = NG * NG;
   __shared__ float s_p[N3];
   __shared__ float s_q[3 * N3];
   __shared__ float s_D[ND + NG];  // D (row-major), then the GLL nodes
 
-  if constexpr (!ATOMIC)
-    if (run_aux(a.aux)) return;  // uniform over the block
+  if (run_aux(aux)) return;  // uniform over the block
   const int ngrp = (int)a.count;
-  const int grp = xcd_group(ngrp, ATOMIC ? 0 : a.aux.blocks);
+  const int grp = xcd_group(ngrp, aux_lead(aux));
   if (grp >= ngrp) return;  // uniform over the block
   const int pos = elem_pos(a, grp);
 
@@ -295,10 +294,11 @@ template <int NG, int GEO, bool ATOMIC, bool AFF>
 hipError_t launch_ac(const ForceArgs& a, hipStream_t s) {
   const int64_t nb = ((a.count + kNumXcd - 1) / kNumXcd) * kNumXcd;
   if constexpr (NG <= kMaxNLow) {
-    ForceArgs b = a;
-    b.aux.blocks = (int)aux_blocks(a.aux, Shape<NG>::BLK, kNumXcd);
-    dim3 grid((unsigned)nb + b.aux.blocks, (unsigned)a.nmodels), block(Shape<NG>::BLK);
-    force_ac_kernel<NG, GEO, ATOMIC, AFF><<<grid, block, 0, s>>>(b);
+    auto go = [&](auto aux, unsigned lead) {
+      force_ac_kernel<NG, GEO, ATOMIC, AFF><<<dim3((unsigned)nb + lead, (unsigned)a.nmodels), Shape<NG>::BLK, 0, s>>>(a, aux);
+    };
+    if constexpr (ATOMIC) go(NoAux{}, 0u);
+    else with_aux(a.aux, Shape<NG>::BLK, kNumXcd, go);
   } else {
     dim3 grid((unsigned)nb, (unsigned)a.nmodels), block(AcColShape<NG>::BLK);
     force_ac_col_kernel<NG, GEO, ATOMIC><<<grid, block, 0, s>>>(a);

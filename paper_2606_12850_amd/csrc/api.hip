@@ -1071,7 +1071,7 @@ int force_accumulate(semx_ctx* c, const float* u, float* f, bool first_touch = f
   if (colored) a.list = colour_list(c);
   if (atomic) a.list = c->d_alist.as<int32_t>();
   if (parts) a.part = c->d_part.as<float>();
-  if (parts && aux) a.aux = *aux;
+  if (parts) a.aux = aux;
   const auto& launches = colored ? c->colored_launches : c->kind_launches;
   hipEvent_t e1 = nullptr;
   if (!launches.empty() && c->timing_stride > 0 && (c->timing_seq++ % c->timing_stride) == 0) {
@@ -1096,7 +1096,7 @@ int force_accumulate(semx_ctx* c, const float* u, float* f, bool first_touch = f
       case kPoint: e = launch_force_f32_split(c->n, geo, atomic, L.naff, a, c->stream); break;
       case kMixed: e = launch_force_mfma(c->n, c->contraction, geo, atomic, a, c->stream); break;
     }
-    a.aux.units = 0;  // rode in the first launch
+    a.aux = nullptr;  // rode in the first launch
     if (e != hipSuccess) return hip_fail(c, e, "force kernel launch");
   }
   if (parts && defer) {

@@ -41,6 +41,11 @@ struct AuxArgs {
   T* f;
 };
 
+// A launch that carries none of these waves: its kernel has neither their code
+// nor their arguments (with both in every kernel an apply of one element took
+// 0.1-0.5 us more, and each launch of a pass colour by colour as much).
+struct NoAux {};
+
 // Leading blocks of a launch with `threads` lanes a block; a multiple of the
 // XCD count, so that the blocks after them keep their XCDs.
 template <class T>
@@ -181,6 +186,27 @@ __device__ __forceinline__ bool run_aux(const AuxArgs<T>& A) {
     else aux_source(A, (int64_t)(rest - A.energy) * 64 + lane);
   }
   return true;
+}
+__device__ __forceinline__ bool run_aux(const NoAux&) { return false; }
+
+// Blocks that come before the launch's own.
+template <class T>
+__device__ __forceinline__ int aux_lead(const AuxArgs<T>& A) {
+  return A.blocks;
+}
+__device__ __forceinline__ int aux_lead(const NoAux&) { return 0; }
+
+// Calls launch(aux, lead): the waves `p` of a launch with `threads` lanes a block
+// and their leading blocks, or NoAux and 0.
+template <class T, class F>
+inline void with_aux(const AuxArgs<T>* p, int threads, int xcds, F launch) {
+  if (p && p->units > 0) {
+    AuxArgs<T> A = *p;
+    A.blocks = (int)aux_blocks(A, threads, xcds);
+    launch(A, (unsigned)A.blocks);
+  } else {
+    launch(NoAux{}, 0u);
+  }
 }
 
 }  // namespace semx

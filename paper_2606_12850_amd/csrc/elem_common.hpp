@@ -307,7 +307,7 @@ inline hipError_t split_affine(int64_t naff, const A& a, F launch) {
   b.count = naff;
   hipError_t e = naff > 0 ? launch(b, true) : hipSuccess;
   if (e != hipSuccess || naff == a.count) return e;
-  if (naff > 0) b.aux.units = 0;
+  if (naff > 0) b.aux = nullptr;
   b.pos0 = a.pos0 + naff;
   b.count = a.count - naff;
   return launch(b, false);

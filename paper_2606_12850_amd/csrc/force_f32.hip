@@ -38,18 +38,17 @@ namespace {
 // and the u gather.  The prior-force read depends only on the first-touch bit
 // (a scalar load) and is consumed at the very end, so its latency runs under
 // the transpose contractions.
-template <int NG, int GEO, bool ATOMIC, bool AFF>
-__global__ __launch_bounds__(Shape<NG>::BLK) void force_f32_kernel(ForceArgs a) {
+template <int NG, int GEO, bool ATOMIC, bool AFF, class X>
+__global__ __launch_bounds__(Shape<NG>::BLK) void force_f32_kernel(ForceArgs a, X aux) {
   constexpr int N3 = Shape<NG>::N3;
   constexpr int ND = NG * NG;
   __shared__ float s_u[3 * N3];
   __shared__ float s_q[9 * N3];
   __shared__ float s_D[ND + NG];  // D (row-major), then the GLL nodes
 
-  if constexpr (!ATOMIC)
-    if (run_aux(a.aux)) return;  // uniform over the block
+  if (run_aux(aux)) return;  // uniform over the block
   const int ngrp = (int)a.count;
-  const int grp = xcd_group(ngrp, ATOMIC ? 0 : a.aux.blocks);
+  const int grp = xcd_group(ngrp, aux_lead(aux));
   if (grp >= ngrp) return;  // uniform over the block
   const int pos = elem_pos(a, grp);
 
@@ -169,10 +168,11 @@ __global__ __launch_bounds__(Shape<NG>::BLK) void force_f32_kernel(ForceArgs a) 
 template <int NG, int GEO, bool ATOMIC, bool AFF>
 hipError_t launch_one(const ForceArgs& a, hipStream_t s) {
   const int64_t nb = ((a.count + kNumXcd - 1) / kNumXcd) * kNumXcd;
-  ForceArgs b = a;
-  b.aux.blocks = (int)aux_blocks(a.aux, Shape<NG>::BLK, kNumXcd);
-  dim3 grid((unsigned)nb + b.aux.blocks, (unsigned)a.nmodels), block(Shape<NG>::BLK);
-  force_f32_kernel<NG, GEO, ATOMIC, AFF><<<grid, block, 0, s>>>(b);
+  auto go = [&](auto aux, unsigned lead) {
+    force_f32_kernel<NG, GEO, ATOMIC, AFF><<<dim3((unsigned)nb + lead, (unsigned)a.nmodels), Shape<NG>::BLK, 0, s>>>(a, aux);
+  };
+  if constexpr (ATOMIC) go(NoAux{}, 0u);
+  else with_aux(a.aux, Shape<NG>::BLK, kNumXcd, go);
   return hipGetLastError();
 }
 

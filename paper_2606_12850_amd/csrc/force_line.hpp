@@ -238,16 +238,16 @@ __device__ __forceinline__ void scalar_flux(T d[3], const T Mg[9], T scale, T w)
   for (int q = 0; q < 3; ++q) d[q] = s * (g[0] * Mg[q * 3 + 0] + g[1] * Mg[q * 3 + 1] + g[2] * Mg[q * 3 + 2]);
 }
 
-template <class T, int NG, int NC, int GEO, bool AFF>
-__global__ __launch_bounds__((LineShape<T, NG>::BLK)) void force_line_kernel(LineArgs<T> a) {
+template <class T, int NG, int NC, int GEO, bool AFF, class X>
+__global__ __launch_bounds__((LineShape<T, NG>::BLK)) void force_line_kernel(LineArgs<T> a, X aux) {
   using S = LineShape<T, NG>;
   constexpr int N2 = S::N2, N3 = S::N3, P = S::P, EPW = S::EPW;
   constexpr int AS = EPW * S::ESZ;  // words of one field
   __shared__ T s[2 * NC * AS];
 
-  if (run_aux(a.aux)) return;  // uniform over the block
+  if (run_aux(aux)) return;  // uniform over the block
   const int ngrp = ((int)a.count + EPW - 1) / EPW;
-  const int grp = xcd_group(ngrp, a.aux.blocks);
+  const int grp = xcd_group(ngrp, aux_lead(aux));
   if (grp >= ngrp) return;  // uniform over the block
   // spare lanes repeat the last line (the same values to the same places),
   // spare elements of the last group the last element; neither stores a result
@@ -406,11 +406,12 @@ template <class T, int NG, int NC, int GEO>
 hipError_t launch_line(bool aff, const LineArgs<T>& a, hipStream_t s) {
   using S = LineShape<T, NG>;
   const int64_t ngrp = (a.count + S::EPW - 1) / S::EPW;
-  LineArgs<T> b = a;
-  b.aux.blocks = (int)aux_blocks(a.aux, S::BLK, kNumXcd);
-  const dim3 grid((unsigned)((ngrp + kNumXcd - 1) / kNumXcd * kNumXcd) + b.aux.blocks, (unsigned)a.nmodels);
-  if (aff) force_line_kernel<T, NG, NC, GEO, true><<<grid, S::BLK, 0, s>>>(b);
-  else force_line_kernel<T, NG, NC, GEO, false><<<grid, S::BLK, 0, s>>>(b);
+  const unsigned nb = (unsigned)((ngrp + kNumXcd - 1) / kNumXcd * kNumXcd);
+  with_aux(a.aux, S::BLK, kNumXcd, [&](auto aux, unsigned lead) {
+    const dim3 grid(nb + lead, (unsigned)a.nmodels);
+    if (aff) force_line_kernel<T, NG, NC, GEO, true><<<grid, S::BLK, 0, s>>>(a, aux);
+    else force_line_kernel<T, NG, NC, GEO, false><<<grid, S::BLK, 0, s>>>(a, aux);
+  });
   return hipGetLastError();
 }
 

@@ -23,17 +23,17 @@ namespace semx {
 namespace {
 
 constexpr int kT = 256;
-template <int NG>
+template <int NG, class X>
 __global__ void force64_kernel(int64_t pos0, const int32_t* __restrict__ list, int64_t nspec, int64_t nglob, int atomic,
                                const int32_t* __restrict__ ibool, const double* __restrict__ gam,
                                const double* __restrict__ mat, const double* __restrict__ Dg,
                                const double* __restrict__ u, double* __restrict__ f, double* __restrict__ part,
-                               AuxArgs<double> aux) {
+                               X aux) {
   if (run_aux(aux)) return;  // uniform over the block
   constexpr int n3 = NG * NG * NG;
   __shared__ double D[NG * NG];  // D[a * NG + b] = l'_b(xi_a)
   __shared__ double s[3][n3];
-  const int64_t slot = pos0 + (blockIdx.x - aux.blocks);
+  const int64_t slot = pos0 + ((int)blockIdx.x - aux_lead(aux));
   const int64_t pos = list ? list[slot] : slot;
   const int64_t model = blockIdx.y;
   const int q = threadIdx.x;
@@ -316,7 +316,7 @@ LineArgs<double> line_args64(const semx_ctx* c, const double* u) {
 }
 
 template <int NG>
-hipError_t launch_force64_n(const semx_ctx* c, const double* u, double* f, AuxArgs<double> aux) {
+hipError_t launch_force64_n(const semx_ctx* c, const double* u, double* f, const AuxArgs<double>* aux) {
   constexpr int n3 = NG * NG * NG;
   const unsigned threads = (unsigned)((n3 + 63) / 64 * 64);
   const bool atomic = c->assembly == SEMX_ASM_ATOMIC;
@@ -329,18 +329,18 @@ hipError_t launch_force64_n(const semx_ctx* c, const double* u, double* f, AuxAr
       a.pos0 = L.pos0;
       a.count = L.count;
       a.aux = aux;
-      aux.units = 0;
+      aux = nullptr;  // rides in the first launch
       const hipError_t e = launch_force_line64(NG, geo, L.naff, a, c->stream);
       if (e != hipSuccess) return e;
       continue;
     }
-    aux.blocks = (int)aux_blocks(aux, (int)threads, kNumXcd);
-    dim3 grid((unsigned)L.count + aux.blocks, (unsigned)c->nmodels);
-    force64_kernel<NG><<<grid, threads, 0, c->stream>>>(
-        L.pos0, colored ? colour_list(c) : atomic ? c->d_alist.as<int32_t>() : nullptr, c->nspec, c->nglob, atomic ? 1 : 0,
-        c->d_ibool.as<int32_t>(), c->d_gam64.as<double>(), c->d_mat64.as<double>(), c->d_D64.as<double>(), u, f,
-        parts ? c->d_part.as<double>() : nullptr, aux);
-    aux.units = 0;
+    const int32_t* list = colored ? colour_list(c) : atomic ? c->d_alist.as<int32_t>() : nullptr;
+    with_aux(aux, (int)threads, kNumXcd, [&](auto x, unsigned lead) {
+      force64_kernel<NG><<<dim3((unsigned)L.count + lead, (unsigned)c->nmodels), threads, 0, c->stream>>>(
+          L.pos0, list, c->nspec, c->nglob, atomic ? 1 : 0, c->d_ibool.as<int32_t>(), c->d_gam64.as<double>(),
+          c->d_mat64.as<double>(), c->d_D64.as<double>(), u, f, parts ? c->d_part.as<double>() : nullptr, x);
+    });
+    aux = nullptr;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -348,7 +348,7 @@ hipError_t launch_force64_n(const semx_ctx* c, const double* u, double* f, AuxAr
 }
 
 // aux: bookkeeping waves of the step that ride in the pass (element-local forces only)
-hipError_t launch_force64(const semx_ctx* c, const double* u, double* f, const AuxArgs<double>& aux = {}) {
+hipError_t launch_force64(const semx_ctx* c, const double* u, double* f, const AuxArgs<double>* aux = nullptr) {
   switch (c->n) {
     case 2: return launch_force64_n<2>(c, u, f, aux);
     case 3: return launch_force64_n<3>(c, u, f, aux);
@@ -525,7 +525,8 @@ int f64_step_once(semx_ctx* c, bool record) {
     const bool pre = prestores(c);
     if (pre) rc = build_first_tl(c);
     if (rc) return rc;
-    const hipError_t e = launch_force64(c, u, f, aux_args64(c, c->it, track && src_in_f, record, pre));
+    const AuxArgs<double> aux = aux_args64(c, c->it, track && src_in_f, record, pre);
+    const hipError_t e = launch_force64(c, u, f, &aux);
     if (e != hipSuccess) return hip_fail(c, e, "FP64 force kernel launch");
     c->f_in_part = true;
     c->part_src = pre;

@@ -313,7 +313,7 @@ struct ForceArgs {
   int64_t count;
   int64_t nspec, nglob;
   int nmodels;
-  AuxArgs<float> aux;    // bookkeeping waves that ride in the launch (part set)
+  const AuxArgs<float>* aux;  // bookkeeping waves that ride in the launch (part set; host pointer), or null
 };
 hipError_t launch_force_f32(int n, int geo, bool atomic, const ForceArgs& a, hipStream_t s);
 // The same over a launch whose first `naff` elements have an affine numbering:
@@ -348,7 +348,7 @@ struct LineArgs {
   T* part;
   int64_t pos0, count, nspec, nglob;
   int nmodels;
-  AuxArgs<T> aux;
+  const AuxArgs<T>* aux;  // host pointer or null
 };
 hipError_t launch_force_line64(int n, int geo, int64_t naff, const LineArgs<double>& a, hipStream_t s);
 hipError_t launch_force_line(int n, int geo, int64_t naff, const ForceArgs& a, hipStream_t s);
