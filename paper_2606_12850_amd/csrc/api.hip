@@ -1028,10 +1028,23 @@ bool carries_aux(const semx_ctx* c) {
 // one element point (elements that touch nowhere; a mesh of one).  The nodal
 // sum would be a second launch that only copies, some 2 us on applies of 7 to
 // 11 us.  The tables are there from the upload.  The line kernel has no such
-// form; it gives more than the launch costs.
+// form, so the kernel that it replaces runs; us per apply, that / line and sum:
+//   NGLL 2 up to 2^17 points: 1 element 3.9 / 7.7, 16384 6.5 / 7.5, 32768 9.8 / 7.4;
+//   NGLL 3-10 up to 2^22: NGLL 8, 512 elements 5.3 / 9.7, NGLL 5, 33600 elements
+//   42 / 51, NGLL 10, 4096 elements 69 / 63;
+//   NGLL 12 (tile) up to 2^20: 1 element 10.6 / 12.8, 512 21.8 / 23.4, 1024 40 / 39;
+//   the column kernels never: NGLL 11, 1 element 22 / 11.
 bool stores_direct(const semx_ctx* c) {
-  return parts_active(c) && c->one_point_nodes && c->d_clist.p && !c->kind_launches.empty() &&
-         kernel_for(c, true, c->kind_launches[0].irregular ? c->irregular_geo : kRegular) != kLine;
+  if (!parts_active(c) || !c->one_point_nodes || !c->d_clist.p) return false;
+  const int64_t points = (int64_t)c->nmodels * c->nspec * c->n3;
+  for (const auto& L : c->kind_launches) {
+    const int geo = L.irregular ? c->irregular_geo : kRegular;
+    if (kernel_for(c, true, geo) != kLine) continue;
+    const ForceKernel k = kernel_for(c, false, geo);
+    const bool column = k == kColumn || (k == kAcoustic && c->n > kMaxNLow);
+    if (column || points >= (c->n == 2 ? 1 << 17 : c->n > kMaxNLow ? 1 << 20 : 1 << 22)) return false;
+  }
+  return true;
 }
 
 // `tl`: the time loop's pass after the source force was stored into f
