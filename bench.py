@@ -39,7 +39,7 @@ NE, NGLL = 64, 5
 
 
 def bytes_per_element_model(n: int, nglob: int, nspec: int, geometry: str = "stored") -> float:
-    """The roofline's algorithmic HBM bytes per element per force apply, for the
+    """The byte model: algorithmic HBM bytes per element per force apply, for the
     formulation with a per-point inverse Jacobian: node numbers 4 n^3, Gamma and
     det J 10 s n^3 (10 s per element on affine elements), lambda and mu 2 s n^3,
     u read once and f written once per unique node 3 s G/E each (s = 4, FP32).
@@ -63,10 +63,17 @@ def bytes_per_element(n: int, nglob: int, nspec: int, geometry: str = "stored", 
     return nodes + geo + 8 * n3 + 2 * 12.0 * nglob / nspec
 
 
+def bytes_per_element_pass(n: int, nglob: int, nspec: int, geometry: str, affine: bool) -> float:
+    """The bytes that the element launch of a time step needs per element where
+    its nodal sum belongs to the Newmark pass: what bytes_per_element counts,
+    with the element-local forces (3*4 n^3) written in the place of f."""
+    return bytes_per_element(n, nglob, nspec, geometry, affine) + 12.0 * n ** 3 - 12.0 * nglob / nspec
+
+
 def traffic_from_profiles(src_hash: str, key: str = "trilinear"):
     """HBM bytes per launch measured with rocprofv3 PMC counters (`key`: the
-    force kernel's geometry path, or that path's skeleton with the suffix
-    `_skeleton`), if they were taken on the current force kernel source."""
+    geometry path, whose element launch is meant, or that path with the suffix
+    `_skeleton` or `_sum`), if they were taken on the current kernel sources."""
     p = os.path.join(ROOT, "profiles", "force_traffic.json")
     if not os.path.exists(p):
         return None
@@ -79,20 +86,23 @@ def traffic_from_profiles(src_hash: str, key: str = "trilinear"):
     return d.get(key, {}).get("bytes_per_launch")
 
 
+def kernel_source_hash() -> str:
+    src = b"".join(open(os.path.join(ROOT, "paper_2606_12850_amd", "csrc", f), "rb").read()
+                   for f in ("force_line.hpp", "force_line.hip", "elem_common.hpp", "nodal.hpp"))
+    return hashlib.sha256(src).hexdigest()
+
+
 def write_traffic(run_dir: str):
     """profiles/force_traffic.json from the FETCH_SIZE and WRITE_SIZE runs of
-    `bench.py --profile-force` (trilinear and stored): KiB per dispatch of the
-    NGLL 5 coloured force kernel and of its memory skeleton, each scaled by
-    what the same counter reads for the 1 GiB device copy that follows them."""
+    `bench.py --profile-force` (trilinear): KiB per dispatch of the NGLL 5 line
+    kernel, its memory skeleton and the nodal sum, each scaled by what the same
+    counter reads for the 1 GiB device copy that follows them."""
     import collections
     import csv
     copy_bytes = 1 << 30
-    src = b"".join(open(os.path.join(ROOT, "paper_2606_12850_amd", "csrc", f), "rb").read()
-                   for f in ("force_f32.hip", "elem_common.hpp"))
-    out = {"kernel_source_sha256": hashlib.sha256(src).hexdigest(), "unit": "bytes per launch",
-           "workload": "layered jittered cube 64^3, NGLL 5, colored (8 launches of 32768 elements), "
-                       "affine node numbering"}
-    for geo, gid in (("trilinear", 2), ("stored", 1)):
+    out = {"kernel_source_sha256": kernel_source_hash(), "unit": "bytes per launch",
+           "workload": "layered jittered cube 64^3, NGLL 5 (one launch of 262144 elements, one nodal sum)"}
+    for geo, gid in (("trilinear", 2),):
         d = {}
         for ctr in ("FETCH_SIZE", "WRITE_SIZE"):
             agg = collections.defaultdict(list)
@@ -102,8 +112,9 @@ def write_traffic(run_dir: str):
                     agg[r["Kernel_Name"]].append(float(r["Counter_Value"]))
             cp = [v for k, vs in agg.items() if "copyBuffer" in k for v in vs][-3:]
             scale = copy_bytes / (sum(cp) / len(cp) * 1024.0)
-            for tag, pat in (("kernel", f"force_f32_kernel<5, {gid}, false, true>"),
-                             ("skeleton", f"force_skeleton_kernel<5, {gid}, true>")):
+            for tag, pat in (("kernel", f"force_line_kernel<float, 5, 3, {gid}, true"),
+                             ("skeleton", f"force_line_skeleton_kernel<5, {gid}, true>"),
+                             ("sum", "gather_kernel<float, 3")):
                 kv = [v for k, vs in agg.items() if pat in k for v in vs]
                 if kv:
                     d.setdefault(tag, {})[ctr] = {
@@ -113,8 +124,9 @@ def write_traffic(run_dir: str):
         for tag in d:
             d[tag]["bytes_per_launch"] = sum(d[tag][c]["bytes_per_launch"] for c in ("FETCH_SIZE", "WRITE_SIZE"))
         out[geo] = d["kernel"]
-        if "skeleton" in d:
-            out[geo + "_skeleton"] = d["skeleton"]
+        for tag in ("skeleton", "sum"):
+            if tag in d:
+                out[f"{geo}_{tag}"] = d[tag]
     out["bytes_per_launch"] = out["trilinear"]["bytes_per_launch"]
     with open(os.path.join(ROOT, "profiles", "force_traffic.json"), "w") as fh:
         json.dump(out, fh, indent=1)
@@ -581,6 +593,16 @@ def order_sweep_leg(reps: int = 20, orders=None):
     return rows
 
 
+def launches_of_apply(s, u, f) -> int:
+    """Launches of one force apply as the library counts them."""
+    import paper_2606_12850_amd as P
+    P.semx_set_timing(s.ctx, 1)
+    P.semx_apply_force(s.ctx, u, f)
+    n, _ = P.semx_force_timing(s.ctx)
+    P.semx_set_timing(s.ctx, 0)
+    return n
+
+
 def single_order_apply(n: int, reps: int, mode: str = "f32"):
     """Coloured force applies (contraction `mode`: f32, bf16, f16) on the
     order-sweep mesh of one NGLL (regular hexahedra, about 2e7 unique
@@ -611,9 +633,9 @@ def single_order_apply(n: int, reps: int, mode: str = "f32"):
     e1.record(s.stream)
     e1.synchronize()
     ms = e0.elapsed_time(e1) / reps
+    launches = launches_of_apply(s, u, f)
     s.set_mode(P.SEMX_C_F32, P.SEMX_ASM_COLORED)
-    sk = P.semx_force_skeleton(s.ctx, u, f, reps)  # the memory skeleton of the same pass
-    info = P.semx_mesh_info(s.ctx)
+    sk = P.semx_force_skeleton(s.ctx, u, f, reps)  # the memory skeleton of the FP32 pass
     s.close()
     nbytes = 1 << 30
     a = torch.ones(nbytes // 4, device="cuda")
@@ -624,7 +646,7 @@ def single_order_apply(n: int, reps: int, mode: str = "f32"):
     bm = bytes_per_element_model(n, mesh.nglob, mesh.nspec, "regular")
     be = bytes_per_element(n, mesh.nglob, mesh.nspec, "regular", affine=n <= 10 or n == 16)
     return {"ngll": n, "mode": mode, "ne": ne, "nspec": mesh.nspec, "nglob": mesh.nglob, "ms_per_apply": round(ms, 4),
-            "launches_per_apply": info["ncolors"], "bytes_per_element": bm, "bytes_per_element_impl": be,
+            "launches_per_apply": launches, "bytes_per_element": bm, "bytes_per_element_impl": be,
             "hbm_frac": round(bm * mesh.nspec / (ms * 1e-3) / (HBM_PEAK_GBS * 1e9), 4),
             "hbm_frac_impl": round(be * mesh.nspec / (ms * 1e-3) / (HBM_PEAK_GBS * 1e9), 4),
             "skeleton_ms_per_apply": round(sk, 4), "frac_of_skeleton": round(sk / ms, 4),
@@ -865,7 +887,7 @@ def main():
     ap.add_argument("--no-surrogate", action="store_true",
                     help="skip the bounded surrogate leg (16^3 box at 10 Hz, reduced model counts)")
     ap.add_argument("--write-traffic", metavar="DIR",
-                    help="no GPU: read the four rocprofv3 --pmc runs of --profile-force (DIR/pmc_<geometry>_"
+                    help="no GPU: read the two rocprofv3 --pmc runs of --profile-force (DIR/pmc_<geometry>_"
                          "<counter>/run_counter_collection.csv) and write profiles/force_traffic.json")
     ap.add_argument("--write-acoustic-traffic", metavar="DIR",
                     help="no GPU: read the two rocprofv3 --pmc runs of --acoustic-only (DIR/pmc_ac_<counter>/"
@@ -930,7 +952,7 @@ def main():
     geo_of = (lambda g: g if info["nirregular"] > 0 else "regular")
     # the roofline's byte model (per-point inverse Jacobian) and what this path reads
     b_model = bytes_per_element_model(NGLL, mesh.nglob, E, geo_of(args.geometry))
-    b_elem = bytes_per_element(NGLL, mesh.nglob, E, geo_of(args.geometry), affine=args.assembly == "colored")
+    b_elem = bytes_per_element(NGLL, mesh.nglob, E, geo_of(args.geometry), affine=True)
 
     # ---- force apply alone (FP32 and mixed contractions, coloured and atomic):
     #      median over `apply_reps` applies after 10 warm-ups, each apply
@@ -958,7 +980,7 @@ def main():
         P.semx_set_mode(s.ctx, CONTRACTION[cname], ASSEMBLY[aname])
         bm = bytes_per_element_model(NGLL, mesh.nglob, E, geo_of(gname))
         bg = bytes_per_element(NGLL, mesh.nglob, E, geo_of(gname),
-                               affine=cname == "f32" and aname == "colored")
+                               affine=cname == "f32")
         for _ in range(10):
             P.semx_apply_force(s.ctx, u, f)
         ts = []
@@ -1007,7 +1029,7 @@ def main():
         torch.cuda.synchronize()
         print(json.dumps({"profile_force": apply, "skeleton_ms_per_apply": sk, "elements": E,
                           "copy_bytes_each_way": nbytes,
-                          "force_launches_per_apply": info["ncolors"] if args.assembly == "colored" else 1}))
+                          "force_launches_per_apply": launches_of_apply(s, u, f)}))
         s.close()
         return
     P.semx_set_mode(s.ctx, P.SEMX_C_F32, asm)
@@ -1015,11 +1037,11 @@ def main():
 
     # ---- time loop: warmup, then exactly `steps` timed steps.  The force
     # kernel's launch duration is measured over the same region: one HIP
-    # event pair around the force pass of every second step, divided by the
-    # launches that a pass colour by colour takes (element-local forces run it
-    # as one launch, its nodal sum inside the Newmark pass).  An event pair around every
-    # launch would add the event-to-kernel latency to each duration and slow
-    # the step itself by about 9 %.
+    # event pair around the force pass of every second step, divided by its
+    # launches (element-local forces run it as one launch, its nodal sum inside
+    # the Newmark pass).  An event pair around every launch would add the
+    # event-to-kernel latency to each duration and slow the step itself by about
+    # 9 %.
     stride = 2
     P.semx_reset(s.ctx)
     s.step(args.warmup)
@@ -1048,23 +1070,25 @@ def main():
     launches_per_apply = launches / ((args.steps + stride - 1) // stride)
     avg_launch_ms = force_ms / launches
 
-    # ---- access-pattern reference: the memory skeleton of the same force
-    # pass (same launches, grid, loads and stores, no arithmetic) on scratch
-    # fields; the kernel cannot be faster than its skeleton
+    # ---- access-pattern reference: the memory skeleton of a force apply (same
+    # launches, grid, loads and stores, no arithmetic; element launches and
+    # nodal sum) on scratch fields, against the apply's own time
     skeleton = None
     if args.assembly == "colored":
         uu = torch.zeros((mesh.nglob, 3), device="cuda")
         ff = torch.zeros_like(uu)
-        sk_launch_ms = P.semx_force_skeleton(s.ctx, uu, ff, 20) / launches_per_apply
+        sk_ms = P.semx_force_skeleton(s.ctx, uu, ff, 20)
         del uu, ff
-        skeleton = {"skeleton_ms_per_launch": round(sk_launch_ms, 5),
-                    "frac_of_skeleton": round(sk_launch_ms / avg_launch_ms, 4)}
-    bytes_per_launch = b_model * E / launches_per_apply
+        skeleton = {"skeleton_ms_per_apply": round(sk_ms, 5)}
+        if fa:
+            skeleton["frac_of_skeleton"] = round(sk_ms / fa["ms_per_apply"], 4)
+    # element-local forces: one launch a pass (this box is all of one kind)
+    parts = args.assembly == "colored" and launches_per_apply == 1
+    b_pass = (bytes_per_element_pass(NGLL, mesh.nglob, E, geo_of(args.geometry), affine=True) if parts else b_elem)
+    bytes_per_launch = b_pass * E / launches_per_apply
     achieved = bytes_per_launch / (avg_launch_ms * 1e-3) / 1e9
-    achieved_impl = b_elem * E / launches_per_apply / (avg_launch_ms * 1e-3) / 1e9
-    src = b"".join(open(os.path.join(ROOT, "paper_2606_12850_amd", "csrc", f), "rb").read()
-                   for f in ("force_f32.hip", "elem_common.hpp"))
-    src_hash = hashlib.sha256(src).hexdigest()
+    achieved_model = b_model * E / launches_per_apply / (avg_launch_ms * 1e-3) / 1e9
+    src_hash = kernel_source_hash()
     traffic = traffic_from_profiles(src_hash, args.geometry)
     if skeleton is not None:
         skeleton["skeleton_traffic"] = traffic_from_profiles(src_hash, args.geometry + "_skeleton")
@@ -1092,16 +1116,15 @@ def main():
                      "kernel": f"FP32 force pass, NGLL 5, {args.geometry}, {args.assembly}"
                                + (" (one launch of element-local forces on a box, the nodal sum in the Newmark pass)"
                                   if args.assembly == "colored" and args.geometry == "trilinear" else ""),
-                     "note": "achieved and frac price the pass at the model's bytes, which the trilinear path does "
-                             "not move (no Gamma or det J per point): frac may exceed 1, frac_impl counts what its "
-                             "inputs and forces need; per-launch figures are the pass divided by the mesh's colours; "
-                             "the skeleton includes the nodal sum, the pass in the loop does not",
+                     "note": "achieved and frac price the timed launch at the bytes that it cannot do without (inputs "
+                             "and forces once); achieved_model prices it at the byte model, whose Gamma and det J per "
+                             "point the trilinear path does not move; the skeleton is that of an apply, nodal sum "
+                             "included, and is compared with an apply",
+                     "bytes_per_element": b_pass, "bytes_per_launch": bytes_per_launch,
+                     "avg_launch_ms": round(avg_launch_ms, 5), "launches": launches, "timed_pass_stride": stride,
                      "bytes_model": "4 n^3 + 10 s n^3 + 2 s n^3 + 6 s G/E (node numbers, Gamma and det J per "
                                     "point, lambda and mu, u read and f written once per unique node; s = 4)",
-                     "bytes_per_element": b_model, "bytes_per_launch": bytes_per_launch,
-                     "avg_launch_ms": round(avg_launch_ms, 5), "launches": launches, "timed_pass_stride": stride,
-                     "bytes_per_element_impl": b_elem, "achieved_impl": round(achieved_impl, 1),
-                     "frac_impl": round(achieved_impl / HBM_PEAK_GBS, 4),
+                     "bytes_per_element_model": b_model, "achieved_model": round(achieved_model, 1),
                      "launch_ms_for_frac_0.6": round(bytes_per_launch / (0.6 * HBM_PEAK_GBS * 1e9) * 1e3, 5),
                      "bw_copy": round(bw_copy, 1), "frac_of_copy": round(achieved / bw_copy, 4),
                      **(skeleton or {})},

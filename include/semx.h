@@ -22,7 +22,9 @@
  *     are freed by semx_destroy().
  *   - All GPU work is ordered on the HIP stream given to semx_create(); a
  *     call that returns data to host memory synchronises that stream.
- *     A context is not thread-safe; use one context per host thread.
+ *     A context is not thread-safe; use one context per host thread.  Its
+ *     calls share its buffers: a graph that a caller captures from them is
+ *     replayed in order with the context's other calls.
  *   - ngll = n = N+1 GLL points per direction, 2 <= n <= 16 (N = polynomial
  *     degree up to 15).  Up to NGLL 12 the FP32 operator runs one lane per
  *     point or per line of points by the size of the pass, from 13 on
@@ -273,7 +275,9 @@ int semx_set_watchdog(semx_ctx *ctx, int64_t interval, double max_energy);
 /* Forward checkpoints for the adjoint: with every > 0, semx_reset() and every
  * `every`-th semx_step() keep a copy of (u, v, a) on the device (3 vectors
  * per checkpoint, owned by the library).  0 turns checkpointing off and
- * frees the copies. */
+ * frees the copies.  A run with checkpoints steps on the kernels whose
+ * arithmetic the adjoint repeats: its results may differ in their rounding from
+ * those of a run without. */
 int semx_set_checkpointing(semx_ctx *ctx, int64_t every);
 
 /* Discrete adjoint of the explicit Newmark run (exact gradient of a
@@ -384,12 +388,12 @@ int semx_gll(int ngll, double *xi, double *w);
  * 2k, ... counted from this call) is bracketed by one pair of HIP events
  * recorded on the context stream; 0 turns timing off, a negative stride is
  * SEMX_EINVAL.  semx_force_timing() synchronises the stream, returns the
- * number of colour ranges that the timed passes covered (SEMX_ASM_COLORED: the
- * mesh's colours, also where one launch covers them all; SEMX_ASM_ATOMIC: its
- * launches) and the passes' summed event-measured duration in milliseconds
- * since the last read, and clears the record.  In the time loop the nodal sum
- * of the element-local forces belongs to the Newmark pass that follows, not to
- * the force pass. */
+ * number of launches inside the timed passes (per pass: colours or blocks'
+ * colours, or one launch per geometry kind and, in an apply, one nodal sum) and
+ * the passes' summed event-measured duration in milliseconds since the last
+ * read, and clears the record.  In the time loop the nodal sum of the
+ * element-local forces belongs to the Newmark pass that follows, not to the
+ * force pass. */
 int semx_set_timing(semx_ctx *ctx, int stride);
 int semx_force_timing(semx_ctx *ctx, int64_t *launches, double *total_ms);
 
@@ -404,16 +408,17 @@ int semx_stream_bandwidth(semx_ctx *ctx, int64_t nbytes, int reps, double *gbps)
 
 /* Access-pattern reference for the force pass (Sec. II-B operator, Sec. IV-D
  * fused traversal): runs, reps times after one warm-up pass, the memory
- * skeleton of the FP32 per-element force pass that semx_apply_force launches
- * with SEMX_ASM_COLORED (one lane per point up to NGLL 10, one lane per column
- * from 11): the same launches, grid, block-to-element mapping and per-point
- * loads and stores (node numbers, geometry, material, the gather of u, the
- * element-local forces and their nodal sum; colour by colour the first-touch
- * bits and f instead) without the contractions, the stress arithmetic and the
- * slice barriers.  The clearing of f that a pass
- * without first-touch coverage needs is not included.  Returns the average
- * milliseconds per pass (HIP events on the context stream); the force pass
- * cannot take less time than its skeleton.
+ * skeleton of the FP32 force pass that semx_apply_force launches with
+ * SEMX_ASM_COLORED (one lane per point, per line of points or, where a pass
+ * from NGLL 11 assembles into f or runs on matrix-core tiles, per column): the
+ * same launches, grid, block-to-element mapping and per-point loads and stores
+ * (node numbers, geometry, material, the gather of u, the element-local forces
+ * and their nodal sum; colour by colour the first-touch bits and f instead)
+ * without the contractions, the stress arithmetic and the barriers.  The
+ * clearing of f that a pass without first-touch coverage needs is not
+ * included.  Returns the average milliseconds per pass (HIP events on the
+ * context stream); an apply on a kernel per point, line or column cannot take
+ * less time than its skeleton.
  *   u_dev: device [nmodels][nglob][3] FP32, read only.
  *   f_dev: device [nmodels][nglob][3] FP32, overwritten with meaningless
  *          values; must not overlap u_dev.

@@ -1092,8 +1092,7 @@ int force_accumulate(semx_ctx* c, const float* u, float* f, bool first_touch = f
   hipEvent_t e1 = nullptr;
   if (!launches.empty() && c->timing_stride > 0 && (c->timing_seq++ % c->timing_stride) == 0) {
     SEMX_HIP(c, time_pass_begin(c, &e1));
-    // a pass of the deterministic assembly covers every colour
-    c->timed_launches += (int64_t)(atomic ? launches : c->colored_launches).size();
+    c->timed_launches += (int64_t)launches.size() + (parts && !defer ? 1 : 0);  // the nodal sum is one
   }
   for (const auto& L : launches) {
     a.pos0 = L.pos0;
@@ -1980,8 +1979,10 @@ int semx_force_skeleton(semx_ctx* c, const float* u_dev, float* f_dev, int reps,
       a.pos0 = L.pos0;
       a.count = L.count;
       const int geo = L.irregular ? c->irregular_geo : kRegular;
-      const hipError_t e = c->n > kMaxNLow ? launch_force_high_skeleton(c->n, geo, a, c->stream)
-                                           : launch_force_skeleton(c->n, geo, L.naff, a, c->stream);
+      const hipError_t e = kernel_for(c, parts, geo) == kLine
+                               ? launch_force_line_skeleton(c->n, geo, L.naff, a, c->stream)
+                           : c->n > kMaxNLow ? launch_force_high_skeleton(c->n, geo, a, c->stream)
+                                             : launch_force_skeleton(c->n, geo, L.naff, a, c->stream);
       if (e != hipSuccess) return e;
     }
     return parts ? launch_gather(c, f_dev, nullptr, c->stream) : hipSuccess;

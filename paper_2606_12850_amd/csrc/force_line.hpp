@@ -453,14 +453,15 @@ hipError_t launch_line_any(int n, int geo, int64_t naff, const LineArgs<T>& a, h
 }
 
 // The FP32 launch from the arguments that the force kernels share.
+inline LineArgs<float> line_args(const ForceArgs& a) {
+  return LineArgs<float>{a.ibool, a.aff,  a.gam_pt, a.gam_el, a.tri,   a.xi,    a.mat,     a.u,
+                         a.dtab,  a.part, a.pos0,   a.count,  a.nspec, a.nglob, a.nmodels, a.aux};
+}
+
 template <int NC>
 hipError_t launch_line_f32(int n, int geo, int64_t naff, const ForceArgs& a, hipStream_t s) {
   if (a.list) return hipErrorInvalidValue;
-  return launch_line_any<float, NC, kLineMaxN>(
-      n, geo, naff,
-      LineArgs<float>{a.ibool, a.aff, a.gam_pt, a.gam_el, a.tri, a.xi, a.mat, a.u, a.dtab, a.part, a.pos0, a.count,
-                      a.nspec, a.nglob, a.nmodels, a.aux},
-      s);
+  return launch_line_any<float, NC, kLineMaxN>(n, geo, naff, line_args(a), s);
 }
 
 }  // namespace

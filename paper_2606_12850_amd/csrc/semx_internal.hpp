@@ -352,6 +352,8 @@ struct LineArgs {
 };
 hipError_t launch_force_line64(int n, int geo, int64_t naff, const LineArgs<double>& a, hipStream_t s);
 hipError_t launch_force_line(int n, int geo, int64_t naff, const ForceArgs& a, hipStream_t s);
+// Memory skeleton of the same (same loads and stores, no arithmetic).
+hipError_t launch_force_line_skeleton(int n, int geo, int64_t naff, const ForceArgs& a, hipStream_t s);
 hipError_t launch_force_line_acoustic(int n, int geo, int64_t naff, const ForceArgs& a, hipStream_t s);
 constexpr int kLineMaxN = 12;
 
