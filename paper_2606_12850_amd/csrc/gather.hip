@@ -252,6 +252,8 @@ hipError_t newmark_t(const semx_ctx* c, T dt, const T* minv, const uint32_t* src
   });
 }
 
+// Division by an invariant divisor as a multiplication and a shift (Granlund
+// and Montgomery 1994, Fig. 4.1); nodal.hpp's div() applies it.
 FastDiv fast_div(uint32_t d) {
   uint32_t s = 0;
   while ((uint64_t(1) << s) < d) ++s;
@@ -297,7 +299,7 @@ void find_lattice(semx_ctx* c, const std::vector<std::array<int32_t, 4>>& aff) {
   int64_t least = INT64_MAX;
   for (int txs = 6; txs >= 2; --txs) {
     const int64_t tx = int64_t(1) << txs, ty = kT / tx, lanes = (Gx + tx - 1) / tx * tx * ((Gy + ty - 1) / ty * ty);
-    if (lanes * 20 < least * 19 || least == INT64_MAX) {
+    if (least == INT64_MAX || lanes * 20 < least * 19) {
       least = lanes;
       L.txs = (uint32_t)txs;
     }
