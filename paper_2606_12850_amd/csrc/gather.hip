@@ -179,24 +179,29 @@ __global__ __launch_bounds__(kT) void newmark_parts_kernel(MAP m, int64_t nglob,
   }
 }
 
-__global__ __launch_bounds__(kT) void mass_kernel(int n3, int64_t nspec, int64_t nglob,
-                                                  const int32_t* __restrict__ order, const int32_t* __restrict__ ptr,
-                                                  const int32_t* __restrict__ idx, const double* __restrict__ rho,
+template <class MAP>
+__global__ __launch_bounds__(kT) void mass_kernel(MAP m, int n3, int64_t nspec, int64_t nglob,
+                                                  const int32_t* __restrict__ order, const double* __restrict__ rho,
                                                   const double* __restrict__ wdet, double* __restrict__ mass) {
-  const int64_t g = blockIdx.x * (int64_t)kT + threadIdx.x;
-  if (g >= nglob) return;
+  int64_t g;
+  if (!m.locate(g)) return;
   const double* __restrict__ rm = rho + (int64_t)blockIdx.y * nspec * n3;
   double s = 0.0;
-  for (int32_t k = ptr[g]; k < ptr[g + 1]; ++k) {
-    const int32_t t = idx[k], pos = t / n3;
-    s += rm[(int64_t)order[pos] * n3 + (t - pos * n3)] * wdet[t];
-  }
+  m.each(g, [&](int32_t t) {
+    const int32_t pos = t / n3;
+    s = fma(rm[(int64_t)order[pos] * n3 + (t - pos * n3)], wdet[t], s);  // the same bits on every map
+  });
   mass[(int64_t)blockIdx.y * nglob + g] = s;
 }
 
 }  // namespace
 
 int build_node_points(semx_ctx* c) {
+  if (c->lattice.n > 0) {  // the points follow from the node's place
+    dev_free(c->d_nptr);
+    dev_free(c->d_nidx);
+    return SEMX_OK;
+  }
   // rank of each position: its place colour by colour (or itself)
   std::vector<int32_t> rank(c->nspec);
   for (int64_t t = 0; t < c->nspec; ++t) rank[c->h_clist.empty() ? t : c->h_clist[t]] = (int32_t)t;
@@ -337,10 +342,10 @@ hipError_t launch_newmark_parts64(const semx_ctx* c, const uint32_t* srcbits, hi
 }
 
 hipError_t launch_mass(const semx_ctx* c, const double* rho, double* mass, hipStream_t s) {
-  const dim3 grid(node_blocks(c->nglob), (unsigned)c->nmodels);
-  mass_kernel<<<grid, kT, 0, s>>>(c->n3, c->nspec, c->nglob, c->d_order.as<int32_t>(), c->d_nptr.as<int32_t>(),
-                                  c->d_nidx.as<int32_t>(), rho, c->d_wdet.as<double>(), mass);
-  return hipGetLastError();
+  return with_map(c, [&](auto m, dim3 grid) {
+    mass_kernel<decltype(m)><<<grid, kT, 0, s>>>(m, c->n3, c->nspec, c->nglob, c->d_order.as<int32_t>(), rho,
+                                                 c->d_wdet.as<double>(), mass);
+  });
 }
 
 }  // namespace semx

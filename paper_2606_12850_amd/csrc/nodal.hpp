@@ -55,6 +55,11 @@ struct TableMap {
         }
     }
   }
+  // fn(point) for the node's points in their order
+  template <class F>
+  __device__ __forceinline__ void each(int64_t g, F fn) const {
+    for (int32_t k = ptr[g]; k < ptr[g + 1]; ++k) fn(idx[k]);
+  }
 };
 
 // A box of nex x ney x nez elements on one node lattice, x fastest: node
@@ -118,6 +123,13 @@ struct LatticeMap {
         for (int x = 0; x < 2; ++x)
 #pragma unroll
           for (int c = 0; c < NC; ++c) s[c] += v[z][y][x][c];
+  }
+  template <class F>
+  __device__ __forceinline__ void each(int64_t, F fn) const {
+    for (int z = 0; z <= (z2 ? 1 : 0); ++z)
+      for (int y = 0; y <= (y2 ? 1 : 0); ++y)
+        for (int x = 0; x <= (x2 ? 1 : 0); ++x)
+          fn((z ? oz[1] : oz[0]) + (y ? oy[1] : oy[0]) + (x ? ox[1] : ox[0]));
   }
 };
 

@@ -144,7 +144,8 @@ struct semx_ctx {
   double hmin = 0.0;               // min distance between adjacent GLL points
 
   // the points of each node: ids pos * n3 + q in the order in which a pass
-  // colour by colour reaches them, at d_nidx[d_nptr[g] .. d_nptr[g + 1])
+  // colour by colour reaches them, at d_nidx[d_nptr[g] .. d_nptr[g + 1]) (a
+  // lattice has no tables)
   semx::DevBuf d_nptr;  // int32 [nglob + 1]
   semx::DevBuf d_nidx;  // int32 [nspec * n3]
   std::vector<semx::Launch> kind_launches;  // whole mesh: regular, irregular elements
@@ -419,7 +420,7 @@ int build_colored(semx_ctx* c);
 // The list that its launches index, or null: positions.
 inline const int32_t* colour_list(const semx_ctx* c) { return c->user_colors ? nullptr : c->d_clist.as<int32_t>(); }
 
-// gather.hip: node tables, and the sum of the element-local forces per node
+// gather.hip: node tables (after find_lattice), and the sum of the element-local forces per node
 int build_node_points(semx_ctx* c);
 void find_lattice(semx_ctx* c, const std::vector<std::array<int32_t, 4>>& aff);
 // f[model][g][c] = sum over the node's points of part, in their order; a node without points gets 0.  srcbits: nodes whose sum starts from

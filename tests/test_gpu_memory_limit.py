@@ -5,7 +5,8 @@ colour by colour, with the same sums).  On a device whose memory is counted and
 limited (tests/native/limited_memory.cpp) a model is accepted with no more
 memory than its upload takes under a colouring of the caller's, which has no
 element-local forces, and records, checkpoints and the adjoint's buffers that
-leave no room for them are accepted too, with unchanged results.
+leave no room for them are accepted too, with unchanged results.  The points of
+a node of a structured box follow from its place: no tables are kept.
 """
 import os
 import subprocess
@@ -60,7 +61,20 @@ ref = solver()
 u = ref.empty_field().normal_(generator=gen)
 want = forces(ref, u)
 assert M.limited_used() > part, "allocations are not counted"
-if kind.startswith("upload"):
+if kind == "tables":
+    used = []
+    for scrambled in (False, True):
+        m = W.box_mesh(ne, n, 4000.0)
+        if scrambled:
+            m.ibool = np.random.default_rng(1).permutation(m.nglob).astype(np.int32)[m.ibool]
+        s = P.Solver(n)
+        base = M.limited_used()
+        s.upload_mesh(m)
+        used.append(M.limited_used() - base)
+        s.upload_model(*W.homogeneous_model(m))
+        s.close()
+    assert used[1] - used[0] >= 4 * mesh.nspec * n ** 3, used  # a lattice keeps no node tables
+elif kind.startswith("upload"):
     own = solver(own_colours=True)
     s = solver(limit=own.peak)
     np.testing.assert_array_equal(forces(s, u), want)
@@ -123,7 +137,7 @@ def limited(tmp_path_factory):
     return so
 
 
-@pytest.mark.parametrize("kind", ["upload", "upload64", "records", "checkpoints", "adjoint"])
+@pytest.mark.parametrize("kind", ["upload", "upload64", "records", "checkpoints", "adjoint", "tables"])
 def test_room_is_made(limited, kind):
     r = subprocess.run([sys.executable, "-c", SCRIPT, limited, kind], cwd=os.path.dirname(HERE), capture_output=True,
                        text=True, timeout=100)
