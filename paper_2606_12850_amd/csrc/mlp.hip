@@ -38,6 +38,7 @@ struct semx_mlp {
   semx::DevBuf splitk;             // split-K partial sums
   char* stage = nullptr;           // pinned, kStageSlots pieces of kStageBytes (download)
   hipEvent_t staged[2] = {nullptr, nullptr};
+  std::mutex stage_use;            // one download through them at a time
   const float* x_saved = nullptr;
   int batch_saved = 0;
   int device = 0;                  // device current at creation (allocation-free forward)
@@ -707,7 +708,8 @@ int malloc_buf(semx_mlp* p, DevBuf& b, size_t bytes) {
 // made present first, while the kernels queued on the stream still run, and the
 // data comes through two pinned pieces, one on its way while the other is
 // copied out.  Anything unusual (small, pinned or device memory, a stream under
-// capture, pages that cannot be written) goes the direct way.
+// capture, pages that cannot be written, the pieces in use by another thread)
+// goes the direct way.
 constexpr int kStageSlots = 2;
 constexpr int64_t kStageBytes = 4 << 20;
 
@@ -715,7 +717,8 @@ int download(semx_mlp* p, float* dst, const float* src) {
   const int64_t bytes = sizeof(float) * p->nparam;
   char* d = reinterpret_cast<char*>(dst);
   const char* s = reinterpret_cast<const char*>(src);
-  bool staged = p->stage && bytes >= kStageBytes;
+  std::unique_lock<std::mutex> use(p->stage_use, std::defer_lock);
+  bool staged = p->stage && bytes >= kStageBytes && use.try_lock();
   if (staged) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusActive;
     hipPointerAttribute_t at{};
@@ -730,6 +733,7 @@ int download(semx_mlp* p, float* dst, const float* src) {
     staged = madvise(reinterpret_cast<void*>(beg), end - beg, MADV_POPULATE_WRITE) == 0;
   }
   if (!staged) {
+    if (use.owns_lock()) use.unlock();
     hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, p->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
     return e == hipSuccess ? SEMX_OK : mhip(p, e, "parameter download");
