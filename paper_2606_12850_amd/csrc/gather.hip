@@ -102,7 +102,11 @@ __global__ __launch_bounds__(kT) void place_points_kernel(int64_t npt, const int
     idx[atomicAdd(cursor + ibool[t], 1)] = (int32_t)t;
 }
 
-// each node's points (a few) in ascending order of their element's rank
+// Each node's points in ascending order of their element's rank: by insertion
+// where they are few, as on any ordinary mesh; the points of a node that very many
+// elements share (the axis of a fan) come in no order and go through a heap, so
+// that the lane ends in n log n.
+constexpr int32_t kInsertion = 32;
 __global__ __launch_bounds__(kT) void sort_points_kernel(int64_t nglob, int n3, const int32_t* __restrict__ rank,
                                                          const int32_t* __restrict__ ptr, int32_t* __restrict__ idx) {
   auto before = [&](int32_t x, int32_t y) {
@@ -111,6 +115,26 @@ __global__ __launch_bounds__(kT) void sort_points_kernel(int64_t nglob, int n3, 
   };
   for (int64_t g = blockIdx.x * (int64_t)kT + threadIdx.x; g < nglob; g += (int64_t)gridDim.x * kT) {
     const int32_t b = ptr[g], e = ptr[g + 1];
+    if (e - b > kInsertion) {
+      int32_t* h = idx + b;
+      auto sift = [&](int32_t at, int32_t n) {
+        const int32_t v = h[at];
+        for (int32_t k; (k = 2 * at + 1) < n; at = k) {
+          if (k + 1 < n && before(h[k], h[k + 1])) ++k;
+          if (!before(v, h[k])) break;
+          h[at] = h[k];
+        }
+        h[at] = v;
+      };
+      for (int32_t i = (e - b) / 2 - 1; i >= 0; --i) sift(i, e - b);
+      for (int32_t n = e - b - 1; n > 0; --n) {
+        const int32_t top = h[0];
+        h[0] = h[n];
+        h[n] = top;
+        sift(0, n);
+      }
+      continue;
+    }
     for (int32_t i = b + 1; i < e; ++i) {
       const int32_t v = idx[i];
       int32_t j = i - 1;
