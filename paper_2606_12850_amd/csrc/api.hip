@@ -1020,11 +1020,15 @@ ForceKernel kernel_for(const semx_ctx* c, bool parts, int geo) {
 
 // True when the first launch of the force pass can take the step's bookkeeping
 // along (element-local forces; not the column kernels and the 16-bit kernel of
-// the low orders).
+// the low orders; nor the tile kernels, whose orders make a receiver's wave a
+// chain of up to 4096 points that holds a compute unit's only workgroup: us per
+// step, in the force launch / in a launch of its own, acoustic rods of 100-130
+// elements NGLL 13 20.4 / 16.1, 16 31.7 / 20.8, elastic boxes of NGLL 16, one
+// element 42 / 29, 4^3 48 / 37, 10^3 101 / 103, 18^3 564 / 544).
 bool carries_aux(const semx_ctx* c) {
   if (!parts_active(c) || c->kind_launches.empty()) return false;
   const ForceKernel k = kernel_for(c, true, c->kind_launches[0].irregular ? c->irregular_geo : kRegular);
-  return k != kColumn && k != kMixed && !(k == kAcoustic && c->n > kMaxNLow);
+  return k != kTile && k != kTileAcoustic && k != kColumn && k != kMixed && !(k == kAcoustic && c->n > kMaxNLow);
 }
 
 // True when a pass with nothing to sum stores into f at once: every node has

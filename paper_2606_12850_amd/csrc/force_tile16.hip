@@ -251,8 +251,8 @@ constexpr bool tile_persistent() {
   return NC == 1 || (GEO == kRegular && (ASM == kPart || NG == kN || PREC != SEMX_C_F16));
 }
 
-template <int NG, int GEO, int ASM, bool AFF, int PREC, int NC, class X>
-__global__ __launch_bounds__(kBlk) void force_tile16_kernel(ForceArgs a, X aux) {
+template <int NG, int GEO, int ASM, bool AFF, int PREC, int NC>
+__global__ __launch_bounds__(kBlk) void force_tile16_kernel(ForceArgs a) {
   static_assert(NC == 3 || PREC == SEMX_C_F32, "the scalar (acoustic) operator runs in FP32");
   constexpr int E3 = NG * NG * NG;
   // persistent, next element requested ahead
@@ -268,14 +268,12 @@ __global__ __launch_bounds__(kBlk) void force_tile16_kernel(ForceArgs a, X aux) 
   __shared__ __attribute__((aligned(16))) float r2[NC * kN3];
   __shared__ float s_red[2][kWaves];  // FP16: per-wave maxima of the operands
 
-  if (run_aux(aux)) return;  // uniform over the block
-  const int lead = aux_lead(aux);
   const int ngrp = (int)a.count;
   const int gpx = (ngrp + kNumXcd - 1) / kNumXcd;
-  const int per_xcd = ((int)gridDim.x - lead) / kNumXcd;
-  const int xbeg = (((int)blockIdx.x - lead) % kNumXcd) * gpx;
+  const int per_xcd = (int)gridDim.x / kNumXcd;
+  const int xbeg = ((int)blockIdx.x % kNumXcd) * gpx;
   const int xend = min(xbeg + gpx, ngrp);
-  int grp = xbeg + ((int)blockIdx.x - lead) / kNumXcd;
+  int grp = xbeg + (int)blockIdx.x / kNumXcd;
   if (grp >= xend) return;  // uniform over the block
 
   const int w = threadIdx.x >> 6;
@@ -609,11 +607,7 @@ template <int NG, int GEO, int ASM, bool AFF, int PREC, int NC>
 hipError_t launch_t16(const ForceArgs& a, hipStream_t s) {
   int64_t nb = ((a.count + kNumXcd - 1) / kNumXcd) * kNumXcd;
   if (tile_persistent<NG, GEO, ASM, PREC, NC>()) nb = std::min<int64_t>(nb, resident_groups());
-  auto go = [&](auto aux, unsigned lead) {
-    force_tile16_kernel<NG, GEO, ASM, AFF, PREC, NC><<<dim3((unsigned)nb + lead, (unsigned)a.nmodels), kBlk, 0, s>>>(a, aux);
-  };
-  if constexpr (ASM != kPart) go(NoAux{}, 0u);
-  else with_aux(a.aux, kBlk, kNumXcd, go);
+  force_tile16_kernel<NG, GEO, ASM, AFF, PREC, NC><<<dim3((unsigned)nb, (unsigned)a.nmodels), kBlk, 0, s>>>(a);
   return hipGetLastError();
 }
 
@@ -642,7 +636,6 @@ hipError_t launch_t16_split(int geo, bool atomic, int64_t naff, const ForceArgs&
   b.count = naff;
   hipError_t e = launch_t16_geo<NG, true, PREC, NC>(geo, atomic, b, s);
   if (e != hipSuccess || naff == a.count) return e;
-  if (naff > 0) b.aux = nullptr;
   b.pos0 = a.pos0 + naff;
   b.count = a.count - naff;
   return launch_t16_geo<NG, false, PREC, NC>(geo, atomic, b, s);
