@@ -1026,7 +1026,7 @@ ForceKernel kernel_for(const semx_ctx* c, bool parts, int geo) {
 // elements NGLL 13 20.4 / 16.1, 16 31.7 / 20.8, elastic boxes of NGLL 16, one
 // element 42 / 29, 4^3 48 / 37, 10^3 101 / 103, 18^3 564 / 544).
 bool carries_aux(const semx_ctx* c) {
-  if (!parts_active(c) || c->kind_launches.empty()) return false;
+  if (!parts_active(c) || c->kind_launches.empty() || !aux_fits(c)) return false;
   const ForceKernel k = kernel_for(c, true, c->kind_launches[0].irregular ? c->irregular_geo : kRegular);
   return k != kTile && k != kTileAcoustic && k != kColumn && k != kMixed && !(k == kAcoustic && c->n > kMaxNLow);
 }

@@ -124,16 +124,42 @@ __global__ __launch_bounds__(kT) void step_aux_kernel(AuxArgs<T> A) {
   T* slot = A.hist + (size_t)((n + 1) & 1) * A.per;
   const bool live = n >= 0 && n < A.nstf;
   double work = 0.0, corr = 0.0;
-  for (int k = lane; k < A.npt; k += kT) {
-    const int p = A.pts[k];
-    const int64_t g = (int64_t)A.snodes[p] * A.nc;
-    const T amp = live ? A.stf[(int64_t)(p / A.n3) * A.nstf + n] : (T)0;
-    for (int c = 0; c < A.nc; ++c) {
-      const T un = A.u[g + c], old = slot[(int64_t)A.nc * k + c];
-      const double fs = (double)amp * (double)A.wdir[(int64_t)A.nc * p + c];
-      work += 0.5 * ((double)un - (double)old) * fs;
-      corr += (double)un * fs;
-      slot[(int64_t)A.nc * k + c] = un;
+  // four points a lane at a time, their loads in one round trip each (a step of
+  // 16^3 elements of NGLL 5 with 1024 sources, 128000 points, took 728 us one at
+  // a time, now 622; with 32 sources 36, now 30)
+  constexpr int kPts = 4;
+  for (int k0 = lane; k0 < A.npt; k0 += kPts * kT) {
+    int p[kPts], g[kPts];
+    T amp[kPts], un[kPts][3], old[kPts][3], wd[kPts][3];
+#pragma unroll
+    for (int j = 0; j < kPts; ++j) p[j] = A.pts[min(k0 + j * kT, A.npt - 1)];
+#pragma unroll
+    for (int j = 0; j < kPts; ++j) {
+      g[j] = A.snodes[p[j]] * A.nc;
+      amp[j] = live ? A.stf[(int64_t)(p[j] / A.n3) * A.nstf + n] : (T)0;
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        if (c < A.nc) {
+          wd[j][c] = A.wdir[(int64_t)A.nc * p[j] + c];
+          old[j][c] = slot[(int64_t)A.nc * min(k0 + j * kT, A.npt - 1) + c];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kPts; ++j)
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        if (c < A.nc) un[j][c] = A.u[g[j] + c];
+#pragma unroll
+    for (int j = 0; j < kPts; ++j) {
+      if (k0 + j * kT >= A.npt) break;
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        if (c < A.nc) {
+          const double fs = (double)amp[j] * (double)wd[j][c];
+          work += 0.5 * ((double)un[j][c] - (double)old[j][c]) * fs;
+          corr += (double)un[j][c] * fs;
+          slot[(int64_t)A.nc * (k0 + j * kT) + c] = un[j][c];
+        }
     }
   }
   work = block_sum(work, red);
@@ -259,8 +285,19 @@ int step_aux(semx_ctx* c, int64_t n, bool with_corr, bool record, const int64_t*
   return launch_aux(c, aux_args(c, n, with_corr, record, dstep, prestore));
 }
 
-int energy_source_step(semx_ctx* c, int64_t n, bool with_corr) {
-  return launch_aux(c, aux_args64(c, n, with_corr, false, false));
+int step_aux64(semx_ctx* c, int64_t n, bool with_corr, bool record, bool prestore) {
+  return launch_aux(c, aux_args64(c, n, with_corr, record, prestore));
+}
+
+// One wave sums the source work in the force launch, 256 lanes in a launch of
+// its own: some 10 and 5 us per 1000 source points, the launch itself 5.  Up to
+// 1024 points, or what the mesh's force takes as long for, the wave ends with the
+// elements (us per step, in the force launch / before it: NGLL 5, 16^3, 32
+// sources of 125 points 54 / 30, 1024 of them 1660 / 622; 48^3, 32 sources
+// 238 / 215; with 8 sources 20 and 186 in the force launch).
+bool aux_fits(const semx_ctx* c) {
+  const int64_t points = (int64_t)c->nmodels * c->nspec * c->n3;
+  return c->src.nsrc == 0 || c->src.npts <= std::max<int64_t>(1024, points / 4096);
 }
 
 int energy_track(semx_ctx* c, const void* f_pe, bool source_in_f) {

@@ -521,17 +521,20 @@ int f64_step_once(semx_ctx* c, bool record) {
   }
   int rc = SEMX_OK;
   if (parts) {
-    // receivers, source work and the coming source force ride in the force launch
+    // receivers, source work and the coming source force ride in the force launch,
+    // or go before it
     const bool pre = prestores(c);
     if (pre) rc = build_first_tl(c);
+    const bool ride = aux_fits(c);
+    const AuxArgs<double> aux = ride ? aux_args64(c, c->it, track && src_in_f, record, pre) : AuxArgs<double>{};
+    if (!rc && !ride) rc = step_aux64(c, c->it, track && src_in_f, record, pre);
     if (rc) return rc;
-    const AuxArgs<double> aux = aux_args64(c, c->it, track && src_in_f, record, pre);
     const hipError_t e = launch_force64(c, u, f, &aux);
     if (e != hipSuccess) return hip_fail(c, e, "FP64 force kernel launch");
     c->f_in_part = true;
     c->part_src = pre;
   } else {
-    rc = energy_source_step(c, c->it, track && src_in_f);
+    rc = step_aux64(c, c->it, track && src_in_f, false, false);
     if (!rc) rc = f64_force_into(c, u, f, !track);
     if (!rc) rc = inject64(c, c->it + 1, f);
     if (!rc && record) rc = record64(c, c->it);

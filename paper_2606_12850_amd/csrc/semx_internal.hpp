@@ -442,18 +442,17 @@ int energy_reset(semx_ctx* c);
 // after the Newmark pass of step n: f_pe holds f^n (-K u^n + f_src^n when
 // source_in_f, else -K u^n)
 int energy_track(semx_ctx* c, const void* f_pe, bool source_in_f);
-// FP64 storage without element-local forces: the source work of step n after
-// the Newmark pass (u holds u^{n+1})
-int energy_source_step(semx_ctx* c, int64_t n, bool with_corr);
 // The bookkeeping of step n after the Newmark pass (aux.hpp): source work and,
 // with `record`, the receivers' sample n (u^{n+1}); `prestore`: also the source
 // force of sample n + 1 into f at the source nodes, to which the force pass
 // adds.  dstep: the device step counter of graph-captured steps, else null.
 // step_aux launches it by itself; a force pass that can take it along is given
-// aux_args().
+// aux_args(), if aux_fits().
+bool aux_fits(const semx_ctx* c);
 AuxArgs<float> aux_args(semx_ctx* c, int64_t n, bool with_corr, bool record, const int64_t* dstep, bool prestore);
 AuxArgs<double> aux_args64(semx_ctx* c, int64_t n, bool with_corr, bool record, bool prestore);
 int step_aux(semx_ctx* c, int64_t n, bool with_corr, bool record, const int64_t* dstep, bool prestore);
+int step_aux64(semx_ctx* c, int64_t n, bool with_corr, bool record, bool prestore);
 int energy_read(semx_ctx* c, double* kin, double* pot, double* work);
 
 // fp64.hip: the FP64 storage path (state buffers hold doubles)
