@@ -85,7 +85,7 @@ __global__ void energy_reduce_kernel(int nblk, const double* __restrict__ part, 
 // waves' launch took 25 us more than this one.
 template <class T>
 __global__ __launch_bounds__(kT) void step_aux_kernel(AuxArgs<T> A) {
-  __shared__ double red[kT];
+  __shared__ double red[2][kT];
   __shared__ T rred[3][kT];
   const int unit = blockIdx.x, model = blockIdx.y, lane = threadIdx.x;
   if (unit < A.nrec) {  // uniform over the block, as are all branches here
@@ -106,12 +106,11 @@ __global__ __launch_bounds__(kT) void step_aux_kernel(AuxArgs<T> A) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) rred[c][lane] = s[c];
     __syncthreads();
-    for (int st = kT / 2; st > 0; st >>= 1) {
-      if (lane < st)
-        for (int c = 0; c < A.nc; ++c) rred[c][lane] += rred[c][lane + st];
-      __syncthreads();
+    if (lane >= 64) return;
+    for (int c = 0; c < A.nc; ++c) {
+      const T v = tree_sum(rred[c][lane], rred[c][lane + 64], rred[c][lane + 128], rred[c][lane + 192]);
+      if (lane == 0) A.seis[(((int64_t)model * A.nrec + unit) * A.nc + c) * A.nt_max + it] = v;
     }
-    if (lane < A.nc) A.seis[(((int64_t)model * A.nrec + unit) * A.nc + lane) * A.nt_max + it] = rred[lane][0];
     return;
   }
   if (model != 0) return;
@@ -162,8 +161,12 @@ __global__ __launch_bounds__(kT) void step_aux_kernel(AuxArgs<T> A) {
         }
     }
   }
-  work = block_sum(work, red);
-  corr = block_sum(corr, red);
+  red[0][lane] = work;
+  red[1][lane] = corr;
+  __syncthreads();
+  if (lane >= 64) return;
+  work = tree_sum(red[0][lane], red[0][lane + 64], red[0][lane + 128], red[0][lane + 192]);
+  corr = tree_sum(red[1][lane], red[1][lane + 64], red[1][lane + 128], red[1][lane + 192]);
   if (lane == 0) {
     if (n > A.it0) A.acc[3] += work;
     if (A.with_corr) A.acc[2] = corr;
