@@ -916,13 +916,17 @@ int run_graph_chunks(semx_ctx* c, int64_t nchunks, int64_t G) {
 }
 
 // True when the FP32 elastic coloured force runs on 2 x 2 x 2 element blocks.
-// In the automatic mode only where the block kernel measured faster than the
-// per-element kernel: the stored-Gamma path, which streams 36 B of Gamma per
-// point and gains from the block's single pass over its nodes (0.583 against
-// 0.603 ms per apply at 64^3).  On the trilinear and regular paths the
-// per-element kernel keeps 16 elements per compute unit in flight against
-// the blocks' two workgroups, and wins (0.42-0.44 against 0.50 ms, 0.49
-// against 0.55 ms).
+// In the automatic mode that is the stored-Gamma path, where the block kernel is
+// faster than the per-element kernel assembling colour by colour (0.583 against
+// 0.603 ms per apply at 64^3: 36 B of Gamma a point, and one pass over a block's
+// nodes); on the trilinear and regular paths the per-element kernel keeps 16
+// elements per compute unit in flight against the blocks' two workgroups, and
+// wins (0.42-0.44 against 0.50 ms, 0.49 against 0.55 ms).  Element-local forces
+// and a nodal sum are faster than either on most sizes; us per apply, blocks /
+// element-local, jittered boxes, stored Gamma: NGLL 5, 2^3 elements 5.5 / 6.2,
+// 4^3 45 / 7.8, 16^3 57 / 12.4, 32^3 103 / 63, 64^3 577 / 559 (and a step there
+// 765 / 727); NGLL 4, 64^3 330 / 249; NGLL 3, 80^3 531 / 248; NGLL 2, 100^3
+// 803 / 206.  SEMX_BLOCKS_OFF takes them.
 bool blocks_active(const semx_ctx* c) {
   if (c->blocks_mode == SEMX_BLOCKS_OFF || c->nblocks == 0 || c->physics != SEMX_ELASTIC ||
       c->storage != SEMX_F32 || c->contraction != SEMX_C_F32 || c->assembly != SEMX_ASM_COLORED ||
@@ -981,18 +985,18 @@ void note_capture(semx_ctx* c) {
 
 // True when a launch of geometry path `geo` runs on the line kernel
 // (force_line.hpp), FP32 with element-local forces.  Where the lines lie
-// (us per apply, line / kernel it replaces, 2e5 and 3e6 nodes):
+// (us per apply, line / kernel it replaces):
 //   * from 2^18 points, a chip's worth of lines: below, a line's longer chain
-//     costs more than its fewer instructions give (NGLL 5, 4^3: 8.1 / 8.2,
-//     NGLL 10, 2^3: 13 / 10.5; NGLL 5, 15^3 10.6 / 11.6; 36^3 trilinear
-//     62 / 84; NGLL 8, 21^3 53 / 78);
+//     costs more than its fewer instructions give (NGLL 5, 4^3: 7.3 / 6.2,
+//     NGLL 10, 2^3: 10.6 / 9.2; NGLL 5, 15^3 9.7 / 10.3; 36^3 trilinear
+//     60 / 77; NGLL 8, 21^3 50 / 68);
 //   * at NGLL 2 and from 11 at any size: 8 points leave seven eighths of the
-//     per-point kernel's lanes idle (58^3: 19 / 60), and the slices of the
-//     column kernel follow each other (NGLL 11, one element: 11 / 24, 14^3:
-//     54 / 90; NGLL 12, 13^3: 70 / 99 for the padded tile);
+//     per-point kernel's lanes idle (58^3: 18 / 59), and the slices of the
+//     column kernel follow each other (NGLL 11, one element: 11 / 22, 14^3:
+//     52 / 84; NGLL 12, 13^3: 66 / 92 for the padded tile);
 //   * stored geometry at NGLL 3-5 stays on the per-point kernel, whose many
 //     small workgroups keep more of the 36 bytes a point in flight (NGLL 4,
-//     48^3: 101 / 94, NGLL 6, 29^3: 94 / 107);
+//     48^3: 98 / 90, NGLL 5, 24^3: 34 / 30, NGLL 6, 29^3: 91 / 93);
 //   * a run with checkpoints stays on the kernels of one lane per point or
 //     column, whose arithmetic the adjoint repeats: sensitivities, which are
 //     FP64 results, keep their bits.  On the line kernel they move by 4e-7 at

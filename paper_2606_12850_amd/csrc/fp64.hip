@@ -290,9 +290,9 @@ __global__ void finite64_kernel(int64_t n, const double* __restrict__ x, int* __
 // Line kernel (force_line.hpp) instead of one lane per point: where a launch
 // fills the chip.  Per-point Gamma: at NGLL 2-5 the line kernel has fewer of
 // its 72 bytes a point in flight.  Force applies of a box, lane per point / line:
-//   one Gamma per element  NGLL 5, 1000000 points 35.7 / 25.8 us, 216000 13.4 / 11.5, 42875 7.9 / 8.6;
-//                          NGLL 9, 729000 47.4 / 26.3;  NGLL 10, 125000 16.3 / 15.9
-//   Gamma at each point    NGLL 5, 1000000 points 35.7 / 38.8;  NGLL 7, 753571 41.3 / 36.2, 175616 14.2 / 14.5
+//   one Gamma per element  NGLL 5, 1000000 points 33.9 / 25.5 us, 216000 12.8 / 11.6, 42875 8.8 / 8.4;
+//                          NGLL 9, 729000 44.9 / 24.8;  NGLL 10, 125000 15.7 / 16.3
+//   Gamma at each point    NGLL 5, 1000000 points 33.9 / 38.2;  NGLL 7, 753571 38.5 / 31.0, 175616 13.5 / 12.5
 bool use_line64(const semx_ctx* c, bool parts, int geo) {
   const int64_t points = (int64_t)c->nmodels * c->nspec * c->n3;
   if (!parts) return false;

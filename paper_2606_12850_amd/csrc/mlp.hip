@@ -173,7 +173,7 @@ struct Tile {
 // time.  The lanes of a wave run over k first, so that their writes (rows 80
 // bytes apart) fall on different banks; with eight rows of one k a thread,
 // written element by element, up to 16 lanes met on a bank: the weight gradient
-// of 24576 outputs at batch 128 took 34.5 us, now 23 (its 50 MB of output alone 10),
+// of 24576 outputs at batch 128 took 34.5 us, now 26 (its 50 MB of output alone 10),
 // the input gradient 28, now 23.
 template <class T, int ROWS, Loads LD>
 struct Tile<T, false, ROWS, LD> {
@@ -240,11 +240,11 @@ constexpr int kGradW = 5;     // C = sum; db[m] = sum of A over k
 // waits for its own.  The loads of PF steps are therefore in flight at a time,
 // held as they came from memory and converted on the way into LDS (64 x 64
 // tiles that waited for each step: the hidden layers' products at batch 128 18
-// us, now 7).  WT = 2 (64 x 64) where few tiles would leave compute units idle,
+// us, now 6.8).  WT = 2 (64 x 64) where few tiles would leave compute units idle,
 // WT = 4 (128 x 128: half the operand traffic and LDS reads per product) from
 // 512 tiles: the 4096 x 24576 x 512 output layer 344 -> 172 us, with permuted
 // LDS rows, whole-line stores and tile order below (L2 misses 8.7 -> 3.8
-// million lines) 162, 640 TFLOP/s.  Its products alone take 115 us, its 402 MB
+// million lines) 164, 630 TFLOP/s.  Its products alone take 115 us, its 402 MB
 // of stores alone 74: the two hardly overlap.  The order of the sum over k is
 // the same in both.
 template <class TA, class TB, int EPI, bool AKC, bool BKC, int WT, Loads LD>

@@ -369,13 +369,18 @@ hipError_t launch_force_high_skeleton(int n, int geo, const ForceArgs& a, hipStr
 // operands), SEMX_C_BF16, SEMX_C_F16 (the launch's first naff elements have
 // an affine numbering).  FP32 contractions take it from kTileMinN (below,
 // the line and column kernels are faster: at NGLL 11-12 the padded tile does
-// 2.4-3x the useful matrix work), the matrix-core modes from kTileMinNMixed.
+// 2.4-3x the useful matrix work), the matrix-core modes from kTileMinNMixed
+// (ms per apply at 2e7 nodes, BF16 here / FP32 on the line kernel: NGLL 11
+// 0.563 / 0.344, 12 0.491 / 0.427; BF16 / FP32 both here: 13 0.442 / 0.539, 16
+// 0.292 / 0.340).
 constexpr int kTileMinN = 13;
 constexpr int kTileMinNMixed = 11;
-// FP32 at NGLL 12 where the line kernel does not run (assembly into f): the
-// tile kernel for launches of regular elements (its persistent form, 0.754 against 0.917 ms per apply for the column kernel
-// at 2e7 nodes); with per-point or trilinear geometry the column kernel
-// stays faster (0.98 against 1.05-1.19 ms), as at NGLL 11 on every path.
+// FP32 at NGLL 12 where the line kernel does not run (assembly into f, runs
+// with checkpoints): the tile kernel for launches of regular elements (its
+// persistent form, 0.754 against 0.917 ms per apply for the column kernel at
+// 2e7 nodes, assembling into f); with per-point or trilinear geometry the
+// column kernel stays faster (0.98 against 1.05-1.19 ms), as at NGLL 11 on
+// every path.
 constexpr int kTileRegularN = 12;
 hipError_t launch_force_tile16(int n, int prec, int geo, bool atomic, int64_t naff, const ForceArgs& a,
                                hipStream_t s);
